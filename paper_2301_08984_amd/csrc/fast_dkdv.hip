@@ -15,7 +15,7 @@ namespace {
 // Q / dO tiles (64 rows) are double-buffered in LDS, one barrier per tile; the next
 // tile travels global -> registers meanwhile.
 // ---------------------------------------------------------------------------
-template <int D, bool BIAS, bool CAUSAL, int NW, bool SLICE32>
+template <int D, int BIAS, bool CAUSAL, int NW, bool SLICE32>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 32 ? (BIAS && CAUSAL ? 2 : 3) : 1, D <= 32 ? (BIAS && CAUSAL ? 2 : 3) : 1))) void dkdv_fast_kernel(KP p) {
   constexpr int KS = D / 16, DB = D / 32, LD = D + 24, NT = 64 * NW, BK = 32 * NW;  // tiles read both ways
   constexpr int CPR = D / 8, CPT = BN * CPR / NT;
@@ -39,7 +39,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 32
   const float* dl_b = p.delta + (int64_t)(b - p.dl_b0) * p.dl_sb + (int64_t)(h - p.dl_h0) * p.dl_sh;
   // bias comes from the transposed copy biasT[h][key][query], so that a lane (= key) finds four
   // consecutive queries in 8 bytes
-  BiasTile bt;
+  BiasTile<BIAS == BIAS_ODD> bt;
   if (BIAS) bt.init((const uint16_t*)p.biasT + (int64_t)h * p.S * p.S, k0, p.S, sBias + w * BIAS_TILE_ELEMS, lane);
   auto bload = [&](int qt) { bt.load(qt); };
 
@@ -297,6 +297,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 32
 // HP = 2 (D = 32, heads side by side in memory): eight wavefronts cover the same tile of two
 // neighbouring heads, whose row slices are fetched together as 128 contiguous bytes: whole cache
 // lines instead of halves, at twice the bytes per cycle through the load path.
+typedef f32x4 f32x4_u __attribute__((aligned(4)));  // rows of S floats start anywhere
 template <int D, bool CAUSAL, int HP>
 __global__ __launch_bounds__(256 * HP)
 __attribute__((amdgpu_waves_per_eu(D <= 32 ? 4 : 1, D <= 32 ? 4 : (D <= 64 ? 2 : 1))))
@@ -417,7 +418,7 @@ void dbias_tile_kernel(KP p) {
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const int kb = k0 + 8 * g + 4 * hl;
-      if (kb + 3 < p.S) *(f32x4*)(dst + kb) = f32x4{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
+      if (kb + 3 < p.S) *(f32x4_u*)(dst + kb) = f32x4{acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]};
       else for (int e = 0; e < 4; ++e) if (kb + e < p.S) dst[kb + e] = acc[4 * g + e];
     }
   }
@@ -439,11 +440,9 @@ __global__ __launch_bounds__(256) void bias_transpose_kernel(const uint16_t* src
 template <int D, int NW, bool SLICE32>
 void dkdv_fast_launch(const KP& p, hipStream_t st) {
   const dim3 g((p.S + 32 * NW - 1) / (32 * NW), p.h1 - p.h0, p.b1 - p.b0);
-  const bool bias = p.bias_kind == 1, causal = p.mask_kind == 1;
-  if (bias && causal) dkdv_fast_kernel<D, true, true, NW, SLICE32><<<g, 64 * NW, 0, st>>>(p);
-  else if (bias) dkdv_fast_kernel<D, true, false, NW, SLICE32><<<g, 64 * NW, 0, st>>>(p);
-  else if (causal) dkdv_fast_kernel<D, false, true, NW, SLICE32><<<g, 64 * NW, 0, st>>>(p);
-  else dkdv_fast_kernel<D, false, false, NW, SLICE32><<<g, 64 * NW, 0, st>>>(p);
+  dispatch_bias(p, [&](auto bias, auto causal) {
+    dkdv_fast_kernel<D, bias(), causal(), NW, SLICE32><<<g, 64 * NW, 0, st>>>(p);
+  });
 }
 template <int D>
 hipError_t dkdv_d(const KP& p, hipStream_t st) {
@@ -456,7 +455,7 @@ hipError_t dkdv_d(const KP& p, hipStream_t st) {
 }
 template <int D>
 hipError_t dbias_d(const KP& p, hipStream_t st) {
-  {  // callers guarantee S > 64 and S a multiple of 4 (fast_ok)
+  {  // callers guarantee S > 64 (fast_ok)
     int ng = 1;
     if (p.sm_partial) ng = (p.b1 - 1) / p.sm_gw - p.b0 / p.sm_gw + 1;
     const int heads = p.h1 - p.h0;

@@ -12,7 +12,7 @@ namespace {
 // from the matrix cores, dS from the vector ALUs, and dQ^T += K^T dS^T reads the same K
 // tile transposed.
 // ---------------------------------------------------------------------------
-template <int D, bool BIAS, bool CAUSAL, int QW, int NG>
+template <int D, int BIAS, bool CAUSAL, int QW, int NG>
 // D = 32 needs 100 - 140 registers: three (with a bias) or four wavefronts per SIMD instead of two
 __global__ __launch_bounds__(64 * QW * NG)
 __attribute__((amdgpu_waves_per_eu(D <= 32 ? (BIAS ? 3 : 4) : 2, D <= 32 ? (BIAS ? 3 : 4) : 2))) void dq_fast_kernel(KP p) {
@@ -39,7 +39,7 @@ __attribute__((amdgpu_waves_per_eu(D <= 32 ? (BIAS ? 3 : 4) : 2, D <= 32 ? (BIAS
   const uint16_t* Kb = (const uint16_t*)p.K + base;
   const uint16_t* Vb = (const uint16_t*)p.V + base;
   const uint16_t* dOb = (const uint16_t*)p.dO + (int64_t)(b - p.do_b0) * p.do_sb + (int64_t)(h - p.do_h0) * p.do_sh;
-  BiasTile bt;
+  BiasTile<BIAS == BIAS_ODD> bt;
   if (BIAS)
     bt.init((const uint16_t*)p.bias + (int64_t)h * p.S * p.S, q0, p.S,
             smem + KV_ELEMS + (threadIdx.x >> 6) * BIAS_TILE_ELEMS, lane);
@@ -192,11 +192,7 @@ __attribute__((amdgpu_waves_per_eu(D <= 32 ? (BIAS ? 3 : 4) : 2, D <= 32 ? (BIAS
 template <int D, int QW, int NG>
 void dq_fast_launch(const KP& p, hipStream_t st) {
   const dim3 g((p.S + 32 * QW - 1) / (32 * QW), p.h1 - p.h0, p.b1 - p.b0);
-  const bool bias = p.bias_kind == 1, causal = p.mask_kind == 1;
-  if (bias && causal) dq_fast_kernel<D, true, true, QW, NG><<<g, 64 * QW * NG, 0, st>>>(p);
-  else if (bias) dq_fast_kernel<D, true, false, QW, NG><<<g, 64 * QW * NG, 0, st>>>(p);
-  else if (causal) dq_fast_kernel<D, false, true, QW, NG><<<g, 64 * QW * NG, 0, st>>>(p);
-  else dq_fast_kernel<D, false, false, QW, NG><<<g, 64 * QW * NG, 0, st>>>(p);
+  dispatch_bias(p, [&](auto bias, auto causal) { dq_fast_kernel<D, bias(), causal(), QW, NG><<<g, 64 * QW * NG, 0, st>>>(p); });
 }
 
 template <int D>

@@ -22,7 +22,7 @@ namespace {
 // chosen from the size of the whole share, never from the chunk, so results do
 // not depend on k.
 // ---------------------------------------------------------------------------
-template <int D, bool BIAS, bool CAUSAL, bool RECOMP, int QW, int NG>
+template <int D, int BIAS, bool CAUSAL, bool RECOMP, int QW, int NG>
 __global__ __launch_bounds__(64 * QW * NG) __attribute__((amdgpu_waves_per_eu(D <= 32 ? (BIAS && (CAUSAL || NG > 1) ? 3 : 4) : 2, D <= 32 ? (BIAS && (CAUSAL || NG > 1) ? 3 : 4) : 2))) void fwd_fast_kernel(KP p) {
   constexpr int KS = D / 16, DB = D / 32, NT = 64 * QW, BM = 32 * QW;
   constexpr int LDK = D + 8, LDV = D + 16;  // row pads chosen for conflict-free b128 / transpose reads
@@ -48,7 +48,7 @@ __global__ __launch_bounds__(64 * QW * NG) __attribute__((amdgpu_waves_per_eu(D 
   const uint16_t* Qb = (const uint16_t*)p.Q + base;
   const uint16_t* Kb = (const uint16_t*)p.K + base;
   const uint16_t* Vb = (const uint16_t*)p.V + base;
-  BiasTile bt;
+  BiasTile<BIAS == BIAS_ODD> bt;
   if (BIAS)
     bt.init((const uint16_t*)p.bias + (int64_t)h * p.S * p.S, q0, p.S,
             smem + KV_ELEMS + (threadIdx.x >> 6) * BIAS_TILE_ELEMS, lane);
@@ -295,11 +295,7 @@ __global__ __launch_bounds__(64 * QW * NG) __attribute__((amdgpu_waves_per_eu(D 
 template <int D, bool RECOMP, int QW, int NG>
 void fwd_fast_launch(const KP& p, hipStream_t st) {
   const dim3 g((p.S + 32 * QW - 1) / (32 * QW), p.h1 - p.h0, p.b1 - p.b0);
-  const bool bias = p.bias_kind == 1, causal = p.mask_kind == 1;
-  if (bias && causal) fwd_fast_kernel<D, true, true, RECOMP, QW, NG><<<g, 64 * QW * NG, 0, st>>>(p);
-  else if (bias) fwd_fast_kernel<D, true, false, RECOMP, QW, NG><<<g, 64 * QW * NG, 0, st>>>(p);
-  else if (causal) fwd_fast_kernel<D, false, true, RECOMP, QW, NG><<<g, 64 * QW * NG, 0, st>>>(p);
-  else fwd_fast_kernel<D, false, false, RECOMP, QW, NG><<<g, 64 * QW * NG, 0, st>>>(p);
+  dispatch_bias(p, [&](auto bias, auto causal) { fwd_fast_kernel<D, bias(), causal(), RECOMP, QW, NG><<<g, 64 * QW * NG, 0, st>>>(p); });
 }
 
 template <int D, bool RECOMP>

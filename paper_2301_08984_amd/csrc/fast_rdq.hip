@@ -30,7 +30,7 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 // per SIMD overlap the vector and matrix work better than a longer software pipeline does with two
 // (measured on the triangle shape: 141 against 158 us per launch).
 // ---------------------------------------------------------------------------
-template <int D, bool BIAS, bool CAUSAL>
+template <int D, int BIAS, bool CAUSAL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAUSAL ? 2 : 3, BIAS && CAUSAL ? 2 : 3))) void rdq_fast_kernel(KP p) {
   constexpr int KS = D / 16, DB = D / 32, NT = 256, BM = 128;
   constexpr int LDT = D + 24;  // conflict-free for b128 and transposed reads
@@ -49,7 +49,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
   const int64_t base = (int64_t)b * p.sb + (int64_t)h * p.sh;
   const uint16_t* Kb = (const uint16_t*)p.K + base;
   const uint16_t* Vb = (const uint16_t*)p.V + base;
-  BiasTile bt;
+  BiasTile<BIAS == BIAS_ODD> bt;
   if (BIAS)
     bt.init((const uint16_t*)p.bias + (int64_t)h * p.S * p.S, q0, p.S, smem + KV_ELEMS + w * BIAS_TILE_ELEMS, lane);
 
@@ -279,11 +279,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
 template <int D>
 hipError_t rdq_launch(const KP& p, hipStream_t st) {
   const dim3 g((p.S + 127) / 128, p.h1 - p.h0, p.b1 - p.b0);
-  const bool bias = p.bias_kind == 1, causal = p.mask_kind == 1;
-  if (bias && causal) rdq_fast_kernel<D, true, true><<<g, 256, 0, st>>>(p);
-  else if (bias) rdq_fast_kernel<D, true, false><<<g, 256, 0, st>>>(p);
-  else if (causal) rdq_fast_kernel<D, false, true><<<g, 256, 0, st>>>(p);
-  else rdq_fast_kernel<D, false, false><<<g, 256, 0, st>>>(p);
+  dispatch_bias(p, [&](auto bias, auto causal) { rdq_fast_kernel<D, bias(), causal()><<<g, 256, 0, st>>>(p); });
   return hipGetLastError();
 }
 

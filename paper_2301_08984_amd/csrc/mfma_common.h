@@ -9,6 +9,8 @@
 #pragma once
 #include "kparams.h"
 
+#include <type_traits>
+
 namespace ssa {
 namespace {
 
@@ -150,23 +152,37 @@ __device__ inline BlockId xcd_block_id(bool z_fast = false) {
 // in the layout of the accumulator.  LDS rows are padded to 136 bytes so that the 8-byte reads of 32
 // rows fall into distinct banks.  The loads are buffer loads over the head's S x S matrix: a row past
 // S - 1 lies past the end and reads as zeros, columns past S - 1 read the next row; both belong to
-// scores that are masked or never stored.  S is a multiple of 4 and S * S * 2 bytes at most 2 GiB.
+// scores that are masked or never stored.  S * S * 2 is at most 2 GiB.
+// Any S: rows start at multiples of 2 S bytes, so with S % 8 != 0 the 16-byte loads are unaligned
+// (down to 2 bytes), which the hardware takes; only the bytes of a row then touch one cache line
+// more.  With S odd the matrix ends inside a dword: the descriptor stops before it and the one entry
+// that lies there, (S - 1, S - 1), is put into the parked tile by hand.
+// (ODD: a variant of its own, the registers of that step cost the others a spill.)
 constexpr int BIAS_LD = 68, BIAS_TILE_ELEMS = 32 * BIAS_LD;
+enum { BIAS_OFF = 0, BIAS_EVEN = 1, BIAS_ODD = 2 };  // no dense bias, S even, S odd
+template <bool ODD>
 struct BiasTile {
   __amdgpu_buffer_rsrc_t rs;  // the head's matrix
   uint16_t* lds;              // the wavefront's area, BIAS_TILE_ELEMS elements
   uint32_t off, rstep;        // byte offset of this lane's chunk in tile 0; bytes between its rows
   u32x4 nxt[4];
+  const uint16_t* last;       // S odd: the entry added by hand, the tile that holds it (-1: not in these rows), its place
+  int last_tile, last_at, in_flight;  // ... and the tile in the registers; all uniform
   __device__ void init(const uint16_t* head, int row0, int S, uint16_t* area, int lane) {
-    rs = __builtin_amdgcn_make_buffer_rsrc((void*)head, 0, (int)((int64_t)S * S * 2), 0x00020000);
+    rs = __builtin_amdgcn_make_buffer_rsrc((void*)head, 0, (int)((int64_t)S * S * 2) & ~3, 0x00020000);
     const int first = __builtin_amdgcn_readfirstlane(min(row0, S - 1));
     off = ((uint32_t)(first + (lane >> 3)) * (uint32_t)S + 8u * (lane & 7)) * 2u;
     rstep = 16u * (uint32_t)S;  // 8 rows
     lds = area;
+    last = head + ((int64_t)S * S - 1);
+    last_tile = first + 32 >= S ? (S - 1) >> 6 : -1;
+    last_at = (S - 1 - first) * BIAS_LD + ((S - 1) & 63);
+    in_flight = -1;
   }
   __device__ void load(int tile) {
 #pragma unroll
     for (int c = 0; c < 4; ++c) nxt[c] = __builtin_amdgcn_raw_buffer_load_b128(rs, off + tile * 128 + c * rstep, 0, 0);
+    in_flight = tile;
   }
   __device__ void park(int lane) {
 #pragma unroll
@@ -175,6 +191,7 @@ struct BiasTile {
       *(uint2*)d = uint2{nxt[c][0], nxt[c][1]};
       *(uint2*)(d + 4) = uint2{nxt[c][2], nxt[c][3]};
     }
+    if (ODD && in_flight == last_tile) lds[last_at] = *last;
   }
   // columns col .. col + 3 (col a multiple of 4) of row r of the parked tile
   __device__ uint2 read(int r, int col) const { return *(const uint2*)(lds + r * BIAS_LD + col); }
@@ -280,11 +297,11 @@ __device__ inline void fwd_epilogue(const KP& p, f32x16 (&oacc)[DB], float m, fl
   fwd_epilogue_rowsum<DB, RECOMP>(p, oacc, m, half_sum(l), b, h, q, hl, base);
 }
 
-// the specialised kernels serve: no bias or a dense bf16 bias with S % 4 == 0; no mask or the
-// causal mask; a positive scale; more than one 64-key tile's worth of rows
+// the specialised kernels serve: no bias or a dense bf16 bias; no mask or the causal mask; a
+// positive scale; more than one 64-key tile's worth of rows
 inline bool fast_ok(const KP& p) {
   if (p.S <= 64 || !(p.scale > 0.f) || p.mask_kind == 2 || p.bias_kind == 2) return false;
-  if (p.bias_kind == 1 && (!p.bias_bf16 || (p.S & 3) || p.S > 32768)) return false;
+  if (p.bias_kind == 1 && (!p.bias_bf16 || p.S > 32768)) return false;
   return true;
 }
 
@@ -302,11 +319,26 @@ inline int dbias_group_rows(const KP& p) {
   return tiles >= 512 ? 0 : 64;
 }
 
+// calls f with the compile-time bias variant and causal flag of the launch
+template <class F>
+inline void dispatch_bias(const KP& p, F f) {
+  const int bias = p.bias_kind == 1 ? ((p.S & 1) ? BIAS_ODD : BIAS_EVEN) : BIAS_OFF;
+  auto with = [&](auto causal) {
+    if (bias == BIAS_ODD) f(std::integral_constant<int, BIAS_ODD>{}, causal);
+    else if (bias == BIAS_EVEN) f(std::integral_constant<int, BIAS_EVEN>{}, causal);
+    else f(std::integral_constant<int, BIAS_OFF>{}, causal);
+  };
+  if (p.mask_kind == 1) with(std::true_type{});
+  else with(std::false_type{});
+}
+
 enum WgShape { WG_4x1, WG_4x2, WG_2x4 };
 inline WgShape wg_shape(const KP& p) {
   const int64_t wgs = (int64_t)((p.S + 127) / 128) * p.share_units;
   if (wgs >= 512 || p.S < 512) return WG_4x1;
   if (wgs >= 256) return WG_4x2;
+  // the kernels of the smallest shape read the bias four aligned columns at a time
+  if (p.bias_kind == 1 && (p.S & 3)) return WG_4x2;
   // the kernels of the smallest shape address one (row, head) slice with 32-bit buffer offsets
   const int64_t row_stride = p.ss > (int64_t)p.H * p.D ? p.ss : (int64_t)p.H * p.D;
   if (((int64_t)(p.S - 1) * row_stride + p.D) * 2 >= (1ll << 31)) return WG_4x2;
