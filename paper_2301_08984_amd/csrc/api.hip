@@ -414,6 +414,11 @@ int ss_attn_bwd(const ss_attn_desc* d, const void* Q, const void* K, const void*
       continue;
     }
     if (mfma) {
+      if (want_dbias && w.gw > 0) {  // grouped sum: partials in the workspace, folded into the result as the groups complete
+        p.sm_partial = (float*)(ws + w.partial);
+        set_groups(p);
+      }
+      p.sm_gw = w.gw > 0 ? w.gw : SMALL_GW;
       if (ssa::mfma_fuses_recompute_dq(p)) {
         SS_LAUNCH(SS_K_RECOMPUTE_DQ, ssa::launch_mfma_recompute_dq(p, st), "recompute + dQ");
         SS_LAUNCH(SS_K_DKDV, ssa::launch_mfma_dkdv(p, st), "dK/dV");
@@ -427,12 +432,7 @@ int ss_attn_bwd(const ss_attn_desc* d, const void* Q, const void* K, const void*
         }
       }
       if (want_dbias) {
-        if (w.gw > 0) {  // grouped sum: partials in the workspace, folded into the result as the groups complete
-          p.sm_partial = (float*)(ws + w.partial);
-          p.sm_gw = w.gw;
-          set_groups(p);
-        }
-        SS_LAUNCH(SS_K_DBIAS, ssa::launch_mfma_dbias(p, st), "dBias");
+        if (!ssa::mfma_dkdv_has_dbias(p)) SS_LAUNCH(SS_K_DBIAS, ssa::launch_mfma_dbias(p, st), "dBias");
         if (w.gw > 0) {
           const int rf = fold_groups(p, c);
           if (rf != SS_OK) return rf;

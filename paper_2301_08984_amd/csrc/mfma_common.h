@@ -305,6 +305,14 @@ inline bool fast_ok(const KP& p) {
   return true;
 }
 
+// the window kernels (win_kernels.hip) serve: head size 32, 65 to 160 tokens, a relative-position bias or a
+// region mask (a bf16 bias of either kind, or none; no causal mask), a positive scale
+inline bool win_ok(const KP& p) {
+  if (p.D != 32 || p.S <= 64 || p.S > 160 || !(p.scale > 0.f) || p.mask_kind == 1) return false;
+  if (p.bias_kind != 0 && !p.bias_bf16) return false;
+  return p.bias_kind == 2 || p.mask_kind == 2;
+}
+
 // Work-group shape of the forward / dQ kernels: query wavefronts x key-tile groups.  Large shares
 // use 4x1 (many independent work-groups per compute unit); when the whole share offers fewer than
 // two 128-query work-groups per compute unit the key tiles are split over groups inside the
@@ -314,6 +322,12 @@ inline bool fast_ok(const KP& p) {
 // Rows per group of the tiled bias-gradient kernel: 0 = one group (the sum continues in the output);
 // otherwise the share's rows are cut into groups so that about two work-groups per compute unit exist.
 inline int dbias_group_rows(const KP& p) {
+  if (win_ok(p)) {
+    // one work-group per group: short groups while the share has few rows to go round
+    int gw = 8;
+    while (gw > 1 && p.share_units / gw < 1024) gw >>= 1;
+    return p.bias_kind != 0 ? gw : 0;
+  }
   if (p.bias_kind != 1 || !fast_ok(p)) return 0;
   const int64_t tiles = (int64_t)((p.S + 63) / 64) * ((p.S + 63) / 64) * p.H;
   return tiles >= 512 ? 0 : 64;
@@ -360,5 +374,8 @@ hipError_t launch_fast_fwd_wave128(const KP& p, bool recompute, hipStream_t st);
 hipError_t launch_fast_bwd_wave(const KP& p, hipStream_t st);
 hipError_t launch_fast_bwd_wave3(const KP& p, hipStream_t st);
 hipError_t launch_fast_dbias(const KP& p, hipStream_t st);
+hipError_t launch_win_fwd(const KP& p, hipStream_t st);
+hipError_t launch_win_recompute_dq(const KP& p, hipStream_t st);
+hipError_t launch_win_kv(const KP& p, hipStream_t st);  // with the bias gradient's group partials
 
 }  // namespace ssa

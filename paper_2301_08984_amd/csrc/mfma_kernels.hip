@@ -617,6 +617,7 @@ bool mfma_supported(const KP& p, bool bf16) {
 // the specialised kernels (one translation unit each) serve what fast_ok() accepts; the
 // all-feature kernels above serve the rest
 hipError_t launch_mfma_fwd(const KP& p, bool recompute, hipStream_t st) {
+  if (!recompute && win_ok(p)) return launch_win_fwd(p, st);
   if (fast_ok(p)) return launch_fast_fwd(p, recompute, st);
   SS_DISPATCH_D(fwd_d, p, recompute, st)
 }
@@ -625,6 +626,7 @@ hipError_t launch_mfma_dq(const KP& p, hipStream_t st) {
   SS_DISPATCH_D(dq_d, p, st)
 }
 hipError_t launch_mfma_dkdv(const KP& p, hipStream_t st) {
+  if (win_ok(p)) return launch_win_kv(p, st);
   if (fast_ok(p)) return launch_fast_dkdv(p, st);
   SS_DISPATCH_D(dkdv_d, p, st)
 }
@@ -644,10 +646,15 @@ hipError_t launch_mfma_dq_dkdv(const KP& p, hipStream_t st) {
 // head size 32 on the large-share work-group shape: the vector arithmetic per score element binds, and
 // the recompute pass and dQ share all of it
 bool mfma_fuses_recompute_dq(const KP& p) {
+  if (win_ok(p)) return true;
   if (!fast_ok(p) || p.D != 32 || wg_shape(p) != WG_4x1) return false;
   return ((int64_t)(p.S - 1) * p.ss + p.D) * 2 < (1ll << 31);  // the kernel addresses a (row, head) slice with 32-bit offsets
 }
-hipError_t launch_mfma_recompute_dq(const KP& p, hipStream_t st) { return launch_fast_recompute_dq(p, st); }
+hipError_t launch_mfma_recompute_dq(const KP& p, hipStream_t st) {
+  return win_ok(p) ? launch_win_recompute_dq(p, st) : launch_fast_recompute_dq(p, st);
+}
+// the window kernels' dK/dV launch leaves the group partials of the bias gradient too
+bool mfma_dkdv_has_dbias(const KP& p) { return win_ok(p); }
 int mfma_dbias_group_rows(const KP& p) { return dbias_group_rows(p); }
 
 }  // namespace ssa
