@@ -403,7 +403,7 @@ def main():
                 per_kernel[name] = {"avg_us": tot / n * 1e3, "launches_per_step": n / a.steps,
                                     "ms_per_step": tot / a.steps}
         dom = max(per_kernel, key=lambda n: per_kernel[n]["ms_per_step"])
-        units = ext / k_main
+        units = ext / max(1.0, per_kernel[dom]["launches_per_step"])  # what one launch covers
         dur = per_kernel[dom]["avg_us"] * 1e-6
         gbs = kernel_bytes(w, dom, units, ext) / dur / 1e9
         tfs = kernel_flops(w, dom, units, ext) / dur / 1e12

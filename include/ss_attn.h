@@ -107,7 +107,9 @@ int ss_attn_workspace_bytes(const ss_attn_desc* desc, size_t* fwd_bytes, size_t*
 /* Host-only helper: the sub-range of chunk c (0 <= c < k) under the rule above. */
 int ss_attn_chunk_range(const ss_attn_desc* desc, int32_t c, int32_t* chunk_lo, int32_t* chunk_hi);
 
-/* Forward (Section 2, co-shard; operator as defined at the top of this file).
+/* Forward (Section 2, co-shard; operator as defined at the top of this file).  A forward sub-operator
+ * needs no scratch and its results do not depend on the others, so the chunks of a forward are one
+ * launch: k decides nothing but the order in which the backward goes.
  *   Q,K,V   in : activations, whole-operator tensors.
  *   bias    in : per bias_kind, NULL iff SS_BIAS_NONE.
  *   region_ids in : per mask_kind, NULL unless SS_MASK_REGION.

@@ -290,12 +290,16 @@ int ss_attn_fwd(const ss_attn_desc* d, const void* Q, const void* K, const void*
   p.Q = Q; p.K = K; p.V = V; p.G = G; p.Y = Y; p.bias = bias; p.region = region_ids;
   p.lse_out = lse; p.lse_sb = (int64_t)d->H * d->S; p.lse_sh = d->S;
   const Family fam = family_of(d);
-  for (int c = 0; c < d->k; ++c) {
-    set_chunk(p, d, c);
-    if (fam == FAM_SMALL) SS_LAUNCH(SS_K_FWD, ssa::launch_small_fwd(p, st), "forward (short)");
-    else if (fam == FAM_MFMA) SS_LAUNCH(SS_K_FWD, ssa::launch_mfma_fwd(p, false, st), "forward");
-    else SS_LAUNCH(SS_K_FWD, ssa::launch_generic_fwd(p, bf16, false, st), "forward (generic)");
-  }
+  // A forward needs no scratch, so running its chunks one at a time saves no memory, and a row's
+  // results do not depend on the chunk: the whole share is one launch.  (Small chunks leave compute
+  // units idle: 6 heads of 2048 queries took 17.7 us, 12 take 28.)
+  p.b0 = d->shard_axis == SS_AXIS_ROW ? d->lo : 0;
+  p.b1 = d->shard_axis == SS_AXIS_ROW ? d->hi : d->B;
+  p.h0 = d->shard_axis == SS_AXIS_HEAD ? d->lo : 0;
+  p.h1 = d->shard_axis == SS_AXIS_HEAD ? d->hi : d->H;
+  if (fam == FAM_SMALL) SS_LAUNCH(SS_K_FWD, ssa::launch_small_fwd(p, st), "forward (short)");
+  else if (fam == FAM_MFMA) SS_LAUNCH(SS_K_FWD, ssa::launch_mfma_fwd(p, false, st), "forward");
+  else SS_LAUNCH(SS_K_FWD, ssa::launch_generic_fwd(p, bf16, false, st), "forward (generic)");
   return SS_OK;
 }
 

@@ -119,10 +119,10 @@ struct RowStage {
 template <int NB>
 __device__ inline bool row_is_masked(const int* ids, int S, int lane) {
   const int first = ids[0];
-  bool other = false;
+  int other = 0;  // all loads in flight together
 #pragma unroll
-  for (int c = 0; c < (NB + 1) / 2; ++c) other = other || ids[min(lane + 64 * c, S - 1)] != first;
-  return __builtin_amdgcn_ballot_w64(other) != 0;
+  for (int c = 0; c < (NB + 1) / 2; ++c) other |= ids[min(lane + 64 * c, S - 1)] ^ first;
+  return __builtin_amdgcn_ballot_w64(other != 0) != 0;
 }
 
 // adds the bias to a block of scores (natural units) and masks pairs of different regions
