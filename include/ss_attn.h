@@ -100,7 +100,10 @@ typedef struct {
  * reused by every chunk, so it shrinks as k grows; this is what makes
  * peak memory = caller tensors + workspace fall with k (Section 6.3).  Parts that
  * do not depend on k (a transposed copy of a dense bias, group partial sums of the
- * bias gradient) are included in the figure.
+ * bias gradient) are included in the figure.  A larger workspace is used to run chunks
+ * together, and the chunks of a share that needs no more than 32 MiB run together in a
+ * buffer that the library holds on each GPU, unless another stream is using it or the
+ * call is being captured into a graph; the results are the same bits.
  * Needs no GPU.  Returns SS_OK or a negative error. */
 int ss_attn_workspace_bytes(const ss_attn_desc* desc, size_t* fwd_bytes, size_t* bwd_bytes);
 

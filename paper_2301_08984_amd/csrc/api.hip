@@ -14,6 +14,10 @@
 // device address once per device (static_scratch below) and passes that pointer on.
 static __device__ __align__(256) unsigned char scratch[SS_ATTN_STATIC_SCRATCH_BYTES];
 
+// Scratch in which a small share runs its chunks together (see Shared below), one per GPU.
+constexpr size_t SHARED_BYTES = 32u << 20;
+static __device__ __align__(256) unsigned char shared_scratch[SHARED_BYTES];
+
 namespace {
 
 using ssa::KP;
@@ -143,7 +147,7 @@ inline void set_chunk(KP& p, const ss_attn_desc* d, int c) {
   else { p.b0 = a; p.b1 = b; p.h0 = 0; p.h1 = d->H; }
 }
 
-// Device address of this GPU's copy of `scratch`, looked up on the first call per device.
+// Device address of this GPU's copy of a __device__ buffer, looked up on the first call per device.
 constexpr int MAX_DEVICES = 64;
 std::mutex g_scratch_mu;
 void* g_scratch_ptr[MAX_DEVICES] = {nullptr};
@@ -168,6 +172,70 @@ int static_scratch(void** out) {
   *out = g_scratch_ptr[dev];
   return SS_OK;
 }
+
+// Chunks of a small share cannot fill the chip (a launch of 4 rows x 1 head takes as long as one of
+// 4 rows x 6), and what keeps them apart is only that they reuse one chunk's scratch.  The results do
+// not depend on k, so where the scratch of fewer, larger chunks fits into SHARED_BYTES they run like
+// that, in a buffer of the library's own: one per GPU, used by one stream at a time.  A call takes it if
+// it is on the stream of the last call that had it (stream order keeps them apart) or if that call's
+// work has finished; any other call, and any call that is being captured into a graph (a replay
+// is ordered after nothing that the host can see), runs its chunks one by one in the caller's workspace.
+// Nothing ever waits for the buffer.  Backward of 4 rows x 6 heads x 215 queries, D = 128, k = 4:
+// 131 -> 37 us; pair attention of 18 rows x 8 heads x 472, k = 16, forward and backward: 729 -> 103 us.
+struct Shared {
+  void* ptr = nullptr;
+  hipEvent_t done = nullptr;      // end of the last call that used the buffer
+  hipStream_t stream = nullptr;   // its stream
+  bool used = false, broken = false;
+};
+std::mutex g_shared_mu;
+Shared g_shared[MAX_DEVICES];
+
+// holds the lock from the moment the buffer is taken until the call's launches are enqueued
+struct SharedUse {
+  std::unique_lock<std::mutex> lock;
+  Shared* s = nullptr;
+  hipStream_t st = nullptr;
+  void* take(hipStream_t stream) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    int dev = -1;
+    if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone ||
+        hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) {
+      (void)hipGetLastError();
+      return nullptr;
+    }
+    std::unique_lock<std::mutex> l(g_shared_mu, std::try_to_lock);
+    if (!l.owns_lock()) return nullptr;
+    Shared& x = g_shared[dev];
+    if (x.broken) return nullptr;
+    // a capture under way in another thread must not see these calls as its own
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (!x.ptr && (hipGetSymbolAddress(&x.ptr, HIP_SYMBOL(shared_scratch)) != hipSuccess || !x.ptr ||
+                   hipEventCreateWithFlags(&x.done, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess)) {
+      x.broken = true;
+      (void)hipGetLastError();
+    }
+    // (the wait on what should be the same stream is for a handle that was destroyed and handed out again)
+    const bool mine = !x.broken && (!x.used || (x.stream == stream ? hipStreamWaitEvent(stream, x.done, 0)
+                                                                   : hipEventQuery(x.done)) == hipSuccess);
+    if (!mine) (void)hipGetLastError();
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (!mine) return nullptr;
+    x.used = true;
+    x.stream = stream;
+    s = &x;
+    st = stream;
+    lock = std::move(l);
+    return x.ptr;
+  }
+  ~SharedUse() {
+    if (s && hipEventRecord(s->done, st) != hipSuccess) {  // nobody could tell when this call's work ends
+      s->broken = true;
+      (void)hipGetLastError();
+    }
+  }
+};
 
 int hip_fail(hipError_t e, const char* what) {
   fprintf(stderr, "ss_attn: %s: %s\n", what, hipGetErrorString(e));
@@ -202,6 +270,144 @@ struct ProfScope {
     }                                                 \
     if (e_ != hipSuccess) return hip_fail(e_, what);  \
   } while (0)
+
+// The smallest co-shard factor, at most d->k, whose scratch fits `bytes` (d->k if none does).  Powers of
+// two: every one of them gives the same results, so the search needs no finer steps.
+int fewest_chunks(const ss_attn_desc* d, Family fam, size_t bytes) {
+  ss_attn_desc t = *d;
+  for (t.k = 1; t.k < d->k; t.k *= 2)
+    if (bwd_layout(&t, fam).total <= bytes) return t.k;
+  return d->k;
+}
+
+// the k chunks of `d` one after another, in the scratch at `ws`
+int run_bwd(const ss_attn_desc* d, Family fam, const WsLayout& w, const void* Q, const void* K, const void* V,
+            const void* bias, const int32_t* region_ids, const void* G, const void* dY, const float* lse, void* dQ,
+            void* dK, void* dV, float* dBias, void* dG, char* ws, hipStream_t st) {
+  const bool bf16 = d->dtype == SS_BF16;
+  const bool want_dbias = d->bias_kind != SS_BIAS_NONE && dBias != nullptr;
+  KP p = base_params(d);
+  p.Q = Q; p.K = K; p.V = V; p.G = G; p.dY = dY; p.bias = bias; p.region = region_ids;
+  p.dQ = dQ; p.dK = dK; p.dV = dV; p.dG = dG;
+  const bool mfma = fam == FAM_MFMA;
+  if (mfma && ssa::mfma_wants_bias_transpose(p)) {
+    // the K-stationary kernels read bias[h][i][j] along i: give them a transposed copy, once per call
+    const int h0 = d->shard_axis == SS_AXIS_HEAD ? d->lo : 0, h1 = d->shard_axis == SS_AXIS_HEAD ? d->hi : d->H;
+    SS_LAUNCH(SS_K_TABLE_REDUCE, ssa::launch_bias_transpose(bias, ws + w.biasT, d->S, h0, h1, st), "bias transpose");
+    p.biasT = ws + w.biasT;
+  }
+  float* dense = nullptr;
+  if (want_dbias) {
+    dense = d->bias_kind == SS_BIAS_DENSE ? dBias : (float*)(ws + w.dense);
+    p.dbias_acc = dense;
+  }
+  // grouped bias-gradient sums: slot addressing for the chunk, and the fold of the slices that the
+  // chunk just completed (ROW split: groups complete as the rows go by; HEAD split: a chunk walks
+  // every row of its heads, so all of its groups complete at once)
+  int slices_done = 0;
+  auto set_groups = [&](KP& q) {
+    q.sm_g0 = w.g0; q.sm_ring = w.ring; q.sm_hs = w.hs;
+    q.sm_h0 = d->shard_axis == SS_AXIS_HEAD ? q.h0 : 0;
+  };
+  auto fold_groups = [&](const KP& q, int c) -> int {
+    const int nslices = (w.ngroups + w.slice - 1) / w.slice;
+    int s0, s1, hd0, nh;
+    if (d->shard_axis == SS_AXIS_HEAD) {
+      s0 = 0; s1 = nslices; hd0 = q.h0; nh = q.h1 - q.h0;
+    } else {
+      const int done = c == d->k - 1 ? nslices : (q.b1 / w.gw - w.g0) / w.slice;
+      s0 = slices_done; s1 = done > slices_done ? done : slices_done; hd0 = 0; nh = d->H;
+      slices_done = s1;
+    }
+    if (s1 <= s0) return SS_OK;
+    SS_LAUNCH(SS_K_DBIAS_FOLD,
+              ssa::launch_group_fold(q.sm_partial, dense, w.ring, w.hs, hd0, nh, d->S, w.slice, s0, s1, w.ngroups,
+                                     s0 == 0, st),
+              "bias gradient group fold");
+    return SS_OK;
+  };
+  for (int c = 0; c < d->k; ++c) {
+    set_chunk(p, d, c);
+    const int64_t Bc = p.b1 - p.b0, Hc = p.h1 - p.h0;
+    (void)Bc;
+    // chunk-sized scratch holds the chunk's (row, head) pairs from its origin (b0, h0) on
+    const int64_t st_sb = Hc * d->S, st_sh = d->S;
+    p.delta = (float*)(ws + w.delta); p.dl_sb = st_sb; p.dl_sh = st_sh; p.dl_b0 = p.b0; p.dl_h0 = p.h0;
+    if (lse) {
+      p.lse = lse; p.lse_out = nullptr; p.lse_sb = (int64_t)d->H * d->S; p.lse_sh = d->S; p.lse_b0 = 0; p.lse_h0 = 0;
+    } else {
+      p.lse_out = (float*)(ws + w.lse); p.lse = p.lse_out; p.lse_sb = st_sb; p.lse_sh = st_sh;
+      p.lse_b0 = p.b0; p.lse_h0 = p.h0;
+    }
+    if (d->gated) {
+      p.do_sh = d->D; p.do_ss = Hc * d->D; p.do_sb = (int64_t)d->S * p.do_ss;
+      p.dO_out = (void*)(ws + w.dO); p.dO = p.dO_out; p.do_b0 = p.b0; p.do_h0 = p.h0;
+    } else {
+      p.dO = dY; p.dO_out = nullptr; p.do_sb = p.sb; p.do_ss = p.ss; p.do_sh = p.sh; p.do_b0 = 0; p.do_h0 = 0;
+    }
+    // the first chunk that touches a bias-gradient entry starts its sum: for a HEAD split every
+    // chunk owns its heads; for a ROW split chunk 0 starts and later chunks continue in row order
+    p.dbias_accumulate = (d->shard_axis == SS_AXIS_ROW && c > 0) ? 1 : 0;
+    if (fam == FAM_SMALL) {
+      // one fused kernel per chunk; group partial sums of the bias gradient live in the workspace
+      // across chunks and are reduced once the last chunk that touches them is enqueued
+      p.sm_partial = want_dbias ? (float*)(ws + w.partial) : nullptr;
+      set_groups(p);
+      SS_LAUNCH(SS_K_DKDV, ssa::launch_small_bwd(p, st), "backward (short)");
+      if (want_dbias) {
+        const int rf = fold_groups(p, c);
+        if (rf != SS_OK) return rf;
+        if (d->bias_kind == SS_BIAS_RELPOS && (d->shard_axis == SS_AXIS_HEAD || c == d->k - 1)) {
+          const int h0 = d->shard_axis == SS_AXIS_HEAD ? p.h0 : 0;
+          const int h1 = d->shard_axis == SS_AXIS_HEAD ? p.h1 : d->H;
+          SS_LAUNCH(SS_K_TABLE_REDUCE,
+                    ssa::launch_relpos_reduce(dense, dBias, h0, h1, d->S, d->win_h, d->win_w, st),
+                    "relative-position table reduce");
+        }
+      }
+      continue;
+    }
+    if (mfma) {
+      if (want_dbias && w.gw > 0) {  // grouped sum: partials in the workspace, folded into the result as the groups complete
+        p.sm_partial = (float*)(ws + w.partial);
+        set_groups(p);
+      }
+      p.sm_gw = w.gw > 0 ? w.gw : SMALL_GW;
+      if (ssa::mfma_fuses_recompute_dq(p)) {
+        SS_LAUNCH(SS_K_RECOMPUTE_DQ, ssa::launch_mfma_recompute_dq(p, st), "recompute + dQ");
+        SS_LAUNCH(SS_K_DKDV, ssa::launch_mfma_dkdv(p, st), "dK/dV");
+      } else {
+        SS_LAUNCH(SS_K_RECOMPUTE, ssa::launch_mfma_fwd(p, true, st), "recompute");
+        if (ssa::mfma_fuses_dq_dkdv(p)) {
+          SS_LAUNCH(SS_K_DQ_DKDV, ssa::launch_mfma_dq_dkdv(p, st), "dQ + dK/dV");
+        } else {
+          SS_LAUNCH(SS_K_DQ, ssa::launch_mfma_dq(p, st), "dQ");
+          SS_LAUNCH(SS_K_DKDV, ssa::launch_mfma_dkdv(p, st), "dK/dV");
+        }
+      }
+      if (want_dbias) {
+        if (!ssa::mfma_dkdv_has_dbias(p)) SS_LAUNCH(SS_K_DBIAS, ssa::launch_mfma_dbias(p, st), "dBias");
+        if (w.gw > 0) {
+          const int rf = fold_groups(p, c);
+          if (rf != SS_OK) return rf;
+        }
+      }
+    } else {
+      SS_LAUNCH(SS_K_RECOMPUTE, ssa::launch_generic_fwd(p, bf16, true, st), "recompute (generic)");
+      SS_LAUNCH(SS_K_DQ, ssa::launch_generic_dq(p, bf16, st), "dQ (generic)");
+      SS_LAUNCH(SS_K_DKDV, ssa::launch_generic_dkdv(p, bf16, st), "dK/dV (generic)");
+      if (want_dbias) SS_LAUNCH(SS_K_DBIAS, ssa::launch_generic_dbias(p, bf16, st), "dBias (generic)");
+    }
+    if (want_dbias && d->bias_kind == SS_BIAS_RELPOS &&
+        (d->shard_axis == SS_AXIS_HEAD || c == d->k - 1)) {
+      const int h0 = d->shard_axis == SS_AXIS_HEAD ? p.h0 : 0;
+      const int h1 = d->shard_axis == SS_AXIS_HEAD ? p.h1 : d->H;
+      SS_LAUNCH(SS_K_TABLE_REDUCE, ssa::launch_relpos_reduce(dense, dBias, h0, h1, d->S, d->win_h, d->win_w, st),
+                "relative-position table reduce");
+    }
+  }
+  return SS_OK;
+}
 
 }  // namespace
 
@@ -329,134 +535,21 @@ int ss_attn_bwd(const ss_attn_desc* d, const void* Q, const void* K, const void*
   if (d->mask_kind == SS_MASK_REGION && !region_ids) return SS_ERR_NULL;
   if (d->gated && (!G || !dG)) return SS_ERR_NULL;
   const Family fam = family_of(d);
-  const WsLayout w = bwd_layout(d, fam);
+  WsLayout w = bwd_layout(d, fam);
   if (!workspace || workspace_bytes < w.total || ((uintptr_t)workspace % ALIGN)) return SS_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)hip_stream;
-  const bool bf16 = d->dtype == SS_BF16;
   char* ws = (char*)workspace;
-  const bool want_dbias = d->bias_kind != SS_BIAS_NONE && dBias != nullptr;
-
-  KP p = base_params(d);
-  p.Q = Q; p.K = K; p.V = V; p.G = G; p.dY = dY; p.bias = bias; p.region = region_ids;
-  p.dQ = dQ; p.dK = dK; p.dV = dV; p.dG = dG;
-  const bool mfma = fam == FAM_MFMA;
-  if (mfma && ssa::mfma_wants_bias_transpose(p)) {
-    // the K-stationary kernels read bias[h][i][j] along i: give them a transposed copy, once per call
-    const int h0 = d->shard_axis == SS_AXIS_HEAD ? d->lo : 0, h1 = d->shard_axis == SS_AXIS_HEAD ? d->hi : d->H;
-    SS_LAUNCH(SS_K_TABLE_REDUCE, ssa::launch_bias_transpose(bias, ws + w.biasT, d->S, h0, h1, st), "bias transpose");
-    p.biasT = ws + w.biasT;
+  ss_attn_desc run = *d;
+  SharedUse shared;
+  if (d->k > 1) {
+    // the fewest chunks whose scratch fits what the caller handed over, or else the library's buffer
+    const int kw = fewest_chunks(d, fam, workspace_bytes), ks = fewest_chunks(d, fam, SHARED_BYTES);
+    void* own = ks < kw ? shared.take(st) : nullptr;
+    if (own) ws = (char*)own;
+    run.k = own ? ks : kw;
+    if (run.k != d->k) w = bwd_layout(&run, fam);
   }
-  float* dense = nullptr;
-  if (want_dbias) {
-    dense = d->bias_kind == SS_BIAS_DENSE ? dBias : (float*)(ws + w.dense);
-    p.dbias_acc = dense;
-  }
-  // grouped bias-gradient sums: slot addressing for the chunk, and the fold of the slices that the
-  // chunk just completed (ROW split: groups complete as the rows go by; HEAD split: a chunk walks
-  // every row of its heads, so all of its groups complete at once)
-  int slices_done = 0;
-  auto set_groups = [&](KP& q) {
-    q.sm_g0 = w.g0; q.sm_ring = w.ring; q.sm_hs = w.hs;
-    q.sm_h0 = d->shard_axis == SS_AXIS_HEAD ? q.h0 : 0;
-  };
-  auto fold_groups = [&](const KP& q, int c) -> int {
-    const int nslices = (w.ngroups + w.slice - 1) / w.slice;
-    int s0, s1, hd0, nh;
-    if (d->shard_axis == SS_AXIS_HEAD) {
-      s0 = 0; s1 = nslices; hd0 = q.h0; nh = q.h1 - q.h0;
-    } else {
-      const int done = c == d->k - 1 ? nslices : (q.b1 / w.gw - w.g0) / w.slice;
-      s0 = slices_done; s1 = done > slices_done ? done : slices_done; hd0 = 0; nh = d->H;
-      slices_done = s1;
-    }
-    if (s1 <= s0) return SS_OK;
-    SS_LAUNCH(SS_K_DBIAS_FOLD,
-              ssa::launch_group_fold(q.sm_partial, dense, w.ring, w.hs, hd0, nh, d->S, w.slice, s0, s1, w.ngroups,
-                                     s0 == 0, st),
-              "bias gradient group fold");
-    return SS_OK;
-  };
-  for (int c = 0; c < d->k; ++c) {
-    set_chunk(p, d, c);
-    const int64_t Bc = p.b1 - p.b0, Hc = p.h1 - p.h0;
-    (void)Bc;
-    // chunk-sized scratch holds the chunk's (row, head) pairs from its origin (b0, h0) on
-    const int64_t st_sb = Hc * d->S, st_sh = d->S;
-    p.delta = (float*)(ws + w.delta); p.dl_sb = st_sb; p.dl_sh = st_sh; p.dl_b0 = p.b0; p.dl_h0 = p.h0;
-    if (lse) {
-      p.lse = lse; p.lse_out = nullptr; p.lse_sb = (int64_t)d->H * d->S; p.lse_sh = d->S; p.lse_b0 = 0; p.lse_h0 = 0;
-    } else {
-      p.lse_out = (float*)(ws + w.lse); p.lse = p.lse_out; p.lse_sb = st_sb; p.lse_sh = st_sh;
-      p.lse_b0 = p.b0; p.lse_h0 = p.h0;
-    }
-    if (d->gated) {
-      p.do_sh = d->D; p.do_ss = Hc * d->D; p.do_sb = (int64_t)d->S * p.do_ss;
-      p.dO_out = (void*)(ws + w.dO); p.dO = p.dO_out; p.do_b0 = p.b0; p.do_h0 = p.h0;
-    } else {
-      p.dO = dY; p.dO_out = nullptr; p.do_sb = p.sb; p.do_ss = p.ss; p.do_sh = p.sh; p.do_b0 = 0; p.do_h0 = 0;
-    }
-    // the first chunk that touches a bias-gradient entry starts its sum: for a HEAD split every
-    // chunk owns its heads; for a ROW split chunk 0 starts and later chunks continue in row order
-    p.dbias_accumulate = (d->shard_axis == SS_AXIS_ROW && c > 0) ? 1 : 0;
-    if (fam == FAM_SMALL) {
-      // one fused kernel per chunk; group partial sums of the bias gradient live in the workspace
-      // across chunks and are reduced once the last chunk that touches them is enqueued
-      p.sm_partial = want_dbias ? (float*)(ws + w.partial) : nullptr;
-      set_groups(p);
-      SS_LAUNCH(SS_K_DKDV, ssa::launch_small_bwd(p, st), "backward (short)");
-      if (want_dbias) {
-        const int rf = fold_groups(p, c);
-        if (rf != SS_OK) return rf;
-        if (d->bias_kind == SS_BIAS_RELPOS && (d->shard_axis == SS_AXIS_HEAD || c == d->k - 1)) {
-          const int h0 = d->shard_axis == SS_AXIS_HEAD ? p.h0 : 0;
-          const int h1 = d->shard_axis == SS_AXIS_HEAD ? p.h1 : d->H;
-          SS_LAUNCH(SS_K_TABLE_REDUCE,
-                    ssa::launch_relpos_reduce(dense, dBias, h0, h1, d->S, d->win_h, d->win_w, st),
-                    "relative-position table reduce");
-        }
-      }
-      continue;
-    }
-    if (mfma) {
-      if (want_dbias && w.gw > 0) {  // grouped sum: partials in the workspace, folded into the result as the groups complete
-        p.sm_partial = (float*)(ws + w.partial);
-        set_groups(p);
-      }
-      p.sm_gw = w.gw > 0 ? w.gw : SMALL_GW;
-      if (ssa::mfma_fuses_recompute_dq(p)) {
-        SS_LAUNCH(SS_K_RECOMPUTE_DQ, ssa::launch_mfma_recompute_dq(p, st), "recompute + dQ");
-        SS_LAUNCH(SS_K_DKDV, ssa::launch_mfma_dkdv(p, st), "dK/dV");
-      } else {
-        SS_LAUNCH(SS_K_RECOMPUTE, ssa::launch_mfma_fwd(p, true, st), "recompute");
-        if (ssa::mfma_fuses_dq_dkdv(p)) {
-          SS_LAUNCH(SS_K_DQ_DKDV, ssa::launch_mfma_dq_dkdv(p, st), "dQ + dK/dV");
-        } else {
-          SS_LAUNCH(SS_K_DQ, ssa::launch_mfma_dq(p, st), "dQ");
-          SS_LAUNCH(SS_K_DKDV, ssa::launch_mfma_dkdv(p, st), "dK/dV");
-        }
-      }
-      if (want_dbias) {
-        if (!ssa::mfma_dkdv_has_dbias(p)) SS_LAUNCH(SS_K_DBIAS, ssa::launch_mfma_dbias(p, st), "dBias");
-        if (w.gw > 0) {
-          const int rf = fold_groups(p, c);
-          if (rf != SS_OK) return rf;
-        }
-      }
-    } else {
-      SS_LAUNCH(SS_K_RECOMPUTE, ssa::launch_generic_fwd(p, bf16, true, st), "recompute (generic)");
-      SS_LAUNCH(SS_K_DQ, ssa::launch_generic_dq(p, bf16, st), "dQ (generic)");
-      SS_LAUNCH(SS_K_DKDV, ssa::launch_generic_dkdv(p, bf16, st), "dK/dV (generic)");
-      if (want_dbias) SS_LAUNCH(SS_K_DBIAS, ssa::launch_generic_dbias(p, bf16, st), "dBias (generic)");
-    }
-    if (want_dbias && d->bias_kind == SS_BIAS_RELPOS &&
-        (d->shard_axis == SS_AXIS_HEAD || c == d->k - 1)) {
-      const int h0 = d->shard_axis == SS_AXIS_HEAD ? p.h0 : 0;
-      const int h1 = d->shard_axis == SS_AXIS_HEAD ? p.h1 : d->H;
-      SS_LAUNCH(SS_K_TABLE_REDUCE, ssa::launch_relpos_reduce(dense, dBias, h0, h1, d->S, d->win_h, d->win_w, st),
-                "relative-position table reduce");
-    }
-  }
-  return SS_OK;
+  return run_bwd(&run, fam, w, Q, K, V, bias, region_ids, G, dY, lse, dQ, dK, dV, dBias, dG, ws, st);
 }
 
 }  // extern "C"

@@ -1,0 +1,51 @@
+"""Chunks of a small share run together in the library's own scratch when nobody else is using it, and one
+by one in the caller's workspace otherwise: under graph capture, and on a second stream while the first
+one's work is under way.  Both ways give the same bits."""
+import pytest
+
+from test_gpu_parity import SMALL
+
+pytestmark = pytest.mark.gpu
+OUTS = ("dQ", "dK", "dV", "dG", "dBias")
+
+
+@pytest.mark.parametrize("name,k", [("gpt_like", 2), ("tri_like", 3), ("swin_like", 4), ("f32_all", 2)])
+def test_chunked_and_merged_runs_agree(name, k):
+    import torch
+    from paper_2301_08984_amd.runner import DeviceCase
+    from paper_2301_08984_amd.workloads import make_inputs
+    cfg = SMALL[name]
+    inp = make_inputs(**cfg)
+    dc, other = (DeviceCase(inp, dtype=cfg["dtype"], bias=cfg.get("bias"), mask=cfg.get("mask"), gated=cfg.get("gated", False),
+                            win=cfg.get("win"), layout=cfg.get("layout", "bshd")) for _ in range(2))
+    ext = dc.H if cfg["axis"] == "head" else dc.B
+    d = dc.desc(cfg["axis"], 0, ext, min(k, ext))
+    dc.bwd(d, poison=True)
+    torch.cuda.synchronize()
+    names = [n for n in OUTS if getattr(dc, n) is not None]
+    merged = {n: getattr(dc, n).clone() for n in names}
+
+    def check(case, what):
+        torch.cuda.synchronize()
+        for n in names:
+            assert torch.equal(torch.nan_to_num(getattr(case, n), nan=12345.0), torch.nan_to_num(merged[n], nan=12345.0)), (what, n)
+            getattr(case, n).fill_(float("nan"))
+
+    dc.ws.fill_(0xFF)
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        dc.bwd(d)
+    for n in names:
+        getattr(dc, n).fill_(float("nan"))
+    graph.replay()
+    check(dc, "captured")
+    # two streams at a time, several calls deep
+    other.workspace(d)
+    torch.cuda.synchronize()
+    for _ in range(8):
+        dc.bwd(d)
+        with torch.cuda.stream(side):
+            other.bwd(d)
+    check(dc, "first stream")
+    check(other, "second stream")
