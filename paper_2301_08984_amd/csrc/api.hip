@@ -4,6 +4,7 @@
 // workspace (co-shard, Section 2 of the paper).
 #include "../../include/ss_attn.h"
 #include "kparams.h"
+#include "shared_scratch.h"
 
 #include <cstdio>
 #include <mutex>
@@ -14,9 +15,9 @@
 // device address once per device (static_scratch below) and passes that pointer on.
 static __device__ __align__(256) unsigned char scratch[SS_ATTN_STATIC_SCRATCH_BYTES];
 
-// Scratch in which a small share runs its chunks together (see Shared below), one per GPU.
-constexpr size_t SHARED_BYTES = 32u << 20;
-static __device__ __align__(256) unsigned char shared_scratch[SHARED_BYTES];
+// The scratch of shared_scratch.h.
+static __device__ __align__(256) unsigned char shared_scratch[ssa::SHARED_BYTES];
+static __device__ unsigned shared_counters[ssa::SHARED_COUNTERS];
 
 namespace {
 
@@ -173,69 +174,8 @@ int static_scratch(void** out) {
   return SS_OK;
 }
 
-// Chunks of a small share cannot fill the chip (a launch of 4 rows x 1 head takes as long as one of
-// 4 rows x 6), and what keeps them apart is only that they reuse one chunk's scratch.  The results do
-// not depend on k, so where the scratch of fewer, larger chunks fits into SHARED_BYTES they run like
-// that, in a buffer of the library's own: one per GPU, used by one stream at a time.  A call takes it if
-// it is on the stream of the last call that had it (stream order keeps them apart) or if that call's
-// work has finished; any other call, and any call that is being captured into a graph (a replay
-// is ordered after nothing that the host can see), runs its chunks one by one in the caller's workspace.
-// Nothing ever waits for the buffer.  Backward of 4 rows x 6 heads x 215 queries, D = 128, k = 4:
-// 131 -> 37 us; pair attention of 18 rows x 8 heads x 472, k = 16, forward and backward: 729 -> 103 us.
-struct Shared {
-  void* ptr = nullptr;
-  hipEvent_t done = nullptr;      // end of the last call that used the buffer
-  hipStream_t stream = nullptr;   // its stream
-  bool used = false, broken = false;
-};
 std::mutex g_shared_mu;
-Shared g_shared[MAX_DEVICES];
-
-// holds the lock from the moment the buffer is taken until the call's launches are enqueued
-struct SharedUse {
-  std::unique_lock<std::mutex> lock;
-  Shared* s = nullptr;
-  hipStream_t st = nullptr;
-  void* take(hipStream_t stream) {
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    int dev = -1;
-    if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone ||
-        hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) {
-      (void)hipGetLastError();
-      return nullptr;
-    }
-    std::unique_lock<std::mutex> l(g_shared_mu, std::try_to_lock);
-    if (!l.owns_lock()) return nullptr;
-    Shared& x = g_shared[dev];
-    if (x.broken) return nullptr;
-    // a capture under way in another thread must not see these calls as its own
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    if (!x.ptr && (hipGetSymbolAddress(&x.ptr, HIP_SYMBOL(shared_scratch)) != hipSuccess || !x.ptr ||
-                   hipEventCreateWithFlags(&x.done, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess)) {
-      x.broken = true;
-      (void)hipGetLastError();
-    }
-    // (the wait on what should be the same stream is for a handle that was destroyed and handed out again)
-    const bool mine = !x.broken && (!x.used || (x.stream == stream ? hipStreamWaitEvent(stream, x.done, 0)
-                                                                   : hipEventQuery(x.done)) == hipSuccess);
-    if (!mine) (void)hipGetLastError();
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    if (!mine) return nullptr;
-    x.used = true;
-    x.stream = stream;
-    s = &x;
-    st = stream;
-    lock = std::move(l);
-    return x.ptr;
-  }
-  ~SharedUse() {
-    if (s && hipEventRecord(s->done, st) != hipSuccess) {  // nobody could tell when this call's work ends
-      s->broken = true;
-      (void)hipGetLastError();
-    }
-  }
-};
+ssa::Shared g_shared[MAX_DEVICES];
 
 int hip_fail(hipError_t e, const char* what) {
   fprintf(stderr, "ss_attn: %s: %s\n", what, hipGetErrorString(e));
@@ -386,7 +326,7 @@ int run_bwd(const ss_attn_desc* d, Family fam, const WsLayout& w, const void* Q,
         }
       }
       if (want_dbias) {
-        if (!ssa::mfma_dkdv_has_dbias(p)) SS_LAUNCH(SS_K_DBIAS, ssa::launch_mfma_dbias(p, st), "dBias");
+        SS_LAUNCH(SS_K_DBIAS, ssa::launch_mfma_dbias(p, st), "dBias");
         if (w.gw > 0) {
           const int rf = fold_groups(p, c);
           if (rf != SS_OK) return rf;
@@ -410,6 +350,50 @@ int run_bwd(const ss_attn_desc* d, Family fam, const WsLayout& w, const void* Q,
 }
 
 }  // namespace
+
+namespace ssa {
+
+void* SharedUse::take(hipStream_t stream) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  int dev = -1;
+  if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone ||
+      hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  std::unique_lock<std::mutex> l(g_shared_mu, std::try_to_lock);
+  if (!l.owns_lock()) return nullptr;
+  Shared& x = g_shared[dev];
+  if (x.broken) return nullptr;
+  // a capture under way in another thread must not see these calls as its own
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (!x.ptr && (hipGetSymbolAddress(&x.ptr, HIP_SYMBOL(shared_scratch)) != hipSuccess || !x.ptr ||
+                 hipGetSymbolAddress((void**)&x.counters, HIP_SYMBOL(shared_counters)) != hipSuccess || !x.counters ||
+                 hipEventCreateWithFlags(&x.done, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess))
+    x.broken = true;
+  // (the wait on what should be the same stream is for a handle that was destroyed and handed out again)
+  const bool mine = !x.broken && (!x.used || (x.stream == stream ? hipStreamWaitEvent(stream, x.done, 0)
+                                                                 : hipEventQuery(x.done)) == hipSuccess);
+  if (!mine) (void)hipGetLastError();
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (!mine) return nullptr;
+  x.used = true;
+  x.stream = stream;
+  s_ = &x;
+  st_ = stream;
+  lock_ = std::move(l);
+  return x.ptr;
+}
+
+SharedUse::~SharedUse() {
+  if (s_ && hipEventRecord(s_->done, st_) != hipSuccess) {  // nobody could tell when this call's work ends
+    s_->broken = true;
+    (void)hipGetLastError();
+  }
+}
+
+}  // namespace ssa
 
 extern "C" {
 
@@ -540,10 +524,14 @@ int ss_attn_bwd(const ss_attn_desc* d, const void* Q, const void* K, const void*
   hipStream_t st = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;
   ss_attn_desc run = *d;
-  SharedUse shared;
+  ssa::SharedUse shared;
   if (d->k > 1) {
-    // the fewest chunks whose scratch fits what the caller handed over, or else the library's buffer
-    const int kw = fewest_chunks(d, fam, workspace_bytes), ks = fewest_chunks(d, fam, SHARED_BYTES);
+    // Chunks of a small share cannot fill the chip (a launch of 4 rows x 1 head takes as long as one of
+    // 4 rows x 6), and what keeps them apart is only that they reuse one chunk's scratch.  The results
+    // do not depend on k: run the fewest chunks whose scratch fits what the caller handed over, or
+    // else the library's buffer.  Backward of 4 rows x 6 heads x 215 queries, D = 128, k = 4: 131 -> 36 us;
+    // pair attention of 18 rows x 8 heads x 472, k = 16, forward and backward: 729 -> 113 us.
+    const int kw = fewest_chunks(d, fam, workspace_bytes), ks = fewest_chunks(d, fam, ssa::SHARED_BYTES);
     void* own = ks < kw ? shared.take(st) : nullptr;
     if (own) ws = (char*)own;
     run.k = own ? ks : kw;

@@ -6,6 +6,7 @@
 #include <mutex>
 
 #include "ffn_kernels.h"
+#include "shared_scratch.h"
 
 namespace {
 
@@ -157,6 +158,22 @@ ssa::GemmArgs gemm(const void* A, int64_t lda, const void* B, int64_t ldb, int M
   return g;
 }
 
+// The library's scratch for split contractions, taken if any product of the call is split: one half for the
+// caller's stream, one for the helper stream.
+static_assert(2 * ssa::SPLIT_BYTES <= ssa::SHARED_BYTES && 2 * ssa::SPLIT_TILES <= ssa::SHARED_COUNTERS, "split scratch");
+struct SplitScratch {
+  ssa::SharedUse use;
+  char* base = nullptr;
+  SplitScratch(hipStream_t st, bool want) { if (want) base = (char*)use.take(st); }
+  void set(ssa::GemmArgs& g, ssa::GemmPlan plan, int half) const {
+    g.cols = plan.cols;
+    g.split = plan.split;
+    if (!base || plan.split < 2) return;
+    g.parts = (float*)(base + half * ssa::SPLIT_BYTES);
+    g.counters = use.counters() + half * ssa::SPLIT_TILES;
+  }
+};
+
 }  // namespace
 
 extern "C" {
@@ -191,7 +208,10 @@ int ss_ffn_fwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
   char* ws = (char*)workspace;
   const uint16_t* W1p = (const uint16_t*)W1;
   const uint16_t* W2p = (const uint16_t*)W2;
-  const bool exact = (d->flags & SS_FFN_FLAG_EXACT_SUM) != 0 || d->k == 1;
+  const bool exact = (d->flags & SS_FFN_FLAG_EXACT_SUM) != 0;
+  const int n = d->hi - d->lo;
+  const ssa::GemmPlan plan_up = ssa::gemm_plan(d->T, n, d->dm);
+  SplitScratch scratch(st, plan_up.split > 1 || (!exact && ssa::gemm_plan(d->T, d->dm, n).split > 1));
   for (int c = 0; c < d->k; ++c) {
     int a, b;
     chunk(d, c, &a, &b);
@@ -200,11 +220,13 @@ int ss_ffn_fwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
     // H_c = act(X W1[:, a:b] + b1[a:b])
     ssa::GemmArgs up = gemm(X, d->ld_x, W1p + a, d->ld_w1, d->T, nc, d->dm);
     up.bias = (const uint16_t*)b1 + a; up.out = (uint16_t*)(ws + w.H); up.ldo = w.ldh; up.act = d->act;
+    scratch.set(up, plan_up, 0);
     FF_LAUNCH(SS_FK_UP, ssa::launch_gemm(up, false, false, ssa::EPI_ACT, st), "H = act(X W1 + b1)");
     // Y += H_c W2[a:b, :]; the last chunk adds b2 and writes Y
     ssa::GemmArgs dn = gemm(ws + w.H, w.ldh, W2p + (int64_t)a * d->ld_w2, d->ld_w2, d->T, d->dm, nc);
     dn.acc32 = (float*)(ws + w.acc); dn.accumulate = c > 0; dn.last = c == d->k - 1;
     dn.bias = dn.last ? (const uint16_t*)b2 : nullptr; dn.out = (uint16_t*)Y; dn.ldo = d->ld_x;
+    if (!exact) scratch.set(dn, ssa::gemm_plan(d->T, d->dm, nc), 0);
     FF_LAUNCH(SS_FK_DOWN, ssa::launch_gemm(dn, false, false, exact ? ssa::EPI_ACC : ssa::EPI_ACC16, st), "Y += H W2");
   }
   return SS_OK;
@@ -224,7 +246,12 @@ int ss_ffn_bwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
   const uint16_t* W2p = (const uint16_t*)W2;
   uint16_t* Hc = (uint16_t*)(ws + w.H);
   uint16_t* Dc = (uint16_t*)(ws + w.D);
-  const bool exact = (d->flags & SS_FFN_FLAG_EXACT_SUM) != 0 || d->k == 1;
+  const bool exact = (d->flags & SS_FFN_FLAG_EXACT_SUM) != 0;
+  const int n = d->hi - d->lo;
+  const ssa::GemmPlan plan_up = ssa::gemm_plan(d->T, n, d->dm), plan_dh = ssa::gemm_plan_tiled(d->T, n, d->dm);
+  const ssa::GemmPlan plan_w1 = ssa::gemm_plan_tiled(d->dm, n, d->T), plan_w2 = ssa::gemm_plan_tiled(n, d->dm, d->T);
+  SplitScratch scratch(st, plan_up.split > 1 || plan_dh.split > 1 || plan_w1.split > 1 || plan_w2.split > 1 ||
+                               (!exact && ssa::gemm_plan_tiled(d->T, d->dm, n).split > 1));
   Side side_obj(!g_on);  // per-kernel timing wants the kernels one at a time
   Side* side = side_obj.ok ? &side_obj : nullptr;
   bool pending = false;  // work on the helper stream that the caller's stream has not waited for yet
@@ -259,10 +286,12 @@ int ss_ffn_bwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
     // recompute: H_c = act(Z_c), D_c = act'(Z_c)
     ssa::GemmArgs up = gemm(X, d->ld_x, W1p + a, d->ld_w1, d->T, nc, d->dm);
     up.bias = (const uint16_t*)b1 + a; up.out = Hc; up.out2 = Dc; up.ldo = w.ldh; up.act = d->act;
+    scratch.set(up, plan_up, 0);
     FF_LAUNCH(SS_FK_UP, ssa::launch_gemm(up, false, false, ssa::EPI_ACT, st), "recompute H, act'(Z)");
     // dW2[a:b, :] = H_c^T dY, beside the products that follow when the helper stream is there
     ssa::GemmArgs gw2 = gemm(Hc, w.ldh, dY, d->ld_x, nc, d->dm, d->T);
     gw2.out = (uint16_t*)dW2 + (int64_t)a * d->ld_w2; gw2.ldo = d->ld_w2;
+    scratch.set(gw2, plan_w2, 1);
     if (fork()) {
       pending = true;
       FF_LAUNCH_ON(side->s, SS_FK_DW2, ssa::launch_gemm(gw2, true, false, ssa::EPI_STORE, side->s), "dW2 = H^T dY");
@@ -272,6 +301,7 @@ int ss_ffn_bwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
     // dZ_c = (dY W2[a:b,:]^T) * D_c, in place over D_c
     ssa::GemmArgs dh = gemm(dY, d->ld_x, W2p + (int64_t)a * d->ld_w2, d->ld_w2, d->T, nc, d->dm);
     dh.mul = Dc; dh.ldm = w.ldh; dh.out = Dc; dh.ldo = w.ldh;
+    scratch.set(dh, plan_dh, 0);
     FF_LAUNCH(SS_FK_DH, ssa::launch_gemm(dh, false, true, ssa::EPI_MUL, st), "dZ = (dY W2^T) act'(Z)");
     // db1[a:b] = column sums of dZ_c
     if (fork()) {
@@ -283,11 +313,13 @@ int ss_ffn_bwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
     // dW1[:, a:b] = X^T dZ_c
     ssa::GemmArgs gw1 = gemm(X, d->ld_x, Dc, w.ldh, d->dm, nc, d->T);
     gw1.out = (uint16_t*)dW1 + a; gw1.ldo = d->ld_w1;
+    scratch.set(gw1, plan_w1, 0);
     FF_LAUNCH(SS_FK_DW1, ssa::launch_gemm(gw1, true, false, ssa::EPI_STORE, st), "dW1 = X^T dZ");
     // dX += dZ_c W1[:, a:b]^T; the last chunk writes dX
     ssa::GemmArgs gx = gemm(Dc, w.ldh, W1p + a, d->ld_w1, d->T, d->dm, nc);
     gx.acc32 = (float*)(ws + w.acc); gx.accumulate = c > 0; gx.last = c == d->k - 1;
     gx.out = (uint16_t*)dX; gx.ldo = d->ld_x;
+    if (!exact) scratch.set(gx, ssa::gemm_plan_tiled(d->T, d->dm, nc), 0);
     FF_LAUNCH(SS_FK_DX, ssa::launch_gemm(gx, false, true, exact ? ssa::EPI_ACC : ssa::EPI_ACC16, st), "dX += dZ W1^T");
   }
   if (join() != hipSuccess) return hip_fail(hipGetLastError(), "join");

@@ -28,11 +28,45 @@ struct GemmArgs {
   int64_t ldm;
   float* acc32;  // ceil(M/256) * ceil(N/256) tiles of 256 x 256 fp32, in the kernel's own order
   int accumulate, last, act;
+  // how the product is cut up (gemm_plan)
+  int cols;            // 0: the tiled kernel; 64 or 32: the few-rows kernel, that many columns per work-group
+  int split;           // parts of the contraction
+  float* parts;        // fp32 partial sums, SPLIT_BYTES, and
+  unsigned* counters;  // SPLIT_TILES zeros (left zero); NULL: one work-group takes a tile's parts in turn
 };
+
+// A product with few tiles leaves most of the chip idle while each tile walks the whole contraction, so
+// its contraction is cut into parts that work-groups of their own sum up.  `M` and `N` are the extents
+// of the whole share, so that an element's sum does not depend on the chunk it falls into.
+struct GemmPlan { int cols, split; };
+constexpr int SPLIT_TILES = 256;
+constexpr size_t SPLIT_BYTES = (size_t)SPLIT_TILES * 128 * 128 * sizeof(float);
+// The tiled kernel: as many parts as keep one 128 x 128 tile per compute unit (256), none shorter than 8
+// stages of 64 (a part's sum takes some 4 us to hand over).
+inline GemmPlan gemm_plan_tiled(int M, int N, int K) {
+  const int64_t tiles = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
+  const int by_tiles = tiles > SPLIT_TILES ? 1 : (int)(SPLIT_TILES / tiles), by_depth = K / 512;
+  const int p = by_tiles < by_depth ? by_tiles : by_depth;
+  return {0, p < 2 ? 1 : p > 16 ? 16 : p};
+}
+// A of at most 64 rows, neither operand transposed.  The few-rows kernel starts faster (1 x 768 x 768: 5 us
+// against 9), the tiled kernel streams a large B faster (64 x 6144 x 12288: 41 us against 57, one row 36
+// against 37; 64 x 3000 x 2168: 20 against 12; the line lies near 16 million elements).  Narrow column tiles,
+// up to one work-group per compute unit, no part with less than 3 steps of 32 for each of the 8 wavefronts;
+// wide tiles where the narrow ones are more than the compute units (16 x 12288 x 768: 9.1 us against 11.3).
+inline GemmPlan gemm_plan(int M, int N, int K) {
+  if (M > 64 || (int64_t)N * K > (1 << 24)) return gemm_plan_tiled(M, N, K);
+  const int tiles = (N + 31) / 32, deepest = K / (32 * 8 * 3);
+  if (tiles > SPLIT_TILES) return {64, 1};
+  const int p = SPLIT_TILES / tiles < deepest ? SPLIT_TILES / tiles : deepest;
+  return {32, p < 1 ? 1 : p > 16 ? 16 : p};
+}
 
 // bytes of the fp32 partial-result buffer of an M x N product
 size_t gemm_acc_bytes(int M, int N);
 hipError_t launch_gemm(const GemmArgs& g, bool a_transposed, bool b_transposed, int epilogue, hipStream_t st);
+// the few-rows kernel (g.cols != 0): A and B untransposed, EPI_ACT or EPI_ACC16
+hipError_t launch_skinny(const GemmArgs& g, int epilogue, hipStream_t st);
 // out[n] (bf16) = sum over m of A[m][n] (bf16 in, fp32 sum, fixed order)
 hipError_t launch_colsum(const void* A, int64_t lda, int M, int N, void* out, hipStream_t st);
 

@@ -2,59 +2,21 @@
 // fixed-order column sum for the bias gradients.
 #include "ffn_kernels.h"
 
-#include "mfma_common.h"
+#include "ffn_common.h"
 
 namespace ssa {
 namespace {
 
 constexpr int GBK = 32;  // contraction depth of one stage
-constexpr float GELU_C0 = 0.7978845608028654f, GELU_C1 = 0.044715f;
-
-// gelu(z) = z (1 - r), r = 1 / (1 + exp(2u)), u = C0 (z + C1 z^3)   [0.5 (1 + tanh u) = 1 - r]
-// gelu'(z) = (1 - r) (1 + 2 z r u'(z)), u'(z) = C0 (1 + 3 C1 z^2)      [1 - tanh^2 u = 4 r (1 - r)]
-template <bool GRAD>
-__device__ inline void gelu4(const float (&z)[4], float (&h)[4], float (&d)[4]) {
-  constexpr float K0 = 2.f * LOG2E * GELU_C0, K1 = K0 * GELU_C1;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    const float z2 = z[e] * z[e];
-    const float r = __builtin_amdgcn_rcpf(1.f + fast_exp2(z[e] * fmaf(z2, K1, K0)));
-    const float s = 1.f - r;
-    h[e] = z[e] * s;
-    if (GRAD) d[e] = s * fmaf(2.f * z[e] * r, fmaf(z2, 3.f * GELU_C0 * GELU_C1, GELU_C0), 1.f);
-  }
-}
-template <bool GRAD>
-__device__ inline void relu4(const float (&z)[4], float (&h)[4], float (&d)[4]) {
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    h[e] = fmaxf(z[e], 0.f);
-    if (GRAD) d[e] = z[e] > 0.f ? 1.f : 0.f;
-  }
-}
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-// four fp32 -> four bf16 (round to nearest even, the hardware conversion)
-__device__ inline uint2 pack4(const float (&y)[4]) {
-  union { bf16x2 v; uint32_t u; } a, b;
-  a.v = __builtin_convertvector(f32x2{y[0], y[1]}, bf16x2);
-  b.v = __builtin_convertvector(f32x2{y[2], y[3]}, bf16x2);
-  return uint2{a.u, b.u};
-}
-__device__ inline void unpack4(uint2 u, float (&y)[4]) {
-  y[0] = __uint_as_float(u.x << 16); y[1] = __uint_as_float(u.x & 0xffff0000u);
-  y[2] = __uint_as_float(u.y << 16); y[3] = __uint_as_float(u.y & 0xffff0000u);
-}
-
 // Work-group -> tile.  Work-groups go to the 8 XCDs round-robin in launch order and each XCD has its
 // own L2: work-group b becomes logical index (b % 8) * (tiles / 8) + b / 8, so an XCD works on a
 // contiguous range of logical indices, and logical indices walk the tile grid in bands of four
 // tile rows, down the band's rows first: the tiles an XCD runs at a time share a few row panels of
 // A and column panels of B.
 struct TilePos { int mt, nt; };
-__device__ inline TilePos tile_pos(int mtiles, int ntiles) {
+__device__ inline TilePos tile_pos(int b, int mtiles, int ntiles) {
   const int tiles = mtiles * ntiles;
-  const int b = blockIdx.x, xcd = b % 8, idx = b / 8;
+  const int xcd = b % 8, idx = b / 8;
   const int id = xcd * (tiles / 8) + min(xcd, tiles % 8) + idx;
   constexpr int BAND = 4;
   const int per_band = BAND * ntiles, band = id / per_band, in_band = id % per_band;
@@ -67,7 +29,6 @@ __device__ inline TilePos tile_pos(int mtiles, int ntiles) {
 
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-constexpr uint32_t OUTSIDE = 0x7ffffff0u;  // a lane offset past every descriptor's extent: the load returns zeros
 
 // One operand of a 16 KS deep contraction stage (KS = 16-wide contraction steps per stage), 64 F
 // rows (of A) or columns (of B) -- "rho" below; F = 32-wide fragments per wavefront -- fetched from
@@ -87,15 +48,15 @@ struct Stager {
   static constexpr int BYTES = 2048 * F * KS, NI = F * KS / 2, BK = 16 * KS;
   const char* base;      // start of the next stage to fetch
   int64_t step;          // bytes from one stage to the next
-  int left;              // bytes from `base` to the end of the matrix (meaningful while k0 < ktot)
-  int k0, kcur, ktot;
+  int left;              // bytes from `base` to the end of the matrix (meaningful while k0 < kend)
+  int k0, kcur, kend;
   uint32_t lane_off[NI]; // lane offset of instruction t inside a stage (OUTSIDE if its rho are not in the matrix)
   int klimit[2];         // !TR: the lane's chunk (even / odd instruction) is inside the contraction range while k0 <= klimit
   __amdgpu_buffer_rsrc_t rs;
   __device__ void init(const uint16_t* base_, int64_t ld, int rho_tot, int ktot_, int rho0, int lane, int w) {
     base = (const char*)base_;
     const uint32_t ld2 = (uint32_t)ld * 2u;
-    ktot = ktot_;
+    kend = ktot_;
     k0 = kcur = 0;
     klimit[0] = klimit[1] = 0;
     if (!TR) {
@@ -121,11 +82,18 @@ struct Stager {
       }
     }
   }
+  // start at stage s0 and stop before stage s1
+  __device__ void range(int s0, int s1) {
+    base += s0 * step;
+    left -= (int)(s0 * step);
+    k0 = s0 * BK;
+    kend = min(kend, s1 * BK);
+  }
   // Scalar work once per stage, stages in ascending order: a descriptor that starts at the stage's
   // first contraction index and ends with the matrix, so the lane offsets are the same for every
   // stage, and is empty for stages past the end of the contraction (they load zeros).
   __device__ void begin_stage() {
-    rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, k0 < ktot ? left : 0, 0x00020000);
+    rs = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, k0 < kend ? left : 0, 0x00020000);
     kcur = k0;
     base += step;
     left -= (int)step;
@@ -190,6 +158,8 @@ constexpr int items_before(int slot, int n, int slots) {
 //        barriers.  For products whose operands are both read transposed.
 //   FI = 4, FJ = 2, KS = 4, NS = 3: 144 KB of LDS, one work-group per compute unit, half as many
 //        barriers per MFMA.  For products with a contraction-contiguous operand (see Stager).
+//   FI = FJ = 2, KS = 4, NS = 3: 128 x 128 tile, for products with few tiles; the contraction may be cut into
+//        g.split parts (gemm_plan_tiled).  Forward of 127 tokens x 12288 x 6144: 185 -> 92 us.
 //   FI = FJ = 4, KS = 2, NS = 4: 256 x 256 tile, 256 accumulation registers (half the LDS reads and
 //        loads per MFMA of the others); not instantiated: the feed-forward shapes have too few such
 //        tiles to go round.
@@ -206,6 +176,7 @@ constexpr int items_before(int slot, int n, int slots) {
 // ---------------------------------------------------------------------------
 template <bool AT, bool BT, int EPI, int FI, int FJ, int KS>
 __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_kernel(GemmArgs g) {
+  constexpr bool SPLIT = FI == 2 && FJ == 2 && EPI != EPI_ACC;  // g.split parts
   constexpr int NS = FI * FJ <= 8 ? 3 : 4;  // stage buffers
   constexpr int GBM = 64 * FI, GBN = 64 * FJ;
   using StageA = Stager<AT, FI, KS>;
@@ -225,13 +196,13 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = w >> 1, wn = w & 1;
   const int mtiles = (g.M + GBM - 1) / GBM, ntiles = (g.N + GBN - 1) / GBN;
-  const TilePos tp = tile_pos(mtiles, ntiles);
+  const int tiles = mtiles * ntiles;
+  const int tile = SPLIT ? (int)blockIdx.x % tiles : (int)blockIdx.x;
+  const TilePos tp = tile_pos(tile, mtiles, ntiles);
   const int m0 = tp.mt * GBM, n0 = tp.nt * GBN;
 
   StageA sa;
   StageB sb;
-  sa.init(g.A, g.lda, g.M, g.K, m0, lane, w);
-  sb.init(g.B, g.ldb, g.N, g.K, n0, lane, w);
   FragReader<AT, FI, KS> ra;
   FragReader<!BT, FJ, KS> rb;
   ra.init(lane, wm);
@@ -243,28 +214,8 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
   f32x16 acc[FJ][FI];
   f32x4* frag32 = nullptr;
   if (EPI == EPI_ACC) frag32 = (f32x4*)g.acc32 + ((int64_t)(tp.mt * ntiles + tp.nt) * 4 + w) * (NM * 4 * 64) + lane;
-  if (EPI == EPI_ACC && g.accumulate) {
-#pragma unroll
-    for (int j = 0; j < FJ; ++j)
-#pragma unroll
-      for (int i = 0; i < FI; ++i)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x4 v = frag32[((j * FI + i) * 4 + q) * 64];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) acc[j][i][4 * q + e] = v[e];
-        }
-  } else {
-#pragma unroll
-    for (int j = 0; j < FJ; ++j)
-#pragma unroll
-      for (int i = 0; i < FI; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[j][i][v] = 0.f;
-  }
 
-  // the stage count is rounded up to a multiple of the ring: stages past the end load zeros and add nothing
-  const int nk = (g.K + 16 * KS - 1) / (16 * KS), nkr = (nk + NS - 1) / NS * NS;
+  const int nk = (g.K + 16 * KS - 1) / (16 * KS);
   bf16x8 fa[2][FI], fb[2][FJ];  // fragments of the contraction step being multiplied and of the next one
   // fragment reads of one contraction step in the order of their first use: B 0, A 0 .. FI-1, B 1 .. FJ-1
   auto read_item = [&](const char* st, int item, int ks, int set) {
@@ -321,59 +272,167 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
 #pragma unroll
     for (int t = 0; t < NL - LA; ++t) sb.issue(dst + A_BYTES, w, t);
   };
-  fetch_all(stage0);
-  fetch_all(stage1);
-  if (NS == 4) fetch_all(stage2);
-  if constexpr (EPI == EPI_ACC16) {
-   if (g.accumulate) {
-    // The partial sum of the earlier chunks is the output itself (bf16): read as whole rows (64 FJ
-    // contiguous bytes per row), widened, and turned into the register layout through a piece of
-    // LDS of the wavefront's own -- the epilogue's path backwards.  The pieces lie in the third stage
-    // buffer, which no load targets before the barrier that ends the prologue.
-    constexpr int TLD = 128 * FJ + 16, LPR = 8 * FJ, RPI = 64 / LPR;
-    static_assert(NS == 3 && 4 * 32 * TLD <= STAGE_BYTES, "accumulator staging does not fit");
-    char* tb = stage2 + w * (32 * TLD);
-    const int c4 = 4 * (lane % LPR), rsub = lane / LPR;
-    const int n = n0 + wn * 32 * FJ + c4;
-#pragma unroll
-    for (int i = 0; i < FI; ++i) {
-#pragma unroll
-      for (int it = 0; it < 32 / RPI; ++it) {
-        const int row = RPI * it + rsub, m = m0 + wm * 32 * FI + 32 * i + row;
-        float x[4] = {0.f, 0.f, 0.f, 0.f};
-        if (m < g.M && n < g.N) unpack4(*(const uint2*)(g.out + (int64_t)m * g.ldo + n), x);
-        *(f32x4*)(tb + row * TLD + c4 * 4) = f32x4{x[0], x[1], x[2], x[3]};
-      }
+  const int parts = SPLIT ? g.split : 1;
+  const bool alone = SPLIT && parts > 1 && g.parts;  // one part per work-group; otherwise all of them in turn
+  const int first = alone ? (int)blockIdx.x / tiles : 0, last = alone ? first + 1 : parts;
+  f32x16 sum[SPLIT ? FJ : 1][SPLIT ? FI : 1];
+  for (int part = first; part < last; ++part) {
+    // stages s0 .. s1 - 1, their count rounded up to a multiple of the ring: stages past the end load zeros
+    // and add nothing
+    const int s0 = (int)((int64_t)nk * part / parts), s1 = (int)((int64_t)nk * (part + 1) / parts);
+    sa.init(g.A, g.lda, g.M, g.K, m0, lane, w);
+    sb.init(g.B, g.ldb, g.N, g.K, n0, lane, w);
+    if (SPLIT) {
+      sa.range(s0, s1);
+      sb.range(s0, s1);
+    }
+    if (EPI == EPI_ACC && g.accumulate) {
 #pragma unroll
       for (int j = 0; j < FJ; ++j)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x4 v = *(const f32x4*)(tb + r * TLD + (32 * j + 8 * q + 4 * hl) * 4);
+        for (int i = 0; i < FI; ++i)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc[j][i][4 * q + e] = v[e];
-        }
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-   }
-  }
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * NL) : "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
+          for (int q = 0; q < 4; ++q) {
+            const f32x4 v = frag32[((j * FI + i) * 4 + q) * 64];
 #pragma unroll
-  for (int item = 0; item < NR; ++item) read_item(stage0, item, 0, 0);
-  for (int kt = 0; kt < nkr; kt += NS) {
-    if (NS == 4) {
-      stage(stage0, stage1, stage3);
-      stage(stage1, stage2, stage0);
-      stage(stage2, stage3, stage1);
-      stage(stage3, stage0, stage2);
+            for (int e = 0; e < 4; ++e) acc[j][i][4 * q + e] = v[e];
+          }
     } else {
-      stage(stage0, stage1, stage2);
-      stage(stage1, stage2, stage0);
-      stage(stage2, stage0, stage1);
+#pragma unroll
+      for (int j = 0; j < FJ; ++j)
+#pragma unroll
+        for (int i = 0; i < FI; ++i)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) acc[j][i][v] = 0.f;
+    }
+    fetch_all(stage0);
+    fetch_all(stage1);
+    if (NS == 4) fetch_all(stage2);
+    if constexpr (EPI == EPI_ACC16) {
+     if (g.accumulate && part == 0) {
+      // The partial sum of the earlier chunks is the output itself (bf16): read as whole rows (64 FJ
+      // contiguous bytes per row), widened, and turned into the register layout through a piece of
+      // LDS of the wavefront's own -- the epilogue's path backwards.  The pieces lie in the last stage
+      // buffer, which no load targets before the barrier that ends the prologue; 16-byte pieces are swizzled
+      // by row, conflict-free both ways.
+      constexpr int TLD = 128 * FJ, LPR = 8 * FJ, RPI = 64 / LPR;
+      static_assert(4 * 32 * TLD <= STAGE_BYTES, "accumulator staging does not fit");
+      char* tb = (NS == 4 ? stage3 : stage2) + w * (32 * TLD);
+      const int c4 = 4 * (lane % LPR), rsub = lane / LPR;
+      const int n = n0 + wn * 32 * FJ + c4;
+#pragma unroll
+      for (int i = 0; i < FI; ++i) {
+#pragma unroll
+        for (int it = 0; it < 32 / RPI; ++it) {
+          const int row = RPI * it + rsub, m = m0 + wm * 32 * FI + 32 * i + row;
+          float x[4] = {0.f, 0.f, 0.f, 0.f};
+          if (m < g.M && n < g.N) unpack4(*(const uint2*)(g.out + (int64_t)m * g.ldo + n), x);
+          *(f32x4*)(tb + row * TLD + ((c4 * 4) ^ ((row & 15) << 4))) = f32x4{x[0], x[1], x[2], x[3]};
+        }
+#pragma unroll
+        for (int j = 0; j < FJ; ++j)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x4 v = *(const f32x4*)(tb + r * TLD + (((32 * j + 8 * q + 4 * hl) * 4) ^ ((r & 15) << 4)));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[j][i][4 * q + e] = v[e];
+          }
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+     }
+    }
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"((NS - 2) * NL) : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int item = 0; item < NR; ++item) read_item(stage0, item, 0, 0);
+    for (int kt = s0; kt < s1; kt += NS) {
+      if (NS == 4) {
+        stage(stage0, stage1, stage3);
+        stage(stage1, stage2, stage0);
+        stage(stage2, stage3, stage1);
+        stage(stage3, stage0, stage2);
+      } else {
+        stage(stage0, stage1, stage2);
+        stage(stage1, stage2, stage0);
+        stage(stage2, stage0, stage1);
+      }
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    if constexpr (SPLIT) {
+      if (last - first > 1) {
+        __builtin_amdgcn_s_barrier();  // everybody has left the stage buffers
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int j = 0; j < FJ; ++j)
+#pragma unroll
+          for (int i = 0; i < FI; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sum[j][i][v] = part == first ? acc[j][i][v] : sum[j][i][v] + acc[j][i][v];
+      }
     }
   }
-  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  if constexpr (SPLIT) {
+    if (alone) {
+      // Partial sums go to the scratch in the order the registers hold them; the work-group that finishes
+      // a tile last adds them in the order of the parts (so the result does not depend on who that is)
+      // and runs the epilogue.  Blocks of 32 rows past the end of the matrix are left out.  The sums
+      // are stored and loaded at device scope (past the L2s, which the XCDs do not share), so no fence
+      // has to write a whole L2 back: with fences a product of 16 x 1624 x 1760 took 25 us.
+      __shared__ int is_last;
+      const __amdgpu_buffer_rsrc_t rp = __builtin_amdgcn_make_buffer_rsrc(
+          (char*)g.parts + (int64_t)tile * parts * (NM * 16384), 0, parts * (NM * 16384), 0x00020000);
+      const int at = (w * (NM * 4 * 64) + lane) * 16;
+#pragma unroll
+      for (int i = 0; i < FI; ++i)
+        if (m0 + wm * 32 * FI + 32 * i < g.M)
+#pragma unroll
+          for (int j = 0; j < FJ; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              union { f32x4 f; u32x4 u; } v;
+              v.f = f32x4{acc[j][i][4 * q], acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]};
+              __builtin_amdgcn_raw_buffer_store_b128(v.u, rp, at + ((j * FI + i) * 4 + q) * 1024, first * (NM * 16384), DEVICE_SCOPE);
+            }
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // in memory, before the barrier that the count follows
+      __syncthreads();
+      if (tid == 0) {
+        is_last = __hip_atomic_fetch_add(g.counters + tile, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)parts - 1u;
+        if (is_last) __hip_atomic_store(g.counters + tile, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // nobody else comes
+      }
+      __syncthreads();
+      if (!is_last) return;
+#pragma unroll
+      for (int i = 0; i < FI; ++i)
+        if (m0 + wm * 32 * FI + 32 * i < g.M)
+          for (int part = 0; part < parts; part += 4) {  // the loads of four parts at a time (past the last: zeros)
+            union { u32x4 u; f32x4 f; } v[4][FJ][4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+#pragma unroll
+              for (int j = 0; j < FJ; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q)
+                  v[u][j][q].u = __builtin_amdgcn_raw_buffer_load_b128(
+                      rp, at + ((part + u) * NM * 16 + (j * FI + i) * 4 + q) * 1024, 0, DEVICE_SCOPE);
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+              if (part + u < parts)
+#pragma unroll
+                for (int j = 0; j < FJ; ++j)
+#pragma unroll
+                  for (int q = 0; q < 4; ++q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                      acc[j][i][4 * q + e] = part + u ? acc[j][i][4 * q + e] + v[u][j][q].f[e] : v[u][j][q].f[e];
+          }
+    } else if (parts > 1) {
+#pragma unroll
+      for (int j = 0; j < FJ; ++j)
+#pragma unroll
+        for (int i = 0; i < FI; ++i) acc[j][i] = sum[j][i];
+    }
+  }
 
   if (EPI == EPI_ACC && !g.last) {
 #pragma unroll
@@ -419,10 +478,10 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
         if (EPI == EPI_ACT) {
           float h[4], d[4];
           if (g.out2) {
-            if (g.act == 0) relu4<true>(x, h, d); else gelu4<true>(x, h, d);
+            if (g.act == 0) relu_n<true>(x, h, d); else gelu_n<true>(x, h, d);
             *(uint2*)(g.out2 + (int64_t)m * g.ldo + n) = pack4(d);
           } else {
-            if (g.act == 0) relu4<false>(x, h, d); else gelu4<false>(x, h, d);
+            if (g.act == 0) relu_n<false>(x, h, d); else gelu_n<false>(x, h, d);
           }
           *(uint2*)orow = pack4(h);
         } else if (EPI == EPI_MUL) {
@@ -474,50 +533,32 @@ __global__ __launch_bounds__(256) void colsum_kernel(const uint16_t* A, int64_t 
 // Explicit instantiations: the host compiler emits the launch stub of the first implicit
 // instantiation only.
 #define SS_GEMM_INST(a, b, e, fi, fj, ks) template __global__ void gemm_kernel<a, b, e, fi, fj, ks>(GemmArgs);
-#define SS_GEMM_INST4(a, b, fi, fj, ks) \
-  SS_GEMM_INST(a, b, 0, fi, fj, ks) SS_GEMM_INST(a, b, 1, fi, fj, ks) SS_GEMM_INST(a, b, 2, fi, fj, ks) SS_GEMM_INST(a, b, 3, fi, fj, ks)
-SS_GEMM_INST4(false, false, 4, 2, 4)
-SS_GEMM_INST4(false, true, 4, 2, 4)
-SS_GEMM_INST4(true, false, 4, 2, 2)
-SS_GEMM_INST(false, false, 4, 4, 2, 4) SS_GEMM_INST(false, true, 4, 4, 2, 4)
-// 128 x 128 tiles for products that are not accumulated over chunks, when the large tiles are few
-SS_GEMM_INST(false, false, 0, 2, 2, 4) SS_GEMM_INST(false, false, 1, 2, 2, 4) SS_GEMM_INST(false, false, 3, 2, 2, 4)
-SS_GEMM_INST(false, true, 0, 2, 2, 4) SS_GEMM_INST(false, true, 1, 2, 2, 4) SS_GEMM_INST(false, true, 3, 2, 2, 4)
-SS_GEMM_INST(true, false, 0, 2, 2, 4) SS_GEMM_INST(true, false, 1, 2, 2, 4) SS_GEMM_INST(true, false, 3, 2, 2, 4)
-#undef SS_GEMM_INST4
+SS_GEMM_INST(false, false, 0, 4, 2, 4) SS_GEMM_INST(false, false, 2, 4, 2, 4) SS_GEMM_INST(false, false, 4, 4, 2, 4)
+SS_GEMM_INST(false, true, 1, 4, 2, 4) SS_GEMM_INST(false, true, 2, 4, 2, 4) SS_GEMM_INST(false, true, 4, 4, 2, 4)
+SS_GEMM_INST(true, false, 3, 4, 2, 2)
+// 128 x 128 tiles for products with few of the large ones
+SS_GEMM_INST(false, false, 0, 2, 2, 4) SS_GEMM_INST(false, false, 2, 2, 2, 4) SS_GEMM_INST(false, false, 4, 2, 2, 4)
+SS_GEMM_INST(false, true, 1, 2, 2, 4) SS_GEMM_INST(false, true, 2, 2, 2, 4) SS_GEMM_INST(false, true, 4, 2, 2, 4)
+SS_GEMM_INST(true, false, 3, 2, 2, 4)
 #undef SS_GEMM_INST
 
 template <bool AT, bool BT, int EPI, int FI, int FJ, int KS>
 hipError_t launch_one(const GemmArgs& g, hipStream_t st) {
   const int tiles = ((g.M + 64 * FI - 1) / (64 * FI)) * ((g.N + 64 * FJ - 1) / (64 * FJ));
-  gemm_kernel<AT, BT, EPI, FI, FJ, KS><<<tiles, 256, 0, st>>>(g);
+  const bool split = FI == 2 && EPI != EPI_ACC && g.split > 1 && g.parts;
+  gemm_kernel<AT, BT, EPI, FI, FJ, KS><<<split ? tiles * g.split : tiles, 256, 0, st>>>(g);
   return hipGetLastError();
 }
 
-// For an accumulated product the tile shape depends on the operand layouts only, never on the
-// sizes: every chunk must cut its fp32 partial result into the same tiles.  The other products may
-// choose: an output element is the same chain of MFMA steps whatever tile it falls into, so when
-// fewer than 160 of the 256 x 128 tiles exist (k = 4 on the GPT-3 share: 96) they take 128 x 128
-// tiles, twice as many work-groups at 4/3 of the operand traffic per flop.
-template <bool AT, bool BT>
-hipError_t launch_epi(const GemmArgs& g, int epi, hipStream_t st) {
-  constexpr int FI = 4, FJ = 2, KS = AT ? 2 : 4;
-  if (epi != EPI_ACC && epi != EPI_ACC16 && (int64_t)((g.M + 255) / 256) * ((g.N + 127) / 128) < 160) {
-    switch (epi) {
-      case EPI_ACT: return launch_one<AT, BT, EPI_ACT, 2, 2, 4>(g, st);
-      case EPI_MUL: return launch_one<AT, BT, EPI_MUL, 2, 2, 4>(g, st);
-      default: return launch_one<AT, BT, EPI_STORE, 2, 2, 4>(g, st);
-    }
-  }
-  switch (epi) {
-    case EPI_ACT: return launch_one<AT, BT, EPI_ACT, FI, FJ, KS>(g, st);
-    case EPI_MUL: return launch_one<AT, BT, EPI_MUL, FI, FJ, KS>(g, st);
-    case EPI_ACC: return launch_one<AT, BT, EPI_ACC, FI, FJ, KS>(g, st);
-    case EPI_ACC16:
-      if constexpr (AT) return hipErrorInvalidValue;  // the accumulated products read A untransposed
-      else return launch_one<AT, BT, EPI_ACC16, FI, FJ, KS>(g, st);
-    default: return launch_one<AT, BT, EPI_STORE, FI, FJ, KS>(g, st);
-  }
+// An output element is the same chain of MFMA steps whatever tile it falls into, so the tile shape goes
+// by the sizes: when fewer than 160 of the 256 x 128 tiles exist, 128 x 128 tiles, twice as many
+// work-groups at 4/3 of the operand traffic per flop, and those may cut the contraction into parts.  (An
+// accumulated product keeps its M and N from chunk to chunk, so all chunks cut its fp32 partial result
+// into the same tiles.)
+template <bool AT, bool BT, int EPI>
+hipError_t launch_shape(const GemmArgs& g, hipStream_t st) {
+  if ((int64_t)((g.M + 255) / 256) * ((g.N + 127) / 128) < 160 || g.split > 1) return launch_one<AT, BT, EPI, 2, 2, 4>(g, st);
+  return launch_one<AT, BT, EPI, 4, 2, AT ? 2 : 4>(g, st);
 }
 
 }  // namespace
@@ -527,12 +568,28 @@ size_t gemm_acc_bytes(int M, int N) {
   return (size_t)((M + 255) / 256) * ((N + 255) / 256) * 256 * 256 * sizeof(float);
 }
 
-hipError_t launch_gemm(const GemmArgs& g, bool at, bool bt, int epi, hipStream_t st) {
-  if (g.M <= 0 || g.N <= 0 || g.K <= 0) return hipErrorInvalidValue;
-  if (!at && !bt) return launch_epi<false, false>(g, epi, st);
-  if (!at && bt) return launch_epi<false, true>(g, epi, st);
-  if (at && !bt) return launch_epi<true, false>(g, epi, st);
-  return hipErrorInvalidValue;  // A^T B^T is not needed by the feed-forward operator
+hipError_t launch_gemm(const GemmArgs& args, bool at, bool bt, int epi, hipStream_t st) {
+  if (args.M <= 0 || args.N <= 0 || args.K <= 0) return hipErrorInvalidValue;
+  GemmArgs g = args;
+  if (g.split < 1) g.split = 1;
+  // each operand layout comes with the epilogues that the feed-forward operator has for it
+  if (!at && !bt) {
+    if (g.cols) return launch_skinny(g, epi, st);
+    switch (epi) {
+      case EPI_ACT: return launch_shape<false, false, EPI_ACT>(g, st);
+      case EPI_ACC: return launch_shape<false, false, EPI_ACC>(g, st);
+      case EPI_ACC16: return launch_shape<false, false, EPI_ACC16>(g, st);
+    }
+  } else if (!at && bt) {
+    switch (epi) {
+      case EPI_MUL: return launch_shape<false, true, EPI_MUL>(g, st);
+      case EPI_ACC: return launch_shape<false, true, EPI_ACC>(g, st);
+      case EPI_ACC16: return launch_shape<false, true, EPI_ACC16>(g, st);
+    }
+  } else if (at && !bt && epi == EPI_STORE) {
+    return launch_shape<true, false, EPI_STORE>(g, st);
+  }
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_colsum(const void* A, int64_t lda, int M, int N, void* out, hipStream_t st) {

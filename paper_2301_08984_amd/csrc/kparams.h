@@ -75,7 +75,6 @@ hipError_t launch_mfma_fwd(const KP& p, bool recompute, hipStream_t st);
 hipError_t launch_mfma_dq(const KP& p, hipStream_t st);
 hipError_t launch_mfma_dkdv(const KP& p, hipStream_t st);
 hipError_t launch_mfma_dbias(const KP& p, hipStream_t st);
-bool mfma_dkdv_has_dbias(const KP& p);         // the dK/dV launch includes the bias gradient (group partials)
 bool mfma_fuses_dq_dkdv(const KP& p);
 hipError_t launch_mfma_dq_dkdv(const KP& p, hipStream_t st);
 bool mfma_fuses_recompute_dq(const KP& p);

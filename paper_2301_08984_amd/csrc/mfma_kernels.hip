@@ -631,6 +631,7 @@ hipError_t launch_mfma_dkdv(const KP& p, hipStream_t st) {
   SS_DISPATCH_D(dkdv_d, p, st)
 }
 hipError_t launch_mfma_dbias(const KP& p, hipStream_t st) {
+  if (win_ok(p)) return hipSuccess;  // the window kernels' dK/dV launch leaves the group partials of the bias gradient too
   if (fast_ok(p) && p.bias_kind == 1) return launch_fast_dbias(p, st);
   SS_DISPATCH_D(dbias_d, p, st)
 }
@@ -653,8 +654,6 @@ bool mfma_fuses_recompute_dq(const KP& p) {
 hipError_t launch_mfma_recompute_dq(const KP& p, hipStream_t st) {
   return win_ok(p) ? launch_win_recompute_dq(p, st) : launch_fast_recompute_dq(p, st);
 }
-// the window kernels' dK/dV launch leaves the group partials of the bias gradient too
-bool mfma_dkdv_has_dbias(const KP& p) { return win_ok(p); }
 int mfma_dbias_group_rows(const KP& p) { return dbias_group_rows(p); }
 
 }  // namespace ssa

@@ -1,0 +1,59 @@
+"""Products with few tiles: the few-rows kernel (up to 64 tokens) and contractions that are cut into parts
+over work-groups, against the oracle at the edges of both (token blocks of 16, column tiles of 32, 64
+and 128, parts of uneven length), and bit for bit with the run that has no scratch for the parts (under graph
+capture)."""
+import numpy as np
+import pytest
+
+from oracle import ffn as orc
+from paper_2301_08984_amd.workloads import make_ffn_inputs
+from parity import rel_err
+
+pytestmark = pytest.mark.gpu
+
+CASES = {  # T, dm, dh, k, flags
+    "one_token_long_up": (1, 3208, 72, 1, 0),
+    "block_edge_16": (16, 1544, 1032, 1, 0),
+    "one_over_16_long_down": (17, 104, 3080, 1, 0),
+    "block_edge_32_chunks": (32, 2056, 600, 3, 0),
+    "one_over_32_exact": (33, 1288, 808, 2, 1),
+    "block_edge_64": (64, 1032, 2312, 1, 0),
+    "one_over_64": (65, 1800, 520, 1, 0),
+    "wide": (7, 8200, 136, 1, 0),
+    "two_row_tiles": (130, 776, 1544, 2, 0),
+    "two_row_tiles_exact": (130, 776, 1544, 2, 1),
+    "long_weight_gradients": (2056, 136, 200, 1, 0),
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_few_tiles(name):
+    import torch
+    from paper_2301_08984_amd.runner import FfnCase
+    T, dm, dh, k, flags = CASES[name]
+    inp = make_ffn_inputs(seed=4000 + T, T=T, dm=dm, dh=dh, lo=0, hi=dh, act="gelu")
+    fc = FfnCase(inp, act="gelu")
+    d = fc.desc(0, dh, k, flags)
+    print(f"few tiles {name}", flush=True)
+    fc.fwd(d, poison=True)
+    fc.bwd(d, poison=True)
+    torch.cuda.synchronize()
+    p = orc.FfnProblem(inp["X"], inp["W1"], inp["b1"], inp["W2"], inp["b2"], orc.ACT_GELU_TANH)
+    g = orc.ffn_backward(p, inp["dY"].astype(np.float64), 0, dh)
+    g["Y"] = orc.ffn_forward(p, 0, dh)
+    names = ("Y", "dX", "dW1", "db1", "dW2", "db2")
+    for n in names:
+        assert rel_err(fc.host(n), g[n]) <= 2e-2, n
+    eager = {n: getattr(fc, n).clone() for n in names}
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=side):
+        fc.fwd(d)
+        fc.bwd(d)
+    for rep in range(2):
+        for n in names:
+            getattr(fc, n).fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        for n in names:
+            assert torch.equal(getattr(fc, n), eager[n]), (n, rep)
