@@ -482,10 +482,8 @@ __global__ __launch_bounds__(256) void bwd_wave_kernel(KP p) {
   constexpr int LDS_ELEMS = dq_wave_lds_elems<D, NG>() > dkdv_wave_lds_elems<D, NG>() ? dq_wave_lds_elems<D, NG>()
                                                                                        : dkdv_wave_lds_elems<D, NG>();
   __shared__ __attribute__((aligned(16))) uint16_t smem[LDS_ELEMS];
-  const int units = gridDim.y * gridDim.z;
-  const int lin = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-  const int pos = lin / units, unit = lin % units;
-  const int by = unit % gridDim.y, bz_ = unit / gridDim.y;
+  const BlockId blk = CAUSAL ? causal_block_id(true) : xcd_block_id(false);
+  const int pos = blk.x, by = blk.y, bz_ = blk.z;
   if ((pos & 1) == 0) dkdv_wave_block<D, BIAS, CAUSAL, NG>(p, smem, pos >> 1, by, bz_);
   else dq_wave_block<D, BIAS, CAUSAL, NG>(p, smem, pos >> 1, by, bz_);
 }

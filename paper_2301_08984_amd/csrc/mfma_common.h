@@ -197,6 +197,64 @@ struct BiasTile {
   __device__ uint2 read(int r, int col) const { return *(const uint2*)(lds + r * BIAS_LD + col); }
 };
 
+// Block order of launches whose blocks of a (row, head) unit differ in work (causal), x counting from the
+// heaviest.  The XCDs are dealt the work-groups round-robin, and inside an XCD the dispatcher deals the
+// first 32 out one per compute unit and then starts over, so both the share of an XCD and the company
+// a work-group gets on its compute unit follow from the launch position:
+//  - every XCD gets units / 8 whole units, whose K / V (or Q / dO) stay in its L2; the blocks of the units
+//    left over are dealt round-robin, 4, 2 and 1 of those units at a time, so that a unit is spread over
+//    2, 4 or 8 XCDs in equal parts (contiguous pieces gave one XCD the heavy half of a unit and the next
+//    one the light half);
+//  - an XCD takes its blocks heaviest first, the units' blocks of one rank next to each other;
+//  - with 32 to 64 blocks, and two to a compute unit (`pairs`), the heaviest stay alone and the others are
+//    paired medium with light.
+// Any order gives the same results.  Causal forward of 12 heads x 12288 x 128: 568 -> 457 us, backward 2.69 ->
+// 2.23 ms; 12 x 4000 x 128: 102 -> 77 us (before: heaviest first in contiguous pieces, xcd_block_id).
+__device__ inline BlockId causal_block_id(bool pairs) {
+  constexpr int NX = 8, NCU = 32;
+  const int gx = gridDim.x, units = gridDim.y * gridDim.z, n = gx * units;
+  const int lin = blockIdx.x + gx * (blockIdx.y + gridDim.y * blockIdx.z), xcd = lin % NX, idx = lin / NX;
+  const int count = (n - xcd + NX - 1) / NX;
+  int at = idx;  // rank in the XCD's order
+  if (pairs && count > NCU && count <= 2 * NCU) {
+    const int m = count - NCU;
+    at = idx < m ? NCU - m + idx : idx < NCU ? idx - m : count - 1 - (idx - NCU);
+  }
+  // the whole units' blocks and the dealt ones, mixed in proportion; then the dealt ones by group
+  const int own = units / NX;
+  int over = count - own * gx, unit, x;
+  auto before = [&](int pos, int part, int all) { return (int)((int64_t)pos * part / all); };
+  int lo = before(at, over, count);
+  if (before(at + 1, over, count) == lo) {
+    const int f = at - lo;
+    x = f / own;
+    unit = xcd * own + f % own;
+  } else {
+    int first = own * NX, start = 0;  // first unit of the group, XCD at which its dealing starts
+    unit = first;
+    x = 0;
+    for (int g = 4; g >= 1; g >>= 1) {
+      if (!(units & g)) continue;
+      const int place = (xcd - start + NX) % NX, here = (g * gx - place + NX - 1) / NX;  // blocks of the group on this XCD
+      const int taken = before(lo, here, over);
+      if (here == over || before(lo + 1, here, over) != taken) {
+        unit = first + place % g;
+        x = taken * (NX / g) + place / g;
+        break;
+      }
+      lo -= taken;
+      over -= here;
+      first += g;
+      start = (start + g * gx) % NX;
+    }
+  }
+  BlockId b;
+  b.x = x;
+  b.y = unit % (int)gridDim.y;
+  b.z = unit / (int)gridDim.y;
+  return b;
+}
+
 __device__ inline int key_of(int v, int hl) { return 8 * (v >> 2) + 4 * hl + (v & 3); }
 
 // Forward epilogue for one 32-column block `db` of a query's output (lane = query, registers =
@@ -349,8 +407,24 @@ inline void dispatch_bias(const KP& p, F f) {
 enum WgShape { WG_4x1, WG_4x2, WG_2x4 };
 inline WgShape wg_shape(const KP& p) {
   const int64_t wgs = (int64_t)((p.S + 127) / 128) * p.share_units;
-  if (wgs >= 512 || p.S < 512) return WG_4x1;
-  if (wgs >= 256) return WG_4x2;
+  const bool causal = p.mask_kind == 1;
+  if (p.bias_kind == 0 && p.D >= 64) {
+    // Where the lines lie (measured on 40 shapes each, forward and backward): at head size 128 the 4x1
+    // kernels are a family of their own (fast_fwd128.hip) that beats 4x2 at any fill (12 x 4000: 325 us
+    // backward against 389), and without a mask already below one work-group per compute unit (8 x 3500: 68
+    // against 77 us forward); short rows leave the chip to fewer, longer work-groups unless the smallest
+    // shape is used (4 x 10 x 400: 53 -> 35 us backward, 12 heads x 450: 49 -> 20), which loses its edge
+    // near 160 work-groups, 128 without a mask.
+    if (p.S < 512) {
+      if (wgs >= (causal ? 168 : 128)) return WG_4x1;
+    } else {
+      if (wgs >= (p.D == 128 ? (causal ? 256 : 192) : 512)) return WG_4x1;
+      if (wgs >= (causal ? 256 : 192)) return WG_4x2;
+    }
+  } else {
+    if (wgs >= 512 || p.S < 512) return WG_4x1;
+    if (wgs >= 256) return WG_4x2;
+  }
   // the kernels of the smallest shape read the bias four aligned columns at a time
   if (p.bias_kind == 1 && (p.S & 3)) return WG_4x2;
   // the kernels of the smallest shape address one (row, head) slice with 32-bit buffer offsets
