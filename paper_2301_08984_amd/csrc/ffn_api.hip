@@ -114,9 +114,9 @@ void drain() {
 #define FF_LAUNCH(kind, expr, what) FF_LAUNCH_ON(st, kind, expr, what)
 
 // A helper stream per device (default priority, created on first use under a lock, kept until the
-// process ends): dW2 = H^T dY needs only H, and the bias gradients only dY or dZ, so they are forked
-// onto the helper stream, run beside the products of the caller's stream -- dZ = (dY W2^T) act'(Z)
-// has too few tiles to fill the chip -- and are joined back before the next chunk overwrites H and
+// process ends): dW2 = H^T dY needs only H (and the column sums only dY or dZ), so where it pays (see
+// ss_ffn_bwd) it is forked onto the helper stream, runs beside the products of the caller's stream and
+// is joined back before the next chunk overwrites H and
 // dZ, and before the call returns.  The fork and join events belong to ONE call (created when it
 // starts, released when it returns; the runtime keeps a released event alive until the work that
 // waits on it has passed), so calls from several host threads or on several caller streams share
@@ -252,7 +252,18 @@ int ss_ffn_bwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
   const ssa::GemmPlan plan_w1 = ssa::gemm_plan_tiled(d->dm, n, d->T), plan_w2 = ssa::gemm_plan_tiled(n, d->dm, d->T);
   SplitScratch scratch(st, plan_up.split > 1 || plan_dh.split > 1 || plan_w1.split > 1 || plan_w2.split > 1 ||
                                (!exact && ssa::gemm_plan_tiled(d->T, d->dm, n).split > 1));
-  Side side_obj(!g_on);  // per-kernel timing wants the kernels one at a time
+  // The helper stream costs some 10 us of waits between the streams, and two products at once that each
+  // fill the chip get in each other's way (8192 tokens x 12288 x 6144: 5.5 ms against 5.1 in turn), so dW2 goes
+  // beside dZ only where dZ leaves part of the chip idle, if need be with the tiles that leave more of
+  // it (2048 tokens, chunks of 3072: 192 tiles of 256 x 128 instead of 256 of 128 x 192).  Per-kernel timing wants
+  // the kernels one at a time.
+  int nc0, nc1;
+  chunk(d, 0, &nc0, &nc1);
+  const ssa::GemmShape fit = ssa::gemm_shape(d->T, nc1 - nc0, d->dm, plan_dh.split, false);
+  const ssa::GemmShape loose = ssa::gemm_shape(d->T, nc1 - nc0, d->dm, plan_dh.split, true);
+  const bool beside_fit = fit.idle >= 0.1 && fit.idle * fit.round >= 1.6;
+  const bool beside_loose = !beside_fit && loose.idle >= 0.2 && loose.idle * loose.round >= 8. && loose.cost * 5 <= fit.cost * 6;
+  Side side_obj(!g_on && (beside_fit || beside_loose));
   Side* side = side_obj.ok ? &side_obj : nullptr;
   bool pending = false;  // work on the helper stream that the caller's stream has not waited for yet
   // run `launch` on the helper stream after everything enqueued on the caller's stream so far
@@ -268,7 +279,9 @@ int ss_ffn_bwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
   // a failed launch still leaves the caller's stream ordered after whatever runs on the helper stream
 #undef FF_ON_ERROR
 #define FF_ON_ERROR ((void)join())
-  if (db2) {
+  // the bias gradients ride on the weight-gradient products that read dY and dZ anyway, unless those are
+  // cut into parts
+  if (db2 && plan_w2.split > 1) {
     if (fork()) {
       pending = true;
       FF_LAUNCH_ON(side->s, SS_FK_COLSUM, ssa::launch_colsum(dY, d->ld_x, d->T, d->dm, db2, side->s), "db2");
@@ -292,6 +305,7 @@ int ss_ffn_bwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
     ssa::GemmArgs gw2 = gemm(Hc, w.ldh, dY, d->ld_x, nc, d->dm, d->T);
     gw2.out = (uint16_t*)dW2 + (int64_t)a * d->ld_w2; gw2.ldo = d->ld_w2;
     scratch.set(gw2, plan_w2, 1);
+    if (plan_w2.split == 1 && c == 0) gw2.colsum = (uint16_t*)db2;
     if (fork()) {
       pending = true;
       FF_LAUNCH_ON(side->s, SS_FK_DW2, ssa::launch_gemm(gw2, true, false, ssa::EPI_STORE, side->s), "dW2 = H^T dY");
@@ -302,9 +316,11 @@ int ss_ffn_bwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
     ssa::GemmArgs dh = gemm(dY, d->ld_x, W2p + (int64_t)a * d->ld_w2, d->ld_w2, d->T, nc, d->dm);
     dh.mul = Dc; dh.ldm = w.ldh; dh.out = Dc; dh.ldo = w.ldh;
     scratch.set(dh, plan_dh, 0);
+    dh.narrow = side && beside_loose;
     FF_LAUNCH(SS_FK_DH, ssa::launch_gemm(dh, false, true, ssa::EPI_MUL, st), "dZ = (dY W2^T) act'(Z)");
     // db1[a:b] = column sums of dZ_c
-    if (fork()) {
+    if (plan_w1.split == 1) {
+    } else if (fork()) {
       pending = true;
       FF_LAUNCH_ON(side->s, SS_FK_COLSUM, ssa::launch_colsum(Dc, w.ldh, d->T, nc, (uint16_t*)db1 + a, side->s), "db1");
     } else {
@@ -314,6 +330,7 @@ int ss_ffn_bwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
     ssa::GemmArgs gw1 = gemm(X, d->ld_x, Dc, w.ldh, d->dm, nc, d->T);
     gw1.out = (uint16_t*)dW1 + a; gw1.ldo = d->ld_w1;
     scratch.set(gw1, plan_w1, 0);
+    if (plan_w1.split == 1) gw1.colsum = (uint16_t*)db1 + a;
     FF_LAUNCH(SS_FK_DW1, ssa::launch_gemm(gw1, true, false, ssa::EPI_STORE, st), "dW1 = X^T dZ");
     // dX += dZ_c W1[:, a:b]^T; the last chunk writes dX
     ssa::GemmArgs gx = gemm(Dc, w.ldh, W1p + a, d->ld_w1, d->T, d->dm, nc);

@@ -28,7 +28,9 @@ struct GemmArgs {
   int64_t ldm;
   float* acc32;  // ceil(M/256) * ceil(N/256) tiles of 256 x 256 fp32, in the kernel's own order
   int accumulate, last, act;
+  uint16_t* colsum;  // EPI_STORE: if given (split = 1 only), colsum[n] (bf16) = sum over k of B[k][n]
   // how the product is cut up (gemm_plan)
+  int narrow;          // tiled kernel: no 192-wide tiles
   int cols;            // 0: the tiled kernel; 64 or 32: the few-rows kernel, that many columns per work-group
   int split;           // parts of the contraction
   float* parts;        // fp32 partial sums, SPLIT_BYTES, and
@@ -48,6 +50,32 @@ inline GemmPlan gemm_plan_tiled(int M, int N, int K) {
   const int by_tiles = tiles > SPLIT_TILES ? 1 : (int)(SPLIT_TILES / tiles), by_depth = K / 512;
   const int p = by_tiles < by_depth ? by_tiles : by_depth;
   return {0, p < 2 ? 1 : p > 16 ? 16 : p};
+}
+// Tile shape of a product.  An output element is the same chain of MFMA steps whatever tile it falls into, so
+// the shape goes by the sizes: the one that needs the least time for its rounds of one work-group per
+// compute unit (256), a round of 256 x 128 tiles being 100 (168 us at a depth of 12288, measured; per
+// element 128 x 128 takes 1.33, 128 x 192 1.13 and 256 x 192 1.07 times as long, the last two longer on short
+// contractions).  Products cut into parts use 128 x 128.  `narrow`: no 192-wide tiles (a sum that continues
+// from chunk to chunk has no such variant).  2048 x 6144 x 12288 (384 tiles of 256 x 128, one and a half
+// rounds): 304 -> 259 us; 3000 x 3000 x 3000: 105 -> 77.
+enum GemmTile { TILE_256x128, TILE_128x128, TILE_128x192, TILE_256x192 };
+struct GemmShape {
+  GemmTile tile;
+  int cost;      // time in hundredths of a round of 256 x 128 tiles
+  double idle;   // part of the chip that the last round leaves idle
+  double round;  // us of a round
+};
+inline GemmShape gemm_shape(int M, int N, int K, int split, bool narrow) {
+  constexpr int COST[4] = {100, 66, 85, 160}, BM[4] = {256, 128, 128, 256}, BN[4] = {128, 128, 192, 192};
+  GemmShape best{TILE_256x128, 0, 0., 0.};
+  for (int t = 0; t < 4; ++t) {
+    if ((split > 1 && t != TILE_128x128) || (narrow && BN[t] == 192)) continue;
+    const int64_t n = (int64_t)((M + BM[t] - 1) / BM[t]) * ((N + BN[t] - 1) / BN[t]) * split, rounds = (n + 255) / 256;
+    const int64_t cost = rounds * COST[t] * (BN[t] == 192 ? K + 160 : K) / K;
+    if (best.cost && cost >= best.cost) continue;
+    best = {(GemmTile)t, (int)(cost < 1000000 ? cost : 1000000), 1. - n / (256. * rounds), 0.0075 * COST[t] * K / (64. * split)};
+  }
+  return best;
 }
 // A of at most 64 rows, neither operand transposed.  The few-rows kernel starts faster (1 x 768 x 768: 5 us
 // against 9), the tiled kernel streams a large B faster (64 x 6144 x 12288: 41 us against 57, one row 36

@@ -40,9 +40,16 @@ typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 //   TR = false (contraction index contiguous in memory): LDS row = rho, 32 KS bytes = 2 KS chunks;
 //        chunk c of row rho sits at slot c ^ ((rho >> 2) & 3) (KS = 2), c ^ ((rho >> 1) & 7) (KS = 4)
 //   TR = true  (rho contiguous in memory): LDS row = k, 128 F bytes = 8 F chunks; chunk c of row k
-//        sits at slot c ^ (4 * (k & 3))
+//        sits at slot c ^ (4 * (k & 3)) (F = 3: see swizzle)
 // With KS = 2 a row of a contraction-contiguous operand is half a cache line per stage, and the
 // compute unit's load path then moves whole lines for half the bytes: KS = 4 for such operands.
+// place of 64-byte block `blk` of row k of a TR operand (k3 = k & 3), and back; three fragments (six blocks)
+// rotate instead
+template <int F>
+__device__ inline int swizzle(int blk, int k3) { return (F & (F - 1)) == 0 ? blk ^ k3 : (blk + k3) % (2 * F); }
+template <int F>
+__device__ inline int unswizzle(int blk, int k3) { return (F & (F - 1)) == 0 ? blk ^ k3 : (blk + 2 * F - k3) % (2 * F); }
+
 template <bool TR, int F, int KS>
 struct Stager {
   static constexpr int BYTES = 2048 * F * KS, NI = F * KS / 2, BK = 16 * KS;
@@ -71,13 +78,13 @@ struct Stager {
         if (t < 2) klimit[t] = ktot_ - 8 * c - 8;  // the chunk depends on the parity of t only
       }
     } else {
-      constexpr int LPR = 8 * F, RPI = 64 / LPR;  // lanes per LDS row, rows per instruction
+      constexpr int LPR = 8 * F;  // 16-byte chunks per LDS row
       step = (int64_t)BK * ld * 2;
       left = (int)(((int64_t)(ktot_ - 1) * ld + rho_tot) * 2);
 #pragma unroll
       for (int t = 0; t < NI; ++t) {
-        const int krow = RPI * (w * NI + t) + lane / LPR;
-        const int c = (lane % LPR) ^ (4 * (krow & 3));
+        const int slot = 64 * (w * NI + t) + lane, krow = slot / LPR, s = slot % LPR;
+        const int c = 4 * unswizzle<F>(s >> 2, krow & 3) + (s & 3);
         lane_off[t] = rho0 + 8 * c + 8 <= rho_tot ? (uint32_t)krow * ld2 + (uint32_t)(rho0 + 8 * c) * 2u : OUTSIDE;
       }
     }
@@ -122,7 +129,7 @@ struct FragReader {
       const int i = lane & 15, bk = lane >> 4, kk = 8 * (bk >> 1) + (i >> 2);
       a0 = (uint32_t)kk * (128u * F) + 32u * (bk & 1) + 8u * (i & 3);
 #pragma unroll
-      for (int f = 0; f < F; ++f) blk[f] = (uint32_t)(((F * wr + f) ^ ((i >> 2) & 3)) << 6);
+      for (int f = 0; f < F; ++f) blk[f] = (uint32_t)swizzle<F>(F * wr + f, (i >> 2) & 3) << 6;
     }
   }
   // fragment f (rho = 32 F wr + 32 f ..) of contraction step ks of the stage at `op`
@@ -160,9 +167,8 @@ constexpr int items_before(int slot, int n, int slots) {
 //        barriers per MFMA.  For products with a contraction-contiguous operand (see Stager).
 //   FI = FJ = 2, KS = 4, NS = 3: 128 x 128 tile, for products with few tiles; the contraction may be cut into
 //        g.split parts (gemm_plan_tiled).  Forward of 127 tokens x 12288 x 6144: 185 -> 92 us.
-//   FI = FJ = 4, KS = 2, NS = 4: 256 x 256 tile, 256 accumulation registers (half the LDS reads and
-//        loads per MFMA of the others); not instantiated: the feed-forward shapes have too few such
-//        tiles to go round.
+//   FI = 2, FJ = 3, KS = 4, NS = 3 and FI = 4, FJ = 3, KS = 2, NS = 4: 128 x 192 and 256 x 192 tiles, for
+//        sizes of which the others leave the last round of work-groups nearly empty (gemm_shape).
 // Stages travel global -> LDS directly, NS - 1 stages ahead of the multiplication, the load
 // instructions spread evenly between the MFMAs (the compute unit's load path moves 64 bytes per
 // cycle, of which the kernel needs 32 to 48), and one barrier per stage, issued with half a step of
@@ -216,6 +222,17 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
   if (EPI == EPI_ACC) frag32 = (f32x4*)g.acc32 + ((int64_t)(tp.mt * ntiles + tp.nt) * 4 + w) * (NM * 4 * 64) + lane;
 
   const int nk = (g.K + 16 * KS - 1) / (16 * KS);
+  // Column sums of B (the bias gradients: B is dY or dZ, on its way through the registers anyway), by the
+  // wavefronts of the first tile row: packed pairs against (1, 1), two instructions per MFMA and under it.
+  // A kernel of their own read B once more (8192 tokens x 12288: 59 us).
+  constexpr bool SUMS = EPI == EPI_STORE;
+  const bf16x2 ones2 = {(__bf16)1.f, (__bf16)1.f};
+  const bool sums = SUMS && g.colsum && m0 == 0 && wm == 0;
+  float csum[SUMS ? FJ : 1];
+  if (SUMS) {
+#pragma unroll
+    for (int j = 0; j < FJ; ++j) csum[SUMS ? j : 0] = 0.f;
+  }
   bf16x8 fa[2][FI], fb[2][FJ];  // fragments of the contraction step being multiplied and of the next one
   // fragment reads of one contraction step in the order of their first use: B 0, A 0 .. FI-1, B 1 .. FJ-1
   auto read_item = [&](const char* st, int item, int ks, int set) {
@@ -231,7 +248,7 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
   // order of their first use) and the scheduler is told to keep every slot together: the matrix
   // cores stall as soon as the instructions between two MFMAs take longer to issue than one MFMA
   // takes to run.
-  auto stage = [&](const char* cur, const char* nxt, char* ldst) {
+  auto stage = [&](auto with_sums, const char* cur, const char* nxt, char* ldst) __attribute__((always_inline)) {
     sa.begin_stage();
     sb.begin_stage();
 #pragma unroll
@@ -246,6 +263,14 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
         asm volatile("" ::: "memory");
       }
       acc[j][i] = mfma(fb[ks & 1][j], fa[ks & 1][i], acc[j][i]);
+      if (decltype(with_sums)::value && i == FI - 1) {
+        if (wm == 0) {
+          union { bf16x8 v; bf16x2 h[4]; } b;
+          b.v = fb[ks & 1][j];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) csum[SUMS ? j : 0] = __builtin_amdgcn_fdot2_f32_bf16(b.h[e], ones2, csum[SUMS ? j : 0], false);
+        }
+      }
 #pragma unroll
       for (int l = 0; l < NL; ++l)
         if (s == slot_of(l, NL, SLOTS)) {
@@ -308,7 +333,7 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
     fetch_all(stage0);
     fetch_all(stage1);
     if (NS == 4) fetch_all(stage2);
-    if constexpr (EPI == EPI_ACC16) {
+    if constexpr (EPI == EPI_ACC16 && FJ != 3) {  // (three-fragment tiles do not continue sums)
      if (g.accumulate && part == 0) {
       // The partial sum of the earlier chunks is the output itself (bf16): read as whole rows (64 FJ
       // contiguous bytes per row), widened, and turned into the register layout through a piece of
@@ -346,16 +371,36 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int item = 0; item < NR; ++item) read_item(stage0, item, 0, 0);
-    for (int kt = s0; kt < s1; kt += NS) {
-      if (NS == 4) {
-        stage(stage0, stage1, stage3);
-        stage(stage1, stage2, stage0);
-        stage(stage2, stage3, stage1);
-        stage(stage3, stage0, stage2);
-      } else {
-        stage(stage0, stage1, stage2);
-        stage(stage1, stage2, stage0);
-        stage(stage2, stage0, stage1);
+    bool plain = true;
+    if constexpr (SUMS) {
+      if (g.colsum && m0 == 0) {
+        plain = false;
+        for (int kt = s0; kt < s1; kt += NS) {
+          if (NS == 4) {
+            stage(std::true_type{}, stage0, stage1, stage3);
+            stage(std::true_type{}, stage1, stage2, stage0);
+            stage(std::true_type{}, stage2, stage3, stage1);
+            stage(std::true_type{}, stage3, stage0, stage2);
+          } else {
+            stage(std::true_type{}, stage0, stage1, stage2);
+            stage(std::true_type{}, stage1, stage2, stage0);
+            stage(std::true_type{}, stage2, stage0, stage1);
+          }
+        }
+      }
+    }
+    if (plain) {
+      for (int kt = s0; kt < s1; kt += NS) {
+        if (NS == 4) {
+          stage(std::false_type{}, stage0, stage1, stage3);
+          stage(std::false_type{}, stage1, stage2, stage0);
+          stage(std::false_type{}, stage2, stage3, stage1);
+          stage(std::false_type{}, stage3, stage0, stage2);
+        } else {
+          stage(std::false_type{}, stage0, stage1, stage2);
+          stage(std::false_type{}, stage1, stage2, stage0);
+          stage(std::false_type{}, stage2, stage0, stage1);
+        }
       }
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
@@ -370,6 +415,14 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
 #pragma unroll
             for (int v = 0; v < 16; ++v) sum[j][i][v] = part == first ? acc[j][i][v] : sum[j][i][v] + acc[j][i][v];
       }
+    }
+  }
+  if (sums) {
+#pragma unroll
+    for (int j = 0; j < FJ; ++j) {
+      const float t = half_sum(csum[SUMS ? j : 0]);
+      const int n = n0 + wn * 32 * FJ + 32 * j + r;
+      if (hl == 0 && n < g.N) g.colsum[n] = f2bf(t);
     }
   }
   if constexpr (SPLIT) {
@@ -452,14 +505,21 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
     // before a buffer is reused.
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    constexpr int TLD = 128 * FJ + 16, LPR = 8 * FJ, RPI = 64 / LPR;
+    constexpr int TLD = 128 * FJ + 16, LPR = 8 * FJ;
+    constexpr int CY = FJ == 3 ? 3 : 1, RPC = 64 * CY / LPR;  // passes of 64 lanes until the columns repeat, rows they cover
     static_assert(32 * TLD <= (NS == 4 ? STAGE_BYTES : STAGE_BYTES / 2), "epilogue staging does not fit");
     char* tb = NS == 4 ? (w == 0 ? stage0 : w == 1 ? stage1 : w == 2 ? stage2 : stage3)
                        : (w == 0 ? stage0 : w == 1 ? stage1 : w == 2 ? stage2 : stage0 + STAGE_BYTES / 2);
-    const int c4 = 4 * (lane % LPR), rsub = lane / LPR;
-    const int n = n0 + wn * 32 * FJ + c4;
-    float bias[4] = {0.f, 0.f, 0.f, 0.f};
-    if ((EPI == EPI_ACT || EPI == EPI_ACC || EPI == EPI_ACC16) && g.bias && n < g.N) unpack4(*(const uint2*)(g.bias + n), bias);
+    int col[CY], rsub[CY];
+    float bias[CY][4];
+#pragma unroll
+    for (int y = 0; y < CY; ++y) {
+      col[y] = 4 * ((64 * y + lane) % LPR);
+      rsub[y] = (64 * y + lane) / LPR;
+      const int n = n0 + wn * 32 * FJ + col[y];
+      bias[y][0] = bias[y][1] = bias[y][2] = bias[y][3] = 0.f;
+      if ((EPI == EPI_ACT || EPI == EPI_ACC || EPI == EPI_ACC16) && g.bias && n < g.N) unpack4(*(const uint2*)(g.bias + n), bias[y]);
+    }
 #pragma unroll
     for (int i = 0; i < FI; ++i) {
 #pragma unroll
@@ -469,11 +529,11 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
           *(f32x4*)(tb + r * TLD + (32 * j + 8 * q + 4 * hl) * 4) =
               f32x4{acc[j][i][4 * q], acc[j][i][4 * q + 1], acc[j][i][4 * q + 2], acc[j][i][4 * q + 3]};
 #pragma unroll
-      for (int it = 0; it < 32 / RPI; ++it) {
-        const int row = RPI * it + rsub, m = m0 + wm * 32 * FI + 32 * i + row;
-        const f32x4 v = *(const f32x4*)(tb + row * TLD + c4 * 4);
+      for (int it = 0; it < 32 / RPC * CY; ++it) {
+        const int y = it % CY, row = RPC * (it / CY) + rsub[y], m = m0 + wm * 32 * FI + 32 * i + row, n = n0 + wn * 32 * FJ + col[y];
+        const f32x4 v = *(const f32x4*)(tb + row * TLD + col[y] * 4);
         if (m >= g.M || n >= g.N) continue;
-        float x[4] = {v[0] + bias[0], v[1] + bias[1], v[2] + bias[2], v[3] + bias[3]};
+        float x[4] = {v[0] + bias[y][0], v[1] + bias[y][1], v[2] + bias[y][2], v[3] + bias[y][3]};
         uint16_t* orow = g.out + (int64_t)m * g.ldo + n;
         if (EPI == EPI_ACT) {
           float h[4], d[4];
@@ -536,6 +596,9 @@ __global__ __launch_bounds__(256) void colsum_kernel(const uint16_t* A, int64_t 
 SS_GEMM_INST(false, false, 0, 4, 2, 4) SS_GEMM_INST(false, false, 2, 4, 2, 4) SS_GEMM_INST(false, false, 4, 4, 2, 4)
 SS_GEMM_INST(false, true, 1, 4, 2, 4) SS_GEMM_INST(false, true, 2, 4, 2, 4) SS_GEMM_INST(false, true, 4, 4, 2, 4)
 SS_GEMM_INST(true, false, 3, 4, 2, 2)
+SS_GEMM_INST(false, false, 0, 2, 3, 4) SS_GEMM_INST(false, false, 4, 2, 3, 4) SS_GEMM_INST(false, true, 1, 2, 3, 4) SS_GEMM_INST(false, true, 4, 2, 3, 4) SS_GEMM_INST(true, false, 3, 2, 3, 4) 
+SS_GEMM_INST(false, false, 0, 4, 3, 2) SS_GEMM_INST(false, false, 4, 4, 3, 2) SS_GEMM_INST(false, true, 1, 4, 3, 2) SS_GEMM_INST(false, true, 4, 4, 3, 2) SS_GEMM_INST(true, false, 3, 4, 3, 2) 
+
 // 128 x 128 tiles for products with few of the large ones
 SS_GEMM_INST(false, false, 0, 2, 2, 4) SS_GEMM_INST(false, false, 2, 2, 2, 4) SS_GEMM_INST(false, false, 4, 2, 2, 4)
 SS_GEMM_INST(false, true, 1, 2, 2, 4) SS_GEMM_INST(false, true, 2, 2, 2, 4) SS_GEMM_INST(false, true, 4, 2, 2, 4)
@@ -550,15 +613,14 @@ hipError_t launch_one(const GemmArgs& g, hipStream_t st) {
   return hipGetLastError();
 }
 
-// An output element is the same chain of MFMA steps whatever tile it falls into, so the tile shape goes
-// by the sizes: when fewer than 160 of the 256 x 128 tiles exist, 128 x 128 tiles, twice as many
-// work-groups at 4/3 of the operand traffic per flop, and those may cut the contraction into parts.  (An
-// accumulated product keeps its M and N from chunk to chunk, so all chunks cut its fp32 partial result
-// into the same tiles.)
 template <bool AT, bool BT, int EPI>
 hipError_t launch_shape(const GemmArgs& g, hipStream_t st) {
-  if ((int64_t)((g.M + 255) / 256) * ((g.N + 127) / 128) < 160 || g.split > 1) return launch_one<AT, BT, EPI, 2, 2, 4>(g, st);
-  return launch_one<AT, BT, EPI, 4, 2, AT ? 2 : 4>(g, st);
+  const bool narrow = g.narrow || EPI == EPI_ACC || (EPI == EPI_ACC16 && g.accumulate);
+  const GemmTile t = gemm_shape(g.M, g.N, g.K, g.split, narrow).tile;
+  if (t == TILE_128x128) return launch_one<AT, BT, EPI, 2, 2, 4>(g, st);
+  if (t == TILE_256x128) return launch_one<AT, BT, EPI, 4, 2, AT ? 2 : 4>(g, st);
+  if constexpr (EPI != EPI_ACC) return t == TILE_128x192 ? launch_one<AT, BT, EPI, 2, 3, 4>(g, st) : launch_one<AT, BT, EPI, 4, 3, 2>(g, st);
+  return hipErrorInvalidValue;
 }
 
 }  // namespace

@@ -1,5 +1,5 @@
-"""Products with few tiles: the few-rows kernel (up to 64 tokens) and contractions that are cut into parts
-over work-groups, against the oracle at the edges of both (token blocks of 16, column tiles of 32, 64
+"""Tile shapes of the feed-forward products: the few-rows kernel (up to 64 tokens), contractions that are cut
+into parts over work-groups, and the 192-wide tiles, against the oracle at the edges of both (token blocks of 16, column tiles of 32, 64
 and 128, parts of uneven length), and bit for bit with the run that has no scratch for the parts (under graph
 capture)."""
 import numpy as np
@@ -23,6 +23,13 @@ CASES = {  # T, dm, dh, k, flags
     "two_row_tiles": (130, 776, 1544, 2, 0),
     "two_row_tiles_exact": (130, 776, 1544, 2, 1),
     "long_weight_gradients": (2056, 136, 200, 1, 0),
+    # tiles of 128 x 192 and of 256 x 192, ragged both ways: hidden activations, outputs, weight gradients
+    "up_128x192": (2100, 72, 2392, 1, 0),
+    "up_256x192": (2990, 72, 3000, 1, 0),
+    "down_128x192": (2100, 2392, 72, 1, 0),
+    "down_256x192": (2990, 3000, 72, 1, 0),
+    "weights_128x192": (40, 2392, 2104, 1, 0),
+    "weights_256x192_chunks": (72, 3000, 5992, 2, 0),
 }
 
 
