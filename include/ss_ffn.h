@@ -20,13 +20,16 @@
  * activations the split frees when hi-lo < 2 dm) and Y and dX are the same bits for every k.
  * dW1, db1, dW2 and db2 are disjoint slices or whole-operator sums and never depend on k.  Only one
  * chunk's hidden activations [T, (hi-lo)/k] are alive at a time, and the backward recomputes them.
+ * (Where those of the whole share need no more than 32 MiB they stand in a buffer that the library holds
+ * on each GPU, unless another stream is using it or the call is being captured into a graph: the products
+ * that do not sum over the hidden columns are then one launch for the share.  The bits are the same.)
  *
  * All pointers are DEVICE pointers unless said otherwise; the descriptor and size outputs are HOST
  * memory.  The library allocates no device memory and never synchronises the host; the work is
- * enqueued on the caller's stream, except that ss_ffn_bwd forks dW2 and the bias gradients onto a
+ * enqueued on the caller's stream, except that ss_ffn_bwd may fork dW2 and the bias gradients onto a
  * helper stream of the library's own (one per device, default priority, created on first use) and
  * joins it back into the caller's stream with events before the call returns: to the caller the
- * call is ordered on its stream like any other.  That stream is the only state the library keeps;
+ * call is ordered on its stream like any other.  That stream and the buffer are the only state the library keeps;
  * the fork / join events are created and released per call, so calls from several host threads or
  * on several caller streams of one device are independent (their helper work is merely queued on
  * the same helper stream).  Error codes are those of ss_attn.h.

@@ -531,7 +531,7 @@ int ss_attn_bwd(const ss_attn_desc* d, const void* Q, const void* K, const void*
     // do not depend on k: run the fewest chunks whose scratch fits what the caller handed over, or
     // else the library's buffer.  Backward of 4 rows x 6 heads x 215 queries, D = 128, k = 4: 131 -> 36 us;
     // pair attention of 18 rows x 8 heads x 472, k = 16, forward and backward: 729 -> 113 us.
-    const int kw = fewest_chunks(d, fam, workspace_bytes), ks = fewest_chunks(d, fam, ssa::SHARED_BYTES);
+    const int kw = fewest_chunks(d, fam, workspace_bytes), ks = fewest_chunks(d, fam, (size_t)SS_ATTN_STATIC_SCRATCH_BYTES);
     void* own = ks < kw ? shared.take(st) : nullptr;
     if (own) ws = (char*)own;
     run.k = own ? ks : kw;

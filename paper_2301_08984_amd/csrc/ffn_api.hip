@@ -158,19 +158,52 @@ ssa::GemmArgs gemm(const void* A, int64_t lda, const void* B, int64_t ldb, int M
   return g;
 }
 
-// The library's scratch for split contractions, taken if any product of the call is split: one half for the
-// caller's stream, one for the helper stream.
-static_assert(2 * ssa::SPLIT_BYTES <= ssa::SHARED_BYTES && 2 * ssa::SPLIT_TILES <= ssa::SHARED_COUNTERS, "split scratch");
-struct SplitScratch {
+// The library's scratch, for split contractions (one half of SPLIT_BYTES for the caller's stream, one for
+// the helper stream) and for the hidden activations of a whole small share.
+constexpr size_t HIDDEN_BYTES = 32u << 20;
+static_assert(HIDDEN_BYTES + 2 * ssa::SPLIT_BYTES <= ssa::SHARED_BYTES && 2 * ssa::SPLIT_TILES <= ssa::SHARED_COUNTERS, "library scratch");
+struct Scratch {
   ssa::SharedUse use;
   char* base = nullptr;
-  SplitScratch(hipStream_t st, bool want) { if (want) base = (char*)use.take(st); }
+  Scratch(hipStream_t st, bool want) { if (want) base = (char*)use.take(st); }
   void set(ssa::GemmArgs& g, ssa::GemmPlan plan, int half) const {
     g.cols = plan.cols;
     g.split = plan.split;
     if (!base || plan.split < 2) return;
-    g.parts = (float*)(base + half * ssa::SPLIT_BYTES);
+    g.parts = (float*)(base + HIDDEN_BYTES + half * ssa::SPLIT_BYTES);
     g.counters = use.counters() + half * ssa::SPLIT_TILES;
+  }
+};
+
+// Where the products over the hidden columns [a, b) of a share keep H and D: one chunk's in the caller's
+// workspace, and the chunks in turn; or, if the share's fit the library's scratch (and nobody else is using
+// it), all of them there, so that the products that produce or consume H and D are one launch for the
+// share (their elements are the same sums either way) and only the sums over the hidden columns, Y and
+// dX, go chunk by chunk.  Chunks of a small share cannot fill the chip: backward of 366 x 1264 x 3384, k = 4:
+// 295 -> 137 us.
+struct Hidden {
+  bool whole;
+  char *H, *D;
+  int64_t ld;
+  int groups;  // passes over the columns
+  Hidden(const ss_ffn_desc* d, const Ws& w, char* ws, const Scratch& scratch, bool backward) {
+    const int64_t n8 = (d->hi - d->lo + 7) & ~7;
+    const size_t one = align256((size_t)d->T * n8 * 2);
+    whole = scratch.base && d->k > 1 && one * (backward ? 2 : 1) <= HIDDEN_BYTES;
+    H = whole ? scratch.base : ws + w.H;
+    D = whole ? scratch.base + one : ws + w.D;
+    ld = whole ? n8 : w.ldh;
+    groups = whole ? 1 : d->k;
+  }
+  static bool wanted(const ss_ffn_desc* d, bool backward) {
+    return d->k > 1 && align256((size_t)d->T * ((d->hi - d->lo + 7) & ~7) * 2) * (backward ? 2 : 1) <= HIDDEN_BYTES;
+  }
+  // columns and chunks of a pass
+  void pass(const ss_ffn_desc* d, int g, int* a, int* b, int* c0, int* c1) const {
+    *c0 = whole ? 0 : g;
+    *c1 = whole ? d->k : g + 1;
+    if (whole) { *a = d->lo; *b = d->hi; }
+    else chunk(d, g, a, b);
   }
 };
 
@@ -211,23 +244,28 @@ int ss_ffn_fwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
   const bool exact = (d->flags & SS_FFN_FLAG_EXACT_SUM) != 0;
   const int n = d->hi - d->lo;
   const ssa::GemmPlan plan_up = ssa::gemm_plan(d->T, n, d->dm);
-  SplitScratch scratch(st, plan_up.split > 1 || (!exact && ssa::gemm_plan(d->T, d->dm, n).split > 1));
-  for (int c = 0; c < d->k; ++c) {
-    int a, b;
-    chunk(d, c, &a, &b);
-    const int nc = b - a;
-    if (nc <= 0) continue;
-    // H_c = act(X W1[:, a:b] + b1[a:b])
-    ssa::GemmArgs up = gemm(X, d->ld_x, W1p + a, d->ld_w1, d->T, nc, d->dm);
-    up.bias = (const uint16_t*)b1 + a; up.out = (uint16_t*)(ws + w.H); up.ldo = w.ldh; up.act = d->act;
+  Scratch scratch(st, Hidden::wanted(d, false) || plan_up.split > 1 || (!exact && ssa::gemm_plan(d->T, d->dm, n).split > 1));
+  const Hidden hid(d, w, ws, scratch, false);
+  for (int g = 0; g < hid.groups; ++g) {
+    int a, b, c0, c1;
+    hid.pass(d, g, &a, &b, &c0, &c1);
+    if (b <= a) continue;
+    // H = act(X W1[:, a:b] + b1[a:b])
+    ssa::GemmArgs up = gemm(X, d->ld_x, W1p + a, d->ld_w1, d->T, b - a, d->dm);
+    up.bias = (const uint16_t*)b1 + a; up.out = (uint16_t*)hid.H; up.ldo = hid.ld; up.act = d->act;
     scratch.set(up, plan_up, 0);
     FF_LAUNCH(SS_FK_UP, ssa::launch_gemm(up, false, false, ssa::EPI_ACT, st), "H = act(X W1 + b1)");
-    // Y += H_c W2[a:b, :]; the last chunk adds b2 and writes Y
-    ssa::GemmArgs dn = gemm(ws + w.H, w.ldh, W2p + (int64_t)a * d->ld_w2, d->ld_w2, d->T, d->dm, nc);
-    dn.acc32 = (float*)(ws + w.acc); dn.accumulate = c > 0; dn.last = c == d->k - 1;
-    dn.bias = dn.last ? (const uint16_t*)b2 : nullptr; dn.out = (uint16_t*)Y; dn.ldo = d->ld_x;
-    if (!exact) scratch.set(dn, ssa::gemm_plan(d->T, d->dm, nc), 0);
-    FF_LAUNCH(SS_FK_DOWN, ssa::launch_gemm(dn, false, false, exact ? ssa::EPI_ACC : ssa::EPI_ACC16, st), "Y += H W2");
+    for (int c = c0; c < c1; ++c) {
+      int ca, cb;
+      chunk(d, c, &ca, &cb);
+      if (cb <= ca) continue;
+      // Y += H_c W2[ca:cb, :]; the last chunk adds b2 and writes Y
+      ssa::GemmArgs dn = gemm((const uint16_t*)hid.H + (ca - a), hid.ld, W2p + (int64_t)ca * d->ld_w2, d->ld_w2, d->T, d->dm, cb - ca);
+      dn.acc32 = (float*)(ws + w.acc); dn.accumulate = c > 0; dn.last = c == d->k - 1;
+      dn.bias = dn.last ? (const uint16_t*)b2 : nullptr; dn.out = (uint16_t*)Y; dn.ldo = d->ld_x;
+      if (!exact) scratch.set(dn, ssa::gemm_plan(d->T, d->dm, cb - ca), 0);
+      FF_LAUNCH(SS_FK_DOWN, ssa::launch_gemm(dn, false, false, exact ? ssa::EPI_ACC : ssa::EPI_ACC16, st), "Y += H W2");
+    }
   }
   return SS_OK;
 }
@@ -244,21 +282,21 @@ int ss_ffn_bwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
   char* ws = (char*)workspace;
   const uint16_t* W1p = (const uint16_t*)W1;
   const uint16_t* W2p = (const uint16_t*)W2;
-  uint16_t* Hc = (uint16_t*)(ws + w.H);
-  uint16_t* Dc = (uint16_t*)(ws + w.D);
   const bool exact = (d->flags & SS_FFN_FLAG_EXACT_SUM) != 0;
   const int n = d->hi - d->lo;
   const ssa::GemmPlan plan_up = ssa::gemm_plan(d->T, n, d->dm), plan_dh = ssa::gemm_plan_tiled(d->T, n, d->dm);
   const ssa::GemmPlan plan_w1 = ssa::gemm_plan_tiled(d->dm, n, d->T), plan_w2 = ssa::gemm_plan_tiled(n, d->dm, d->T);
-  SplitScratch scratch(st, plan_up.split > 1 || plan_dh.split > 1 || plan_w1.split > 1 || plan_w2.split > 1 ||
-                               (!exact && ssa::gemm_plan_tiled(d->T, d->dm, n).split > 1));
+  Scratch scratch(st, Hidden::wanted(d, true) || plan_up.split > 1 || plan_dh.split > 1 || plan_w1.split > 1 || plan_w2.split > 1 ||
+                          (!exact && ssa::gemm_plan_tiled(d->T, d->dm, n).split > 1));
+  const Hidden hid(d, w, ws, scratch, true);
+  uint16_t *Hp = (uint16_t*)hid.H, *Dp = (uint16_t*)hid.D;
   // The helper stream costs some 10 us of waits between the streams, and two products at once that each
   // fill the chip get in each other's way (8192 tokens x 12288 x 6144: 5.5 ms against 5.1 in turn), so dW2 goes
   // beside dZ only where dZ leaves part of the chip idle, if need be with the tiles that leave more of
   // it (2048 tokens, chunks of 3072: 192 tiles of 256 x 128 instead of 256 of 128 x 192).  Per-kernel timing wants
   // the kernels one at a time.
-  int nc0, nc1;
-  chunk(d, 0, &nc0, &nc1);
+  int nc0, nc1, unused0, unused1;
+  hid.pass(d, 0, &nc0, &nc1, &unused0, &unused1);
   const ssa::GemmShape fit = ssa::gemm_shape(d->T, nc1 - nc0, d->dm, plan_dh.split, false);
   const ssa::GemmShape loose = ssa::gemm_shape(d->T, nc1 - nc0, d->dm, plan_dh.split, true);
   const bool beside_fit = fit.idle >= 0.1 && fit.idle * fit.round >= 1.6;
@@ -289,23 +327,23 @@ int ss_ffn_bwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
       FF_LAUNCH(SS_FK_COLSUM, ssa::launch_colsum(dY, d->ld_x, d->T, d->dm, db2, st), "db2");
     }
   }
-  for (int c = 0; c < d->k; ++c) {
-    int a, b;
-    chunk(d, c, &a, &b);
+  for (int g = 0; g < hid.groups; ++g) {
+    int a, b, c0, c1;
+    hid.pass(d, g, &a, &b, &c0, &c1);
     const int nc = b - a;
     if (nc <= 0) continue;
-    // the helper stream still reads H and dZ of the previous chunk
+    // the helper stream still reads H and dZ of the previous pass
     if (join() != hipSuccess) return hip_fail(hipGetLastError(), "join");
     // recompute: H_c = act(Z_c), D_c = act'(Z_c)
     ssa::GemmArgs up = gemm(X, d->ld_x, W1p + a, d->ld_w1, d->T, nc, d->dm);
-    up.bias = (const uint16_t*)b1 + a; up.out = Hc; up.out2 = Dc; up.ldo = w.ldh; up.act = d->act;
+    up.bias = (const uint16_t*)b1 + a; up.out = Hp; up.out2 = Dp; up.ldo = hid.ld; up.act = d->act;
     scratch.set(up, plan_up, 0);
     FF_LAUNCH(SS_FK_UP, ssa::launch_gemm(up, false, false, ssa::EPI_ACT, st), "recompute H, act'(Z)");
     // dW2[a:b, :] = H_c^T dY, beside the products that follow when the helper stream is there
-    ssa::GemmArgs gw2 = gemm(Hc, w.ldh, dY, d->ld_x, nc, d->dm, d->T);
+    ssa::GemmArgs gw2 = gemm(Hp, hid.ld, dY, d->ld_x, nc, d->dm, d->T);
     gw2.out = (uint16_t*)dW2 + (int64_t)a * d->ld_w2; gw2.ldo = d->ld_w2;
     scratch.set(gw2, plan_w2, 1);
-    if (plan_w2.split == 1 && c == 0) gw2.colsum = (uint16_t*)db2;
+    if (plan_w2.split == 1 && g == 0) gw2.colsum = (uint16_t*)db2;
     if (fork()) {
       pending = true;
       FF_LAUNCH_ON(side->s, SS_FK_DW2, ssa::launch_gemm(gw2, true, false, ssa::EPI_STORE, side->s), "dW2 = H^T dY");
@@ -314,7 +352,7 @@ int ss_ffn_bwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
     }
     // dZ_c = (dY W2[a:b,:]^T) * D_c, in place over D_c
     ssa::GemmArgs dh = gemm(dY, d->ld_x, W2p + (int64_t)a * d->ld_w2, d->ld_w2, d->T, nc, d->dm);
-    dh.mul = Dc; dh.ldm = w.ldh; dh.out = Dc; dh.ldo = w.ldh;
+    dh.mul = Dp; dh.ldm = hid.ld; dh.out = Dp; dh.ldo = hid.ld;
     scratch.set(dh, plan_dh, 0);
     dh.narrow = side && beside_loose;
     FF_LAUNCH(SS_FK_DH, ssa::launch_gemm(dh, false, true, ssa::EPI_MUL, st), "dZ = (dY W2^T) act'(Z)");
@@ -322,22 +360,27 @@ int ss_ffn_bwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
     if (plan_w1.split == 1) {
     } else if (fork()) {
       pending = true;
-      FF_LAUNCH_ON(side->s, SS_FK_COLSUM, ssa::launch_colsum(Dc, w.ldh, d->T, nc, (uint16_t*)db1 + a, side->s), "db1");
+      FF_LAUNCH_ON(side->s, SS_FK_COLSUM, ssa::launch_colsum(Dp, hid.ld, d->T, nc, (uint16_t*)db1 + a, side->s), "db1");
     } else {
-      FF_LAUNCH(SS_FK_COLSUM, ssa::launch_colsum(Dc, w.ldh, d->T, nc, (uint16_t*)db1 + a, st), "db1");
+      FF_LAUNCH(SS_FK_COLSUM, ssa::launch_colsum(Dp, hid.ld, d->T, nc, (uint16_t*)db1 + a, st), "db1");
     }
     // dW1[:, a:b] = X^T dZ_c
-    ssa::GemmArgs gw1 = gemm(X, d->ld_x, Dc, w.ldh, d->dm, nc, d->T);
+    ssa::GemmArgs gw1 = gemm(X, d->ld_x, Dp, hid.ld, d->dm, nc, d->T);
     gw1.out = (uint16_t*)dW1 + a; gw1.ldo = d->ld_w1;
     scratch.set(gw1, plan_w1, 0);
     if (plan_w1.split == 1) gw1.colsum = (uint16_t*)db1 + a;
     FF_LAUNCH(SS_FK_DW1, ssa::launch_gemm(gw1, true, false, ssa::EPI_STORE, st), "dW1 = X^T dZ");
-    // dX += dZ_c W1[:, a:b]^T; the last chunk writes dX
-    ssa::GemmArgs gx = gemm(Dc, w.ldh, W1p + a, d->ld_w1, d->T, d->dm, nc);
-    gx.acc32 = (float*)(ws + w.acc); gx.accumulate = c > 0; gx.last = c == d->k - 1;
-    gx.out = (uint16_t*)dX; gx.ldo = d->ld_x;
-    if (!exact) scratch.set(gx, ssa::gemm_plan_tiled(d->T, d->dm, nc), 0);
-    FF_LAUNCH(SS_FK_DX, ssa::launch_gemm(gx, false, true, exact ? ssa::EPI_ACC : ssa::EPI_ACC16, st), "dX += dZ W1^T");
+    for (int c = c0; c < c1; ++c) {
+      int ca, cb;
+      chunk(d, c, &ca, &cb);
+      if (cb <= ca) continue;
+      // dX += dZ_c W1[:, ca:cb]^T; the last chunk writes dX
+      ssa::GemmArgs gx = gemm(Dp + (ca - a), hid.ld, W1p + ca, d->ld_w1, d->T, d->dm, cb - ca);
+      gx.acc32 = (float*)(ws + w.acc); gx.accumulate = c > 0; gx.last = c == d->k - 1;
+      gx.out = (uint16_t*)dX; gx.ldo = d->ld_x;
+      if (!exact) scratch.set(gx, ssa::gemm_plan_tiled(d->T, d->dm, cb - ca), 0);
+      FF_LAUNCH(SS_FK_DX, ssa::launch_gemm(gx, false, true, exact ? ssa::EPI_ACC : ssa::EPI_ACC16, st), "dX += dZ W1^T");
+    }
   }
   if (join() != hipSuccess) return hip_fail(hipGetLastError(), "join");
   return SS_OK;

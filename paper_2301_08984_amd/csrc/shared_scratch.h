@@ -7,7 +7,7 @@
 
 namespace ssa {
 
-constexpr size_t SHARED_BYTES = 32u << 20;
+constexpr size_t SHARED_BYTES = 64u << 20;
 constexpr int SHARED_COUNTERS = 512;  // zero whenever no kernel that uses them is running
 
 struct Shared {
