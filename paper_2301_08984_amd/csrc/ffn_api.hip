@@ -175,36 +175,52 @@ struct Scratch {
   }
 };
 
-// Where the products over the hidden columns [a, b) of a share keep H and D: one chunk's in the caller's
-// workspace, and the chunks in turn; or, if the share's fit the library's scratch (and nobody else is using
-// it), all of them there, so that the products that produce or consume H and D are one launch for the
-// share (their elements are the same sums either way) and only the sums over the hidden columns, Y and
-// dX, go chunk by chunk.  Chunks of a small share cannot fill the chip: backward of 366 x 1264 x 3384, k = 4:
-// 295 -> 137 us.
+// Where the products over hidden columns keep H and D: one chunk's in the caller's workspace, and the
+// chunks in turn; or, if nobody else is using the library's scratch, those of as many chunks at a time as
+// fit it, so that the products that produce or consume H and D are one launch for all of them (their
+// elements are the same sums either way) and only the sums over the hidden columns, Y and dX, go chunk by
+// chunk.  Chunks of a small share cannot fill the chip: backward of 366 x 1264 x 3384, k = 4: 295 -> 137 us.
 struct Hidden {
-  bool whole;
   char *H, *D;
   int64_t ld;
   int groups;  // passes over the columns
-  Hidden(const ss_ffn_desc* d, const Ws& w, char* ws, const Scratch& scratch, bool backward) {
-    const int64_t n8 = (d->hi - d->lo + 7) & ~7;
-    const size_t one = align256((size_t)d->T * n8 * 2);
-    whole = scratch.base && d->k > 1 && one * (backward ? 2 : 1) <= HIDDEN_BYTES;
-    H = whole ? scratch.base : ws + w.H;
-    D = whole ? scratch.base + one : ws + w.D;
-    ld = whole ? n8 : w.ldh;
-    groups = whole ? 1 : d->k;
+  // the fewest groups of consecutive chunks whose H (and D) fit HIDDEN_BYTES: d->k if not even two chunks do
+  static int fewest(const ss_ffn_desc* d, bool backward, int64_t* ld) {
+    for (int g = 1; g < d->k; ++g) {
+      int widest = 0;
+      for (int i = 0; i < g; ++i) {
+        int a, b, c0, c1;
+        range(d, g, i, &a, &b, &c0, &c1);
+        if (b - a > widest) widest = b - a;
+      }
+      *ld = (widest + 7) & ~7;
+      if (align256((size_t)d->T * *ld * 2) * (backward ? 2 : 1) <= HIDDEN_BYTES) return g;
+    }
+    return d->k;
   }
   static bool wanted(const ss_ffn_desc* d, bool backward) {
-    return d->k > 1 && align256((size_t)d->T * ((d->hi - d->lo + 7) & ~7) * 2) * (backward ? 2 : 1) <= HIDDEN_BYTES;
+    int64_t unused;
+    return fewest(d, backward, &unused) < d->k;
   }
-  // columns and chunks of a pass
-  void pass(const ss_ffn_desc* d, int g, int* a, int* b, int* c0, int* c1) const {
-    *c0 = whole ? 0 : g;
-    *c1 = whole ? d->k : g + 1;
-    if (whole) { *a = d->lo; *b = d->hi; }
-    else chunk(d, g, a, b);
+  Hidden(const ss_ffn_desc* d, const Ws& w, char* ws, const Scratch& scratch, bool backward)
+      : H(ws + w.H), D(ws + w.D), ld(w.ldh), groups(d->k) {
+    int64_t wide = 0;
+    const int few = scratch.base ? fewest(d, backward, &wide) : d->k;
+    if (few == d->k) return;
+    groups = few;
+    ld = wide;
+    H = scratch.base;
+    D = scratch.base + align256((size_t)d->T * ld * 2);
   }
+  // columns and chunks of group i of `groups`
+  static void range(const ss_ffn_desc* d, int groups, int i, int* a, int* b, int* c0, int* c1) {
+    int x;
+    *c0 = (int)((int64_t)i * d->k / groups);
+    *c1 = (int)((int64_t)(i + 1) * d->k / groups);
+    chunk(d, *c0, a, &x);
+    chunk(d, *c1 - 1, &x, b);
+  }
+  void pass(const ss_ffn_desc* d, int g, int* a, int* b, int* c0, int* c1) const { range(d, groups, g, a, b, c0, c1); }
 };
 
 }  // namespace
@@ -293,14 +309,14 @@ int ss_ffn_bwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
   // The helper stream costs some 10 us of waits between the streams, and two products at once that each
   // fill the chip get in each other's way (8192 tokens x 12288 x 6144: 5.5 ms against 5.1 in turn), so dW2 goes
   // beside dZ only where dZ leaves part of the chip idle, if need be with the tiles that leave more of
-  // it (2048 tokens, chunks of 3072: 192 tiles of 256 x 128 instead of 256 of 128 x 192).  Per-kernel timing wants
-  // the kernels one at a time.
+  // it (2048 tokens, chunks of 3072: 192 tiles of 256 x 128 instead of 256 of 128 x 192), or where the chunks'
+  // products are single rounds with gaps between them.  Per-kernel timing wants the kernels one at a time.
   int nc0, nc1, unused0, unused1;
   hid.pass(d, 0, &nc0, &nc1, &unused0, &unused1);
   const ssa::GemmShape fit = ssa::gemm_shape(d->T, nc1 - nc0, d->dm, plan_dh.split, false);
   const ssa::GemmShape loose = ssa::gemm_shape(d->T, nc1 - nc0, d->dm, plan_dh.split, true);
-  const bool beside_fit = fit.idle >= 0.1 && fit.idle * fit.round >= 1.6;
-  const bool beside_loose = !beside_fit && loose.idle >= 0.2 && loose.idle * loose.round >= 8. && loose.cost * 5 <= fit.cost * 6;
+  const bool beside_fit = (fit.idle >= 0.1 && fit.idle * fit.round >= 1.6) || (hid.groups > 1 && fit.rounds == 1);
+  const bool beside_loose = fit.idle < 0.1 && loose.idle >= 0.2 && loose.idle * loose.round >= 8. && loose.cost * 5 <= fit.cost * 6;
   Side side_obj(!g_on && (beside_fit || beside_loose));
   Side* side = side_obj.ok ? &side_obj : nullptr;
   bool pending = false;  // work on the helper stream that the caller's stream has not waited for yet

@@ -62,18 +62,19 @@ enum GemmTile { TILE_256x128, TILE_128x128, TILE_128x192, TILE_256x192 };
 struct GemmShape {
   GemmTile tile;
   int cost;      // time in hundredths of a round of 256 x 128 tiles
+  int64_t rounds;
   double idle;   // part of the chip that the last round leaves idle
   double round;  // us of a round
 };
 inline GemmShape gemm_shape(int M, int N, int K, int split, bool narrow) {
   constexpr int COST[4] = {100, 66, 85, 160}, BM[4] = {256, 128, 128, 256}, BN[4] = {128, 128, 192, 192};
-  GemmShape best{TILE_256x128, 0, 0., 0.};
+  GemmShape best{TILE_256x128, 0, 0, 0., 0.};
   for (int t = 0; t < 4; ++t) {
     if ((split > 1 && t != TILE_128x128) || (narrow && BN[t] == 192)) continue;
     const int64_t n = (int64_t)((M + BM[t] - 1) / BM[t]) * ((N + BN[t] - 1) / BN[t]) * split, rounds = (n + 255) / 256;
     const int64_t cost = rounds * COST[t] * (BN[t] == 192 ? K + 160 : K) / K;
     if (best.cost && cost >= best.cost) continue;
-    best = {(GemmTile)t, (int)(cost < 1000000 ? cost : 1000000), 1. - n / (256. * rounds), 0.0075 * COST[t] * K / (64. * split)};
+    best = {(GemmTile)t, (int)(cost < 1000000 ? cost : 1000000), rounds, 1. - n / (256. * rounds), 0.0075 * COST[t] * K / (64. * split)};
   }
   return best;
 }

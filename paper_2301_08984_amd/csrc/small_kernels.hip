@@ -26,7 +26,6 @@ namespace {
 constexpr int SD = 32;        // head size
 constexpr int SLD = SD + 8;   // LDS row stride of the per-wave tiles (elements)
 constexpr int BLD = 68;       // LDS row stride of the bias tile (elements)
-constexpr int FWD_ROWS_PER_WAVE = 8;
 
 struct WaveLds {
   uint16_t t0[64 * SLD];  // forward: V ; backward: K
@@ -133,7 +132,7 @@ __device__ inline void scores_by_query(const KP& p, const bf16x8 (&kf)[2][2], co
 // short-sequence kernels are bound by exactly that.
 // ---------------------------------------------------------------------------
 template <bool REGION>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void small_fwd_kernel(KP p) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void small_fwd_kernel(KP p, int rows_per_wave) {
   __shared__ __attribute__((aligned(16))) uint16_t bias_tile[64 * BLD];
   __shared__ __attribute__((aligned(16))) WaveLds wl[4];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 31, hl = lane >> 5;
@@ -142,8 +141,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   __syncthreads();
   WaveLds& L = wl[w];
   const float c1 = p.scale * LOG2E;
-  const int bfirst = p.b0 + (blockIdx.x * 4 + w) * FWD_ROWS_PER_WAVE;
-  const int blast = min(bfirst + FWD_ROWS_PER_WAVE, p.b1);
+  const int bfirst = p.b0 + (blockIdx.x * 4 + w) * rows_per_wave;
+  const int blast = min(bfirst + rows_per_wave, p.b1);
   // the operands of row b + 1 are fetched while row b is computed
   u32x4 qn[4], kn[4], vn[4];
   auto fetch = [&](int b) {
@@ -509,10 +508,12 @@ bool small_supported(const KP& p, bool bf16) {
 }
 
 hipError_t launch_small_fwd(const KP& p, hipStream_t st) {
-  const int rows = p.b1 - p.b0;
-  dim3 g((rows + 4 * FWD_ROWS_PER_WAVE - 1) / (4 * FWD_ROWS_PER_WAVE), p.h1 - p.h0);
-  if (p.mask_kind == 2) small_fwd_kernel<true><<<g, 256, 0, st>>>(p);
-  else small_fwd_kernel<false><<<g, 256, 0, st>>>(p);
+  // A wavefront's rows share its bias tile (a row's results do not depend on how many there are): as many as let
+  // the launch fit the 2048 wavefronts that the chip holds, up to 8.  Forward of 17 rows x 8 heads x 49: 23 -> 10 us.
+  const int rows = p.b1 - p.b0, even = (rows * (p.h1 - p.h0) + 2047) / 2048, rows_per_wave = even > 8 ? 8 : even;
+  dim3 g((rows + 4 * rows_per_wave - 1) / (4 * rows_per_wave), p.h1 - p.h0);
+  if (p.mask_kind == 2) small_fwd_kernel<true><<<g, 256, 0, st>>>(p, rows_per_wave);
+  else small_fwd_kernel<false><<<g, 256, 0, st>>>(p, rows_per_wave);
   return hipGetLastError();
 }
 
