@@ -28,14 +28,20 @@ constexpr int W = 8;  // wavefronts per work-group
 __device__ inline f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 // e^x for x <= a few units above 0, relative error of about 1e-7: 2^(x log2 e) with the product's rounding
-// error put back in; below e^-150 (also for -inf and NaN, the difference of two -inf) zero
+// error put back in; below e^-150 (also for -inf) zero; NaN stays NaN
 __device__ inline float exp_f32(float x) {
   constexpr float L2E = 1.44269502e+00f, L2E_LO = 1.92596299e-08f, LN2 = 6.93147182e-01f;  // log2(e) = L2E + L2E_LO
-  x = fmaxf(x, -150.f);
+  x = x < -150.f ? -150.f : x;
   const float t = x * L2E, r = fmaf(x, L2E_LO, fmaf(x, L2E, -t));
   const float y = __builtin_amdgcn_exp2f(t);
   return fmaf(y, r * LN2, y);
 }
+
+// e^(x - m), the weight under a maximum m of sums taken under a maximum x <= m: 1 where they are equal, also
+// both -inf (no key yet, the sums are 0)
+__device__ inline float weight(float x, float m) { return x == m ? 1.f : exp_f32(x - m); }
+// unnormalised probability of a score: 0 for -inf, also under a maximum of -inf
+__device__ inline float prob(float s, float m) { return s == -INFINITY ? 0.f : exp_f32(s - m); }
 
 template <int DC>
 struct Nat { f32x4 x[DC]; };
@@ -108,9 +114,11 @@ __device__ inline float bias_f32(const KP& p, int h, int i, int j) {
   return p.bias_bf16 ? __uint_as_float((uint32_t)((const uint16_t*)p.bias)[off] << 16) : ((const float*)p.bias)[off];
 }
 // scores of a block in C registers -> scale s + bias, -inf where the pair is masked.  Register v is the
-// pair (q, k + v) if KEYS_RUN, else (q + v, k).
+// pair (q, k + v) if KEYS_RUN, else (q + v, k).  Returns the masked registers, bit v: their gradients are 0
+// whatever the statistics are (a query that sees a NaN has NaN statistics).
 template <bool KEYS_RUN>
-__device__ inline void finish_scores(const KP& p, int h, const int32_t* rid, int q, int k, f32x4& s) {
+__device__ inline uint32_t finish_scores(const KP& p, int h, const int32_t* rid, int q, int k, f32x4& s) {
+  uint32_t masked = 0;
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const int i = KEYS_RUN ? q : q + v, j = KEYS_RUN ? k + v : k;
@@ -120,7 +128,9 @@ __device__ inline void finish_scores(const KP& p, int h, const int32_t* rid, int
     bool dead = i >= p.S || j >= p.S || (p.mask_kind == 1 && j > i);
     if (rid) dead = dead || rid[ic] != rid[jc];
     s[v] = dead ? -INFINITY : x;
+    masked |= (uint32_t)dead << v;
   }
+  return masked;
 }
 
 struct Stats { float m[W][16], l[W][16], lse[16], delta[16]; };
@@ -159,14 +169,16 @@ __global__ __launch_bounds__(64 * W) void f32_query_kernel(KP p) {
   const Nat<DC> qf = load_nat<DC>((const float*)p.Q + base + (int64_t)qc * p.ss, g, D);
 
   f32x4 s[NB], acc[DC];
+  uint32_t masked = 0;  // bit 4t + v: register v of block t
   auto scores = [&](int k0) {
+    masked = 0;
 #pragma unroll
     for (int t = 0; t < NB; ++t) {
       const int kb = k0 + 16 * (w + W * t);
       s[t] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
       if (kb < visible) {
         s[t] = dot<DC>(load_nat<DC>(K + (int64_t)min(kb + i, p.S - 1) * p.ss, g, D), qf);
-        finish_scores<true>(p, h, rid, q, kb + 4 * g, s[t]);
+        masked |= finish_scores<true>(p, h, rid, q, kb + 4 * g, s[t]) << (4 * t);
       }
     }
   };
@@ -181,7 +193,7 @@ __global__ __launch_bounds__(64 * W) void f32_query_kernel(KP p) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) mn = fmaxf(mn, s[t][v]);
     mn = fmaxf(m, over_groups_max(mn));
-    const float alpha = exp_f32(m - mn);
+    const float alpha = weight(m, mn);
     m = mn;
     l *= alpha;
 #pragma unroll
@@ -193,7 +205,7 @@ __global__ __launch_bounds__(64 * W) void f32_query_kernel(KP p) {
         f32x4 pr;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          pr[v] = exp_f32(s[t][v] - mn);
+          pr[v] = prob(s[t][v], mn);
           l += pr[v];
         }
         accumulate<DC>(V, p.ss, kb, p.S, i, g, D, pr, acc);
@@ -215,7 +227,7 @@ __global__ __launch_bounds__(64 * W) void f32_query_kernel(KP p) {
   float wt[W], L = 0.f;
 #pragma unroll
   for (int x = 0; x < W; ++x) {
-    wt[x] = exp_f32(st.m[x][mq] - M);
+    wt[x] = weight(st.m[x][mq], M);
     L = fmaf(wt[x], st.l[x][mq], L);
   }
   const float inv = 1.f / L, lse = M + logf(L);
@@ -275,7 +287,8 @@ __global__ __launch_bounds__(64 * W) void f32_query_kernel(KP p) {
       if (kb < visible) {
         f32x4 ds = dot<DC>(load_nat<DC>(V + (int64_t)min(kb + i, p.S - 1) * p.ss, g, D), gf);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) ds[v] = exp_f32(s[t][v] - my_lse) * (ds[v] - my_delta);
+        for (int v = 0; v < 4; ++v)
+          ds[v] = (masked >> (4 * t + v)) & 1 ? 0.f : exp_f32(s[t][v] - my_lse) * (ds[v] - my_delta);
         accumulate<DC>(K, p.ss, kb, p.S, i, g, D, ds, acc);
       }
     }
@@ -334,9 +347,9 @@ __global__ __launch_bounds__(64 * W) void f32_key_kernel(KP p) {
           const int64_t at = base + (int64_t)min(kb + i, p.S - 1) * p.ss;
           f32x4 s = dot<DC>(load_nat<DC>((const float*)p.K + at, g, D), qf);
           const f32x4 dp = dot<DC>(load_nat<DC>((const float*)p.V + at, g, D), gf);
-          finish_scores<true>(p, h, rid, q, kb + 4 * g, s);
+          const uint32_t masked = finish_scores<true>(p, h, rid, q, kb + 4 * g, s);
 #pragma unroll
-          for (int v = 0; v < 4; ++v) acc[t][v] += exp_f32(s[v] - lse) * (dp[v] - delta);
+          for (int v = 0; v < 4; ++v) acc[t][v] += (masked >> v) & 1 ? 0.f : exp_f32(s[v] - lse) * (dp[v] - delta);
         }
       }
 #pragma unroll
@@ -370,13 +383,14 @@ __global__ __launch_bounds__(64 * W) void f32_key_kernel(KP p) {
       if (qb >= p.S) continue;
       f32x4 s = dot<DC>(load_nat<DC>(Q + (int64_t)row * p.ss, g, D), kf);
       const f32x4 dp = dot<DC>(load_nat<DC>(G + (int64_t)row * p.do_ss, g, D), vf);
-      finish_scores<false>(p, h, rid, qb + 4 * g, key, s);
+      const uint32_t masked = finish_scores<false>(p, h, rid, qb + 4 * g, key, s);
       f32x4 ds;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int r = min(qb + 4 * g + v, p.S - 1);
-        s[v] = exp_f32(s[v] - lse[r]);
-        ds[v] = s[v] * (dp[v] - delta[r]);
+        const bool dead = (masked >> v) & 1;
+        s[v] = dead ? 0.f : exp_f32(s[v] - lse[r]);
+        ds[v] = dead ? 0.f : s[v] * (dp[v] - delta[r]);
       }
       accumulate<DC>(G, p.do_ss, qb, p.S, i, g, D, s, dv);
       accumulate<DC>(Q, p.ss, qb, p.S, i, g, D, ds, dk);

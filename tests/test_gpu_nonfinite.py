@@ -1,0 +1,84 @@
+"""NaN and infinities in the inputs of fp32 operators come out where the definition puts them: a NaN score
+(from K or the bias) makes its query's row and normaliser NaN, a bias of -inf masks its pair, also where
+it masks every key that a wavefront looks at, and pairs that the mask excludes contribute exactly nothing."""
+import math
+
+import numpy as np
+import pytest
+
+from paper_2301_08984_amd.runner import DeviceCase
+from paper_2301_08984_amd.workloads import make_inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _reference(inp, bias, live, scale):
+    """The operator and its gradients in fp64, pair by pair; `live` [B, S, S]: pairs that are not masked."""
+    Q, K, V, dY = (inp[n].astype(np.float64).transpose(0, 2, 1, 3) for n in ("Q", "K", "V", "dY"))
+    live = live[:, None]
+    with np.errstate(all="ignore"):
+        s = scale * Q @ K.transpose(0, 1, 3, 2) + bias.astype(np.float64)[None]
+        m = np.max(np.where(live, s, -np.inf), axis=-1, keepdims=True)
+        p = np.where(live & (s != -np.inf), np.exp(s - m), 0.0)
+        l = p.sum(-1, keepdims=True)
+        lse = m + np.log(l)
+        O = p @ V / l
+        P = np.where(live, np.exp(s - lse), 0.0)
+        dS = np.where(live, P * (dY @ V.transpose(0, 1, 3, 2) - (dY * O).sum(-1, keepdims=True)), 0.0)
+        out = {"Y": O, "dQ": scale * dS @ K, "dK": scale * dS.transpose(0, 1, 3, 2) @ Q, "dV": P.transpose(0, 1, 3, 2) @ dY}
+        out = {n: x.transpose(0, 2, 1, 3) for n, x in out.items()}
+        out["lse"], out["dBias"] = lse[..., 0], dS.sum(0)
+    return out
+
+
+def _plant(name, inp, bias):
+    S = bias.shape[1]
+    if name == "nan_key":
+        inp["K"][0, S // 3, 1] = np.nan
+    elif name == "nan_bias":
+        bias[1, S // 2, S // 3] = np.nan
+    elif name == "inf_bias":
+        bias[0, S // 2, S - 1] = np.inf
+    elif name == "masking_bias":  # all but the last keys of some rows, all but the first of others
+        bias[:, : S // 2, : S - 3] = -np.inf
+        bias[:, S // 2 :, 3:] = -np.inf
+    elif name == "dead_row":
+        bias[1, 5, :] = -np.inf
+
+
+# names of the outputs that are not checked: sums in which a NaN operand meets a probability of 0 are NaN or
+# not depending on whether the kernel skips the block
+SKIP = {("nan_key", "causal"): ("dQ",), ("nan_key", "region"): ("dQ",)}
+
+
+@pytest.mark.parametrize("S,D", [(40, 16), (300, 64), (1030, 32)])
+@pytest.mark.parametrize("name,mask", [("nan_key", None), ("nan_key", "causal"), ("nan_key", "region"), ("nan_bias", None),
+                                       ("nan_bias", "causal"), ("inf_bias", None), ("masking_bias", None), ("dead_row", None)])
+def test_fp32_nonfinite_inputs(name, mask, S, D):
+    import torch
+    inp = make_inputs(seed=61, B=2, H=2, S=S, D=D, dtype="f32", bias="dense", axis="row")
+    bias = inp["bias"]
+    _plant(name, inp, bias)
+    ids = (np.arange(S) * 3 // S).astype(np.int32)[None]
+    i, j = np.arange(S)[:, None], np.arange(S)[None]
+    live = {None: np.ones((S, S), bool), "causal": j <= i, "region": ids[0][:, None] == ids[0][None]}[mask]
+    if mask == "region":
+        inp["region_ids"] = ids
+    dc = DeviceCase(inp, dtype="f32", bias="dense", mask=mask)
+    ref = _reference(inp, bias, np.broadcast_to(live, (2, S, S)), float(np.float32(1.0 / math.sqrt(D))))
+    for use_lse in (False, True):
+        print(f"non-finite {name} mask={mask} S={S} use_lse={use_lse}", flush=True)
+        d = dc.desc("row", 0, 2, 1)
+        dc.fwd(d)
+        dc.bwd(d, use_lse=use_lse, poison=True)
+        torch.cuda.synchronize()
+        for n, r in ref.items():
+            if n in SKIP.get((name, mask), ()):
+                continue
+            x = dc.host(n)
+            assert np.array_equal(np.isnan(x), np.isnan(r)), (n, int(np.isnan(x).sum()), int(np.isnan(r).sum()))
+            inf = np.isinf(r)
+            assert np.array_equal(x[inf], r[inf]), n
+            ok = np.isfinite(r)
+            if ok.any():  # fp32 sums over up to S terms: 2e-5 of the largest entry, as for finite inputs
+                assert np.max(np.abs(x[ok] - r[ok])) <= 2e-5 * max(1.0, np.max(np.abs(r[ok]))), n
