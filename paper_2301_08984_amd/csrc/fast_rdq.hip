@@ -83,6 +83,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
   const bf16x2 ones2 = one_pair.v;
   f32x16 oacc[DB], a1[DB], a2[DB];
   float lsum = 0.f, dsum = 0.f;  // this half-wave's part of l' and delta'
+  DpShift shift;
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -128,7 +129,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
     }
   };
   // one 32-key block of a tile (K at sK, V behind it): scores and dP, online softmax, the three products and the sums
-  auto block = [&](const uint16_t* sK, int kb, int k0) {
+  auto block = [&](const uint16_t* sK, int kb, int k0) __attribute__((always_inline)) {
     const uint16_t* sV = sK + BN * LDT;
     f32x16 sa, pa;
     {
@@ -176,6 +177,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
       const float mn = fmaxf(m, rmax);
       const float alpha = fast_exp2(m - mn);
       m = mn;
+      shift.rescaled(alpha);
       lsum *= alpha;
       dsum *= alpha;
 #pragma unroll
@@ -187,10 +189,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
     {
       float pr[16], dp[16];
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        pr[v] = fast_exp2(fmaf(sa[v], BIAS ? LOG2E : c1, -m));
-        dp[v] = pr[v] * pa[v];
-      }
+      for (int v = 0; v < 16; ++v) pr[v] = fast_exp2(fmaf(sa[v], BIAS ? LOG2E : c1, -m));
+      shift.choose(pr, pa);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) dp[v] = pr[v] * (pa[v] - shift.c);
       pf[0] = pack8(&pr[0]);
       pf[1] = pack8(&pr[8]);
       df[0] = pack8(&dp[0]);

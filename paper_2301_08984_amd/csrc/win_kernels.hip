@@ -288,6 +288,7 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(3, 3)))
 #pragma unroll
     for (int v = 0; v < 16; ++v) { oacc[0][v] = 0.f; a1[v] = 0.f; a2[v] = 0.f; }
     float m = -1e30f, lsum = 0.f, dsum = 0.f;
+    DpShift shift;
 #pragma unroll
     for (int c = 0; c < NB; ++c) {
       block_boundary(bz[c]);
@@ -308,6 +309,7 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(3, 3)))
         const float mn = fmaxf(m, rmax);
         const float alpha = fast_exp2(m - mn);
         m = mn;
+        shift.rescaled(alpha);
         lsum *= alpha;
         dsum *= alpha;
 #pragma unroll
@@ -315,10 +317,10 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(3, 3)))
       }
       float pr[16], dp[16];
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        pr[v] = fast_exp2(fmaf(s[v], LOG2E, -m));
-        dp[v] = pr[v] * pa[v];
-      }
+      for (int v = 0; v < 16; ++v) pr[v] = fast_exp2(fmaf(s[v], LOG2E, -m));
+      shift.choose(pr, pa);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) dp[v] = pr[v] * (pa[v] - shift.c);
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         union { bf16x8 v; bf16x2 h[4]; } pf, df;

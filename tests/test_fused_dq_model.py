@@ -94,3 +94,41 @@ def test_one_hot_row_cancels_exactly():
     assert np.array_equal(a1 - dmean * a2, np.zeros((1, D)))
     # ... and does not with the exact mean, which is not a bf16 number
     assert np.max(np.abs(a1 - dP[:, 17:18] * a2)) > 0
+
+
+def _two_products(Q, K, V, dO, bias, scale, shifted):
+    """dQ of one (row, head) by the kernel's formula, with or without the constant that it subtracts from every dP
+    of a query: the mean of dP over the first 32 keys weighted by their probabilities."""
+    x = scale * Q @ K.T + bias
+    p = np.exp(x - x.max(1, keepdims=True))
+    dP = dO @ V.T
+    if shifted:
+        dP = dP - (p * dP)[:, :32].sum(1, keepdims=True) / p[:, :32].sum(1, keepdims=True)
+    pb, wb = _bf(p), _bf(p * dP)
+    lp = pb.sum(1, keepdims=True)
+    return scale * (wb @ K - (wb.sum(1, keepdims=True) / lp) * (pb @ K)) / lp
+
+
+@pytest.mark.parametrize("S", [144, 901])
+@pytest.mark.parametrize("offset", [0.0, 0.5, 1.0, 2.0])
+def test_common_offset_of_values_and_gradients(offset, S):
+    """V and dO with a mean of their own, `offset` standard deviations: dP is then nearly the same for every key of
+    a query, and only the constant keeps the two products as accurate as dS formed directly."""
+    g = np.random.default_rng(S)
+    D = 32
+    Q, K, V, dO = (_bf(g.standard_normal((S, D)) + o) for o in (0.0, 0.0, offset, offset))
+    bias = _bf(g.standard_normal((S, S)))
+    scale = float(np.float32(1.0 / math.sqrt(D)))
+    x = scale * Q @ K.T + bias
+    P = np.exp(x - x.max(1, keepdims=True))
+    P /= P.sum(1, keepdims=True)
+    dP = dO @ V.T
+    dS = P * (dP - (P * dP).sum(1, keepdims=True))
+    ref = scale * dS @ K
+    err = lambda a: float(np.linalg.norm(a - ref) / np.linalg.norm(ref))
+    direct, plain, shifted = (err(a) for a in (scale * _bf(dS) @ K, _two_products(Q, K, V, dO, bias, scale, False),
+                                               _two_products(Q, K, V, dO, bias, scale, True)))
+    print(f"S={S} offset={offset}: direct {direct:.2e}, two products {plain:.2e}, with the constant {shifted:.2e}")
+    assert shifted <= 1.25 * direct + 2e-4, (direct, plain, shifted)
+    if offset >= 1.0:
+        assert plain >= 2.5 * direct, (direct, plain)  # these data do show the difference
