@@ -19,9 +19,10 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 // operands that went into A1 and A2 (a one-hot row then gives A1 - Delta' A2 = 0 up to the rounding
 // of one division; with the mean of the unrounded values the error of such rows is 2^-9 |dP| |K|).
 // The packed operands are summed pairwise by v_dot2c_f32_bf16 against (1, 1): half an instruction
-// per element and sum.  l' = sum_j bf16(p~) also normalises O and gives the LSE, so the row sum
-// costs no separate addition.  The other backward kernels use Delta = rowsum(dO * O) from the
-// epilogue as before.
+// per element and sum.  l' = sum_j bf16(p~) also normalises O, which is a sum over the same operands (a one-hot
+// row then gives its V exactly).  The LSE, of which dK / dV form the probabilities anew, is taken of the
+// fp32 sum: a peaked row's l' is off by up to 2^-9, and with it every probability of the row would be.
+// The other backward kernels use Delta = rowsum(dO * O) from the epilogue as before.
 //
 // Work-group: four wavefronts of 32 queries sharing 64-key K / V tiles (two buffers, one barrier per
 // tile), as the forward kernel for large shares; K and V are both read as stored (scores, dP) and
@@ -82,7 +83,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
   one_pair.u = 0x3f803f80u;
   const bf16x2 ones2 = one_pair.v;
   f32x16 oacc[DB], a1[DB], a2[DB];
-  float lsum = 0.f, dsum = 0.f;  // this half-wave's part of l' and delta'
+  float lsum = 0.f, dsum = 0.f, l32 = 0.f;  // this half-wave's part of l', delta' and the fp32 row sum
   DpShift shift;
 #pragma unroll
   for (int db = 0; db < DB; ++db)
@@ -180,6 +181,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
       shift.rescaled(alpha);
       lsum *= alpha;
       dsum *= alpha;
+      l32 *= alpha;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -190,6 +192,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
       float pr[16], dp[16];
 #pragma unroll
       for (int v = 0; v < 16; ++v) pr[v] = fast_exp2(fmaf(sa[v], BIAS ? LOG2E : c1, -m));
+      if (p.lse_out) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) l32 += pr[v];
+      }
       shift.choose(pr, pa);
 #pragma unroll
       for (int v = 0; v < 16; ++v) dp[v] = pr[v] * (pa[v] - shift.c);
@@ -198,7 +204,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
       df[0] = pack8(&dp[0]);
       df[1] = pack8(&dp[8]);
     }
-    // the sums run over the rounded operands
+    // these sums run over the rounded operands
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       union { bf16x8 v; bf16x2 h[4]; } a, c;
@@ -275,7 +281,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
                         fmaf(-dmean, a2[db][4 * g + 3], a1[db][4 * g + 3]), f);
     store_row32(out + 32 * db, o, hl, true);
   }
-  fwd_epilogue_rowsum<DB, true>(p, oacc, m, l, b, h, q, hl, base);
+  fwd_epilogue_rowsum<DB, true>(p, oacc, m, l, half_sum(l32), b, h, q, hl, base);
 }
 
 template <int D>

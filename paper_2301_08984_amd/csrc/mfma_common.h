@@ -353,13 +353,14 @@ __device__ inline float fwd_epilogue_block(const KP& p, const f32x16& o16, int d
 }
 
 // forward epilogue: normalise, gate, store Y (and LSE); recompute mode: gate gradient,
-// pre-gated dO copy, Delta = rowsum(dO*O) and LSE into the workspace.  `l` is the complete row sum.
+// pre-gated dO copy, Delta = rowsum(dO*O) and LSE into the workspace.  `l` is the complete row sum that O
+// is divided by, `lse_l` the one that the LSE is taken of.
 template <int DB, bool RECOMP>
-__device__ inline void fwd_epilogue_rowsum(const KP& p, f32x16 (&oacc)[DB], float m, float l, int b, int h, int q,
+__device__ inline void fwd_epilogue_rowsum(const KP& p, f32x16 (&oacc)[DB], float m, float l, float lse_l, int b, int h, int q,
                                            int hl, int64_t base) {
   if (q >= p.S) return;
   const float inv = 1.f / l;
-  const float lse = (m + log2f(l)) * LN2;
+  const float lse = (m + log2f(lse_l)) * LN2;
   float part = 0.f;
 #pragma unroll
   for (int db = 0; db < DB; ++db) part = fwd_epilogue_block<RECOMP>(p, oacc[db], db, inv, b, h, q, hl, base, part);
@@ -378,7 +379,8 @@ template <int DB, bool RECOMP>
 __device__ inline void fwd_epilogue(const KP& p, f32x16 (&oacc)[DB], float m, float l, int b, int h, int q,
                                     int hl, int64_t base) {
   if (q >= p.S) return;
-  fwd_epilogue_rowsum<DB, RECOMP>(p, oacc, m, half_sum(l), b, h, q, hl, base);
+  const float rowsum = half_sum(l);
+  fwd_epilogue_rowsum<DB, RECOMP>(p, oacc, m, rowsum, rowsum, b, h, q, hl, base);
 }
 
 // the specialised kernels serve: no bias or a dense bf16 bias; no mask or the causal mask; a

@@ -287,7 +287,7 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(3, 3)))
     f32x16 oacc[1], a1, a2;
 #pragma unroll
     for (int v = 0; v < 16; ++v) { oacc[0][v] = 0.f; a1[v] = 0.f; a2[v] = 0.f; }
-    float m = -1e30f, lsum = 0.f, dsum = 0.f;
+    float m = -1e30f, lsum = 0.f, dsum = 0.f, l32 = 0.f;
     DpShift shift;
 #pragma unroll
     for (int c = 0; c < NB; ++c) {
@@ -312,12 +312,17 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(3, 3)))
         shift.rescaled(alpha);
         lsum *= alpha;
         dsum *= alpha;
+        l32 *= alpha;
 #pragma unroll
         for (int v = 0; v < 16; ++v) { oacc[0][v] *= alpha; a1[v] *= alpha; a2[v] *= alpha; }
       }
       float pr[16], dp[16];
 #pragma unroll
       for (int v = 0; v < 16; ++v) pr[v] = fast_exp2(fmaf(s[v], LOG2E, -m));
+      if (p.lse_out) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) l32 += pr[v];
+      }
       shift.choose(pr, pa);
 #pragma unroll
       for (int v = 0; v < 16; ++v) dp[v] = pr[v] * (pa[v] - shift.c);
@@ -346,7 +351,7 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(3, 3)))
         o[g] = pack4_bf16(fmaf(-dmean, a2[4 * g], a1[4 * g]), fmaf(-dmean, a2[4 * g + 1], a1[4 * g + 1]),
                           fmaf(-dmean, a2[4 * g + 2], a1[4 * g + 2]), fmaf(-dmean, a2[4 * g + 3], a1[4 * g + 3]), p.scale * inv);
       store_row32((uint16_t*)p.dQ + base + (int64_t)q * p.ss, o, hl, true);
-      fwd_epilogue_rowsum<1, true>(p, oacc, m, l, b, h, q, hl, base);
+      fwd_epilogue_rowsum<1, true>(p, oacc, m, l, half_sum(l32), b, h, q, hl, base);
     }
   }
 }

@@ -18,8 +18,8 @@ def _window(win, **kw):
     return dict(seed=810 + win[0], B=5, H=2, S=win[0] * win[1], D=32, dtype="bf16", bias="relpos", win=win, axis="row", **kw)
 
 
-def _dense(S, **kw):
-    return dict(seed=820 + S, B=3, H=2, S=S, D=32, dtype="bf16", bias="dense", axis="row", **kw)
+def _dense(S, mask=None, **kw):
+    return dict(seed=820 + S, B=3, H=2, S=S, D=32, dtype="bf16", bias="dense", mask=mask, axis="row", **kw)
 
 
 CASES = {
@@ -33,6 +33,13 @@ CASES = {
     "dense_384": _dense(384),
     "no_bias_384": dict(_dense(384), bias=None),
 }
+
+
+def _inputs(cfg):
+    inp = make_inputs(**cfg)
+    if cfg["mask"] == "region":  # regions that begin at every fifth of the tokens: queries whose first block has no key
+        inp["region_ids"] = np.stack([(np.arange(cfg["S"]) >= cfg["S"] * i // 5).astype(np.int32) for i in range(5)])
+    return inp
 
 
 def _check(cfg, inp):
@@ -49,7 +56,7 @@ def _check(cfg, inp):
 @pytest.mark.parametrize("name", list(CASES))
 def test_offset_values_and_gradients(name, offset):
     cfg = CASES[name]
-    inp = make_inputs(**cfg)
+    inp = _inputs(cfg)
     print(f"offset data {name} {offset}", flush=True)
     for n in ("V", "dY"):
         inp[n] = round_to_bf16(inp[n] + np.float32(offset))
@@ -68,3 +75,20 @@ def test_masked_first_keys_have_no_say(fill):
     inp["V"][:, :40] = 1e4
     inp["bias"] = round_to_bf16(np.where(np.arange(200) < 40, np.float32(fill), inp["bias"]))
     _check(cfg, inp)
+
+
+@pytest.mark.parametrize("name", ["9x9", "12x12_region", "dense_66", "dense_131_causal", "dense_384", "no_bias_384"])
+def test_statistics_of_peaked_rows(name):
+    """Queries eight times larger: most of a row's weight lies on a few keys.  The backward forms the same
+    probabilities from the statistics it takes itself as from those the forward left (fp32 sums both): they
+    differ by some 1e-7, which moves a rounding to bf16 (2^-8) in one of 10^4 cases.  Row sums of rounded probabilities
+    are off by up to 2^-9."""
+    cfg = CASES[name]
+    inp = _inputs(cfg)
+    print(f"peaked rows {name}", flush=True)
+    inp["Q"] = inp["Q"] * np.float32(8.0)
+    own, kept = (run_case(cfg, inputs=inp, use_lse=u)[0] for u in (False, True))
+    for n in ("dV", "dK"):
+        d = float(np.linalg.norm(own.host(n) - kept.host(n)) / np.linalg.norm(kept.host(n)))
+        print(n, d, flush=True)
+        assert d <= 2e-4, (n, d)
