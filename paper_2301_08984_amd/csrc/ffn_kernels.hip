@@ -224,14 +224,15 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
   const int nk = (g.K + 16 * KS - 1) / (16 * KS);
   // Column sums of B (the bias gradients: B is dY or dZ, on its way through the registers anyway), by the
   // wavefronts of the first tile row: packed pairs against (1, 1), two instructions per MFMA and under it.
-  // A kernel of their own read B once more (8192 tokens x 12288: 59 us).
+  // A kernel of their own read B once more (8192 tokens x 12288: 59 us).  The sums of each turn of the ring are
+  // added up apart: chains of 24 to 48 additions and one of K / 192 to K / 96, not one of K / 4.
   constexpr bool SUMS = EPI == EPI_STORE;
   const bf16x2 ones2 = {(__bf16)1.f, (__bf16)1.f};
   const bool sums = SUMS && g.colsum && m0 == 0 && wm == 0;
-  float csum[SUMS ? FJ : 1];
+  float csum[SUMS ? FJ : 1], turn[SUMS ? FJ : 1];
   if (SUMS) {
 #pragma unroll
-    for (int j = 0; j < FJ; ++j) csum[SUMS ? j : 0] = 0.f;
+    for (int j = 0; j < FJ; ++j) csum[SUMS ? j : 0] = turn[SUMS ? j : 0] = 0.f;
   }
   bf16x8 fa[2][FI], fb[2][FJ];  // fragments of the contraction step being multiplied and of the next one
   // fragment reads of one contraction step in the order of their first use: B 0, A 0 .. FI-1, B 1 .. FJ-1
@@ -268,7 +269,7 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
           union { bf16x8 v; bf16x2 h[4]; } b;
           b.v = fb[ks & 1][j];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) csum[SUMS ? j : 0] = __builtin_amdgcn_fdot2_f32_bf16(b.h[e], ones2, csum[SUMS ? j : 0], false);
+          for (int e = 0; e < 4; ++e) turn[SUMS ? j : 0] = __builtin_amdgcn_fdot2_f32_bf16(b.h[e], ones2, turn[SUMS ? j : 0], false);
         }
       }
 #pragma unroll
@@ -385,6 +386,11 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
             stage(std::true_type{}, stage0, stage1, stage2);
             stage(std::true_type{}, stage1, stage2, stage0);
             stage(std::true_type{}, stage2, stage0, stage1);
+          }
+#pragma unroll
+          for (int j = 0; j < FJ; ++j) {
+            csum[SUMS ? j : 0] += turn[SUMS ? j : 0];
+            turn[SUMS ? j : 0] = 0.f;
           }
         }
       }
