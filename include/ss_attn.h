@@ -99,9 +99,11 @@ typedef struct {
  * chunk's recomputed softmax statistics and pre-gated output gradient and is
  * reused by every chunk, so it shrinks as k grows; this is what makes
  * peak memory = caller tensors + workspace fall with k (Section 6.3).  Parts that
- * do not depend on k (a transposed copy of a dense bias, group partial sums of the
- * bias gradient) are included in the figure.  A larger workspace is used to run chunks
- * together, and the chunks of a share that needs no more than 32 MiB run together in a
+ * do not depend on k (a transposed copy of a dense bias) and the partial sums of the
+ * bias gradient, which add at most 12 MiB (or four sums over H x S x S, where those are
+ * larger) to what the share needs at least, are included in the figure; to stay within
+ * that it may be the figure of a finer cut than k.  A larger workspace is used to run chunks
+ * together, and the chunks of a share that needs no more than 64 MiB run together in a
  * buffer that the library holds on each GPU, unless another stream is using it or the
  * call is being captured into a graph; the results are the same bits.
  * Needs no GPU.  Returns SS_OK or a negative error. */
@@ -151,9 +153,10 @@ int ss_attn_bwd(const ss_attn_desc* desc, const void* Q, const void* K, const vo
  * Same arguments, results and kernels as ss_attn_bwd, but the scratch is a buffer built into
  * the library (SS_ATTN_STATIC_SCRATCH_BYTES of device memory per GPU the library is used on,
  * held until the process ends) instead of a caller workspace.  The call allocates and frees
- * nothing.  A share whose ss_attn_workspace_bytes backward figure exceeds the buffer is
- * rejected with SS_ERR_STATIC_SCRATCH before anything is enqueued (raise k, or use
- * ss_attn_bwd).  Every call on one GPU shares that GPU's buffer: two calls that may run at
+ * nothing.  A share whose backward does not fit the buffer, not even with the fewest partial
+ * sums of the bias gradient, is rejected with SS_ERR_STATIC_SCRATCH before anything is
+ * enqueued (raise k, or use ss_attn_bwd); one that fits only because of that runs in more chunks.
+ *  Every call on one GPU shares that GPU's buffer: two calls that may run at
  * the same time on one GPU (different streams or threads) race; calls on one stream are safe.
  * The buffer keeps the previous call's contents; no part of it needs to start at zero. */
 #define SS_ATTN_STATIC_SCRATCH_BYTES (32u << 20)

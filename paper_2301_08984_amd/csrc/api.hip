@@ -4,6 +4,7 @@
 // workspace (co-shard, Section 2 of the paper).
 #include "../../include/ss_attn.h"
 #include "kparams.h"
+#include "mfma_common.h"
 #include "shared_scratch.h"
 
 #include <cstdio>
@@ -70,8 +71,9 @@ struct WsLayout {
 // Rows per bias-gradient group of the short-sequence kernels, one wavefront each: 8 (the groups' sums cost a
 // pass over H x S x S per group), fewer while twice as many groups still fit the 2048 wavefronts that the
 // chip holds.  Backward of 17 rows x 8 heads x 49: 60 -> 27 us.
+constexpr int SMALL_GROUP_ROWS = 8;
 inline int small_group_rows(int share_units) {
-  int gw = 8;
+  int gw = SMALL_GROUP_ROWS;
   while (gw > 1 && share_units / gw <= 1024) gw >>= 1;
   return gw;
 }
@@ -80,7 +82,8 @@ enum Family { FAM_PLAIN = 0, FAM_MFMA = 1, FAM_SMALL = 2 };
 
 KP base_params(const ss_attn_desc* d);
 
-WsLayout bwd_layout(const ss_attn_desc* d, Family fam) {
+// the layout with groups of `gw` rows (0: none)
+WsLayout layout_with(const ss_attn_desc* d, int gw) {
   const int64_t n = d->hi - d->lo;
   const int64_t nmax = (n + d->k - 1) / d->k;  // largest chunk of the balanced split
   const int64_t Bc = d->shard_axis == SS_AXIS_ROW ? nmax : d->B;
@@ -96,12 +99,7 @@ WsLayout bwd_layout(const ss_attn_desc* d, Family fam) {
   w.partial = off;
   const int row_lo = d->shard_axis == SS_AXIS_ROW ? d->lo : 0;
   const int row_hi = d->shard_axis == SS_AXIS_ROW ? d->hi : d->B;
-  // rows per group: fixed for the short-sequence kernels, shape-dependent for the tiled kernel
-  w.gw = 0;
-  if (d->bias_kind != SS_BIAS_NONE) {
-    if (fam == FAM_SMALL) w.gw = base_params(d).sm_gw;
-    else if (fam == FAM_MFMA) w.gw = ssa::mfma_dbias_group_rows(base_params(d));
-  }
+  w.gw = gw;
   if (w.gw > 0) {
     w.g0 = row_lo / w.gw;
     w.ngroups = (row_hi - 1) / w.gw - w.g0 + 1;
@@ -123,6 +121,53 @@ WsLayout bwd_layout(const ss_attn_desc* d, Family fam) {
   if (d->bias_kind == SS_BIAS_DENSE && d->bias_dtype == SS_BF16) off += align_up((size_t)d->H * d->S * d->S * 2);
   w.total = off;
   return w;
+}
+
+// What shorter groups of bias-gradient sums may add to a workspace.  (A call whose own workspace does not hold
+// them uses the library's buffer, which costs 3 us: 128 rows x 8 heads x 49 at k = 1, 8.2 MiB more, 31 -> 34.)
+constexpr size_t SPARE = 12u << 20;
+
+// Rows per group of the bias-gradient sums: what fills the chip, or the longest groups that the kernels have
+// (0: a sum that goes on in the result itself, from row to row, and has no partial sums).  A group costs
+// H x S x S floats of workspace, so groups are made longer than the kernels ask for until the share's finest
+// cut needs at most SPARE more than with the longest, and fits the built-in buffer if it does so with those:
+// ss_attn_bwd_static then always finds a number of chunks for a share that it takes.  Decided from the share,
+// never from k: the groups fix the order of the additions.
+int group_rows(const ss_attn_desc* d, Family fam, bool longest) {
+  if (d->bias_kind == SS_BIAS_NONE || fam == FAM_PLAIN) return 0;
+  const KP p = base_params(d);
+  const int most = fam == FAM_SMALL ? SMALL_GROUP_ROWS : ssa::dbias_longest_group(p);
+  const int rows = d->shard_axis == SS_AXIS_ROW ? d->hi - d->lo : d->B;
+  int gw = longest ? most : fam == FAM_SMALL ? p.sm_gw : ssa::mfma_dbias_group_rows(p);
+  if (most == 0 && gw >= rows) gw = 0;
+  ss_attn_desc finest = *d;
+  finest.k = d->hi - d->lo;
+  const size_t least = layout_with(&finest, most).total, limit = SS_ATTN_STATIC_SCRATCH_BYTES;
+  const size_t enough = least <= limit && least + SPARE > limit ? limit : least + SPARE;
+  while (gw != most && layout_with(&finest, gw).total > enough) {
+    gw += (gw + 3) / 4;
+    if (most > 0 && gw > most) gw = most;
+    if (most == 0 && gw >= rows) gw = 0;
+  }
+  return gw;
+}
+
+// The number of chunks, at least d->k, that a caller's workspace is sized for.  Short groups of bias-gradient
+// sums may need much more scratch than long ones (512 rows x 8 heads x 144 at k = 1: 25 MiB against 5): then
+// it is that of more chunks, which need fewer partial sums at a time, until the difference is below SPARE or
+// more chunks no longer help (there: 2 chunks, 15 MiB).  A call with more scratch at hand, its own or the library's,
+// runs fewer.
+int workspace_chunks(const ss_attn_desc* d, Family fam, int gw) {
+  const size_t enough = layout_with(d, group_rows(d, fam, true)).total + SPARE;
+  const int finest = d->hi - d->lo;
+  ss_attn_desc t = *d, u = *d;
+  for (size_t now = layout_with(&t, gw).total; now > enough && t.k < finest; t.k = u.k) {
+    u.k = t.k > finest / 2 ? finest : 2 * t.k;
+    const size_t next = layout_with(&u, gw).total;
+    if (next > now / 5 * 4) break;
+    now = next;
+  }
+  return t.k;
 }
 
 KP base_params(const ss_attn_desc* d) {
@@ -218,12 +263,12 @@ struct ProfScope {
     if (e_ != hipSuccess) return hip_fail(e_, what);  \
   } while (0)
 
-// The smallest co-shard factor, at most d->k, whose scratch fits `bytes` (d->k if none does).  Powers of
-// two: every one of them gives the same results, so the search needs no finer steps.
-int fewest_chunks(const ss_attn_desc* d, Family fam, size_t bytes) {
+// The smallest co-shard factor, at most d->k, whose scratch with groups of `gw` rows fits `bytes` (d->k if none
+// does).  Powers of two: every one of them gives the same results, so the search needs no finer steps.
+int fewest_chunks(const ss_attn_desc* d, int gw, size_t bytes) {
   ss_attn_desc t = *d;
   for (t.k = 1; t.k < d->k; t.k *= 2)
-    if (bwd_layout(&t, fam).total <= bytes) return t.k;
+    if (layout_with(&t, gw).total <= bytes) return t.k;
   return d->k;
 }
 
@@ -299,6 +344,7 @@ int run_bwd(const ss_attn_desc* d, Family fam, const WsLayout& w, const void* Q,
       // one fused kernel per chunk; group partial sums of the bias gradient live in the workspace
       // across chunks and are reduced once the last chunk that touches them is enqueued
       p.sm_partial = want_dbias ? (float*)(ws + w.partial) : nullptr;
+      if (w.gw > 0) p.sm_gw = w.gw;
       set_groups(p);
       SS_LAUNCH(SS_K_DKDV, ssa::launch_small_bwd(p, st), "backward (short)");
       if (want_dbias) {
@@ -456,7 +502,13 @@ int ss_attn_workspace_bytes(const ss_attn_desc* d, size_t* fwd_bytes, size_t* bw
   const int rc = validate(d);
   if (rc != SS_OK) return rc;
   if (fwd_bytes) *fwd_bytes = 0;
-  if (bwd_bytes) *bwd_bytes = bwd_layout(d, family_of(d)).total;
+  if (bwd_bytes) {
+    ss_attn_desc run = *d;
+    const Family fam = family_of(d);
+    const int gw = group_rows(d, fam, false);
+    run.k = workspace_chunks(d, fam, gw);
+    *bwd_bytes = layout_with(&run, gw).total;
+  }
   return SS_OK;
 }
 
@@ -505,14 +557,20 @@ int ss_attn_bwd_static(const ss_attn_desc* d, const void* Q, const void* K, cons
                        void* dK, void* dV, float* dBias, void* dG, void* hip_stream) {
   const int rc = validate(d);
   if (rc != SS_OK) return rc;
-  if (bwd_layout(d, family_of(d)).total > (size_t)SS_ATTN_STATIC_SCRATCH_BYTES) return SS_ERR_STATIC_SCRATCH;
+  const Family fam = family_of(d);
+  const size_t limit = SS_ATTN_STATIC_SCRATCH_BYTES;
+  if (layout_with(d, group_rows(d, fam, true)).total > limit) return SS_ERR_STATIC_SCRATCH;
+  // short groups of bias-gradient sums need more scratch: more chunks then (group_rows sees to it that some number fits)
+  ss_attn_desc run = *d;
+  const int gw = group_rows(d, fam, false), finest = d->hi - d->lo;
+  run.k = workspace_chunks(d, fam, gw);
+  while (run.k < finest && layout_with(&run, gw).total > limit) run.k = run.k > finest / 2 ? finest : 2 * run.k;
   void* ptr = nullptr;
   const int rs = static_scratch(&ptr);
   if (rs != SS_OK) return rs;
   // nothing in the backward relies on scratch that starts at zero: every region is written by
   // the call before it is read, so the previous call's contents need no clearing
-  return ss_attn_bwd(d, Q, K, V, bias, region_ids, G, dY, lse, dQ, dK, dV, dBias, dG, ptr,
-                     (size_t)SS_ATTN_STATIC_SCRATCH_BYTES, hip_stream);
+  return ss_attn_bwd(&run, Q, K, V, bias, region_ids, G, dY, lse, dQ, dK, dV, dBias, dG, ptr, limit, hip_stream);
 }
 
 int ss_attn_bwd(const ss_attn_desc* d, const void* Q, const void* K, const void* V, const void* bias,
@@ -526,23 +584,25 @@ int ss_attn_bwd(const ss_attn_desc* d, const void* Q, const void* K, const void*
   if (d->mask_kind == SS_MASK_REGION && !region_ids) return SS_ERR_NULL;
   if (d->gated && (!G || !dG)) return SS_ERR_NULL;
   const Family fam = family_of(d);
-  WsLayout w = bwd_layout(d, fam);
+  const int gw = group_rows(d, fam, false);
+  ss_attn_desc run = *d;
+  run.k = workspace_chunks(d, fam, gw);
+  WsLayout w = layout_with(&run, gw);
   if (!workspace || workspace_bytes < w.total || ((uintptr_t)workspace % ALIGN)) return SS_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;
-  ss_attn_desc run = *d;
   ssa::SharedUse shared;
-  if (d->k > 1) {
+  if (run.k > 1) {
     // Chunks of a small share cannot fill the chip (a launch of 4 rows x 1 head takes as long as one of
     // 4 rows x 6), and what keeps them apart is only that they reuse one chunk's scratch.  The results
     // do not depend on k: run the fewest chunks whose scratch fits what the caller handed over, or
     // else the library's buffer.  Backward of 4 rows x 6 heads x 215 queries, D = 128, k = 4: 131 -> 36 us;
     // pair attention of 18 rows x 8 heads x 472, k = 16, forward and backward: 729 -> 113 us.
-    const int kw = fewest_chunks(d, fam, workspace_bytes), ks = fewest_chunks(d, fam, (size_t)SS_ATTN_STATIC_SCRATCH_BYTES);
+    const int kw = fewest_chunks(&run, gw, workspace_bytes), ks = fewest_chunks(&run, gw, ssa::SHARED_BYTES);
     void* own = ks < kw ? shared.take(st) : nullptr;
     if (own) ws = (char*)own;
     run.k = own ? ks : kw;
-    if (run.k != d->k) w = bwd_layout(&run, fam);
+    w = layout_with(&run, gw);
   }
   return run_bwd(&run, fam, w, Q, K, V, bias, region_ids, G, dY, lse, dQ, dK, dV, dBias, dG, ws, st);
 }

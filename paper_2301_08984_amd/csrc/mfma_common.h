@@ -409,10 +409,9 @@ inline bool win_ok(const KP& p) {
 // otherwise the share's rows are cut into groups so that about two work-groups per compute unit exist.
 inline int dbias_group_rows(const KP& p) {
   if (win_ok(p)) {
-    // one work-group per group: short groups while the share has few rows to go round
-    int gw = 8;
-    while (gw > 1 && p.share_units / gw < 1024) gw >>= 1;
-    return p.bias_kind != 0 ? gw : 0;
+    // one work-group per group and head, all of them at one time: 256 of five wavefronts, 512 of four or three
+    const int most = p.S > 128 ? 256 : 512;
+    return p.bias_kind != 0 ? (p.share_units + most - 1) / most : 0;
   }
   if (p.bias_kind != 1 || !fast_ok(p)) return 0;
   const int64_t tiles = (int64_t)((p.S + 63) / 64) * ((p.S + 63) / 64);
@@ -423,6 +422,11 @@ inline int dbias_group_rows(const KP& p) {
   int gw = 64;
   while (gw > 8 && tiles * p.share_units < 480 * (int64_t)gw) gw >>= 1;
   return gw;
+}
+
+// the longest such groups (0: one group): 64 rows, but for shapes whose sums can go on in the output
+inline int dbias_longest_group(const KP& p) {
+  return win_ok(p) || (p.S & 3) || dbias_group_rows(p) == 0 ? 0 : 64;
 }
 
 // calls f with the compile-time bias variant and causal flag of the launch

@@ -515,7 +515,13 @@ hipError_t launch_win_recompute_dq(const KP& p, hipStream_t st) {
   const dim3 g((p.b1 - p.b0 + rows - 1) / rows, p.h1 - p.h0);
   return with_shape(p, [&](auto nb, auto region) { win_rdq_kernel<nb(), region()><<<g, 64 * nb(), 0, st>>>(p, rows); });
 }
-hipError_t launch_win_kv(const KP& p, hipStream_t st) {
+hipError_t launch_win_kv(const KP& args, hipStream_t st) {
+  KP p = args;
+  if (p.dbias_acc && !p.sm_partial) {  // no partial sums: all rows are one group, which sums in the result itself
+    p.sm_partial = p.dbias_acc;
+    p.sm_gw = p.B;
+    p.sm_g0 = 0; p.sm_ring = 1; p.sm_hs = p.H; p.sm_h0 = 0;
+  }
   const dim3 g((p.b1 - 1) / p.sm_gw - p.b0 / p.sm_gw + 1, p.h1 - p.h0);
   return with_shape(p, [&](auto nb, auto region) { win_kv_kernel<nb(), region()><<<g, 64 * nb(), 0, st>>>(p); });
 }
