@@ -201,6 +201,7 @@ def ffn_main(a):
     """Co-sharded feed-forward: one step = ss_ffn_fwd + ss_ffn_bwd over the whole hidden share."""
     import torch
     from paper_2301_08984_amd import ffn_binding as fb
+    from paper_2301_08984_amd.binding import SS_LIBRARY_DEVICE_BYTES
     from paper_2301_08984_amd.runner import FfnCase
     from paper_2301_08984_amd.workloads import FFN_WORKLOADS, make_ffn_inputs
 
@@ -272,6 +273,8 @@ def ffn_main(a):
         except OSError:
             pass
         out["kernels"] = per_kernel
+        # the chunks of a small share run together in a buffer of the library's own: chunks_run counts the passes
+        # of the backward (one dW2 product each), and the buffer is part of the peak
         table = []
         caller = fc.caller_bytes()
         for k in ([] if a.no_per_k else sorted(set(ks) | {k_main})):
@@ -280,14 +283,20 @@ def ffn_main(a):
             for _ in range(2):
                 step(d)
             torch.cuda.synchronize()
+            fb.ss_ffn_profile_enable(True)
+            step(d)
+            torch.cuda.synchronize()
+            fb.ss_ffn_profile_enable(False)
+            ran = [fb.ss_ffn_profile_read(kid)[1] for kid in range(len(fb.KERNEL_NAMES))][fb.KERNEL_NAMES.index("dw2")]
             n = max(3, a.steps // 5)
             t0 = time.perf_counter()
             for _ in range(n):
                 step(d)
             torch.cuda.synchronize()
             t = (time.perf_counter() - t0) / n
-            table.append({"k": k, "ms_per_step": t * 1e3, "tflops": flops / t / 1e12, "workspace_bytes": max(fwd_b, bwd_b),
-                          "peak_hbm_bytes": caller + max(fwd_b, bwd_b),
+            table.append({"k": k, "chunks_run": ran, "ms_per_step": t * 1e3, "tflops": flops / t / 1e12,
+                          "workspace_bytes": max(fwd_b, bwd_b), "library_bytes": SS_LIBRARY_DEVICE_BYTES,
+                          "peak_hbm_bytes": caller + max(fwd_b, bwd_b) + SS_LIBRARY_DEVICE_BYTES,
                           "hidden_activation_bytes_per_chunk": int(2 * w["T"] * -(-nh // k) * 2)})
         out["per_k"] = table
     if not a.no_cpu_baseline:
@@ -335,7 +344,6 @@ def main():
     del host_inputs
     torch.cuda.synchronize()
     torch.cuda.empty_cache()   # staging copies of the upload go back to the driver
-    caller_measured = free0 - torch.cuda.mem_get_info()[0]
     desc = dc.desc(w["axis"], 0, ext, k_main)
     family = ss.ss_attn_kernel_family(desc)
     dc.workspace(desc)
@@ -343,6 +351,7 @@ def main():
     def step(d):
         dc.fwd(d, want_lse=False)
         dc.bwd(d)
+
 
     if a.calibration_copy:
         # a plain streaming kernel of known size: reads 1 GiB, writes 1 GiB
@@ -435,9 +444,11 @@ def main():
         out["kernels"] = per_kernel
 
         # throughput, workspace and peak HBM bytes for every co-shard factor of the workload
-        # "measured" = what hipMemGetInfo (through torch) says the device lost: the caller tensors once, the
-        # workspace per k (allocated alone after the allocator's cache was emptied; the allocator
-        # rounds blocks up, 2 MiB granularity for large ones, so the reading sits a little above the exact figure)
+        # the chunks of a small share run together in a buffer of the library's own, which is part of the peak;
+        # chunks_run = launches of the kernel that produces dK and dV in one step.
+        # "measured" = what hipMemGetInfo (through torch) says the device lost since before the caller tensors:
+        # those, the library's buffers and code, the workspace of this k (allocated alone after the allocator's cache
+        # was emptied; it rounds blocks up, 2 MiB granularity for large ones) and what the runtime keeps
         table = []
         caller = dc.caller_bytes()
         for k in ([] if a.no_per_k else sorted(set(ks) | {k_main})):
@@ -446,12 +457,16 @@ def main():
             dc.ws = None
             torch.cuda.synchronize()
             torch.cuda.empty_cache()
-            f0 = torch.cuda.mem_get_info()[0]
             dc.workspace(d)
             for _ in range(3):
                 step(d)
             torch.cuda.synchronize()
-            ws_measured = f0 - torch.cuda.mem_get_info()[0]
+            measured = free0 - torch.cuda.mem_get_info()[0]
+            ss.ss_attn_profile_enable(True)
+            step(d)
+            torch.cuda.synchronize()
+            ss.ss_attn_profile_enable(False)
+            launches = {name: ss.ss_attn_profile_read(kid)[1] for kid, name in enumerate(ss.KERNEL_NAMES)}
             n = max(5, a.steps // 5)
             t0 = time.perf_counter()
             for _ in range(n):
@@ -460,9 +475,11 @@ def main():
             t = (time.perf_counter() - t0) / n
             chunk_units = -(-ext // k)
             sxs = chunk_units * (w["B"] * w["H"] / ext) * w["S"] ** 2 * 2
-            table.append({"k": k, "ms_per_step": t * 1e3, "tflops": job_flops(w) / t / 1e12,
-                          "workspace_bytes": wsb, "peak_hbm_bytes": caller + wsb,
-                          "measured_peak_hbm_bytes": caller_measured + ws_measured,
+            table.append({"k": k, "chunks_run": launches["dkdv"] + launches["dq_dkdv"], "ms_per_step": t * 1e3,
+                          "tflops": job_flops(w) / t / 1e12,
+                          "workspace_bytes": wsb, "library_bytes": ss.SS_LIBRARY_DEVICE_BYTES,
+                          "peak_hbm_bytes": caller + wsb + ss.SS_LIBRARY_DEVICE_BYTES,
+                          "measured_peak_hbm_bytes": measured,
                           "unfused_scores_bytes_per_chunk": int(sxs)})
         out["per_k"] = table
 

@@ -15,10 +15,15 @@
  * and the backward produces dQ, dK, dV, dG and the bias gradient for dY.
  *
  * All pointers are DEVICE pointers unless said otherwise; the descriptor and
- * the size outputs are HOST memory.  The library allocates no device memory and
- * never synchronises: all work is enqueued on the caller's stream and the call
- * returns while it may still be running.  It keeps no state between calls, except
- * the opt-in timing instrumentation at the end of this file.
+ * the size outputs are HOST memory.  No call allocates device memory or
+ * synchronises: all work is enqueued on the caller's stream and the call
+ * returns while it may still be running.  What the library holds for itself, from
+ * its first use on a GPU until the process ends, is SS_LIBRARY_DEVICE_BYTES of that
+ * GPU's memory: the buffer of ss_attn_bwd_static, and a buffer in which calls run
+ * several chunks together or hand partial sums over (ss_attn_workspace_bytes,
+ * ss_ffn.h), with an event that marks the end of the last call that used it.  It keeps
+ * no results between calls, and no other state than that, the helper stream of
+ * ss_ffn_bwd and the opt-in timing instrumentation at the end of this file.
  */
 #ifndef SS_ATTN_H
 #define SS_ATTN_H
@@ -160,6 +165,8 @@ int ss_attn_bwd(const ss_attn_desc* desc, const void* Q, const void* K, const vo
  * the same time on one GPU (different streams or threads) race; calls on one stream are safe.
  * The buffer keeps the previous call's contents; no part of it needs to start at zero. */
 #define SS_ATTN_STATIC_SCRATCH_BYTES (32u << 20)
+/* Device memory that the library holds on every GPU it is used on: that buffer, 64 MiB and 2 KiB. */
+#define SS_LIBRARY_DEVICE_BYTES (SS_ATTN_STATIC_SCRATCH_BYTES + (64u << 20) + 2048u)
 int ss_attn_bwd_static(const ss_attn_desc* desc, const void* Q, const void* K, const void* V,
                        const void* bias, const int32_t* region_ids, const void* G,
                        const void* dY, const float* lse,
@@ -177,8 +184,7 @@ const char* ss_attn_kernel_family(const ss_attn_desc* desc);
 
 /* Benchmark instrumentation, not part of the method.  While enabled, every kernel
  * the scheduler launches is bracketed by two HIP events recorded on the launch
- * stream (this is the only state the library keeps, and the only time it creates
- * HIP objects).  ss_attn_profile_read waits for the recorded events, returns the
+ * stream.  ss_attn_profile_read waits for the recorded events, returns the
  * summed duration in milliseconds and the number of launches of one kernel since
  * the last read, and resets both.  Not thread-safe. */
 typedef enum {

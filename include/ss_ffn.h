@@ -25,12 +25,12 @@
  * that do not sum over the hidden columns are then one launch for the share.  The bits are the same.)
  *
  * All pointers are DEVICE pointers unless said otherwise; the descriptor and size outputs are HOST
- * memory.  The library allocates no device memory and never synchronises the host; the work is
+ * memory.  No call allocates device memory or synchronises the host; the work is
  * enqueued on the caller's stream, except that ss_ffn_bwd may fork dW2 and the bias gradients onto a
  * helper stream of the library's own (one per device, default priority, created on first use) and
  * joins it back into the caller's stream with events before the call returns: to the caller the
- * call is ordered on its stream like any other.  That stream and the buffer are the only state the library keeps;
- * the fork / join events are created and released per call, so calls from several host threads or
+ * call is ordered on its stream like any other.  That stream and the library's buffer (ss_attn.h) are
+ * the only state it keeps; the fork / join events are created and released per call, so calls from several host threads or
  * on several caller streams of one device are independent (their helper work is merely queued on
  * the same helper stream).  Error codes are those of ss_attn.h.
  */

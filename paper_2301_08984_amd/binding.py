@@ -21,6 +21,7 @@ SS_OK = 0
 SS_ERR_NULL, SS_ERR_BAD_SHAPE, SS_ERR_BAD_RANGE, SS_ERR_BAD_K = -1, -2, -3, -4
 SS_ERR_UNSUPPORTED, SS_ERR_WORKSPACE, SS_ERR_HIP, SS_ERR_STATIC_SCRATCH = -5, -6, -7, -8
 SS_ATTN_STATIC_SCRATCH_BYTES = 32 << 20
+SS_LIBRARY_DEVICE_BYTES = SS_ATTN_STATIC_SCRATCH_BYTES + (64 << 20) + 2048
 
 EXPORTS = ("ss_attn_workspace_bytes", "ss_attn_chunk_range", "ss_attn_fwd", "ss_attn_bwd", "ss_attn_bwd_static",
            "ss_strerror",

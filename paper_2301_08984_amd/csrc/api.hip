@@ -19,6 +19,7 @@ static __device__ __align__(256) unsigned char scratch[SS_ATTN_STATIC_SCRATCH_BY
 // The scratch of shared_scratch.h.
 static __device__ __align__(256) unsigned char shared_scratch[ssa::SHARED_BYTES];
 static __device__ unsigned shared_counters[ssa::SHARED_COUNTERS];
+static_assert(sizeof(scratch) + sizeof(shared_scratch) + sizeof(shared_counters) == SS_LIBRARY_DEVICE_BYTES, "as documented");
 
 namespace {
 

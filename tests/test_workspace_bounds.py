@@ -90,3 +90,14 @@ def test_partial_sums_are_bounded_and_never_cost_the_built_in_buffer():
         refused += least > limit
     assert worst <= 4, worst
     assert shorter > 300 and more_chunks >= 1 and refused > 200, (shorter, more_chunks, refused)
+
+
+def test_library_device_memory_is_what_the_header_says():
+    """The sizes in the header, in the binding and (a static assertion) in the library are the same."""
+    import os
+    import re
+    text = open(os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "include", "ss_attn.h")).read()
+    macros = dict(re.findall(r"#define (SS_\w+_BYTES) (.+)", text))
+    value = lambda name: eval(re.sub(r"SS_\w+", lambda m: str(value(m.group(0))), macros[name]).replace("u", ""))
+    assert value("SS_ATTN_STATIC_SCRATCH_BYTES") == ss.SS_ATTN_STATIC_SCRATCH_BYTES
+    assert value("SS_LIBRARY_DEVICE_BYTES") == ss.SS_LIBRARY_DEVICE_BYTES
