@@ -227,7 +227,6 @@ int static_scratch(void** out) {
   return SS_OK;
 }
 
-std::mutex g_shared_mu;
 ssa::Shared g_shared[MAX_DEVICES];
 
 int hip_fail(hipError_t e, const char* what) {
@@ -415,9 +414,9 @@ void* SharedUse::take(hipStream_t stream) {
     (void)hipGetLastError();
     return nullptr;
   }
-  std::unique_lock<std::mutex> l(g_shared_mu, std::try_to_lock);
-  if (!l.owns_lock()) return nullptr;
   Shared& x = g_shared[dev];
+  std::unique_lock<std::mutex> l(x.mu, std::try_to_lock);
+  if (!l.owns_lock()) return nullptr;
   if (x.broken) return nullptr;
   // a capture under way in another thread must not see these calls as its own
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;

@@ -49,3 +49,44 @@ def test_chunked_and_merged_runs_agree(name, k):
             other.bwd(d)
     check(dc, "first stream")
     check(other, "second stream")
+
+
+@pytest.mark.parametrize("name,k", [("gpt_like", 2), ("swin_like", 4)])
+def test_two_host_threads_on_two_streams(name, k):
+    """Whoever holds the buffer, and whoever does without, gets the results of a run alone."""
+    import threading
+    import torch
+    from paper_2301_08984_amd.runner import DeviceCase
+    from paper_2301_08984_amd.workloads import make_inputs
+    cfg = SMALL[name]
+    inp = make_inputs(**cfg)
+    cases = [DeviceCase(inp, dtype=cfg["dtype"], bias=cfg.get("bias"), mask=cfg.get("mask"), gated=cfg.get("gated", False),
+                        win=cfg.get("win"), layout=cfg.get("layout", "bshd")) for _ in range(3)]
+    ext = cases[0].H if cfg["axis"] == "head" else cases[0].B
+    d = cases[0].desc(cfg["axis"], 0, ext, k)
+    for c in cases:
+        c.workspace(d)
+    cases[2].bwd(d, poison=True)
+    streams, errors = [torch.cuda.Stream(), torch.cuda.Stream()], []
+    print(f"attention two threads {name}", flush=True)
+    torch.cuda.synchronize()
+
+    def work(i):
+        try:
+            for _ in range(20):
+                cases[i].bwd(d, stream=streams[i].cuda_stream)
+        except Exception as e:  # noqa: BLE001
+            errors.append(e)
+
+    ts = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors, errors
+    for i in range(2):
+        for n in OUTS:
+            ref = getattr(cases[2], n)
+            if ref is not None:
+                assert torch.equal(torch.nan_to_num(getattr(cases[i], n), nan=12345.0), torch.nan_to_num(ref, nan=12345.0)), (i, n)
