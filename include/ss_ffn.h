@@ -72,7 +72,13 @@ enum {
 
 /* Workspace bytes ss_ffn_fwd / ss_ffn_bwd need (host outputs).  Forward: one chunk's H.  Backward:
  * one chunk's H and act'(Z) (overwritten by dZ).  Both shrink as 1/k.  With SS_FFN_FLAG_EXACT_SUM
- * and k > 1 the fp32 accumulator of Y (forward) or dX (backward) is added. */
+ * and k > 1 the fp32 accumulator of Y (forward) or dX (backward) is added.
+ * Products with few tiles (a few tokens) are cut into parts along their contraction, which are summed up
+ * side by side where there is scratch for their sums: in the library's buffer, or, when a call
+ * cannot have that (under graph capture, beside another stream), in a workspace that is larger than the
+ * figure by SS_FFN_PARTS_BYTES.  With neither the parts go one after the other: the same bits,
+ * more time (16 tokens x 12288 x 6144: 73 us with either, 171 with neither). */
+#define SS_FFN_PARTS_BYTES ((32u << 20) + 2048u)
 int ss_ffn_workspace_bytes(const ss_ffn_desc* desc, size_t* fwd_bytes, size_t* bwd_bytes);
 
 /* Hidden range of chunk c (0 <= c < k): balanced in units of 16 columns counted from lo. */

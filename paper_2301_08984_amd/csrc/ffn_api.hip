@@ -6,6 +6,7 @@
 #include <mutex>
 
 #include "ffn_kernels.h"
+#include "kparams.h"
 #include "shared_scratch.h"
 
 namespace {
@@ -158,20 +159,36 @@ ssa::GemmArgs gemm(const void* A, int64_t lda, const void* B, int64_t ldb, int M
   return g;
 }
 
-// The library's scratch, for split contractions (one half of SPLIT_BYTES for the caller's stream, one for
+// Scratch beyond one chunk's hidden activations, the library's if nobody else is using it: for split contractions (one half of SPLIT_BYTES for the caller's stream, one for
 // the helper stream) and for the hidden activations of a whole small share.
 constexpr size_t HIDDEN_BYTES = 32u << 20;
 static_assert(HIDDEN_BYTES + 2 * ssa::SPLIT_BYTES <= ssa::SHARED_BYTES && 2 * ssa::SPLIT_TILES <= ssa::SHARED_COUNTERS, "library scratch");
+constexpr size_t COUNTER_BYTES = 2 * ssa::SPLIT_TILES * sizeof(unsigned);
+static_assert(SS_FFN_PARTS_BYTES == COUNTER_BYTES + 2 * ssa::SPLIT_BYTES, "as documented");
 struct Scratch {
   ssa::SharedUse use;
-  char* base = nullptr;
-  Scratch(hipStream_t st, bool want) { if (want) base = (char*)use.take(st); }
+  char* base = nullptr;                    // the library's, if this call has it
+  char* parts = nullptr;                   // of the split contractions: the library's, or at the end of the caller's workspace
+  unsigned* counters = nullptr;
+  // `spare`, `bytes`: the caller's workspace beyond what the call needs
+  Scratch(hipStream_t st, bool merge, bool split, char* spare, size_t bytes) {
+    if (merge || split) base = (char*)use.take(st);
+    if (base) {
+      parts = base + HIDDEN_BYTES;
+      counters = use.counters();
+    } else if (split && bytes >= SS_FFN_PARTS_BYTES) {
+      // a kernel of its own sets the counters to zero (3 us), which is how the products leave them
+      if (ssa::launch_fill_zero((float*)spare, COUNTER_BYTES / sizeof(float), st) != hipSuccess) return;
+      counters = (unsigned*)spare;
+      parts = spare + COUNTER_BYTES;
+    }
+  }
   void set(ssa::GemmArgs& g, ssa::GemmPlan plan, int half) const {
     g.cols = plan.cols;
     g.split = plan.split;
-    if (!base || plan.split < 2) return;
-    g.parts = (float*)(base + HIDDEN_BYTES + half * ssa::SPLIT_BYTES);
-    g.counters = use.counters() + half * ssa::SPLIT_TILES;
+    if (!parts || plan.split < 2) return;
+    g.parts = (float*)(parts + half * ssa::SPLIT_BYTES);
+    g.counters = counters + half * ssa::SPLIT_TILES;
   }
 };
 
@@ -260,7 +277,8 @@ int ss_ffn_fwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
   const bool exact = (d->flags & SS_FFN_FLAG_EXACT_SUM) != 0;
   const int n = d->hi - d->lo;
   const ssa::GemmPlan plan_up = ssa::gemm_plan(d->T, n, d->dm);
-  Scratch scratch(st, Hidden::wanted(d, false) || plan_up.split > 1 || (!exact && ssa::gemm_plan(d->T, d->dm, n).split > 1));
+  Scratch scratch(st, Hidden::wanted(d, false), plan_up.split > 1 || (!exact && ssa::gemm_plan(d->T, d->dm, n).split > 1),
+                  ws + w.total, workspace_bytes - w.total);
   const Hidden hid(d, w, ws, scratch, false);
   for (int g = 0; g < hid.groups; ++g) {
     int a, b, c0, c1;
@@ -302,8 +320,10 @@ int ss_ffn_bwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
   const int n = d->hi - d->lo;
   const ssa::GemmPlan plan_up = ssa::gemm_plan(d->T, n, d->dm), plan_dh = ssa::gemm_plan_tiled(d->T, n, d->dm);
   const ssa::GemmPlan plan_w1 = ssa::gemm_plan_tiled(d->dm, n, d->T), plan_w2 = ssa::gemm_plan_tiled(n, d->dm, d->T);
-  Scratch scratch(st, Hidden::wanted(d, true) || plan_up.split > 1 || plan_dh.split > 1 || plan_w1.split > 1 || plan_w2.split > 1 ||
-                          (!exact && ssa::gemm_plan_tiled(d->T, d->dm, n).split > 1));
+  Scratch scratch(st, Hidden::wanted(d, true),
+                  plan_up.split > 1 || plan_dh.split > 1 || plan_w1.split > 1 || plan_w2.split > 1 ||
+                      (!exact && ssa::gemm_plan_tiled(d->T, d->dm, n).split > 1),
+                  ws + w.total, workspace_bytes - w.total);
   const Hidden hid(d, w, ws, scratch, true);
   uint16_t *Hp = (uint16_t*)hid.H, *Dp = (uint16_t*)hid.D;
   // The helper stream costs some 10 us of waits between the streams, and two products at once that each
