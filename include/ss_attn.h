@@ -178,8 +178,10 @@ const char* ss_strerror(int code);
 /* Host-only: which kernel family a descriptor is served by: "mfma_bf16" (bf16
  * activations, D in {32,64,128}), "mfma_bf16_short" (bf16, D = 32, S <= 64, not
  * gated: one wavefront holds a whole score matrix) or "plain_fp32" (everything
- * else, and whenever SS_FLAG_GENERIC_KERNELS is set).  NULL for an invalid
- * descriptor. */
+ * else, and whenever SS_FLAG_GENERIC_KERNELS is set).  fp32 operators of head size up to 64, in rows
+ * of whole 16-byte pieces, are of the last family too: they run on the fp32 matrix
+ * instructions (fp32 operands, products and sums) unless the flag is set.  NULL for an
+ * invalid descriptor. */
 const char* ss_attn_kernel_family(const ss_attn_desc* desc);
 
 /* Benchmark instrumentation, not part of the method.  While enabled, every kernel
@@ -191,7 +193,8 @@ typedef enum {
   SS_K_FWD = 0, SS_K_RECOMPUTE = 1, SS_K_DQ = 2, SS_K_DKDV = 3, SS_K_DBIAS = 4, SS_K_TABLE_REDUCE = 5,
   SS_K_DQ_DKDV = 6,   /* dQ and dK/dV in one launch (small shares with long rows) */
   SS_K_DBIAS_FOLD = 7, /* fold of completed bias-gradient group partials into the result */
-  SS_K_RECOMPUTE_DQ = 8, /* recompute pass and dQ in one launch (head size 32, large shares) */
+  SS_K_RECOMPUTE_DQ = 8, /* recompute pass and dQ in one launch (head size 32, large shares; fp32, whose
+                            SS_K_DKDV launch takes the bias gradient too) */
   SS_K_COUNT = 9
 } ss_kernel_id;
 int ss_attn_profile_enable(int on);

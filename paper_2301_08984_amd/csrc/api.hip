@@ -3,6 +3,7 @@
 // (op-order), all on the current device (op-assign), every chunk reusing the same
 // workspace (co-shard, Section 2 of the paper).
 #include "../../include/ss_attn.h"
+#include "f32_kernels.h"
 #include "kparams.h"
 #include "mfma_common.h"
 #include "shared_scratch.h"
@@ -182,6 +183,7 @@ KP base_params(const ss_attn_desc* d) {
   p.share_units = (d->hi - d->lo) * (d->shard_axis == SS_AXIS_HEAD ? d->B : d->H);
   p.share_b0 = d->shard_axis == SS_AXIS_ROW ? d->lo : 0;
   p.sm_gw = small_group_rows(p.share_units);
+  p.plain = (d->flags & SS_FLAG_GENERIC_KERNELS) != 0;
   return p;
 }
 
@@ -385,6 +387,9 @@ int run_bwd(const ss_attn_desc* d, Family fam, const WsLayout& w, const void* Q,
           if (rf != SS_OK) return rf;
         }
       }
+    } else if (!bf16 && ssa::f32_ok(p)) {
+      SS_LAUNCH(SS_K_RECOMPUTE_DQ, ssa::launch_generic_fwd(p, bf16, true, st), "recompute + dQ (fp32)");
+      SS_LAUNCH(SS_K_DKDV, ssa::launch_generic_dkdv(p, bf16, st), "dK/dV + dBias (fp32)");
     } else {
       SS_LAUNCH(SS_K_RECOMPUTE, ssa::launch_generic_fwd(p, bf16, true, st), "recompute (generic)");
       SS_LAUNCH(SS_K_DQ, ssa::launch_generic_dq(p, bf16, st), "dQ (generic)");

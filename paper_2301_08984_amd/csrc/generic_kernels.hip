@@ -1,7 +1,7 @@
 // Plain (non-MFMA) attention kernels: fp32 arithmetic on the vector ALUs, one
 // wavefront per row of the score matrix.  They cover every dtype / head size /
 // bias / mask combination the C ABI accepts (D <= 256).  fp32 tensors that f32_ok()
-// accepts (head sizes up to 64, rows of whole 16-byte pieces) go to f32_kernels.hip.
+// accepts (head sizes up to 64, rows of whole 16-byte pieces, plain kernels not asked for) go to f32_kernels.hip.
 #include "f32_kernels.h"
 
 namespace ssa {
@@ -372,7 +372,6 @@ hipError_t launch_generic_fwd(const KP& p, bool bf16, bool recompute, hipStream_
   return hipGetLastError();
 }
 hipError_t launch_generic_dq(const KP& p, bool bf16, hipStream_t st) {
-  if (!bf16 && f32_ok(p)) return hipSuccess;  // done by the recompute launch
   dim3 g = row_grid(p), blk(WAVES * 64);
   if (bf16) generic_dq_kernel<bf16_t><<<g, blk, 0, st>>>(p);
   else generic_dq_kernel<float><<<g, blk, 0, st>>>(p);
@@ -386,7 +385,6 @@ hipError_t launch_generic_dkdv(const KP& p, bool bf16, hipStream_t st) {
   return hipGetLastError();
 }
 hipError_t launch_generic_dbias(const KP& p, bool bf16, hipStream_t st) {
-  if (!bf16 && f32_ok(p)) return hipSuccess;  // done by the dK/dV launch
   dim3 g((p.S + 255) / 256, p.S, p.h1 - p.h0), blk(256);
   if (bf16) generic_dbias_kernel<bf16_t><<<g, blk, 0, st>>>(p);
   else generic_dbias_kernel<float><<<g, blk, 0, st>>>(p);

@@ -47,6 +47,7 @@ struct KP {
   int share_units;  // (row, head) pairs in the whole share [lo,hi): kernel-shape choices use this, never the chunk
   float scale;
   int bias_kind, bias_bf16, mask_kind, mask_period, win_h, win_w, gated;
+  int plain;  // the caller asks for the plain kernels (SS_FLAG_GENERIC_KERNELS)
 };
 
 // launchers (each returns the hipError_t of the launch)

@@ -44,3 +44,25 @@ def test_matches_oracle(name):
         ref = ref or outs
         for o, x in outs.items():
             assert np.array_equal(x, ref[o], equal_nan=True), (o, k)
+
+
+def test_the_flag_for_plain_kernels_is_honoured_and_slots_count_launches():
+    """SS_FLAG_GENERIC_KERNELS takes an fp32 operator to the plain kernels (recompute, dQ, dK/dV, dBias: four
+    launches a chunk); without it there are two, and no time slot counts a launch that does not exist."""
+    import torch
+    from paper_2301_08984_amd import binding as ss
+    from paper_2301_08984_amd.runner import DeviceCase
+    from paper_2301_08984_amd.workloads import make_inputs
+    cfg = _cfg(70, 32, bias="dense")
+    dc = DeviceCase(make_inputs(**cfg), dtype="f32", bias="dense")
+    print("f32 launches", flush=True)
+    for flags, want in ((0, {"fwd": 1, "recompute_dq": 1, "dkdv": 1}),
+                        (ss.SS_FLAG_GENERIC_KERNELS, {"fwd": 1, "recompute": 1, "dq": 1, "dkdv": 1, "dbias": 1})):
+        d = dc.desc("row", 0, dc.B, 1, flags)
+        ss.ss_attn_profile_enable(True)
+        dc.fwd(d)
+        dc.bwd(d)
+        torch.cuda.synchronize()
+        ss.ss_attn_profile_enable(False)
+        got = {n: ss.ss_attn_profile_read(i)[1] for i, n in enumerate(ss.KERNEL_NAMES)}
+        assert {n: c for n, c in got.items() if c} == want, (flags, got)

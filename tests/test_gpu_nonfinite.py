@@ -6,6 +6,7 @@ import math
 import numpy as np
 import pytest
 
+from paper_2301_08984_amd import binding as ss
 from paper_2301_08984_amd.runner import DeviceCase
 from paper_2301_08984_amd.workloads import make_inputs
 
@@ -51,10 +52,11 @@ def _plant(name, inp, bias):
 SKIP = {("nan_key", "causal"): ("dQ",), ("nan_key", "region"): ("dQ",)}
 
 
+@pytest.mark.parametrize("flags", [0, ss.SS_FLAG_GENERIC_KERNELS], ids=["default", "plain"])
 @pytest.mark.parametrize("S,D", [(40, 16), (300, 64), (1030, 32)])
 @pytest.mark.parametrize("name,mask", [("nan_key", None), ("nan_key", "causal"), ("nan_key", "region"), ("nan_bias", None),
                                        ("nan_bias", "causal"), ("inf_bias", None), ("masking_bias", None), ("dead_row", None)])
-def test_fp32_nonfinite_inputs(name, mask, S, D):
+def test_fp32_nonfinite_inputs(name, mask, S, D, flags):
     import torch
     inp = make_inputs(seed=61, B=2, H=2, S=S, D=D, dtype="f32", bias="dense", axis="row")
     bias = inp["bias"]
@@ -67,8 +69,8 @@ def test_fp32_nonfinite_inputs(name, mask, S, D):
     dc = DeviceCase(inp, dtype="f32", bias="dense", mask=mask)
     ref = _reference(inp, bias, np.broadcast_to(live, (2, S, S)), float(np.float32(1.0 / math.sqrt(D))))
     for use_lse in (False, True):
-        print(f"non-finite {name} mask={mask} S={S} use_lse={use_lse}", flush=True)
-        d = dc.desc("row", 0, 2, 1)
+        print(f"non-finite {name} mask={mask} S={S} use_lse={use_lse} flags={flags}", flush=True)
+        d = dc.desc("row", 0, 2, 1, flags)
         dc.fwd(d)
         dc.bwd(d, use_lse=use_lse, poison=True)
         torch.cuda.synchronize()
