@@ -223,9 +223,13 @@ __device__ inline BlockId causal_block_id(bool pairs) {
   // the whole units' blocks and the dealt ones, mixed in proportion; then the dealt ones by group
   const int own = units / NX;
   int over = count - own * gx, unit, x;
-  auto before = [&](int pos, int part, int all) { return (int)((int64_t)pos * part / all); };
-  int lo = before(at, over, count);
-  if (before(at + 1, over, count) == lo) {
+  // (a 64-bit division costs a good hundred instructions before the first load: only for launches that need it)
+  const bool wide = (int64_t)(count + 1) * over >= (1ll << 31);
+  auto before = [&](int pos, int part, int all) {
+    return wide ? (int)((int64_t)pos * part / all) : (int)((uint32_t)(pos * part) / (uint32_t)all);
+  };
+  int lo = over ? before(at, over, count) : 0;
+  if (!over || before(at + 1, over, count) == lo) {
     const int f = at - lo;
     x = f / own;
     unit = xcd * own + f % own;
