@@ -201,31 +201,26 @@ struct Hidden {
   char *H, *D;
   int64_t ld;
   int groups;  // passes over the columns
-  // the fewest groups of consecutive chunks whose H (and D) fit HIDDEN_BYTES: d->k if not even two chunks do
-  static int fewest(const ss_ffn_desc* d, bool backward, int64_t* ld) {
-    for (int g = 1; g < d->k; ++g) {
-      int widest = 0;
-      for (int i = 0; i < g; ++i) {
-        int a, b, c0, c1;
-        range(d, g, i, &a, &b, &c0, &c1);
-        if (b - a > widest) widest = b - a;
-      }
-      *ld = (widest + 7) & ~7;
-      if (align256((size_t)d->T * *ld * 2) * (backward ? 2 : 1) <= HIDDEN_BYTES) return g;
-    }
-    return d->k;
+  // groups of consecutive chunks whose H (and D) fit HIDDEN_BYTES: d->k if not even two chunks do.  As few as
+  // surely fit: m consecutive chunks hold at most ceil(m units / k) units of columns.
+  static int fewest(const ss_ffn_desc* d, bool backward) {
+    if (d->k == 1) return 1;
+    const int64_t units = (d->hi - d->lo + UNIT - 1) / UNIT, unit = (int64_t)d->T * UNIT * 2;
+    const int64_t fit = (int64_t)(HIDDEN_BYTES / (backward ? 2 : 1)) / 256 * 256 / unit;  // units of columns whose H fits
+    const int64_t most = fit >= units ? d->k : fit * d->k / units;                        // chunks of a group
+    return most < 2 ? d->k : (int)((d->k + most - 1) / most);
   }
-  static bool wanted(const ss_ffn_desc* d, bool backward) {
-    int64_t unused;
-    return fewest(d, backward, &unused) < d->k;
-  }
-  Hidden(const ss_ffn_desc* d, const Ws& w, char* ws, const Scratch& scratch, bool backward)
+  Hidden(const ss_ffn_desc* d, const Ws& w, char* ws, const Scratch& scratch, int few)
       : H(ws + w.H), D(ws + w.D), ld(w.ldh), groups(d->k) {
-    int64_t wide = 0;
-    const int few = scratch.base ? fewest(d, backward, &wide) : d->k;
-    if (few == d->k) return;
+    if (!scratch.base || few == d->k) return;
+    int widest = 0;
+    for (int i = 0; i < few; ++i) {
+      int a, b, c0, c1;
+      range(d, few, i, &a, &b, &c0, &c1);
+      if (b - a > widest) widest = b - a;
+    }
     groups = few;
-    ld = wide;
+    ld = (widest + 7) & ~7;
     H = scratch.base;
     D = scratch.base + align256((size_t)d->T * ld * 2);
   }
@@ -277,9 +272,10 @@ int ss_ffn_fwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
   const bool exact = (d->flags & SS_FFN_FLAG_EXACT_SUM) != 0;
   const int n = d->hi - d->lo;
   const ssa::GemmPlan plan_up = ssa::gemm_plan(d->T, n, d->dm);
-  Scratch scratch(st, Hidden::wanted(d, false), plan_up.split > 1 || (!exact && ssa::gemm_plan(d->T, d->dm, n).split > 1),
+  const int few = Hidden::fewest(d, false);
+  Scratch scratch(st, few < d->k, plan_up.split > 1 || (!exact && ssa::gemm_plan(d->T, d->dm, n).split > 1),
                   ws + w.total, workspace_bytes - w.total);
-  const Hidden hid(d, w, ws, scratch, false);
+  const Hidden hid(d, w, ws, scratch, few);
   for (int g = 0; g < hid.groups; ++g) {
     int a, b, c0, c1;
     hid.pass(d, g, &a, &b, &c0, &c1);
@@ -320,11 +316,12 @@ int ss_ffn_bwd(const ss_ffn_desc* d, const void* X, const void* W1, const void* 
   const int n = d->hi - d->lo;
   const ssa::GemmPlan plan_up = ssa::gemm_plan(d->T, n, d->dm), plan_dh = ssa::gemm_plan_tiled(d->T, n, d->dm);
   const ssa::GemmPlan plan_w1 = ssa::gemm_plan_tiled(d->dm, n, d->T), plan_w2 = ssa::gemm_plan_tiled(n, d->dm, d->T);
-  Scratch scratch(st, Hidden::wanted(d, true),
+  const int few = Hidden::fewest(d, true);
+  Scratch scratch(st, few < d->k,
                   plan_up.split > 1 || plan_dh.split > 1 || plan_w1.split > 1 || plan_w2.split > 1 ||
                       (!exact && ssa::gemm_plan_tiled(d->T, d->dm, n).split > 1),
                   ws + w.total, workspace_bytes - w.total);
-  const Hidden hid(d, w, ws, scratch, true);
+  const Hidden hid(d, w, ws, scratch, few);
   uint16_t *Hp = (uint16_t*)hid.H, *Dp = (uint16_t*)hid.D;
   // The helper stream costs some 10 us of waits between the streams, and two products at once that each
   // fill the chip get in each other's way (8192 tokens x 12288 x 6144: 5.5 ms against 5.1 in turn), so dW2 goes
