@@ -31,17 +31,15 @@ __device__ inline f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdg
 // error put back in; below e^-150 (also for -inf) zero; NaN stays NaN
 __device__ inline float exp_f32(float x) {
   constexpr float L2E = 1.44269502e+00f, L2E_LO = 1.92596299e-08f, LN2 = 6.93147182e-01f;  // log2(e) = L2E + L2E_LO
-  x = x < -150.f ? -150.f : x;
+  x = __builtin_elementwise_maximum(x, -150.f);
   const float t = x * L2E, r = fmaf(x, L2E_LO, fmaf(x, L2E, -t));
   const float y = __builtin_amdgcn_exp2f(t);
   return fmaf(y, r * LN2, y);
 }
 
-// e^(x - m), the weight under a maximum m of sums taken under a maximum x <= m: 1 where they are equal, also
-// both -inf (no key yet, the sums are 0)
-__device__ inline float weight(float x, float m) { return x == m ? 1.f : exp_f32(x - m); }
-// unnormalised probability of a score: 0 for -inf, also under a maximum of -inf
-__device__ inline float prob(float s, float m) { return s == -INFINITY ? 0.f : exp_f32(s - m); }
+// what is subtracted from scores (and earlier maxima) under a maximum m: not -inf (no key yet), so that they
+// get a weight of 0
+__device__ inline float base_of(float m) { return m == -INFINITY ? 0.f : m; }
 
 template <int DC>
 struct Nat { f32x4 x[DC]; };
@@ -113,24 +111,37 @@ __device__ inline float bias_f32(const KP& p, int h, int i, int j) {
   }
   return p.bias_bf16 ? __uint_as_float((uint32_t)((const uint16_t*)p.bias)[off] << 16) : ((const float*)p.bias)[off];
 }
+// may any pair of the block of 16 queries from q0 and 16 keys from k0 be masked (or lie past the end)?  Uniform.
+__device__ inline bool has_edge(const KP& p, const int32_t* rid, int q0, int k0) {
+  return rid || q0 + 16 > p.S || k0 + 16 > p.S || (p.mask_kind == 1 && k0 + 15 > q0);
+}
 // scores of a block in C registers -> scale s + bias, -inf where the pair is masked.  Register v is the
-// pair (q, k + v) if KEYS_RUN, else (q + v, k).  Returns the masked registers, bit v: their gradients are 0
-// whatever the statistics are (a query that sees a NaN has NaN statistics).
+// pair (q, k + v) if KEYS_RUN, else (q + v, k).  `dead` (of a block with an edge): the masked registers.
 template <bool KEYS_RUN>
-__device__ inline uint32_t finish_scores(const KP& p, int h, const int32_t* rid, int q, int k, f32x4& s) {
-  uint32_t masked = 0;
+__device__ inline void finish_scores(const KP& p, int h, const int32_t* rid, int q, int k, bool edge, f32x4& s, bool (&dead)[4]) {
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
-    const int i = KEYS_RUN ? q : q + v, j = KEYS_RUN ? k + v : k;
-    const int ic = min(i, p.S - 1), jc = min(j, p.S - 1);
-    float x = p.scale * s[v];
-    if (p.bias_kind) x += bias_f32(p, h, ic, jc);
-    bool dead = i >= p.S || j >= p.S || (p.mask_kind == 1 && j > i);
-    if (rid) dead = dead || rid[ic] != rid[jc];
-    s[v] = dead ? -INFINITY : x;
-    masked |= (uint32_t)dead << v;
+    if (p.bias_kind) s[v] = fmaf(p.scale, s[v], bias_f32(p, h, min(KEYS_RUN ? q : q + v, p.S - 1), min(KEYS_RUN ? k + v : k, p.S - 1)));
+    else s[v] *= p.scale;
+    dead[v] = false;
   }
-  return masked;
+  if (edge) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = KEYS_RUN ? q : q + v, j = KEYS_RUN ? k + v : k;
+      dead[v] = i >= p.S || j >= p.S || (p.mask_kind == 1 && j > i);
+      if (rid) dead[v] = dead[v] || rid[min(i, p.S - 1)] != rid[min(j, p.S - 1)];
+      s[v] = dead[v] ? -INFINITY : s[v];
+    }
+  }
+}
+// masked pairs contribute exactly 0 to the gradients, whatever the statistics are (a query that sees a NaN has NaN
+// statistics)
+__device__ inline void kill(bool edge, const bool (&dead)[4], f32x4& x) {
+  if (edge) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) x[v] = dead[v] ? 0.f : x[v];
+  }
 }
 
 struct Stats { float m[W][16], l[W][16], lse[16], delta[16]; };
@@ -159,7 +170,7 @@ __global__ __launch_bounds__(64 * W) void f32_query_kernel(KP p) {
   __shared__ __attribute__((aligned(16))) float buf[W * 16 * LD];
   __shared__ __attribute__((aligned(16))) float sdo[BWD ? 16 * LD : 4];
   __shared__ Stats st;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), i = lane & 15, g = lane >> 4;
   const int q0 = blockIdx.x * 16, h = p.h0 + blockIdx.y, b = p.b0 + blockIdx.z, q = q0 + i, qc = min(q, p.S - 1);
   const int D = p.D;
   const int64_t base = (int64_t)b * p.sb + (int64_t)h * p.sh;
@@ -169,16 +180,15 @@ __global__ __launch_bounds__(64 * W) void f32_query_kernel(KP p) {
   const Nat<DC> qf = load_nat<DC>((const float*)p.Q + base + (int64_t)qc * p.ss, g, D);
 
   f32x4 s[NB], acc[DC];
-  uint32_t masked = 0;  // bit 4t + v: register v of block t
+  bool dead[NB][4];
   auto scores = [&](int k0) {
-    masked = 0;
 #pragma unroll
     for (int t = 0; t < NB; ++t) {
       const int kb = k0 + 16 * (w + W * t);
       s[t] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
       if (kb < visible) {
         s[t] = dot<DC>(load_nat<DC>(K + (int64_t)min(kb + i, p.S - 1) * p.ss, g, D), qf);
-        masked |= finish_scores<true>(p, h, rid, q, kb + 4 * g, s[t]) << (4 * t);
+        finish_scores<true>(p, h, rid, q, kb + 4 * g, has_edge(p, rid, q0, kb), s[t], dead[t]);
       }
     }
   };
@@ -193,7 +203,7 @@ __global__ __launch_bounds__(64 * W) void f32_query_kernel(KP p) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) mn = fmaxf(mn, s[t][v]);
     mn = fmaxf(m, over_groups_max(mn));
-    const float alpha = weight(m, mn);
+    const float ref = base_of(mn), alpha = exp_f32(m - ref);
     m = mn;
     l *= alpha;
 #pragma unroll
@@ -205,7 +215,7 @@ __global__ __launch_bounds__(64 * W) void f32_query_kernel(KP p) {
         f32x4 pr;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          pr[v] = prob(s[t][v], mn);
+          pr[v] = exp_f32(s[t][v] - ref);
           l += pr[v];
         }
         accumulate<DC>(V, p.ss, kb, p.S, i, g, D, pr, acc);
@@ -227,7 +237,7 @@ __global__ __launch_bounds__(64 * W) void f32_query_kernel(KP p) {
   float wt[W], L = 0.f;
 #pragma unroll
   for (int x = 0; x < W; ++x) {
-    wt[x] = weight(st.m[x][mq], M);
+    wt[x] = exp_f32(st.m[x][mq] - base_of(M));
     L = fmaf(wt[x], st.l[x][mq], L);
   }
   const float inv = 1.f / L, lse = M + logf(L);
@@ -287,8 +297,8 @@ __global__ __launch_bounds__(64 * W) void f32_query_kernel(KP p) {
       if (kb < visible) {
         f32x4 ds = dot<DC>(load_nat<DC>(V + (int64_t)min(kb + i, p.S - 1) * p.ss, g, D), gf);
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
-          ds[v] = (masked >> (4 * t + v)) & 1 ? 0.f : exp_f32(s[t][v] - my_lse) * (ds[v] - my_delta);
+        for (int v = 0; v < 4; ++v) ds[v] = exp_f32(s[t][v] - my_lse) * (ds[v] - my_delta);
+        kill(has_edge(p, rid, q0, kb), dead[t], ds);
         accumulate<DC>(K, p.ss, kb, p.S, i, g, D, ds, acc);
       }
     }
@@ -315,7 +325,7 @@ template <int DC, int NB>
 __global__ __launch_bounds__(64 * W) void f32_key_kernel(KP p) {
   constexpr int LD = 16 * DC + 4;
   __shared__ __attribute__((aligned(16))) float buf[W * 16 * LD];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, i = lane & 15, g = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6), i = lane & 15, g = lane >> 4;
   const int D = p.D, nblk = (p.S + 15) / 16, Hc = p.h1 - p.h0, nkv = nblk * Hc * (p.b1 - p.b0);
   const int id = blockIdx.x < nkv ? blockIdx.x : blockIdx.x - nkv;
   const int x0 = id % nblk * 16, h = p.h0 + id / nblk % Hc;
@@ -347,9 +357,13 @@ __global__ __launch_bounds__(64 * W) void f32_key_kernel(KP p) {
           const int64_t at = base + (int64_t)min(kb + i, p.S - 1) * p.ss;
           f32x4 s = dot<DC>(load_nat<DC>((const float*)p.K + at, g, D), qf);
           const f32x4 dp = dot<DC>(load_nat<DC>((const float*)p.V + at, g, D), gf);
-          const uint32_t masked = finish_scores<true>(p, h, rid, q, kb + 4 * g, s);
+          const bool edge = has_edge(p, rid, x0, kb);
+          bool dead[4];
+          finish_scores<true>(p, h, rid, q, kb + 4 * g, edge, s, dead);
 #pragma unroll
-          for (int v = 0; v < 4; ++v) acc[t][v] += (masked >> v) & 1 ? 0.f : exp_f32(s[v] - lse) * (dp[v] - delta);
+          for (int v = 0; v < 4; ++v) s[v] = exp_f32(s[v] - lse) * (dp[v] - delta);
+          kill(edge, dead, s);
+          acc[t] += s;
         }
       }
 #pragma unroll
@@ -383,15 +397,18 @@ __global__ __launch_bounds__(64 * W) void f32_key_kernel(KP p) {
       if (qb >= p.S) continue;
       f32x4 s = dot<DC>(load_nat<DC>(Q + (int64_t)row * p.ss, g, D), kf);
       const f32x4 dp = dot<DC>(load_nat<DC>(G + (int64_t)row * p.do_ss, g, D), vf);
-      const uint32_t masked = finish_scores<false>(p, h, rid, qb + 4 * g, key, s);
+      const bool edge = has_edge(p, rid, qb, x0);
+      bool dead[4];
+      finish_scores<false>(p, h, rid, qb + 4 * g, key, edge, s, dead);
       f32x4 ds;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int r = min(qb + 4 * g + v, p.S - 1);
-        const bool dead = (masked >> v) & 1;
-        s[v] = dead ? 0.f : exp_f32(s[v] - lse[r]);
-        ds[v] = dead ? 0.f : s[v] * (dp[v] - delta[r]);
+        s[v] = exp_f32(s[v] - lse[r]);
+        ds[v] = s[v] * (dp[v] - delta[r]);
       }
+      kill(edge, dead, s);
+      kill(edge, dead, ds);
       accumulate<DC>(G, p.do_ss, qb, p.S, i, g, D, s, dv);
       accumulate<DC>(Q, p.ss, qb, p.S, i, g, D, ds, dk);
     }
