@@ -262,8 +262,9 @@ def ffn_main(a):
             if n:
                 per_kernel[name] = {"avg_us": tot / n * 1e3, "launches_per_step": n / a.steps, "ms_per_step": tot / a.steps}
         dom = max(per_kernel, key=lambda n: per_kernel[n]["ms_per_step"])
-        # every product of a chunk is 2*T*dm*(nh/k) flop; `up` runs twice per step (forward and recompute)
-        ach = 2.0 * w["T"] * w["dm"] * (nh / k_main) / (per_kernel[dom]["avg_us"] * 1e-6) / 1e12
+        # a product over the whole share is 2*T*dm*nh flop, whatever number of launches it is cut into; `up` runs
+        # twice per step (forward and recompute)
+        ach = 2.0 * w["T"] * w["dm"] * nh * (2 if dom == "up" else 1) / (per_kernel[dom]["ms_per_step"] * 1e-3) / 1e12
         out["roofline"] = {"bound": "mfma", "achieved": ach, "peak": PEAK_MFMA_BF16 / 1e12, "unit": "TFLOP/s",
                            "frac": ach * 1e12 / PEAK_MFMA_BF16, "traffic": None, "kernel": dom,
                            "avg_launch_us": per_kernel[dom]["avg_us"]}
