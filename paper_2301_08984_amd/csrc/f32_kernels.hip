@@ -6,7 +6,7 @@
 // every wavefront with a softmax (or sum) of its own; the 8 results meet in LDS.  The recompute pass and
 // dQ share a launch, and so do dK/dV and the bias gradient: 3 launches for forward and backward.
 // Operands go from memory (L2: the tensors are small) to registers, no LDS.  Step of 4 heads x 128 x
-// 32: 85 -> 20 us; 4 x 8 heads x 508 x 16 with bias: 986 -> 163 us (plain vector kernels before).
+// 32: 85 -> 21 us; 4 x 8 heads x 508 x 16 with bias: 986 -> 156 us (plain vector kernels before).
 //
 // v_mfma_f32_16x16x4_f32 (lane l, i = l % 16, g = l / 16): A[m][k]: m = i, k = g;  B[k][n]: n = i, k = g;
 // C[m][n]: n = i, register v holds m = 4g + v.  Which index a k-slot stands for is free as long as A and B

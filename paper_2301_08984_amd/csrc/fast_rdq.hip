@@ -13,7 +13,8 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 // with the same scores, bias additions and exponentials.  dQ needs Delta = sum_j P_ij dP_ij, which
 // is only known after the last key; with the unnormalised probabilities p~ of the online softmax
 //     dQ_i = scale / l * ( sum_j (p~_ij dP_ij) K_j  -  Delta' * sum_j p~_ij K_j ),   l = sum_j p~_ij,
-// so two products are accumulated (A1 with p~ dP, A2 with p~) and combined at the end.  The
+// so two products are accumulated (A1 with p~ dP, A2 with p~; dP less one constant per query, see DpShift) and
+// combined at the end.  The
 // two terms cancel where a row is peaked (dS -> 0), so Delta' must be the mean the matrix cores
 // actually formed: Delta' = sum_j bf16(p~ dP) / sum_j bf16(p~), both sums over the SAME rounded
 // operands that went into A1 and A2 (a one-hot row then gives A1 - Delta' A2 = 0 up to the rounding
@@ -29,7 +30,8 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 // transposed (A1 / A2, O).  A tile is taken as two 32-key blocks, each a complete online-softmax
 // step: that and 32-bit buffer offsets keep a wavefront within 168 registers, and three wavefronts
 // per SIMD overlap the vector and matrix work better than a longer software pipeline does with two
-// (measured on the triangle shape: 141 against 158 us per launch).
+// (measured on the triangle shape, 64 rows a launch: 141 against 158 us; the constant that is taken off dP and the
+// fp32 row sum, one instruction per element each, came later: 3 % of that step).
 // ---------------------------------------------------------------------------
 template <int D, int BIAS, bool CAUSAL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAUSAL ? 2 : 3, BIAS && CAUSAL ? 2 : 3))) void rdq_fast_kernel(KP p) {
