@@ -435,8 +435,8 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(2, 2)))
         s = mfma(lds_nat<WLD>(L.t0, 32 * c + r, ks, hl), kf[ks], s);
         pa = mfma(lds_nat<WLD>(L.t1, 32 * c + r, ks, hl), vf[ks], pa);
       }
-      bias_and_mask(s, bz[c], p.scale, masked, L.rid, my_rid, 32 * c, hl);
-      float pr[16], ds[16];
+      // exponents and dP - Delta; masked pairs get -inf and 0 here, after the statistics went in, so that they contribute
+      // nothing also where a query has NaN statistics
 #pragma unroll
       for (int gq = 0; gq < 4; ++gq) {
         const f32x4 l4 = *(const f32x4*)(L.lse2 + 32 * c + 8 * gq + 4 * hl);
@@ -444,9 +444,27 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int v = 4 * gq + e;
-          pr[v] = fast_exp2(fmaf(s[v], LOG2E, l4[e]));
-          ds[v] = pr[v] * (pa[v] - d4[e]);
+          s[v] = fmaf(fmaf(s[v], p.scale, bias_of(bz[c], v)), LOG2E, l4[e]);
+          pa[v] -= d4[e];
         }
+      }
+      if (REGION && masked) {
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq) {
+          const int4 rk = *(const int4*)(L.rid + 32 * c + 8 * gq + 4 * hl);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const bool dead = (e == 0 ? rk.x : e == 1 ? rk.y : e == 2 ? rk.z : rk.w) != my_rid;
+            s[4 * gq + e] = dead ? -INFINITY : s[4 * gq + e];
+            pa[4 * gq + e] = dead ? 0.f : pa[4 * gq + e];
+          }
+        }
+      }
+      float pr[16], ds[16];
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        pr[v] = fast_exp2(s[v]);
+        ds[v] = pr[v] * pa[v];
       }
       if (part) {
 #pragma unroll

@@ -84,3 +84,36 @@ def test_fp32_nonfinite_inputs(name, mask, S, D, flags):
             ok = np.isfinite(r)
             if ok.any():  # fp32 sums over up to S terms: 2e-5 of the largest entry, as for finite inputs
                 assert np.max(np.abs(x[ok] - r[ok])) <= 2e-5 * max(1.0, np.max(np.abs(r[ok]))), n
+
+
+@pytest.mark.parametrize("S,win,dense", [(81, (9, 9), False), (144, (12, 12), False), (131, None, True), (200, None, True)])
+@pytest.mark.parametrize("name", ["nan_key", "nan_bias", "masking_bias"])
+def test_bf16_nonfinite_inputs(name, S, win, dense):
+    """The window kernels and the one-walk kernel with a pair bias of an odd and of an even length: NaN reaches
+    exactly the rows that it reaches by definition, -inf masks."""
+    import torch
+    inp = make_inputs(seed=63, B=2, H=2, S=S, D=32, dtype="bf16", bias="dense", axis="row")
+    bias = inp["bias"]
+    _plant(name, inp, bias)
+    mask, live = None, np.ones((S, S), bool)
+    if not dense:  # three regions
+        ids = (np.arange(S) * 3 // S).astype(np.int32)[None]
+        inp["region_ids"], mask, live = ids, "region", ids[0][:, None] == ids[0][None]
+        if name == "masking_bias":  # a key of its own region is left to everybody
+            bias[:, np.arange(S), np.arange(S)] = 0.0
+    ref = _reference(inp, bias, np.broadcast_to(live, (2, S, S)), float(np.float32(1.0 / math.sqrt(32))))
+    dc = DeviceCase(inp, dtype="bf16", bias="dense", mask=mask)
+    for use_lse in (False, True):
+        print(f"bf16 non-finite {name} S={S} use_lse={use_lse}", flush=True)
+        d = dc.desc("row", 0, 2, 1)
+        dc.fwd(d)
+        dc.bwd(d, use_lse=use_lse, poison=True)
+        torch.cuda.synchronize()
+        for n, r in ref.items():
+            if n == "dQ" and name == "nan_key":
+                continue
+            x = dc.host(n)
+            assert np.array_equal(np.isnan(x), np.isnan(r)), (n, int(np.isnan(x).sum()), int(np.isnan(r).sum()))
+            ok = np.isfinite(r)
+            if ok.any():
+                assert np.max(np.abs(x[ok] - r[ok])) <= 2e-2 * max(1.0, np.max(np.abs(r[ok]))), n
