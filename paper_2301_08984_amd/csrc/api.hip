@@ -3,6 +3,7 @@
 // (op-order), all on the current device (op-assign), every chunk reusing the same
 // workspace (co-shard, Section 2 of the paper).
 #include "../../include/ss_attn.h"
+#include "bias_copy.h"
 #include "f32_kernels.h"
 #include "kparams.h"
 #include "mfma_common.h"
@@ -177,6 +178,7 @@ KP base_params(const ss_attn_desc* d) {
   p.sb = d->stride_b; p.ss = d->stride_s; p.sh = d->stride_h;
   p.B = d->B; p.H = d->H; p.S = d->S; p.D = d->D;
   p.scale = d->scale;
+  p.inv_scale = 1.f / d->scale;
   p.bias_kind = d->bias_kind; p.bias_bf16 = d->bias_dtype == SS_BF16;
   p.mask_kind = d->mask_kind; p.mask_period = d->mask_period > 0 ? d->mask_period : 1;
   p.win_h = d->win_h; p.win_w = d->win_w; p.gated = d->gated;
@@ -274,17 +276,22 @@ int fewest_chunks(const ss_attn_desc* d, int gw, size_t bytes) {
   return d->k;
 }
 
-// the k chunks of `d` one after another, in the scratch at `ws`
+// the k chunks of `d` one after another, in the scratch at `ws`; `copy`: room for a copy of the bias in accumulator layout
+// by key, or NULL
 int run_bwd(const ss_attn_desc* d, Family fam, const WsLayout& w, const void* Q, const void* K, const void* V,
             const void* bias, const int32_t* region_ids, const void* G, const void* dY, const float* lse, void* dQ,
-            void* dK, void* dV, float* dBias, void* dG, char* ws, hipStream_t st) {
+            void* dK, void* dV, float* dBias, void* dG, char* ws, float* copy, hipStream_t st) {
   const bool bf16 = d->dtype == SS_BF16;
   const bool want_dbias = d->bias_kind != SS_BIAS_NONE && dBias != nullptr;
   KP p = base_params(d);
   p.Q = Q; p.K = K; p.V = V; p.G = G; p.dY = dY; p.bias = bias; p.region = region_ids;
   p.dQ = dQ; p.dK = dK; p.dV = dV; p.dG = dG;
   const bool mfma = fam == FAM_MFMA;
-  if (mfma && ssa::mfma_wants_bias_transpose(p)) {
+  if (copy) {
+    const int h0 = d->shard_axis == SS_AXIS_HEAD ? d->lo : 0, h1 = d->shard_axis == SS_AXIS_HEAD ? d->hi : d->H;
+    SS_LAUNCH(SS_K_TABLE_REDUCE, ssa::launch_bias_copy(bias, copy, true, p.inv_scale, d->S, h0, h1, st), "bias copy");
+    p.bias_k = copy; p.bc_h0 = h0;
+  } else if (mfma && ssa::mfma_wants_bias_transpose(p)) {
     // the K-stationary kernels read bias[h][i][j] along i: give them a transposed copy, once per call
     const int h0 = d->shard_axis == SS_AXIS_HEAD ? d->lo : 0, h1 = d->shard_axis == SS_AXIS_HEAD ? d->hi : d->H;
     SS_LAUNCH(SS_K_TABLE_REDUCE, ssa::launch_bias_transpose(bias, ws + w.biasT, d->S, h0, h1, st), "bias transpose");
@@ -551,6 +558,15 @@ int ss_attn_fwd(const ss_attn_desc* d, const void* Q, const void* K, const void*
   p.b1 = d->shard_axis == SS_AXIS_ROW ? d->hi : d->B;
   p.h0 = d->shard_axis == SS_AXIS_HEAD ? d->lo : 0;
   p.h1 = d->shard_axis == SS_AXIS_HEAD ? d->hi : d->H;
+  ssa::SharedUse shared;
+  if (fam == FAM_MFMA) {
+    const size_t bytes = ssa::bias_copy_bytes_for(p, false, p.b1 - p.b0, p.h1 - p.h0);
+    float* copy = bytes > 0 && bytes <= ssa::SHARED_BYTES ? (float*)shared.take(st) : nullptr;
+    if (copy) {
+      SS_LAUNCH(SS_K_TABLE_REDUCE, ssa::launch_bias_copy(bias, copy, false, p.inv_scale, d->S, p.h0, p.h1, st), "bias copy");
+      p.bias_q = copy; p.bc_h0 = p.h0;
+    }
+  }
   if (fam == FAM_SMALL) SS_LAUNCH(SS_K_FWD, ssa::launch_small_fwd(p, st), "forward (short)");
   else if (fam == FAM_MFMA) SS_LAUNCH(SS_K_FWD, ssa::launch_mfma_fwd(p, false, st), "forward");
   else SS_LAUNCH(SS_K_FWD, ssa::launch_generic_fwd(p, bf16, false, st), "forward (generic)");
@@ -596,20 +612,27 @@ int ss_attn_bwd(const ss_attn_desc* d, const void* Q, const void* K, const void*
   if (!workspace || workspace_bytes < w.total || ((uintptr_t)workspace % ALIGN)) return SS_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;
+  // A copy of the bias in accumulator layout goes into the library's buffer, behind the scratch of the chunks if that goes
+  // there too.
+  const KP p = base_params(&run);
+  const int rows = d->shard_axis == SS_AXIS_ROW ? d->hi - d->lo : d->B, heads = d->shard_axis == SS_AXIS_HEAD ? d->hi - d->lo : d->H;
+  size_t copy_bytes = fam == FAM_MFMA ? ssa::bias_copy_bytes_for(p, true, rows, heads) : 0;
+  if (copy_bytes > ssa::SHARED_BYTES) copy_bytes = 0;
+  const size_t room = ssa::SHARED_BYTES - copy_bytes;
+  // Chunks of a small share cannot fill the chip (a launch of 4 rows x 1 head takes as long as one of
+  // 4 rows x 6), and what keeps them apart is only that they reuse one chunk's scratch.  The results
+  // do not depend on k: run the fewest chunks whose scratch fits what the caller handed over, or
+  // else the library's buffer.  Backward of 4 rows x 6 heads x 215 queries, D = 128, k = 4: 131 -> 36 us;
+  // pair attention of 18 rows x 8 heads x 472, k = 16, forward and backward: 729 -> 113 us.
+  const int kw = fewest_chunks(&run, gw, workspace_bytes);
+  const int ks = run.k > 1 && layout_with(&run, gw).total <= room ? fewest_chunks(&run, gw, room) : kw;
   ssa::SharedUse shared;
-  if (run.k > 1) {
-    // Chunks of a small share cannot fill the chip (a launch of 4 rows x 1 head takes as long as one of
-    // 4 rows x 6), and what keeps them apart is only that they reuse one chunk's scratch.  The results
-    // do not depend on k: run the fewest chunks whose scratch fits what the caller handed over, or
-    // else the library's buffer.  Backward of 4 rows x 6 heads x 215 queries, D = 128, k = 4: 131 -> 36 us;
-    // pair attention of 18 rows x 8 heads x 472, k = 16, forward and backward: 729 -> 113 us.
-    const int kw = fewest_chunks(&run, gw, workspace_bytes), ks = fewest_chunks(&run, gw, ssa::SHARED_BYTES);
-    void* own = ks < kw ? shared.take(st) : nullptr;
-    if (own) ws = (char*)own;
-    run.k = own ? ks : kw;
-    w = layout_with(&run, gw);
-  }
-  return run_bwd(&run, fam, w, Q, K, V, bias, region_ids, G, dY, lse, dQ, dK, dV, dBias, dG, ws, st);
+  char* own = copy_bytes > 0 || ks < kw ? (char*)shared.take(st) : nullptr;
+  float* copy = own && copy_bytes > 0 ? (float*)(own + room) : nullptr;
+  if (own && ks < kw) ws = own;
+  run.k = own && ks < kw ? ks : kw;
+  w = layout_with(&run, gw);
+  return run_bwd(&run, fam, w, Q, K, V, bias, region_ids, G, dY, lse, dQ, dK, dV, dBias, dG, ws, copy, st);
 }
 
 }  // extern "C"

@@ -1,0 +1,52 @@
+// The copies of a dense bias that the kernels of head size 32 start their scores from (BiasCopy in mfma_common.h): who
+// takes them, and the kernel that makes them.
+#pragma once
+#include "mfma_common.h"
+
+namespace ssa {
+namespace {
+
+// Bytes of a copy of the bias of `heads` heads, if the forward (by query) or the backward (by key) of `rows` rows is faster
+// with it, else 0.  For head size 32 without a causal mask on the large-share shapes, slices within 32-bit offsets, and
+// where the scores are enough to pay for the launch (some 6 us with the library's buffer) and for the pass over the bias.
+// Forward without | with the copy, us: 128 rows x 8 heads x 384: 65.6 | 66.5, 256 rows 127.3 | 120.6; 128 x 4 x 1024: 188 | 176,
+// 256 rows 373 | 329; odd lengths, whose parked tiles are loaded unaligned: 64 x 8 x 501: 58.0 | 58.3, 512 x 4 x 301: 107 | 92.
+// Backward: dK / dV 9 % shorter (1024 x 4 x 1024: 2037 -> 1850 us), and the copy replaces the transposed bf16 one; the
+// recompute + dQ kernel gains nothing from a copy of its own (2469 | 2510).
+inline size_t bias_copy_bytes_for(const KP& p, bool backward, int64_t rows, int heads) {
+  if (win_ok(p) || !pair_fwd_ok(p) || p.S > 16384) return 0;
+  const int64_t row_stride = p.ss > (int64_t)p.H * p.D ? p.ss : (int64_t)p.H * p.D;
+  if (((int64_t)(p.S - 1) * row_stride + p.D) * 2 >= (1ll << 31)) return 0;
+  const int64_t entries = (int64_t)heads * p.S * p.S;
+  const int64_t enough = backward ? 1ll << 28 : p.S & 1 ? (1ll << 26) + 32 * entries : (1ll << 27) + 64 * entries;
+  return rows * entries < enough ? 0 : (size_t)bias_copy_bytes(p.S, heads);
+}
+
+// BiasCopy: four wavefronts, a 32 x 32 block each.  1024 x 1024 x 4 heads: 8 MiB in, 16 out.
+__global__ __launch_bounds__(256) void bias_copy_kernel(const uint16_t* src, float* dst, int S, int h0, int by_key, float inv_scale) {
+  const int lane = threadIdx.x & 63, block = blockIdx.x * 4 + (threadIdx.x >> 6), strip = blockIdx.y;
+  if (block >= bias_copy_blocks(S)) return;
+  const uint16_t* m = src + (int64_t)(h0 + blockIdx.z) * S * S;
+  f32x4* out = (f32x4*)dst + ((blockIdx.z * bias_copy_strips(S) + strip) * bias_copy_blocks(S) + block) * 256 + lane;
+  const int row = 32 * strip + (lane & 31), col = 32 * block + 4 * (lane >> 5);
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    f32x4 x;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int c = col + 8 * g + e, r = min(row, S - 1), cc = min(c, S - 1);
+      const float b = bf2f(m[by_key ? (int64_t)cc * S + r : (int64_t)r * S + cc]);
+      x[e] = row < S && c < S ? b * inv_scale : -INFINITY;
+    }
+    out[64 * g] = x;
+  }
+}
+// the heads [h0, h1); `by_key`: a row of the copy is a key, not a query
+inline hipError_t launch_bias_copy(const void* bias, float* copy, bool by_key, float inv_scale, int S, int h0, int h1, hipStream_t st) {
+  const dim3 g((unsigned)((bias_copy_blocks(S) + 3) / 4), (unsigned)bias_copy_strips(S), h1 - h0);
+  bias_copy_kernel<<<g, 256, 0, st>>>((const uint16_t*)bias, copy, S, h0, by_key ? 1 : 0, inv_scale);
+  return hipGetLastError();
+}
+
+}  // namespace
+}  // namespace ssa

@@ -16,16 +16,16 @@ namespace {
 // tile travels global -> registers meanwhile.
 // ---------------------------------------------------------------------------
 template <int D, int BIAS, bool CAUSAL, int NW, bool SLICE32>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 32 ? (BIAS && CAUSAL ? 2 : 3) : 1, D <= 32 ? (BIAS && CAUSAL ? 2 : 3) : 1))) void dkdv_fast_kernel(KP p) {
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 32 ? (BIAS && CAUSAL ? 2 : 3) : 1, D <= 32 ? (BIAS && CAUSAL ? 2 : 3) : 1))) void dkdv_fast_kernel(KP p, int together) {
   constexpr int KS = D / 16, DB = D / 32, LD = D + 24, NT = 64 * NW, BK = 32 * NW;  // tiles read both ways
   constexpr int CPR = D / 8, CPT = BN * CPR / NT;
   __shared__ __attribute__((aligned(16))) uint16_t sQ[2][BN * LD];
   __shared__ __attribute__((aligned(16))) uint16_t sG[2][BN * LD];
   __shared__ __attribute__((aligned(16))) float sL[2][BN];
   __shared__ __attribute__((aligned(16))) float sD[2][BN];
-  __shared__ __attribute__((aligned(16))) uint16_t sBias[BIAS ? NW * BIAS_TILE_ELEMS : 8];  // one parked tile per wavefront
+  __shared__ __attribute__((aligned(16))) uint16_t sBias[BIAS == BIAS_EVEN || BIAS == BIAS_ODD ? NW * BIAS_TILE_ELEMS : 8];  // one parked tile per wavefront
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 31, hl = lane >> 5;
-  const BlockId blk = CAUSAL && !BIAS ? causal_block_id(false) : xcd_block_id(BIAS && bias_rows_first(gridDim.y, p.S));
+  const BlockId blk = CAUSAL && !BIAS ? causal_block_id(false) : xcd_block_id(together);
   const int h = p.h0 + blk.y, b = p.b0 + blk.z;
   const int kblk = blk.x * BK;  // early key blocks see the most queries under a causal mask
   const int k0 = kblk + 32 * w, key = k0 + r;
@@ -39,8 +39,12 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 32
   const float* dl_b = p.delta + (int64_t)(b - p.dl_b0) * p.dl_sb + (int64_t)(h - p.dl_h0) * p.dl_sh;
   // bias comes from the transposed copy biasT[h][key][query], so that a lane (= key) finds four
   // consecutive queries in 8 bytes
+  constexpr bool PARKED = BIAS == BIAS_EVEN || BIAS == BIAS_ODD;
   BiasTile<BIAS == BIAS_ODD> bt;
-  if (BIAS) bt.init((const uint16_t*)p.biasT + (int64_t)h * p.S * p.S, k0, p.S, sBias + w * BIAS_TILE_ELEMS, lane);
+  BiasCopy bc;
+  f32x16 cz;  // BIAS_COPY: of the next sub-block
+  if (BIAS == BIAS_COPY) bc.init(p.bias_k, h - p.bc_h0, k0, p.S, lane);
+  if (PARKED) bt.init((const uint16_t*)p.biasT + (int64_t)h * p.S * p.S, k0, p.S, sBias + w * BIAS_TILE_ELEMS, lane);
   auto bload = [&](int qt) { bt.load(qt); };
 
   bf16x8 kf[KS], vf[KS];
@@ -54,7 +58,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 32
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int v = 0; v < 16; ++v) { dk[db][v] = 0.f; dv[db][v] = 0.f; }
-  const float c1 = p.scale * LOG2E;
+  const float inv_scale = in_vgpr(p.inv_scale), c1 = in_vgpr(p.scale * LOG2E);
   const int ntiles = (p.S + BN - 1) / BN;
   const int first = CAUSAL ? kblk / BN : 0;  // queries before the block's first key see none of it
 
@@ -107,42 +111,40 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 32
     if (tid < BN) sL[buf][tid] = -pstat * LOG2E;  // stored negated: one fused multiply-add per score
     else if (tid < 2 * BN) sD[buf][tid - BN] = pstat;
   };
-  // scores and dP of one 32-query sub-block
-  auto stage_a = [&](const uint16_t* tq, const uint16_t* tg, int sub, f32x16& sa, f32x16& pa) {
+  // scores (starting from bias / scale, see BiasCopy) and dP of one 32-query sub-block
+  auto stage_a = [&](const uint16_t* tq, const uint16_t* tg, int sub, int i0, f32x16& sa, f32x16& pa) {
     bf16x8 fq[KS], fg[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       fq[ks] = lds_nat<LD>(tq, 32 * sub + r, ks, hl);
       fg[ks] = lds_nat<LD>(tg, 32 * sub + r, ks, hl);
     }
+    if (BIAS == BIAS_COPY) sa = cz;
+    else if (PARKED) parked_bias(bt, r, sub, hl, inv_scale, sa);
 #pragma unroll
-    for (int v = 0; v < 16; ++v) { sa[v] = 0.f; pa[v] = 0.f; }
+    for (int v = 0; v < 16; ++v) {
+      if (!BIAS) sa[v] = 0.f;
+      pa[v] = 0.f;
+    }
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       sa = mfma(fq[ks], kf[ks], sa);
       pa = mfma(fg[ks], vf[ks], pa);
     }
+    if (BIAS == BIAS_COPY) bc.load(cz, min((i0 >> 5) + sub + 1, 2 * ntiles - 1));
   };
   // P and dS of one sub-block, as packed bf16 operands
   auto stage_v = [&](const float* tl, const float* td, int i0, int sub, const f32x16& sa, const f32x16& pa,
-                     const uint2* bz, bf16x8 (&pf)[2], bf16x8 (&df)[2], auto edge_tag) {
+                     bf16x8 (&pf)[2], bf16x8 (&df)[2], auto edge_tag) {
     constexpr bool edge = decltype(edge_tag)::value;
     float pr[16], ds[16];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
       const f32x4 l4 = *(const f32x4*)(tl + 32 * sub + 8 * g + 4 * hl);
       const f32x4 d4 = *(const f32x4*)(td + 32 * sub + 8 * g + 4 * hl);
-      float bl[4] = {0.f, 0.f, 0.f, 0.f};
-      if (BIAS) {
-        const uint2 u = bz[4 * sub + g];
-        bl[0] = __uint_as_float(u.x << 16); bl[1] = __uint_as_float(u.x & 0xffff0000u);
-        bl[2] = __uint_as_float(u.y << 16); bl[3] = __uint_as_float(u.y & 0xffff0000u);
-      }
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        // with a bias: natural units first, the change to base 2 rides on the subtraction of the LSE
-        float pe = BIAS ? fast_exp2(fmaf(fmaf(sa[4 * g + e], p.scale, bl[e]), LOG2E, l4[e]))
-                        : fast_exp2(fmaf(sa[4 * g + e], c1, l4[e]));
+        float pe = fast_exp2(fmaf(sa[4 * g + e], c1, l4[e]));
         if (edge) {
           const int i = i0 + 32 * sub + 8 * g + 4 * hl + e;
           const bool dead = i >= p.S || key >= p.S || (CAUSAL && key > i);
@@ -177,14 +179,15 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 32
     gload(first);
     lstore(first & 1);
     if (first + 1 < ntiles) gload(first + 1);
-    if (BIAS) bload(first);
+    if (PARKED) bload(first);
+    if (BIAS == BIAS_COPY) bc.load(cz, 2 * first);
   }
   for (int qt = first; qt < ntiles; ++qt) {
     const int i0 = qt * BN;
     __syncthreads();
     if (qt + 1 < ntiles) lstore((qt + 1) & 1);
     if (qt + 2 < ntiles) gload(qt + 2);
-    if (BIAS) {
+    if (PARKED) {
       bt.park(lane);
       if (qt + 1 < ntiles) bload(qt + 1);
     }
@@ -193,14 +196,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 32
     const uint16_t* tg = sG[qt & 1];
     const float* tl = sL[qt & 1];
     const float* td = sD[qt & 1];
-    const bool edge = (i0 + BN > p.S) || (k0 + 32 > p.S) || (CAUSAL && i0 < k0 + 31);
+    // (the copy of the bias masks what lies past the end)
+    const bool edge = BIAS != BIAS_COPY && ((i0 + BN > p.S) || (k0 + 32 > p.S) || (CAUSAL && i0 < k0 + 31));
     // one straight-line block per tile: A0 | A1 with V0 | B0 with V1 | B1, where A = scores and dP
     // on the matrix cores, V = P and dS on the vector ALUs, B = gradient products
-    uint2 bz[8];
-    if (BIAS && D > 32) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) bz[j] = bt.read(r, 8 * j + 4 * hl);
-    }
     auto tile = [&](auto edge_tag) {
       // D = 128: keeps the 32 operand reads inside this block; they are common to both variants of
       // the tile and would otherwise all be hoisted above the branch, out of reach of the schedule
@@ -215,23 +214,19 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 32
         for (int sub = 0; sub < 2; ++sub) {
           f32x16 sa, pa;
           bf16x8 pf[2], df[2];
-          if (BIAS) {
-#pragma unroll
-            for (int g = 0; g < 4; ++g) bz[4 * sub + g] = bt.read(r, 32 * sub + 8 * g + 4 * hl);
-          }
-          stage_a(tq, tg, sub, sa, pa);
-          stage_v(tl, td, i0, sub, sa, pa, bz, pf, df, edge_tag);
+          stage_a(tq, tg, sub, i0, sa, pa);
+          stage_v(tl, td, i0, sub, sa, pa, pf, df, edge_tag);
           stage_b(tq, tg, sub, pf, df);
         }
         return;
       }
       f32x16 sa0, pa0, sa1, pa1;
       bf16x8 pf0[2], df0[2], pf1[2], df1[2];
-      stage_a(tq, tg, 0, sa0, pa0);
-      stage_a(tq, tg, 1, sa1, pa1);
-      stage_v(tl, td, i0, 0, sa0, pa0, bz, pf0, df0, edge_tag);
+      stage_a(tq, tg, 0, i0, sa0, pa0);
+      stage_a(tq, tg, 1, i0, sa1, pa1);
+      stage_v(tl, td, i0, 0, sa0, pa0, pf0, df0, edge_tag);
       stage_b(tq, tg, 0, pf0, df0);
-      stage_v(tl, td, i0, 1, sa1, pa1, bz, pf1, df1, edge_tag);
+      stage_v(tl, td, i0, 1, sa1, pa1, pf1, df1, edge_tag);
       stage_b(tq, tg, 1, pf1, df1);
       // A0
       __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
@@ -333,14 +328,15 @@ void dbias_tile_kernel(KP p) {
   }
   if (bfirst >= blast) return;
   const bool skip = CAUSAL && k0t > q0t + 63;  // whole tile above the diagonal: gradient is zero
-  float acc[16], bz[16];
+  float acc[16];
+  f32x16 bz;
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     const int k = min(k0 + key_of(v, hl), p.S - 1);
     acc[v] = (resume && !skip) ? dst[k] : 0.f;
-    bz[v] = bf2f(((const uint16_t*)p.bias)[((int64_t)h * p.S + qc) * p.S + k]) * LOG2E;
+    bz[v] = bf2f(((const uint16_t*)p.bias)[((int64_t)h * p.S + qc) * p.S + k]) * p.inv_scale;
   }
-  const float c1 = p.scale * LOG2E;
+  const float c1 = in_vgpr(p.scale * LOG2E);
   if (!skip) {
     // staging: thread -> (tensor-tile row, 16-byte chunk); Q/dO rows q0t.., K/V rows k0t..
     u32x4 pre[4][CPT];
@@ -380,10 +376,10 @@ void dbias_tile_kernel(KP p) {
 #pragma unroll
         for (int t = 0; t < 4; ++t) *(u32x4*)(&sT[buf][t][hh][row * LD + col]) = pre[t][c];
       }
-      // LSE (base 2) and Delta of query i: the two floats after the D elements of row i of the Q tile
+      // -LSE (base 2) and Delta of query i: the two floats after the D elements of row i of the Q tile
       if (tid < 128 * HP) {
         float* st = (float*)(&sT[buf][0][tid / 128][(tid & 63) * LD + D]);
-        if ((tid & 64) == 0) st[0] = pstat * LOG2E;
+        if ((tid & 64) == 0) st[0] = -pstat * LOG2E;
         else st[1] = pstat;
       }
     };
@@ -395,19 +391,19 @@ void dbias_tile_kernel(KP p) {
       __syncthreads();
       if (b + 1 < blast) lstore(buf ^ 1);
       if (b + 2 < blast) gload(b + 2);
-      f32x16 sa, pa;
+      f32x16 sa = bz, pa;  // the scores start from bias / scale
 #pragma unroll
-      for (int v = 0; v < 16; ++v) { sa[v] = 0.f; pa[v] = 0.f; }
+      for (int v = 0; v < 16; ++v) pa[v] = 0.f;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         sa = mfma(lds_nat<LD>(sT[buf][2][hsel], 32 * wk + r, ks, hl), lds_nat<LD>(sT[buf][0][hsel], 32 * wq + r, ks, hl), sa);
         pa = mfma(lds_nat<LD>(sT[buf][3][hsel], 32 * wk + r, ks, hl), lds_nat<LD>(sT[buf][1][hsel], 32 * wq + r, ks, hl), pa);
       }
       const float2 st2 = *(const float2*)(&sT[buf][0][hsel][(32 * wq + r) * LD + D]);
-      const float lse2 = st2.x, dlt = st2.y;
+      const float nlse2 = st2.x, dlt = st2.y;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const float e = fast_exp2(fmaf(sa[v], c1, bz[v] - lse2));
+        const float e = fast_exp2(fmaf(sa[v], c1, nlse2));
         float t = pa[v] - dlt;
         if (CAUSAL) t = k0 + key_of(v, hl) > q ? 0.f : t;
         acc[v] = __builtin_fmaf(e, t, acc[v]);
@@ -436,12 +432,18 @@ __global__ __launch_bounds__(256) void bias_transpose_kernel(const uint16_t* src
     if (j0 + y < S && i0 + tx < S) dst[((int64_t)h * S + j0 + y) * S + i0 + tx] = t[tx][y];
 }
 
-
 template <int D, int NW, bool SLICE32>
 void dkdv_fast_launch(const KP& p, hipStream_t st) {
   const dim3 g((p.S + 32 * NW - 1) / (32 * NW), p.h1 - p.h0, p.b1 - p.b0);
+  const int together = p.bias_kind ? heads_together(p.h1 - p.h0, p.S, p.bias_k ? 4 : 2) : 0;
+  if constexpr (SLICE32) {
+    if (p.bias_k) {
+      dkdv_fast_kernel<D, BIAS_COPY, false, NW, true><<<g, 64 * NW, 0, st>>>(p, together);
+      return;
+    }
+  }
   dispatch_bias(p, [&](auto bias, auto causal) {
-    dkdv_fast_kernel<D, bias(), causal(), NW, SLICE32><<<g, 64 * NW, 0, st>>>(p);
+    dkdv_fast_kernel<D, bias(), causal(), NW, SLICE32><<<g, 64 * NW, 0, st>>>(p, together);
   });
 }
 template <int D>

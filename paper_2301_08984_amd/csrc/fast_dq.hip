@@ -15,7 +15,7 @@ namespace {
 template <int D, int BIAS, bool CAUSAL, int QW, int NG>
 // D = 32 needs 100 - 140 registers: three (with a bias) or four wavefronts per SIMD instead of two
 __global__ __launch_bounds__(64 * QW * NG)
-__attribute__((amdgpu_waves_per_eu(D <= 32 ? (BIAS ? 3 : 4) : 2, D <= 32 ? (BIAS ? 3 : 4) : 2))) void dq_fast_kernel(KP p) {
+__attribute__((amdgpu_waves_per_eu(D <= 32 ? (BIAS ? 3 : 4) : 2, D <= 32 ? (BIAS ? 3 : 4) : 2))) void dq_fast_kernel(KP p, int together) {
   constexpr int KS = D / 16, DB = D / 32, NT = 64 * QW, BM = 32 * QW;
   constexpr int LDK = D + 24, LDV = D + 8;  // K is read both ways: D + 24 is conflict-free for b128 and transposed reads
   constexpr int CPR = D / 8, CPT = BN * CPR / NT;
@@ -29,7 +29,7 @@ __attribute__((amdgpu_waves_per_eu(D <= 32 ? (BIAS ? 3 : 4) : 2, D <= 32 ? (BIAS
   const int lane = tid & 63, w = tid >> 6, r = lane & 31, hl = lane >> 5;
   uint16_t* sK = smem + grp * TILE_ELEMS;
   uint16_t* sV = sK + BN * LDK;
-  const BlockId blk = CAUSAL && !BIAS ? causal_block_id(NG == 1) : xcd_block_id(BIAS && bias_rows_first(gridDim.y, p.S));
+  const BlockId blk = CAUSAL && !BIAS ? causal_block_id(NG == 1) : xcd_block_id(together);
   const int h = p.h0 + blk.y, b = p.b0 + blk.z;
   const int qblk = (gridDim.x - 1 - blk.x) * BM;
   const int q0 = qblk + 32 * w, q = q0 + r;
@@ -192,7 +192,7 @@ __attribute__((amdgpu_waves_per_eu(D <= 32 ? (BIAS ? 3 : 4) : 2, D <= 32 ? (BIAS
 template <int D, int QW, int NG>
 void dq_fast_launch(const KP& p, hipStream_t st) {
   const dim3 g((p.S + 32 * QW - 1) / (32 * QW), p.h1 - p.h0, p.b1 - p.b0);
-  dispatch_bias(p, [&](auto bias, auto causal) { dq_fast_kernel<D, bias(), causal(), QW, NG><<<g, 64 * QW * NG, 0, st>>>(p); });
+  dispatch_bias(p, [&](auto bias, auto causal) { dq_fast_kernel<D, bias(), causal(), QW, NG><<<g, 64 * QW * NG, 0, st>>>(p, p.bias_kind ? heads_together(p.h1 - p.h0, p.S, 2) : 0); });
 }
 
 template <int D>

@@ -18,7 +18,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   __shared__ __attribute__((aligned(1024))) char smem[2 * Q_STAGE_B];
   const int lane = threadIdx.x & 63, r = lane & 31, hl = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const BlockId blk = CAUSAL ? causal_block_id(true) : xcd_block_id(false);
+  const BlockId blk = CAUSAL ? causal_block_id(true) : xcd_block_id();
   const int h = p.h0 + blk.y, b = p.b0 + blk.z;
   const int qblk = (gridDim.x - 1 - blk.x) * BM;
   const int q0 = qblk + 32 * w, q = q0 + r;

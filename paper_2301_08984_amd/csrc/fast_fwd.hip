@@ -22,8 +22,8 @@ namespace {
 // chosen from the size of the whole share, never from the chunk, so results do
 // not depend on k.
 // ---------------------------------------------------------------------------
-template <int D, int BIAS, bool CAUSAL, bool RECOMP, int QW, int NG>
-__global__ __launch_bounds__(64 * QW * NG) __attribute__((amdgpu_waves_per_eu(D <= 32 ? (BIAS && (CAUSAL || NG > 1) ? 3 : 4) : 2, D <= 32 ? (BIAS && (CAUSAL || NG > 1) ? 3 : 4) : 2))) void fwd_fast_kernel(KP p) {
+template <int D, int BIAS, bool CAUSAL, bool RECOMP, int QW, int NG, bool SLICE32>
+__global__ __launch_bounds__(64 * QW * NG) __attribute__((amdgpu_waves_per_eu(D <= 32 ? (BIAS && (CAUSAL || NG > 1) ? 3 : 4) : 2, D <= 32 ? (BIAS && (CAUSAL || NG > 1) ? 3 : 4) : 2))) void fwd_fast_kernel(KP p, int together) {
   constexpr int KS = D / 16, DB = D / 32, NT = 64 * QW, BM = 32 * QW;
   constexpr int LDK = D + 8, LDV = D + 16;  // row pads chosen for conflict-free b128 / transpose reads
   constexpr int CPR = D / 8, CPT = BN * CPR / NT;
@@ -35,11 +35,11 @@ __global__ __launch_bounds__(64 * QW * NG) __attribute__((amdgpu_waves_per_eu(D 
   constexpr int KV_ELEMS = NG * NBUF * TILE_ELEMS;
   constexpr int LDS_ELEMS = KV_ELEMS + BIAS_ELEMS > MERGE_ELEMS ? KV_ELEMS + BIAS_ELEMS : MERGE_ELEMS;
   __shared__ __attribute__((aligned(16))) uint16_t smem[LDS_ELEMS];
-  const int tid = threadIdx.x % NT, grp = threadIdx.x / NT;
+  const int tid = threadIdx.x % NT, grp = NG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / NT);
   const int lane = tid & 63, w = tid >> 6, r = lane & 31, hl = lane >> 5;
   uint16_t* sK = smem + grp * NBUF * TILE_ELEMS;
   uint16_t* sV = sK + BN * LDK;
-  const BlockId blk = CAUSAL && !BIAS ? causal_block_id(NG == 1) : xcd_block_id(BIAS && bias_rows_first(gridDim.y, p.S));
+  const BlockId blk = CAUSAL && !BIAS ? causal_block_id(NG == 1) : xcd_block_id(together);
   const int h = p.h0 + blk.y, b = p.b0 + blk.z;
   const int qblk = (gridDim.x - 1 - blk.x) * BM;  // long (late) causal blocks first
   const int q0 = qblk + 32 * w, q = q0 + r;
@@ -61,8 +61,8 @@ __global__ __launch_bounds__(64 * QW * NG) __attribute__((amdgpu_waves_per_eu(D 
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int v = 0; v < 16; ++v) oacc[db][v] = 0.f;
-  float m = -1e30f, l = 0.f;
-  const float c1 = p.scale * LOG2E;
+  float nm = 1e30f, l = 0.f;  // the negated running maximum, the row sum
+  const float scale = in_vgpr(p.scale), c1 = in_vgpr(p.scale * LOG2E);
 
   int ntiles = (p.S + BN - 1) / BN;
   if (CAUSAL) ntiles = min(ntiles, (min(qblk + BM, p.S) + BN - 1) / BN);
@@ -70,8 +70,31 @@ __global__ __launch_bounds__(64 * QW * NG) __attribute__((amdgpu_waves_per_eu(D 
   if (CAUSAL) wtiles = min(ntiles, (min(q0 + 32, p.S) + BN - 1) / BN);
   if (q0 >= p.S) wtiles = 0;
 
+  // SLICE32: the (row, head) slice is shorter than 2 GiB (decided on the host).  The tiles are then fetched with buffer
+  // loads whose descriptor starts at the tile and ends with the slice: lane offsets that never change (no 64-bit address
+  // per load), and rows past S - 1 arrive as zeros (their scores are masked).
+  const uint32_t ss2 = (uint32_t)p.ss * 2u;
+  uint32_t goff[SLICE32 ? CPT : 1];
+  if (SLICE32) {
+#pragma unroll
+    for (int c = 0; c < CPT; ++c) {
+      const int idx = tid + c * NT;
+      goff[c] = (uint32_t)(idx / CPR) * ss2 + (uint32_t)(idx % CPR) * 16u;
+    }
+  }
   u32x4 pk[CPT], pv[CPT];
   auto gload = [&](int kt) {
+    if (SLICE32) {
+      const uint32_t boff = (uint32_t)(kt * BN) * ss2, left = (uint32_t)(((int64_t)(p.S - 1) * p.ss + D) * 2) - boff;  // kt * BN < S
+      const __amdgpu_buffer_rsrc_t rk = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)Kb + boff), 0, (int)left, 0x00020000);
+      const __amdgpu_buffer_rsrc_t rv = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)Vb + boff), 0, (int)left, 0x00020000);
+#pragma unroll
+      for (int c = 0; c < CPT; ++c) {
+        pk[c] = __builtin_amdgcn_raw_buffer_load_b128(rk, goff[c], 0, 0);
+        pv[c] = __builtin_amdgcn_raw_buffer_load_b128(rv, goff[c], 0, 0);
+      }
+      return;
+    }
 #pragma unroll
     for (int c = 0; c < CPT; ++c) {
       const int idx = tid + c * NT, row = min(kt * BN + idx / CPR, p.S - 1), col = (idx % CPR) * 8;
@@ -128,10 +151,10 @@ __global__ __launch_bounds__(64 * QW * NG) __attribute__((amdgpu_waves_per_eu(D 
         for (int g = 0; g < 4; ++g) {
           const uint2 u = bz[4 * kb + g];
           // natural units here; the change to base 2 rides on the subtraction of the maximum below
-          sa[kb][4 * g + 0] = fmaf(sa[kb][4 * g + 0], p.scale, __uint_as_float(u.x << 16));
-          sa[kb][4 * g + 1] = fmaf(sa[kb][4 * g + 1], p.scale, __uint_as_float(u.x & 0xffff0000u));
-          sa[kb][4 * g + 2] = fmaf(sa[kb][4 * g + 2], p.scale, __uint_as_float(u.y << 16));
-          sa[kb][4 * g + 3] = fmaf(sa[kb][4 * g + 3], p.scale, __uint_as_float(u.y & 0xffff0000u));
+          sa[kb][4 * g + 0] = fmaf(sa[kb][4 * g + 0], scale, __uint_as_float(u.x << 16));
+          sa[kb][4 * g + 1] = fmaf(sa[kb][4 * g + 1], scale, __uint_as_float(u.x & 0xffff0000u));
+          sa[kb][4 * g + 2] = fmaf(sa[kb][4 * g + 2], scale, __uint_as_float(u.y << 16));
+          sa[kb][4 * g + 3] = fmaf(sa[kb][4 * g + 3], scale, __uint_as_float(u.y & 0xffff0000u));
         }
     }
     if (edge) {
@@ -153,25 +176,25 @@ __global__ __launch_bounds__(64 * QW * NG) __attribute__((amdgpu_waves_per_eu(D 
     rmax = half_max(rmax);
     // the running maximum is raised only when exceeded by more than 2^8, so the O rescale is
     // skipped on most tiles; probabilities stay below 2^8, harmless in fp32/bf16 range
-    if (__builtin_amdgcn_ballot_w64(rmax > m + 8.f) != 0) {
-      const float mn = fmaxf(m, rmax);
-      const float alpha = fast_exp2(m - mn);
-      m = mn;
+    if (__builtin_amdgcn_ballot_w64(rmax + nm > 8.f) != 0) {
+      const float mn = fmaxf(-nm, rmax);
+      const float alpha = fast_exp2(-nm - mn);
+      nm = -mn;
       l *= alpha;
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int v = 0; v < 16; ++v) oacc[db][v] *= alpha;
     }
-    float lsum = 0.f;
+    float ls[4];
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        sa[kb][v] = fast_exp2(fmaf(sa[kb][v], BIAS ? LOG2E : c1, -m));
-        lsum += sa[kb][v];
+        sa[kb][v] = fast_exp2(fmaf(sa[kb][v], BIAS ? LOG2E : c1, nm));
+        ls[v & 3] = kb == 0 && v < 4 ? sa[kb][v] : ls[v & 3] + sa[kb][v];
       }
-    l += lsum;
+    l += (ls[0] + ls[1]) + (ls[2] + ls[3]);
     {
       bf16x8 pf[4];
 #pragma unroll
@@ -257,6 +280,7 @@ __global__ __launch_bounds__(64 * QW * NG) __attribute__((amdgpu_waves_per_eu(D 
       if (kt < wtiles) tile(sK, sV, kt * BN);
     }
   }
+  float m = -nm;
   if (NG > 1) {
     // merge the groups' partial softmax results: groups 1.. hand (O, m, l) to group 0, which folds
     // them in group order
@@ -295,7 +319,12 @@ __global__ __launch_bounds__(64 * QW * NG) __attribute__((amdgpu_waves_per_eu(D 
 template <int D, bool RECOMP, int QW, int NG>
 void fwd_fast_launch(const KP& p, hipStream_t st) {
   const dim3 g((p.S + 32 * QW - 1) / (32 * QW), p.h1 - p.h0, p.b1 - p.b0);
-  dispatch_bias(p, [&](auto bias, auto causal) { fwd_fast_kernel<D, bias(), causal(), RECOMP, QW, NG><<<g, 64 * QW * NG, 0, st>>>(p); });
+  const bool slice32 = ((int64_t)(p.S - 1) * p.ss + D) * 2 < (1ll << 31);
+  const int together = p.bias_kind ? heads_together(p.h1 - p.h0, p.S, 2) : 0;
+  dispatch_bias(p, [&](auto bias, auto causal) {
+    if (slice32) fwd_fast_kernel<D, bias(), causal(), RECOMP, QW, NG, true><<<g, 64 * QW * NG, 0, st>>>(p, together);
+    else fwd_fast_kernel<D, bias(), causal(), RECOMP, QW, NG, false><<<g, 64 * QW * NG, 0, st>>>(p, together);
+  });
 }
 
 template <int D, bool RECOMP>
@@ -325,6 +354,8 @@ hipError_t launch_fast_fwd(const KP& p, bool recompute, hipStream_t st) {
   if (wg_shape(p) == WG_2x4) return launch_fast_fwd_wave(p, recompute, st);
   // large shares at head size 128 without a bias: tiles straight into LDS
   if (p.D == 128 && p.bias_kind == 0 && wg_shape(p) == WG_4x1) return launch_fast_fwd128(p, recompute, st);
+  // pair attention
+  if (!recompute && pair_fwd_ok(p)) return launch_pair_fwd(p, st);
   SS_FAST_DISPATCH_D(fwd_d, p, recompute, st)
 }
 

@@ -199,7 +199,7 @@ __device__ __forceinline__ void kv_fast128_block(const KP& p, char* smem, int ra
 template <bool CAUSAL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void kv_fast128_kernel(KP p) {
   __shared__ __attribute__((aligned(1024))) char smem[2 * KV_STAGE_B];
-  const BlockId blk = CAUSAL ? causal_block_id(true) : xcd_block_id(false);
+  const BlockId blk = CAUSAL ? causal_block_id(true) : xcd_block_id();
   if (blk.x & 1) kv_fast128_block<CAUSAL, 0>(p, smem, blk.x >> 1, blk.y, blk.z);
   else kv_fast128_block<CAUSAL, 1>(p, smem, blk.x >> 1, blk.y, blk.z);
 }

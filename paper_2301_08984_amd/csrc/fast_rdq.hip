@@ -5,8 +5,6 @@
 namespace ssa {
 namespace {
 
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-
 // ---------------------------------------------------------------------------
 // A query block walks its keys once and leaves O (for Delta, the gate gradient and the pre-gated
 // dO copy), the softmax statistics AND dQ, instead of once for the statistics and once more for dQ
@@ -34,7 +32,7 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 // fp32 row sum, one instruction per element each, came later: 3 % of that step).
 // ---------------------------------------------------------------------------
 template <int D, int BIAS, bool CAUSAL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAUSAL ? 2 : 3, BIAS && CAUSAL ? 2 : 3))) void rdq_fast_kernel(KP p) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAUSAL ? 2 : 3, BIAS && CAUSAL ? 2 : 3))) void rdq_fast_kernel(KP p, int together) {
   constexpr int KS = D / 16, DB = D / 32, NT = 256, BM = 128;
   constexpr int LDT = D + 24;  // conflict-free for b128 and transposed reads
   constexpr int CPR = D / 8, CPT = BN * CPR / NT;
@@ -44,7 +42,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
   __shared__ __attribute__((aligned(16))) uint16_t smem[KV_ELEMS + BIAS_ELEMS];
   const int tid = threadIdx.x;
   const int lane = tid & 63, w = tid >> 6, r = lane & 31, hl = lane >> 5;
-  const BlockId blk = CAUSAL && !BIAS ? causal_block_id(false) : xcd_block_id(BIAS && bias_rows_first(gridDim.y, p.S));
+  const BlockId blk = CAUSAL && !BIAS ? causal_block_id(false) : xcd_block_id(together);
   const int h = p.h0 + blk.y, b = p.b0 + blk.z;
   const int qblk = (gridDim.x - 1 - blk.x) * BM;  // long (late) causal blocks first
   const int q0 = qblk + 32 * w, q = q0 + r;
@@ -91,8 +89,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int v = 0; v < 16; ++v) { oacc[db][v] = 0.f; a1[db][v] = 0.f; a2[db][v] = 0.f; }
-  float m = -1e30f;
-  const float c1 = p.scale * LOG2E;
+  float nm = 1e30f;  // the negated running maximum
+  const float inv_scale = in_vgpr(p.inv_scale), c1 = in_vgpr(p.scale * LOG2E);
 
   int ntiles = (p.S + BN - 1) / BN;
   if (CAUSAL) ntiles = min(ntiles, (min(qblk + BM, p.S) + BN - 1) / BN);
@@ -142,23 +140,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
         fk[ks] = lds_nat<LDT>(sK, 32 * kb + r, ks, hl);
         fv[ks] = lds_nat<LDT>(sV, 32 * kb + r, ks, hl);
       }
+      // the scores start from bias / scale (see BiasCopy)
+      if (BIAS) parked_bias(bt, r, kb, hl, inv_scale, sa);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) { sa[v] = 0.f; pa[v] = 0.f; }
+      for (int v = 0; v < 16; ++v) {
+        if (!BIAS) sa[v] = 0.f;
+        pa[v] = 0.f;
+      }
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         sa = mfma(fk[ks], qf[ks], sa);
         pa = mfma(fv[ks], gf[ks], pa);
-      }
-    }
-    if (BIAS) {
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const uint2 u = bt.read(r, 32 * kb + 8 * g + 4 * hl);
-        // natural units here; the change to base 2 rides on the subtraction of the maximum below
-        sa[4 * g + 0] = fmaf(sa[4 * g + 0], p.scale, __uint_as_float(u.x << 16));
-        sa[4 * g + 1] = fmaf(sa[4 * g + 1], p.scale, __uint_as_float(u.x & 0xffff0000u));
-        sa[4 * g + 2] = fmaf(sa[4 * g + 2], p.scale, __uint_as_float(u.y << 16));
-        sa[4 * g + 3] = fmaf(sa[4 * g + 3], p.scale, __uint_as_float(u.y & 0xffff0000u));
       }
     }
     if ((k0 + 32 > p.S) || (CAUSAL && k0 + 31 > q0)) {
@@ -172,14 +164,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
     float rmax = -INFINITY;
 #pragma unroll
     for (int v = 0; v < 16; ++v) rmax = fmaxf(rmax, sa[v]);
-    rmax *= BIAS ? LOG2E : c1;  // the running maximum is kept in base-2 units; scale > 0 on this path
+    rmax *= c1;  // the running maximum is kept in base-2 units; scale > 0 on this path
     rmax = half_max(rmax);
     // the running maximum is raised only when exceeded by more than 2^8, so the rescale is skipped
     // on most blocks; probabilities stay below 2^8, harmless in fp32/bf16 range
-    if (__builtin_amdgcn_ballot_w64(rmax > m + 8.f) != 0) {
-      const float mn = fmaxf(m, rmax);
-      const float alpha = fast_exp2(m - mn);
-      m = mn;
+    if (__builtin_amdgcn_ballot_w64(rmax + nm > 8.f) != 0) {
+      const float mn = fmaxf(-nm, rmax);
+      const float alpha = fast_exp2(-nm - mn);
+      nm = -mn;
       shift.rescaled(alpha);
       lsum *= alpha;
       dsum *= alpha;
@@ -193,11 +185,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
     {
       float pr[16], dp[16];
 #pragma unroll
-      for (int v = 0; v < 16; ++v) pr[v] = fast_exp2(fmaf(sa[v], BIAS ? LOG2E : c1, -m));
-      if (p.lse_out) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) l32 += pr[v];
-      }
+      for (int v = 0; v < 16; ++v) pr[v] = fast_exp2(fmaf(sa[v], c1, nm));
+      if (p.lse_out) l32 += sum16(pr);
       shift.choose(pr, pa);
 #pragma unroll
       for (int v = 0; v < 16; ++v) dp[v] = pr[v] * (pa[v] - shift.c);
@@ -283,13 +272,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
                         fmaf(-dmean, a2[db][4 * g + 3], a1[db][4 * g + 3]), f);
     store_row32(out + 32 * db, o, hl, true);
   }
-  fwd_epilogue_rowsum<DB, true>(p, oacc, m, l, half_sum(l32), b, h, q, hl, base);
+  fwd_epilogue_rowsum<DB, true>(p, oacc, -nm, l, half_sum(l32), b, h, q, hl, base);
 }
 
 template <int D>
 hipError_t rdq_launch(const KP& p, hipStream_t st) {
   const dim3 g((p.S + 127) / 128, p.h1 - p.h0, p.b1 - p.b0);
-  dispatch_bias(p, [&](auto bias, auto causal) { rdq_fast_kernel<D, bias(), causal()><<<g, 256, 0, st>>>(p); });
+  const int together = p.bias_kind ? heads_together(p.h1 - p.h0, p.S, 2) : 0;
+  dispatch_bias(p, [&](auto bias, auto causal) { rdq_fast_kernel<D, bias(), causal()><<<g, 256, 0, st>>>(p, together); });
   return hipGetLastError();
 }
 

@@ -482,7 +482,7 @@ __global__ __launch_bounds__(256) void bwd_wave_kernel(KP p) {
   constexpr int LDS_ELEMS = dq_wave_lds_elems<D, NG>() > dkdv_wave_lds_elems<D, NG>() ? dq_wave_lds_elems<D, NG>()
                                                                                        : dkdv_wave_lds_elems<D, NG>();
   __shared__ __attribute__((aligned(16))) uint16_t smem[LDS_ELEMS];
-  const BlockId blk = CAUSAL ? causal_block_id(true) : xcd_block_id(false);
+  const BlockId blk = CAUSAL ? causal_block_id(true) : xcd_block_id();
   const int pos = blk.x, by = blk.y, bz_ = blk.z;
   if ((pos & 1) == 0) dkdv_wave_block<D, BIAS, CAUSAL, NG>(p, smem, pos >> 1, by, bz_);
   else dq_wave_block<D, BIAS, CAUSAL, NG>(p, smem, pos >> 1, by, bz_);

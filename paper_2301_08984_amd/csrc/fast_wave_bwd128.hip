@@ -346,7 +346,7 @@ __device__ __forceinline__ void kv2_block(const KP& p, char* smem, int rank, int
 template <bool CAUSAL>
 __global__ __launch_bounds__(64 * W2_NG) __attribute__((amdgpu_waves_per_eu(2, 2))) void bwd_wave3_kernel(KP p) {
   __shared__ __attribute__((aligned(1024))) char smem[W2_LDS_B];
-  const BlockId blk = CAUSAL ? causal_block_id(true) : xcd_block_id(false);
+  const BlockId blk = CAUSAL ? causal_block_id(true) : xcd_block_id();
   const int pos = blk.x, by = blk.y, bz_ = blk.z;
   const int kind = pos % 3, rank = pos / 3;
   if (kind == 0) kv2_block<CAUSAL, 1>(p, smem, rank, by, bz_);

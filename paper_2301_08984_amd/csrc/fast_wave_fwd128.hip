@@ -23,7 +23,7 @@ __global__ __launch_bounds__(64 * W_NG) __attribute__((amdgpu_waves_per_eu(2, 2)
   const int grp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // uniform: scalar registers
   char* sK = smem + grp * SLOT_B;
   char* sV = sK + TILE_B;
-  const BlockId blk = CAUSAL ? causal_block_id(true) : xcd_block_id(false);
+  const BlockId blk = CAUSAL ? causal_block_id(true) : xcd_block_id();
   const int h = p.h0 + blk.y, b = p.b0 + blk.z;
   const int nsub = (p.S + SUB - 1) / SUB;
   const int qb = CAUSAL ? nsub - 1 - blk.x : blk.x;  // late query blocks see the most keys under a causal mask

@@ -45,7 +45,11 @@ struct KP {
   int sm_gw, sm_g0, sm_ring, sm_hs, sm_h0;
   int share_b0;     // first row of the whole share
   int share_units;  // (row, head) pairs in the whole share [lo,hi): kernel-shape choices use this, never the chunk
-  float scale;
+  // copies of a dense bias in accumulator layout (BiasCopy in mfma_common.h) from head bc_h0 on, or nullptr: a row of
+  // the copy is a query, a key
+  const float *bias_q, *bias_k;
+  int bc_h0;
+  float scale, inv_scale;
   int bias_kind, bias_bf16, mask_kind, mask_period, win_h, win_w, gated;
   int plain;  // the caller asks for the plain kernels (SS_FLAG_GENERIC_KERNELS)
 };

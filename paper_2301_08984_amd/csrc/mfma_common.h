@@ -15,6 +15,7 @@ namespace ssa {
 namespace {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
@@ -27,10 +28,25 @@ constexpr int MAX_RELPOS_S = 256;
 constexpr int MAX_RELPOS_R = 1024;
 
 __device__ inline float bf2f(uint16_t u) { return __uint_as_float(((uint32_t)u) << 16); }
+// Round to nearest even in hardware (v_cvt_pk_bf16_f32): one instruction for two values.  With integer arithmetic it
+// took four for one, which in the epilogues of short rows was a fifth of a kernel's vector instructions.
 __device__ inline uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
+  union { __bf16 b; uint16_t u; } o;
+  o.b = (__bf16)f;
+  return o.u;
+}
+__device__ inline uint32_t pack2_bf16(float lo, float hi) {
+  union { bf16x2 v; uint32_t u; } o;
+  o.v[0] = (__bf16)lo;
+  o.v[1] = (__bf16)hi;
+  return o.u;
+}
+// A uniform factor of the inner loops, in a vector register.  A vector instruction on vector registers and literals issues
+// in 2.3 - 3.4 cycles per wavefront (fma, mul, add, and), one that reads a scalar register in 4.2; the compiler prefers
+// the scalar register.
+__device__ inline float in_vgpr(float x) {
+  asm("" : "+v"(x));
+  return x;
 }
 __device__ inline float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }  // v_exp_f32
 // v_rcp_f32 (1 ulp): the gate 1 / (1 + e^-g) is rounded to bf16 right after, and a full division
@@ -60,8 +76,8 @@ __device__ inline void store_row32(uint16_t* row_ptr, const uint2 (&a)[4], int h
 // four scaled values as packed bf16
 __device__ inline uint2 pack4_bf16(float a, float b, float c, float d, float s) {
   uint2 o;
-  o.x = (uint32_t)f2bf(a * s) | ((uint32_t)f2bf(b * s) << 16);
-  o.y = (uint32_t)f2bf(c * s) | ((uint32_t)f2bf(d * s) << 16);
+  o.x = pack2_bf16(a * s, b * s);
+  o.y = pack2_bf16(c * s, d * s);
   return o;
 }
 // The matching load: every lane fetches 16 contiguous bytes twice and the half-waves exchange pieces,
@@ -76,6 +92,13 @@ __device__ inline void load_row32(const uint16_t* row_ptr, uint2 (&a)[4], int hl
     a[2 * j].x = s[0]; a[2 * j].y = t[0];
     a[2 * j + 1].x = s[1]; a[2 * j + 1].y = t[1];
   }
+}
+// in four sums: a single one would be a chain of dependent additions
+__device__ inline float sum16(const float (&x)[16]) {
+  float s[4] = {x[0], x[1], x[2], x[3]};
+#pragma unroll
+  for (int v = 4; v < 16; ++v) s[v & 3] += x[v];
+  return (s[0] + s[1]) + (s[2] + s[3]);
 }
 __device__ inline f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
@@ -117,30 +140,36 @@ __device__ inline bf16x8 lds_tr(const uint16_t* t, int rbase, int cbase, int lan
 // This maps the hardware block id to a logical (x, y, z) such that blocks with consecutive
 // logical ids (same head and row, neighbouring tiles: the ones that re-read the same K/V or
 // Q/dO) run on the same XCD.  A bijection on [0, gridDim.x*gridDim.y*gridDim.z).
-// `z_fast`: z (the row) varies before y (the head), so that the work-groups an XCD runs at one time
-// belong to one head and a handful of rows: for kernels with a dense bias whose heads together do
-// not fit one L2 (see bias_rows_first), the head's bias then stays in that L2 instead of being
-// fetched again for every row, while a row's K/V (or Q/dO) are still shared by neighbouring tiles.
+// `together`: heads are taken in groups of that many (a divisor of gridDim.y), a group's rows one after the other.  For
+// kernels with a dense bias: the work-groups that an XCD runs at one time then belong to as many heads as its L2
+// holds the bias of (heads_together below), instead of fetching every head's bias again for every row, while a row's K / V
+// (or Q / dO) are still shared by neighbouring tiles.  As many heads as fit, because neighbouring heads' slices of 64
+// bytes share cache lines: forward of 512 rows x 8 heads x 384, one head at a time 230 us,
+// four 216.
 struct BlockId { int x, y, z; };
-__device__ inline bool bias_rows_first(int heads, int S) { return (int64_t)heads * S * S * 2 > (4 << 20); }
-__device__ inline BlockId xcd_block_id(bool z_fast = false) {
+__device__ inline BlockId xcd_block_id(int together = 0) {
   constexpr int NX = 8;
-  const int gx = gridDim.x, gy = gridDim.y;
-  const int n = gx * gy * gridDim.z;
-  const int lin = blockIdx.x + gx * (blockIdx.y + gy * blockIdx.z);
+  const int gx = gridDim.x, gy = together > 0 ? together : gridDim.y, gz = gridDim.z;
+  const int n = gx * gridDim.y * gz;
+  const int lin = blockIdx.x + gx * (blockIdx.y + gridDim.y * blockIdx.z);
   const int xcd = lin % NX, idx = lin / NX;
   const int v = xcd * (n / NX) + min(xcd, n % NX) + idx;
   BlockId b;
   b.x = v % gx;
   const int yz = v / gx;
-  if (z_fast) {
-    b.z = yz % (int)gridDim.z;
-    b.y = yz / (int)gridDim.z;
-  } else {
-    b.y = yz % gy;
-    b.z = yz / gy;
+  b.y = yz % gy;
+  b.z = yz / gy;
+  if (gy < (int)gridDim.y) {
+    b.y += gy * (b.z / gz);
+    b.z %= gz;
   }
   return b;
+}
+// the most heads, dividing `heads`, whose bias of `entry` bytes an entry fits the 4 MiB of an XCD's L2 (1 if none does)
+inline int heads_together(int heads, int S, int entry) {
+  int g = heads;
+  while (g > 1 && (heads % g || (int64_t)g * S * S * entry > (4 << 20))) --g;
+  return g;
 }
 
 // Dense bias tile of one wavefront: 32 rows (queries, or keys of the transposed copy) by 64 columns.
@@ -159,7 +188,7 @@ __device__ inline BlockId xcd_block_id(bool z_fast = false) {
 // that lies there, (S - 1, S - 1), is put into the parked tile by hand.
 // (ODD: a variant of its own, the registers of that step cost the others a spill.)
 constexpr int BIAS_LD = 68, BIAS_TILE_ELEMS = 32 * BIAS_LD;
-enum { BIAS_OFF = 0, BIAS_EVEN = 1, BIAS_ODD = 2 };  // no dense bias, S even, S odd
+enum { BIAS_OFF = 0, BIAS_EVEN = 1, BIAS_ODD = 2, BIAS_COPY = 3 };  // no dense bias; S even, S odd; BiasCopy below
 template <bool ODD>
 struct BiasTile {
   __amdgpu_buffer_rsrc_t rs;  // the head's matrix
@@ -196,6 +225,51 @@ struct BiasTile {
   // columns col .. col + 3 (col a multiple of 4) of row r of the parked tile
   __device__ uint2 read(int r, int col) const { return *(const uint2*)(lds + r * BIAS_LD + col); }
 };
+
+// Dense bias in the form in which the matrix instructions take it: the accumulator that the scores start from.
+// A scale * score + bias is scale * (score + bias / scale), so the quotient, in fp32 and in accumulator layout, is the C
+// operand of a block's first matrix instruction, and a score costs neither the unpacking of a bf16 bias nor an addition.
+// `bias_copy_kernel` lays the heads' matrices out that way once per call, in scratch: blocks of 32 x 32 (strip of 32
+// rows, then column block), a block as four runs of 64 lanes x 16 bytes, so that every load is 1 KB in one piece; entries
+// outside S x S are -inf, which masks them.  Twice the bytes of the parked tile above, but no LDS traffic, no
+// alignment to observe and half the registers in flight.  Both give the same bits (bf16 to fp32 times 1 / scale).
+constexpr int64_t bias_copy_strips(int S) { return (S + 31) / 32; }
+constexpr int64_t bias_copy_blocks(int S) { return 2 * ((S + 63) / 64); }  // of a strip
+constexpr int64_t bias_copy_bytes(int S, int heads) { return heads * bias_copy_strips(S) * bias_copy_blocks(S) * 4096; }
+struct BiasCopy {
+  __amdgpu_buffer_rsrc_t rs;  // the strip
+  uint32_t at;                // of the lane
+  __device__ void init(const float* copy, int head, int row0, int S, int lane) {  // head counts from the copy's first
+    const int64_t strip = head * bias_copy_strips(S) + min(row0 >> 5, (int)bias_copy_strips(S) - 1);
+    const uint32_t bytes = (uint32_t)bias_copy_blocks(S) * 4096u;
+    const uint64_t from = (uint64_t)copy + (uint64_t)strip * bytes;
+    // (the builtin returns an int: unsigned before it is widened)
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)from), hi = __builtin_amdgcn_readfirstlane((uint32_t)(from >> 32));
+    const uint64_t uniform = (uint64_t)hi << 32 | lo;
+    rs = __builtin_amdgcn_make_buffer_rsrc((void*)uniform, 0, (int)bytes, 0x00020000);
+    at = 16u * lane;
+  }
+  __device__ void load(f32x16& x, int block) const {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, at + 1024u * g, block * 4096, 0);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[4 * g + e] = __uint_as_float(v[e]);
+    }
+  }
+};
+// the same of a parked tile: columns 32 kb .. + 31 of the lane's row
+template <bool ODD>
+__device__ inline void parked_bias(const BiasTile<ODD>& bt, int r, int kb, int hl, float inv_scale, f32x16& x) {
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    const uint2 u = bt.read(r, 32 * kb + 8 * g + 4 * hl);
+    x[4 * g + 0] = __uint_as_float(u.x << 16) * inv_scale;
+    x[4 * g + 1] = __uint_as_float(u.x & 0xffff0000u) * inv_scale;
+    x[4 * g + 2] = __uint_as_float(u.y << 16) * inv_scale;
+    x[4 * g + 3] = __uint_as_float(u.y & 0xffff0000u) * inv_scale;
+  }
+}
 
 // Block order of launches whose blocks of a (row, head) unit differ in work (causal), x counting from the
 // heaviest.  The XCDs are dealt the work-groups round-robin, and inside an XCD the dispatcher deals the
@@ -325,8 +399,8 @@ __device__ inline float fwd_epilogue_block(const KP& p, const f32x16& o16, int d
     uint2 out[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      out[g].x = (uint32_t)f2bf(o[4 * g]) | ((uint32_t)f2bf(o[4 * g + 1]) << 16);
-      out[g].y = (uint32_t)f2bf(o[4 * g + 2]) | ((uint32_t)f2bf(o[4 * g + 3]) << 16);
+      out[g].x = pack2_bf16(o[4 * g], o[4 * g + 1]);
+      out[g].y = pack2_bf16(o[4 * g + 2], o[4 * g + 3]);
     }
     store_row32((uint16_t*)p.Y + row, out, hl, true);
   } else {
@@ -342,16 +416,18 @@ __device__ inline float fwd_epilogue_block(const KP& p, const f32x16& o16, int d
       uint2 o1[4], o2[4];
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
-        uint16_t dg[4], dor[4];
+        float dg[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int v = 4 * g + e;
-          dg[e] = f2bf(go[v] * o[v] * gt[v] * (1.f - gt[v]));
-          dor[e] = f2bf(go[v] * gt[v]);
-          go[v] = bf2f(dor[e]);  // the later kernels read the rounded copy
+          dg[e] = go[v] * o[v] * gt[v] * (1.f - gt[v]);
+          go[v] *= gt[v];
         }
-        o1[g].x = (uint32_t)dg[0] | ((uint32_t)dg[1] << 16); o1[g].y = (uint32_t)dg[2] | ((uint32_t)dg[3] << 16);
-        o2[g].x = (uint32_t)dor[0] | ((uint32_t)dor[1] << 16); o2[g].y = (uint32_t)dor[2] | ((uint32_t)dor[3] << 16);
+        o1[g] = uint2{pack2_bf16(dg[0], dg[1]), pack2_bf16(dg[2], dg[3])};
+        o2[g] = uint2{pack2_bf16(go[4 * g], go[4 * g + 1]), pack2_bf16(go[4 * g + 2], go[4 * g + 3])};
+        // the later kernels read the rounded copy
+        go[4 * g] = __uint_as_float(o2[g].x << 16); go[4 * g + 1] = __uint_as_float(o2[g].x & 0xffff0000u);
+        go[4 * g + 2] = __uint_as_float(o2[g].y << 16); go[4 * g + 3] = __uint_as_float(o2[g].y & 0xffff0000u);
       }
       store_row32((uint16_t*)p.dG + row, o1, hl, true);
       store_row32((uint16_t*)p.dO_out + (int64_t)(b - p.do_b0) * p.do_sb + (int64_t)q * p.do_ss + (int64_t)(h - p.do_h0) * p.do_sh + 32 * db, o2, hl,
@@ -398,6 +474,8 @@ __device__ inline void fwd_epilogue(const KP& p, f32x16 (&oacc)[DB], float m, fl
 // positive scale; more than one 64-key tile's worth of rows
 inline bool fast_ok(const KP& p) {
   if (p.S <= 64 || !(p.scale > 0.f) || p.mask_kind == 2 || p.bias_kind == 2) return false;
+  // the bias is divided by the scale: not where that could leave the range of fp32
+  if (p.bias_kind == 1 && !(p.scale > 1e-9f && p.scale < 1e9f)) return false;
   if (p.bias_kind == 1 && (!p.bias_bf16 || p.S > 32768)) return false;
   return true;
 }
@@ -484,10 +562,25 @@ inline WgShape wg_shape(const KP& p) {
   return WG_2x4;
 }
 
+// the forward of pair_fwd.hip: head size 32 with a dense bias, no causal mask, the large-share shape, 32-bit offsets; not the
+// shortest rows, which spend their time on loads and are better off with the general kernel's four wavefronts per SIMD
+// (1024 rows x 8 heads x 72: 66 us against 72, x 128: 90 against 93; 64 x 8 x 384: 32.7 against 31.7)
+inline bool pair_fwd_ok(const KP& p) {
+  return fast_ok(p) && p.D == 32 && p.S > 192 && p.bias_kind == 1 && p.mask_kind == 0 && wg_shape(p) == WG_4x1 &&
+         ((int64_t)(p.S - 1) * p.ss + p.D) * 2 < (1ll << 31);
+}
+// head size 32 on the large-share work-group shape: the vector arithmetic per score element binds, and
+// the recompute pass and dQ share all of it (fast_rdq.hip)
+inline bool rdq_ok(const KP& p) {
+  if (!fast_ok(p) || p.D != 32 || wg_shape(p) != WG_4x1) return false;
+  return ((int64_t)(p.S - 1) * p.ss + p.D) * 2 < (1ll << 31);  // the kernel addresses a (row, head) slice with 32-bit offsets
+}
+
 }  // namespace
 
 // specialised kernels, one translation unit each
 hipError_t launch_fast_fwd(const KP& p, bool recompute, hipStream_t st);
+hipError_t launch_pair_fwd(const KP& p, hipStream_t st);
 hipError_t launch_fast_fwd128(const KP& p, bool recompute, hipStream_t st);
 hipError_t launch_fast_dq(const KP& p, hipStream_t st);
 hipError_t launch_fast_dq128(const KP& p, hipStream_t st);

@@ -369,8 +369,8 @@ __global__ __launch_bounds__(NW * 64) void mfma_dq_kernel(KP p) {
     for (int g = 0; g < 4; ++g) {
       const int d0 = 32 * db + 8 * g + 4 * hl;
       uint2 o;
-      o.x = (uint32_t)f2bf(acc[db][4 * g] * p.scale) | ((uint32_t)f2bf(acc[db][4 * g + 1] * p.scale) << 16);
-      o.y = (uint32_t)f2bf(acc[db][4 * g + 2] * p.scale) | ((uint32_t)f2bf(acc[db][4 * g + 3] * p.scale) << 16);
+      o.x = pack2_bf16(acc[db][4 * g] * p.scale, acc[db][4 * g + 1] * p.scale);
+      o.y = pack2_bf16(acc[db][4 * g + 2] * p.scale, acc[db][4 * g + 3] * p.scale);
       *(uint2*)(out + d0) = o;
     }
 }
@@ -476,10 +476,10 @@ __global__ __launch_bounds__(NW * 64) void mfma_dkdv_kernel(KP p) {
     for (int g = 0; g < 4; ++g) {
       const int d0 = 32 * db + 8 * g + 4 * hl;
       uint2 a, c;
-      a.x = (uint32_t)f2bf(dk[db][4 * g] * p.scale) | ((uint32_t)f2bf(dk[db][4 * g + 1] * p.scale) << 16);
-      a.y = (uint32_t)f2bf(dk[db][4 * g + 2] * p.scale) | ((uint32_t)f2bf(dk[db][4 * g + 3] * p.scale) << 16);
-      c.x = (uint32_t)f2bf(dv[db][4 * g]) | ((uint32_t)f2bf(dv[db][4 * g + 1]) << 16);
-      c.y = (uint32_t)f2bf(dv[db][4 * g + 2]) | ((uint32_t)f2bf(dv[db][4 * g + 3]) << 16);
+      a.x = pack2_bf16(dk[db][4 * g] * p.scale, dk[db][4 * g + 1] * p.scale);
+      a.y = pack2_bf16(dk[db][4 * g + 2] * p.scale, dk[db][4 * g + 3] * p.scale);
+      c.x = pack2_bf16(dv[db][4 * g], dv[db][4 * g + 1]);
+      c.y = pack2_bf16(dv[db][4 * g + 2], dv[db][4 * g + 3]);
       *(uint2*)(oK + d0) = a;
       *(uint2*)(oV + d0) = c;
     }
@@ -644,12 +644,8 @@ hipError_t launch_mfma_dq_dkdv(const KP& p, hipStream_t st) {
   if (p.D == 128 && p.bias_kind == 0) return launch_fast_bwd_wave3(p, st);
   return launch_fast_bwd_wave(p, st);
 }
-// head size 32 on the large-share work-group shape: the vector arithmetic per score element binds, and
-// the recompute pass and dQ share all of it
 bool mfma_fuses_recompute_dq(const KP& p) {
-  if (win_ok(p)) return true;
-  if (!fast_ok(p) || p.D != 32 || wg_shape(p) != WG_4x1) return false;
-  return ((int64_t)(p.S - 1) * p.ss + p.D) * 2 < (1ll << 31);  // the kernel addresses a (row, head) slice with 32-bit offsets
+  return win_ok(p) || rdq_ok(p);
 }
 hipError_t launch_mfma_recompute_dq(const KP& p, hipStream_t st) {
   return win_ok(p) ? launch_win_recompute_dq(p, st) : launch_fast_recompute_dq(p, st);

@@ -210,8 +210,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         uint2 o;
-        o.x = (uint32_t)f2bf(oacc[4 * g] * inv) | ((uint32_t)f2bf(oacc[4 * g + 1] * inv) << 16);
-        o.y = (uint32_t)f2bf(oacc[4 * g + 2] * inv) | ((uint32_t)f2bf(oacc[4 * g + 3] * inv) << 16);
+        o.x = pack2_bf16(oacc[4 * g] * inv, oacc[4 * g + 1] * inv);
+        o.y = pack2_bf16(oacc[4 * g + 2] * inv, oacc[4 * g + 3] * inv);
         *(uint2*)(L.t2 + q * SLD + 8 * g + 4 * hl) = o;
       }
       if (q < p.S && hl == 0 && p.lse_out)
@@ -369,8 +369,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         uint2 o[4];
 #pragma unroll
         for (int gq = 0; gq < 4; ++gq) {
-          o[gq].x = (uint32_t)f2bf(dq[4 * gq] * p.scale) | ((uint32_t)f2bf(dq[4 * gq + 1] * p.scale) << 16);
-          o[gq].y = (uint32_t)f2bf(dq[4 * gq + 2] * p.scale) | ((uint32_t)f2bf(dq[4 * gq + 3] * p.scale) << 16);
+          o[gq].x = pack2_bf16(dq[4 * gq] * p.scale, dq[4 * gq + 1] * p.scale);
+          o[gq].y = pack2_bf16(dq[4 * gq + 2] * p.scale, dq[4 * gq + 3] * p.scale);
         }
         store_row32((uint16_t*)p.dQ + base + (int64_t)min(q, p.S - 1) * p.ss, o, hl, q < p.S);
       }
@@ -433,10 +433,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         uint2 a[4], c[4];
 #pragma unroll
         for (int gd = 0; gd < 4; ++gd) {
-          a[gd].x = (uint32_t)f2bf(dk[4 * gd] * p.scale) | ((uint32_t)f2bf(dk[4 * gd + 1] * p.scale) << 16);
-          a[gd].y = (uint32_t)f2bf(dk[4 * gd + 2] * p.scale) | ((uint32_t)f2bf(dk[4 * gd + 3] * p.scale) << 16);
-          c[gd].x = (uint32_t)f2bf(dv[4 * gd]) | ((uint32_t)f2bf(dv[4 * gd + 1]) << 16);
-          c[gd].y = (uint32_t)f2bf(dv[4 * gd + 2]) | ((uint32_t)f2bf(dv[4 * gd + 3]) << 16);
+          a[gd].x = pack2_bf16(dk[4 * gd] * p.scale, dk[4 * gd + 1] * p.scale);
+          a[gd].y = pack2_bf16(dk[4 * gd + 2] * p.scale, dk[4 * gd + 3] * p.scale);
+          c[gd].x = pack2_bf16(dv[4 * gd], dv[4 * gd + 1]);
+          c[gd].y = pack2_bf16(dv[4 * gd + 2], dv[4 * gd + 3]);
         }
         const int64_t krow = base + (int64_t)min(key, p.S - 1) * p.ss;
         store_row32((uint16_t*)p.dK + krow, a, hl, key < p.S);

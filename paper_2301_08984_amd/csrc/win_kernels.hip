@@ -19,8 +19,6 @@
 namespace ssa {
 namespace {
 
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-
 constexpr int WD = 32;        // head size
 constexpr int WLD = WD + 24;  // LDS row stride of the staged tiles (elements): conflict-free for b128 and transposed reads
 constexpr uint32_t NEG_INF_BF16 = 0xff80u;
