@@ -276,8 +276,8 @@ int fewest_chunks(const ss_attn_desc* d, int gw, size_t bytes) {
   return d->k;
 }
 
-// the k chunks of `d` one after another, in the scratch at `ws`; `copy`: room for a copy of the bias in accumulator layout
-// by key, or NULL
+// the k chunks of `d` one after another, in the scratch at `ws`; `copy`: room for the copies of the bias in accumulator
+// layout (bias_copy.h), or NULL
 int run_bwd(const ss_attn_desc* d, Family fam, const WsLayout& w, const void* Q, const void* K, const void* V,
             const void* bias, const int32_t* region_ids, const void* G, const void* dY, const float* lse, void* dQ,
             void* dK, void* dV, float* dBias, void* dG, char* ws, float* copy, hipStream_t st) {
@@ -289,8 +289,7 @@ int run_bwd(const ss_attn_desc* d, Family fam, const WsLayout& w, const void* Q,
   const bool mfma = fam == FAM_MFMA;
   if (copy) {
     const int h0 = d->shard_axis == SS_AXIS_HEAD ? d->lo : 0, h1 = d->shard_axis == SS_AXIS_HEAD ? d->hi : d->H;
-    SS_LAUNCH(SS_K_TABLE_REDUCE, ssa::launch_bias_copy(bias, copy, true, p.inv_scale, d->S, h0, h1, st), "bias copy");
-    p.bias_k = copy; p.bc_h0 = h0;
+    SS_LAUNCH(SS_K_TABLE_REDUCE, ssa::launch_bias_copies(p, copy, true, h0, h1, st), "bias copy");
   } else if (mfma && ssa::mfma_wants_bias_transpose(p)) {
     // the K-stationary kernels read bias[h][i][j] along i: give them a transposed copy, once per call
     const int h0 = d->shard_axis == SS_AXIS_HEAD ? d->lo : 0, h1 = d->shard_axis == SS_AXIS_HEAD ? d->hi : d->H;
@@ -563,8 +562,7 @@ int ss_attn_fwd(const ss_attn_desc* d, const void* Q, const void* K, const void*
     const size_t bytes = ssa::bias_copy_bytes_for(p, false, p.b1 - p.b0, p.h1 - p.h0);
     float* copy = bytes > 0 && bytes <= ssa::SHARED_BYTES ? (float*)shared.take(st) : nullptr;
     if (copy) {
-      SS_LAUNCH(SS_K_TABLE_REDUCE, ssa::launch_bias_copy(bias, copy, false, p.inv_scale, d->S, p.h0, p.h1, st), "bias copy");
-      p.bias_q = copy; p.bc_h0 = p.h0;
+      SS_LAUNCH(SS_K_TABLE_REDUCE, ssa::launch_bias_copies(p, copy, false, p.h0, p.h1, st), "bias copy");
     }
   }
   if (fam == FAM_SMALL) SS_LAUNCH(SS_K_FWD, ssa::launch_small_fwd(p, st), "forward (short)");
@@ -612,7 +610,7 @@ int ss_attn_bwd(const ss_attn_desc* d, const void* Q, const void* K, const void*
   if (!workspace || workspace_bytes < w.total || ((uintptr_t)workspace % ALIGN)) return SS_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;
-  // A copy of the bias in accumulator layout goes into the library's buffer, behind the scratch of the chunks if that goes
+  // Copies of the bias in accumulator layout go into the library's buffer, behind the scratch of the chunks if that goes
   // there too.
   const KP p = base_params(&run);
   const int rows = d->shard_axis == SS_AXIS_ROW ? d->hi - d->lo : d->B, heads = d->shard_axis == SS_AXIS_HEAD ? d->hi - d->lo : d->H;

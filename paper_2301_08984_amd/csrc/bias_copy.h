@@ -13,8 +13,14 @@ namespace {
 // 256 rows 373 | 329; odd lengths, whose parked tiles are loaded unaligned: 64 x 8 x 501: 58.0 | 58.3, 512 x 4 x 301: 107 | 92.
 // Backward: dK / dV 9 % shorter (1024 x 4 x 1024: 2037 -> 1850 us), and the copy replaces the transposed bf16 one; the
 // recompute + dQ kernel gains nothing from a copy of its own (2469 | 2510).
+// Windows (win_kernels.hip; the backward takes both copies): without one a work-group gathers the bias from the table in
+// LDS and holds it in registers.
 inline size_t bias_copy_bytes_for(const KP& p, bool backward, int64_t rows, int heads) {
-  if (win_ok(p) || !pair_fwd_ok(p) || p.S > 16384) return 0;
+  if (win_ok(p)) {
+    if (p.bias_kind == 0 || (backward ? rows * heads < (p.S <= 128 ? 256 : 64) : p.S <= 128 || rows * heads < 512)) return 0;
+    return (size_t)bias_copy_bytes(p.S, heads) * (backward ? 2 : 1);
+  }
+  if (!pair_fwd_ok(p) || p.S > 16384) return 0;
   const int64_t row_stride = p.ss > (int64_t)p.H * p.D ? p.ss : (int64_t)p.H * p.D;
   if (((int64_t)(p.S - 1) * row_stride + p.D) * 2 >= (1ll << 31)) return 0;
   const int64_t entries = (int64_t)heads * p.S * p.S;
@@ -41,10 +47,43 @@ __global__ __launch_bounds__(256) void bias_copy_kernel(const uint16_t* src, flo
     out[64 * g] = x;
   }
 }
-// the heads [h0, h1); `by_key`: a row of the copy is a key, not a query
-inline hipError_t launch_bias_copy(const void* bias, float* copy, bool by_key, float inv_scale, int S, int h0, int h1, hipStream_t st) {
-  const dim3 g((unsigned)((bias_copy_blocks(S) + 3) / 4), (unsigned)bias_copy_strips(S), h1 - h0);
-  bias_copy_kernel<<<g, 256, 0, st>>>((const uint16_t*)bias, copy, S, h0, by_key ? 1 : 0, inv_scale);
+// The same of a window's bias, from the relative-position table or the dense matrix; z = head, then the copy.
+__global__ __launch_bounds__(256) void win_bias_copy_kernel(KP p, float* dst, int heads) {
+  const int lane = threadIdx.x & 63, block = blockIdx.x * 4 + (threadIdx.x >> 6), strip = blockIdx.y, S = p.S;
+  if (block >= bias_copy_blocks(S)) return;
+  const int head = blockIdx.z % heads, by_key = blockIdx.z / heads, h = p.bc_h0 + head;
+  const int R = (2 * p.win_h - 1) * (2 * p.win_w - 1);
+  const uint16_t* from = (const uint16_t*)p.bias + (p.bias_kind == 2 ? (int64_t)h * R : (int64_t)h * S * S);
+  f32x4* out = (f32x4*)dst + ((blockIdx.z * bias_copy_strips(S) + strip) * bias_copy_blocks(S) + block) * 256 + lane;
+  const int row = 32 * strip + (lane & 31), col = 32 * block + 4 * (lane >> 5), rc = min(row, S - 1);
+  const int ry = rc / p.win_w, rx = rc % p.win_w;
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    f32x4 x;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int c = col + 8 * g + e, cc = min(c, S - 1);
+      int at;
+      if (p.bias_kind == 2) {
+        const int cy = cc / p.win_w, cx = cc % p.win_w, sign = by_key ? -1 : 1;  // query minus key
+        at = (sign * (ry - cy) + p.win_h - 1) * (2 * p.win_w - 1) + sign * (rx - cx) + p.win_w - 1;
+      } else {
+        at = by_key ? cc * S + rc : rc * S + cc;
+      }
+      x[e] = row < S && c < S ? bf2f(from[at]) * p.inv_scale : -INFINITY;
+    }
+    out[64 * g] = x;
+  }
+}
+// Makes the copies that bias_copy_bytes_for asks for, of the heads [h0, h1), and points `p` at them.
+inline hipError_t launch_bias_copies(KP& p, float* copy, bool backward, int h0, int h1, hipStream_t st) {
+  const int heads = h1 - h0, kinds = win_ok(p) && backward ? 2 : 1;
+  p.bc_h0 = h0;
+  const dim3 g((unsigned)((bias_copy_blocks(p.S) + 3) / 4), (unsigned)bias_copy_strips(p.S), heads * kinds);
+  if (win_ok(p)) win_bias_copy_kernel<<<g, 256, 0, st>>>(p, copy, heads);
+  else bias_copy_kernel<<<g, 256, 0, st>>>((const uint16_t*)p.bias, copy, p.S, h0, backward ? 1 : 0, p.inv_scale);
+  if (!backward || kinds == 2) p.bias_q = copy;
+  if (backward) p.bias_k = copy + (kinds - 1) * bias_copy_bytes(p.S, heads) / 4;
   return hipGetLastError();
 }
 

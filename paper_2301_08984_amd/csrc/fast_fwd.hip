@@ -63,6 +63,9 @@ __global__ __launch_bounds__(64 * QW * NG) __attribute__((amdgpu_waves_per_eu(D 
     for (int v = 0; v < 16; ++v) oacc[db][v] = 0.f;
   float nm = 1e30f, l = 0.f;  // the negated running maximum, the row sum
   const float scale = in_vgpr(p.scale), c1 = in_vgpr(p.scale * LOG2E);
+  // the scores start from bias / scale (BiasCopy), as in the backward of the same shapes (fast_rdq.hip): a backward then
+  // takes the same statistics itself that this forward leaves
+  constexpr bool START = BIAS && CAUSAL && D == 32 && NG == 1;
 
   int ntiles = (p.S + BN - 1) / BN;
   if (CAUSAL) ntiles = min(ntiles, (min(qblk + BM, p.S) + BN - 1) / BN);
@@ -122,8 +125,13 @@ __global__ __launch_bounds__(64 * QW * NG) __attribute__((amdgpu_waves_per_eu(D 
         fa[ks] = lds_nat<LDK>(sK, r, ks, hl);
         fb[ks] = lds_nat<LDK>(sK, 32 + r, ks, hl);
       }
+      if (START) {
+        parked_bias(bt, r, 0, hl, p.inv_scale, sa[0]);
+        parked_bias(bt, r, 1, hl, p.inv_scale, sa[1]);
+      } else {
 #pragma unroll
-      for (int v = 0; v < 16; ++v) { sa[0][v] = 0.f; sa[1][v] = 0.f; }
+        for (int v = 0; v < 16; ++v) { sa[0][v] = 0.f; sa[1][v] = 0.f; }
+      }
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         sa[0] = mfma(fa[ks], qf[ks], sa[0]);
@@ -137,14 +145,14 @@ __global__ __launch_bounds__(64 * QW * NG) __attribute__((amdgpu_waves_per_eu(D 
       }
       __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
     }
-    if (BIAS) {
+    if (BIAS && !START) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
         for (int g = 0; g < 4; ++g) bz[4 * kb + g] = bt.read(r, 32 * kb + 8 * g + 4 * hl);
     }
     const bool edge = (k0 + BN > p.S) || (CAUSAL && k0 + BN - 1 > q0);
-    if (BIAS) {
+    if (BIAS && !START) {
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
@@ -172,7 +180,7 @@ __global__ __launch_bounds__(64 * QW * NG) __attribute__((amdgpu_waves_per_eu(D 
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int v = 0; v < 16; ++v) rmax = fmaxf(rmax, sa[kb][v]);
-    rmax *= BIAS ? LOG2E : c1;  // the running maximum is kept in base-2 units; scale > 0 on this path
+    rmax *= BIAS && !START ? LOG2E : c1;  // the running maximum is kept in base-2 units; scale > 0 on this path
     rmax = half_max(rmax);
     // the running maximum is raised only when exceeded by more than 2^8, so the O rescale is
     // skipped on most tiles; probabilities stay below 2^8, harmless in fp32/bf16 range
@@ -191,7 +199,7 @@ __global__ __launch_bounds__(64 * QW * NG) __attribute__((amdgpu_waves_per_eu(D 
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        sa[kb][v] = fast_exp2(fmaf(sa[kb][v], BIAS ? LOG2E : c1, nm));
+        sa[kb][v] = fast_exp2(fmaf(sa[kb][v], BIAS && !START ? LOG2E : c1, nm));
         ls[v & 3] = kb == 0 && v < 4 ? sa[kb][v] : ls[v & 3] + sa[kb][v];
       }
     l += (ls[0] + ls[1]) + (ls[2] + ls[3]);

@@ -562,11 +562,9 @@ inline WgShape wg_shape(const KP& p) {
   return WG_2x4;
 }
 
-// the forward of pair_fwd.hip: head size 32 with a dense bias, no causal mask, the large-share shape, 32-bit offsets; not the
-// shortest rows, which spend their time on loads and are better off with the general kernel's four wavefronts per SIMD
-// (1024 rows x 8 heads x 72: 66 us against 72, x 128: 90 against 93; 64 x 8 x 384: 32.7 against 31.7)
+// the forward of pair_fwd.hip: head size 32 with a dense bias, no causal mask, the large-share shape, 32-bit offsets
 inline bool pair_fwd_ok(const KP& p) {
-  return fast_ok(p) && p.D == 32 && p.S > 192 && p.bias_kind == 1 && p.mask_kind == 0 && wg_shape(p) == WG_4x1 &&
+  return fast_ok(p) && p.D == 32 && p.bias_kind == 1 && p.mask_kind == 0 && wg_shape(p) == WG_4x1 &&
          ((int64_t)(p.S - 1) * p.ss + p.D) * 2 < (1ll << 31);
 }
 // head size 32 on the large-share work-group shape: the vector arithmetic per score element binds, and

@@ -19,8 +19,10 @@ constexpr int PD = 32, PLK = PD + 8, PLV = PD + 16;  // row pads chosen for conf
 constexpr int PTILE = BN * (PLK + PLV);               // K and V of one row, 64 keys
 
 template <int BIAS, int NR>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) void pair_fwd_kernel(KP p, int together) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS == BIAS_COPY ? 3 : 4, BIAS == BIAS_COPY ? 3 : 4))) void pair_fwd_kernel(KP p, int together) {
+#pragma clang fp contract(off)  // the variants are to give the same bits
   constexpr bool PARKED = BIAS != BIAS_COPY;
+  constexpr int BLOCK_UNROLL = PARKED ? 1 : 2;
   __shared__ __attribute__((aligned(16))) uint16_t smem[2][NR][PTILE];  // buffer, row
   __shared__ __attribute__((aligned(16))) uint16_t parked[PARKED ? 4 * BIAS_TILE_ELEMS : 8];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 31, hl = lane >> 5;
@@ -149,8 +151,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 3))) voi
   __syncthreads();
   for (int kt = 0; kt < ntiles; ++kt) {
     if (q0 < p.S) {
-      block(kt & 1, 0, 2 * kt);
-      block(kt & 1, 1, 2 * kt + 1);
+#pragma unroll BLOCK_UNROLL
+      for (int kb = 0; kb < 2; ++kb) block(kt & 1, kb, 2 * kt + kb);
     }
     if (kt + 1 < ntiles) {
       stage((kt + 1) & 1);

@@ -1,19 +1,16 @@
 // Attention over windows of 65 to 160 tokens with head size 32, bf16: a whole row (b, h) is small
 // enough to share one work-group, too large for one wavefront (small_kernels.hip ends at 64 tokens).
 //
-// A work-group has one wavefront per 32-token block (NB = 3, 4 or 5) and walks several rows b of one
-// head.  Each wavefront keeps the bias of its 32 queries (or keys) against every token in registers,
-// packed bf16, 8 per 32 x 32 block, gathered once per work-group (from the relative-position table or
-// the dense matrix; -inf where a pair lies outside the window), so that a row costs no bias traffic and
-// no index arithmetic.  K and V (or Q and dO) of the row are staged in LDS once for all
-// wavefronts, the next row's travel global -> registers meanwhile.
+// A work-group has one wavefront per 32-token block (NB = 3, 4 or 5); K and V (or Q and dO) of the row are staged in LDS
+// once for all of them.  The scores start from the bias (BiasCopy in mfma_common.h): large shares read it in accumulator
+// layout, expanded from the relative-position table once per call into the library's buffer; others, captured calls and
+// forwards of up to 128 tokens gather it once per work-group and keep it in registers, packed bf16, with the same values.
 //
-// What bounds it: the vector arithmetic per score element (bias unpack and addition, exp2 at a quarter of
-// the rate, maximum, sums, conversions) against two to five matrix steps.  The all-feature kernels that
-// served these shapes spent most of their time on a table lookup, an integer subtraction and a mask
-// comparison per element and gave the bias gradient a wavefront per 32 x 32 tile that read the operands
-// in 16-byte pieces.  512 windows of 12 x 12 tokens, 8 heads: 3.57 ms per step with them, 0.52 with these (one
-// chunk: forward 99 us, recompute + dQ 252, dK / dV and the bias gradient 151, folds and table 19).
+// What bounds it: the chain of loads, matrix steps and vector arithmetic of the few wavefronts that fit a compute unit.
+// The bias held in registers by every wavefront (40 of them at NB = 5) left one or two work-groups per compute unit and
+// spills in the recompute + dQ kernel; loaded block by block, and without the sum for O, which nobody needs without a gate, that
+// kernel fits 128 registers, three work-groups.  512 windows of 12 x 12 tokens, 8 heads, us: forward 100 -> 71, recompute +
+// dQ 258 -> 96, dK / dV and the bias gradient 148 -> 129, copies 11, step 518 -> 306; 1024 x 16 x 9 x 9 backward 560 -> 367.
 #include "mfma_common.h"
 
 namespace ssa {
@@ -21,63 +18,17 @@ namespace {
 
 constexpr int WD = 32;        // head size
 constexpr int WLD = WD + 24;  // LDS row stride of the staged tiles (elements): conflict-free for b128 and transposed reads
-constexpr uint32_t NEG_INF_BF16 = 0xff80u;
 
-typedef uint2 uint2_u __attribute__((aligned(2)));
-
-// The blocks of a row are unrolled (the bias and the gradient sums are registers) but meant to run one
-// after the other, other wavefronts fill the gaps; and the bias, which does not change from row to
-// row, is meant to stay packed: the compiler would unpack it once, outside the row loop, into twice the
-// registers (measured: 200 spilled in the dK/dV kernel at NB = 5).
-__device__ inline void block_boundary(uint32_t (&bz)[8]) {
-#pragma unroll
-  for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(bz[i]));
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_sched_barrier(0);
-}
-
-// Registers of a 32-row strip of the score matrix against NB column blocks: element v of block c is the
-// pair (row, 32 c + key_of(v, hl)).  ROW_IS_QUERY: lane = query, registers = keys; else transposed.
-// -inf outside the window on the register axis, and everywhere for a row with `row_dead`; other rows past
-// the end repeat the last one (their results are never stored).  Table and cidx in LDS.
-template <int NB, bool ROW_IS_QUERY>
-__device__ inline void gather_bias(const KP& p, const uint16_t* table, const int* cidx, int h, int row, int hl, bool row_dead,
-                                   uint32_t (&bz)[NB][8]) {
-  const int rc = min(row, p.S - 1);
-  auto fill = [&](auto raw) {  // raw(k): bf16 bits of the pair of this row with register index k < S
-#pragma unroll
-    for (int c = 0; c < NB; ++c) {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int k = 32 * c + 8 * (j >> 1) + 4 * hl + 2 * (j & 1);
-        const uint32_t x = raw(min(k, p.S - 1)), y = raw(min(k + 1, p.S - 1));
-        bz[c][j] = (row_dead || k >= p.S ? NEG_INF_BF16 : x) | ((row_dead || k + 1 >= p.S ? NEG_INF_BF16 : y) << 16);
-      }
-      block_boundary(bz[c]);
-    }
-  };
-  if (p.bias_kind == 2) {
-    const int c0 = (p.win_h - 1) * (2 * p.win_w - 1) + (p.win_w - 1), cr = cidx[rc] + (ROW_IS_QUERY ? c0 : -c0);
-    fill([&](int k) -> uint32_t { return table[ROW_IS_QUERY ? cr - cidx[k] : cidx[k] - cr]; });
-  } else if (p.bias_kind == 1) {
-    const uint16_t* m = (const uint16_t*)p.bias + (int64_t)h * p.S * p.S;
-    fill([&](int k) -> uint32_t { return m[ROW_IS_QUERY ? rc * p.S + k : k * p.S + rc]; });
-  } else {
-    fill([&](int) -> uint32_t { return 0; });
-  }
-}
-// element v of a block
-__device__ inline float bias_of(const uint32_t (&b)[8], int v) {
-  return (v & 1) ? __uint_as_float(b[v >> 1] & 0xffff0000u) : __uint_as_float(b[v >> 1] << 16);
-}
+// where a block's bias comes from
+enum { WB_NONE = 0, WB_COPY = 1, WB_REGS = 2 };
 
 template <int NB>
 struct WinLds {
   uint16_t t0[32 * NB * WLD];  // forward, dQ: K; dK/dV: Q
   uint16_t t1[32 * NB * WLD];  // forward, dQ: V; dK/dV: dO
-  float lse2[32 * NB], delta[32 * NB];
-  int rid[32 * NB];
-  int cidx[32 * NB];
+  alignas(16) float lse2[32 * NB], delta[32 * NB];
+  alignas(16) int rid[32 * NB];
+  alignas(16) int cidx[32 * NB];
   uint16_t table[MAX_RELPOS_R];
 };
 
@@ -86,9 +37,80 @@ template <int NB>
 __device__ inline void table_setup(const KP& p, int h, WinLds<NB>& L, int tid) {
   if (p.bias_kind != 2) return;
   const int R = (2 * p.win_h - 1) * (2 * p.win_w - 1);
-  for (int i = tid; i < p.S; i += 64 * NB) L.cidx[i] = (i / p.win_w) * (2 * p.win_w - 1) + (i % p.win_w);
+  if (tid < 32 * NB) {
+    const int i = min(tid, p.S - 1);
+    L.cidx[tid] = (i / p.win_w) * (2 * p.win_w - 1) + (i % p.win_w);
+  }
   for (int i = tid; i < R; i += 64 * NB) L.table[i] = ((const uint16_t*)p.bias)[(int64_t)h * R + i];
 }
+
+// What the scores of a block start from: element v is the pair (lane's row, column 32 c + key_of(v, hl)), bias / scale,
+// -inf where either lies outside the window.  KEYS: the lane's row is a key and the columns are queries.
+//  WB_COPY: loaded from the copy in accumulator layout;
+//  WB_REGS: gathered once per work-group and kept in registers, packed bf16, 8 per block (the caller unrolls the blocks).
+template <int NB, int WB, bool KEYS>
+struct WinBias {
+  BiasCopy bc;
+  uint32_t bz[WB == WB_REGS ? NB : 1][8];
+  // WB_REGS: the table and the coordinates are in LDS and visible
+  __device__ void init(const KP& p, const WinLds<NB>& L, int h, int w, int lane) {
+    if (WB == WB_COPY) bc.init(KEYS ? p.bias_k : p.bias_q, h - p.bc_h0, 32 * w, p.S, lane);
+    if (WB != WB_REGS) return;
+    const int row = 32 * w + (lane & 31), hl = lane >> 5, rc = min(row, p.S - 1);
+    const int c0 = (p.win_h - 1) * (2 * p.win_w - 1) + (p.win_w - 1);
+    const uint16_t* m = (const uint16_t*)p.bias + (int64_t)h * p.S * p.S;
+    const int cr = p.bias_kind == 2 ? L.cidx[rc] + (KEYS ? -c0 : c0) : 0;
+#pragma unroll
+    for (int c = 0; c < NB; ++c) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const int k = 32 * c + 8 * g + 4 * hl;
+        uint32_t x[4];
+        if (p.bias_kind == 2) {
+          const int4 ck = *(const int4*)(L.cidx + k);
+          x[0] = L.table[KEYS ? ck.x - cr : cr - ck.x];
+          x[1] = L.table[KEYS ? ck.y - cr : cr - ck.y];
+          x[2] = L.table[KEYS ? ck.z - cr : cr - ck.z];
+          x[3] = L.table[KEYS ? ck.w - cr : cr - ck.w];
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int kc = min(k + e, p.S - 1);
+            x[e] = m[KEYS ? kc * p.S + rc : rc * p.S + kc];
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = row < p.S && k + e < p.S ? x[e] : 0xff80u;  // -inf
+        bz[c][2 * g] = x[0] | (x[1] << 16);
+        bz[c][2 * g + 1] = x[2] | (x[3] << 16);
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(bz[c][i]));
+    }
+  }
+  __device__ void get(const KP& p, int w, int c, int lane, f32x16& x) {
+    if (WB == WB_COPY) {
+      bc.load(x, c);
+      return;
+    }
+    if (WB == WB_REGS) {
+      // the bias, which does not change from row to row, is meant to stay packed: the compiler would unpack it once, outside
+      // the row loop, into twice the registers
+#pragma unroll
+      for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(bz[c][i]));
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const uint32_t u = bz[c][v >> 1];
+        x[v] = __uint_as_float((v & 1) ? u & 0xffff0000u : u << 16) * p.inv_scale;
+      }
+      return;
+    }
+    int row = 32 * w + (lane & 31);  // opaque: nothing of this is to be kept in registers from one row b to the next
+    asm volatile("" : "+v"(row));
+#pragma unroll
+    for (int v = 0; v < 16; ++v) x[v] = row < p.S && 32 * c + key_of(v, lane >> 5) < p.S ? 0.f : -INFINITY;
+  }
+};
 
 // a row's two tensors, two 16-byte chunks of each per thread (rows past S - 1 repeat the last one)
 template <int NB>
@@ -123,233 +145,256 @@ __device__ inline bool row_is_masked(const int* ids, int S, int lane) {
   return __builtin_amdgcn_ballot_w64(other != 0) != 0;
 }
 
-// adds the bias to a block of scores (natural units) and masks pairs of different regions
-__device__ inline void bias_and_mask(f32x16& s, const uint32_t (&bz)[8], float scale, bool masked, const int* rid, int my_rid,
-                                     int k0, int hl) {
+// pairs of different regions: -inf
+__device__ inline void mask_regions(f32x16& s, const int* rid, int my_rid, int k0, int hl) {
 #pragma unroll
-  for (int v = 0; v < 16; ++v) s[v] = fmaf(s[v], scale, bias_of(bz, v));
-  if (masked) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int4 rk = *(const int4*)(rid + k0 + 8 * g + 4 * hl);
-      s[4 * g + 0] = rk.x != my_rid ? -INFINITY : s[4 * g + 0];
-      s[4 * g + 1] = rk.y != my_rid ? -INFINITY : s[4 * g + 1];
-      s[4 * g + 2] = rk.z != my_rid ? -INFINITY : s[4 * g + 2];
-      s[4 * g + 3] = rk.w != my_rid ? -INFINITY : s[4 * g + 3];
-    }
+  for (int g = 0; g < 4; ++g) {
+    const int4 rk = *(const int4*)(rid + k0 + 8 * g + 4 * hl);
+    s[4 * g + 0] = rk.x != my_rid ? -INFINITY : s[4 * g + 0];
+    s[4 * g + 1] = rk.y != my_rid ? -INFINITY : s[4 * g + 1];
+    s[4 * g + 2] = rk.z != my_rid ? -INFINITY : s[4 * g + 2];
+    s[4 * g + 3] = rk.w != my_rid ? -INFINITY : s[4 * g + 3];
   }
 }
 
 // ---------------------------------------------------------------------------
-// forward: grid (row groups, heads); lane = query
+// forward: a run of rows of one head per work-group, heads of a row next to each other; lane = query.  WB_REGS: the next row's
+// operands travel global -> registers meanwhile.  WB_COPY: one row, 4 wavefronts per SIMD instead (71 us against 74 for 512
+// windows of 12 x 12 tokens x 8 heads).
 // ---------------------------------------------------------------------------
-template <int NB, bool REGION>
-__global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(3, 3))) void win_fwd_kernel(KP p, int rows_per_wg) {
+template <int NB, bool REGION, int WB>
+__global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB == WB_REGS ? 3 : 4, WB == WB_REGS ? 3 : 4))) void win_fwd_kernel(KP p, int rows_per_wg) {
+#pragma clang fp contract(off)  // the variants are to give the same bits
   __shared__ __attribute__((aligned(16))) WinLds<NB> L;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 31, hl = lane >> 5;
-  const int h = p.h0 + blockIdx.y, q = 32 * w + r, qc = min(q, p.S - 1);
-  const int bfirst = p.b0 + blockIdx.x * rows_per_wg, blast = min(bfirst + rows_per_wg, p.b1);
+  constexpr int BLOCK_UNROLL = WB == WB_REGS ? NB : 1;
+  constexpr bool RUN = WB != WB_COPY;
+  // the next block's bias is at hand before a block's arithmetic (five blocks in registers: no room for a second one)
+  constexpr bool AHEAD = WB == WB_COPY || (WB == WB_REGS && NB < 5);
+  const BlockId blk = xcd_block_id();
+  const int h = p.h0 + blk.x, q = 32 * w + r, qc = min(q, p.S - 1);
+  const int bfirst = p.b0 + blk.z * rows_per_wg, blast = RUN ? min(bfirst + rows_per_wg, p.b1) : bfirst + 1;
   RowStage<NB> next;
   bf16x8 qn[2];
+  int id0 = 0, ids_n[(NB + 1) / 2] = {};
   auto fetch = [&](int b) {
     const int64_t base = (int64_t)b * p.sb + (int64_t)h * p.sh;
     next.load((const uint16_t*)p.K + base, p.ss, (const uint16_t*)p.V + base, p.ss, p.S, tid);
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) qn[ks] = *(const bf16x8*)((const uint16_t*)p.Q + base + (int64_t)qc * p.ss + 16 * ks + 8 * hl);
+    if (REGION) {
+      const int* ids = p.region + (int64_t)(b % p.mask_period) * p.S;
+      id0 = ids[0];
+#pragma unroll
+      for (int c = 0; c < (NB + 1) / 2; ++c) ids_n[c] = ids[min(lane + 64 * c, p.S - 1)];
+    }
   };
   fetch(bfirst);
-  table_setup(p, h, L, tid);
-  __syncthreads();
-  uint32_t bz[NB][8];
-  gather_bias<NB, true>(p, L.table, L.cidx, h, q, hl, false, bz);
+  if (WB == WB_REGS) {
+    table_setup(p, h, L, tid);
+    __syncthreads();
+  }
+  WinBias<NB, WB, false> bias;
+  bias.init(p, L, h, w, lane);
+  f32x16 cz;  // of the block, then of the next one
+  if (AHEAD) bias.get(p, w, 0, lane, cz);
+  const float c1 = in_vgpr(p.scale * LOG2E);
   for (int b = bfirst; b < blast; ++b) {
     const int64_t base = (int64_t)b * p.sb + (int64_t)h * p.sh;
     const bf16x8 qf[2] = {qn[0], qn[1]};
-    __syncthreads();
+    if (b > bfirst) __syncthreads();
     next.store(L, tid);
     bool masked = false;
     int my_rid = 0;
     if (REGION) {
-      const int* ids = p.region + (int64_t)(b % p.mask_period) * p.S;
-      masked = row_is_masked<NB>(ids, p.S, lane);
-      my_rid = ids[qc];
-      if (tid < 32 * NB) L.rid[tid] = ids[min(tid, p.S - 1)];
+      int other = 0;
+#pragma unroll
+      for (int c = 0; c < (NB + 1) / 2; ++c) other |= ids_n[c] ^ id0;
+      masked = __builtin_amdgcn_ballot_w64(other != 0) != 0;
+      if (masked) {
+        const int* ids = p.region + (int64_t)(b % p.mask_period) * p.S;
+        my_rid = ids[qc];
+        if (tid < 32 * NB) L.rid[tid] = ids[min(tid, p.S - 1)];
+      }
     }
     __syncthreads();
-    if (b + 1 < blast) fetch(b + 1);
-    f32x16 oacc;
+    if (RUN && b + 1 < blast) fetch(b + 1);
+    f32x16 oacc[1];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) oacc[v] = 0.f;
-    float m = -1e30f, l = 0.f;
-    f32x16 oacc1[1];
-#pragma unroll
+    for (int v = 0; v < 16; ++v) oacc[0][v] = 0.f;
+    float nm = 1e30f, l = 0.f;  // the negated running maximum, the row sum
+#pragma unroll BLOCK_UNROLL
     for (int c = 0; c < NB; ++c) {
-      block_boundary(bz[c]);
+      // the maximum is taken on blocks that raise it, see pair_fwd.hip
       f32x16 s;
+      float sum = INFINITY;
+      for (bool look = c == 0 || masked;; look = true) {
+        if (!AHEAD) bias.get(p, w, c, lane, cz);
+        s = cz;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) s[v] = 0.f;
+        for (int ks = 0; ks < 2; ++ks) s = mfma(lds_nat<WLD>(L.t0, 32 * c + r, ks, hl), qf[ks], s);
+        if (AHEAD) bias.get(p, w, c + 1 < NB ? c + 1 : 0, lane, cz);
+        if (masked) mask_regions(s, L.rid, my_rid, 32 * c, hl);
+        if (look) {
+          float rmax = s[0];
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) s = mfma(lds_nat<WLD>(L.t0, 32 * c + r, ks, hl), qf[ks], s);
-      bias_and_mask(s, bz[c], p.scale, masked, L.rid, my_rid, 32 * c, hl);
-      float rmax = s[0];
+          for (int v = 1; v < 16; ++v) rmax = fmaxf(rmax, s[v]);
+          rmax = half_max(rmax * c1);
+          const float mn = half_max(sum) > 256.f ? fmaxf(-nm, rmax) : -nm, alpha = fast_exp2(-nm - mn);
+          nm = -mn;
+          l *= alpha;
 #pragma unroll
-      for (int v = 1; v < 16; ++v) rmax = fmaxf(rmax, s[v]);
-      rmax = half_max(rmax * LOG2E);
-      if (__builtin_amdgcn_ballot_w64(rmax > m + 8.f) != 0) {  // raised only when exceeded by 2^8
-        const float mn = fmaxf(m, rmax);
-        const float alpha = fast_exp2(m - mn);
-        m = mn;
-        l *= alpha;
+          for (int v = 0; v < 16; ++v) oacc[0][v] *= alpha;
+        }
+        float x[16];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) oacc[v] *= alpha;
+        for (int v = 0; v < 16; ++v) x[v] = s[v] = fast_exp2(fmaf(s[v], c1, nm));
+        sum = sum16(x);
+        if (look || __builtin_amdgcn_ballot_w64(sum > 256.f) == 0) break;
+        if (AHEAD) bias.get(p, w, c, lane, cz);
       }
-      float pr[16];
+      l += sum;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        pr[v] = fast_exp2(fmaf(s[v], LOG2E, -m));
-        l += pr[v];
+      for (int j = 0; j < 2; ++j) {
+        float x[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[e] = s[8 * j + e];
+        oacc[0] = mfma(lds_tr<WLD>(L.t1, 32 * c + 16 * j, 0, lane), pack8(x), oacc[0]);
       }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) oacc = mfma(lds_tr<WLD>(L.t1, 32 * c + 16 * j, 0, lane), pack8(&pr[8 * j]), oacc);
     }
-    oacc1[0] = oacc;
-    fwd_epilogue<1, false>(p, oacc1, m, l, b, h, q, hl, base);
+    fwd_epilogue<1, false>(p, oacc, -nm, l, b, h, q, hl, base);
   }
 }
 
 // ---------------------------------------------------------------------------
-// recompute pass and dQ in one walk over the keys (the two-product form of fast_rdq.hip): statistics,
-// Delta, dG, the pre-gated dO and dQ; lane = query
+// recompute pass and dQ in one walk over the keys (the two-product form of fast_rdq.hip): statistics, Delta, dQ; lane =
+// query.  GATED: dG and the pre-gated dO too, for which O is summed up; without a gate nobody needs O, and Delta is
+// sum_j p (dP - c) / sum_j p + c with both sums in fp32.
 // ---------------------------------------------------------------------------
-template <int NB, bool REGION>
-__global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(3, 3))) void win_rdq_kernel(KP p, int rows_per_wg) {
+template <int NB, bool REGION, int WB, bool GATED>
+__global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(GATED || WB == WB_REGS ? 3 : 4, GATED || WB == WB_REGS ? 3 : 4))) void win_rdq_kernel(KP p) {
+#pragma clang fp contract(off)  // the variants are to give the same bits
   __shared__ __attribute__((aligned(16))) WinLds<NB> L;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 31, hl = lane >> 5;
-  const int h = p.h0 + blockIdx.y, q = 32 * w + r, qc = min(q, p.S - 1);
-  const int bfirst = p.b0 + blockIdx.x * rows_per_wg, blast = min(bfirst + rows_per_wg, p.b1);
-  RowStage<NB> next;
-  bf16x8 qn[2];
-  u32x4 dyn[2];
-  auto fetch = [&](int b) {
-    const int64_t base = (int64_t)b * p.sb + (int64_t)h * p.sh;
-    next.load((const uint16_t*)p.K + base, p.ss, (const uint16_t*)p.V + base, p.ss, p.S, tid);
-  };
-  auto fetch_q = [&](int b) {
-    const int64_t at = (int64_t)b * p.sb + (int64_t)h * p.sh + (int64_t)qc * p.ss + 8 * hl;
+  constexpr int BLOCK_UNROLL = WB == WB_REGS ? NB : 1;
+  const BlockId blk = xcd_block_id();
+  const int h = p.h0 + blk.x, b = p.b0 + blk.z, q = 32 * w + r, qc = min(q, p.S - 1);
+  const int64_t base = (int64_t)b * p.sb + (int64_t)h * p.sh;
+  RowStage<NB> row;
+  row.load((const uint16_t*)p.K + base, p.ss, (const uint16_t*)p.V + base, p.ss, p.S, tid);
+  bf16x8 qf[2], gf[2];
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      qn[ks] = *(const bf16x8*)((const uint16_t*)p.Q + at + 16 * ks);
-      dyn[ks] = *(const u32x4*)((const uint16_t*)p.dY + at + 16 * ks);
+  for (int ks = 0; ks < 2; ++ks) {
+    const int64_t at = base + (int64_t)qc * p.ss + 16 * ks + 8 * hl;
+    qf[ks] = *(const bf16x8*)((const uint16_t*)p.Q + at);
+    union { u32x4 u; uint32_t w[4]; bf16x8 v; } o;
+    o.u = *(const u32x4*)((const uint16_t*)p.dY + at);
+    if (GATED) {  // dO = dY * gate, rounded as the epilogue rounds the copy that the later kernel reads
+      const u32x4 gg = *(const u32x4*)((const uint16_t*)p.G + at);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float g0 = __uint_as_float(gg[e] << 16), g1 = __uint_as_float(gg[e] & 0xffff0000u);
+        o.w[e] = pack2_bf16(__uint_as_float(o.w[e] << 16) * fast_rcp(1.f + fast_exp2(-g0 * LOG2E)),
+                            __uint_as_float(o.w[e] & 0xffff0000u) * fast_rcp(1.f + fast_exp2(-g1 * LOG2E)));
+      }
     }
-  };
-  fetch(bfirst);
-  fetch_q(bfirst);
-  table_setup(p, h, L, tid);
+    gf[ks] = o.v;
+  }
+  if (WB == WB_REGS) {
+    table_setup(p, h, L, tid);
+    __syncthreads();
+  }
+  WinBias<NB, WB, false> bias;
+  bias.init(p, L, h, w, lane);
+  f32x16 cz;  // of the block, then of the next one
+  if (WB == WB_COPY) bias.get(p, w, 0, lane, cz);
+  bool masked = false;
+  int my_rid = 0;
+  if (REGION) {
+    const int* ids = p.region + (int64_t)(b % p.mask_period) * p.S;
+    masked = row_is_masked<NB>(ids, p.S, lane);
+    my_rid = ids[qc];
+    if (tid < 32 * NB) L.rid[tid] = ids[min(tid, p.S - 1)];
+  }
+  row.store(L, tid);
   __syncthreads();
-  uint32_t bz[NB][8];
-  gather_bias<NB, true>(p, L.table, L.cidx, h, q, hl, false, bz);
   union { uint32_t u; bf16x2 v; } one_pair;
   one_pair.u = 0x3f803f80u;
   const bf16x2 ones2 = one_pair.v;
-  for (int b = bfirst; b < blast; ++b) {
-    const int64_t base = (int64_t)b * p.sb + (int64_t)h * p.sh;
-    const bf16x8 qf[2] = {qn[0], qn[1]};
-    bf16x8 gf[2];
+  f32x16 oacc[1], a1, a2;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) { oacc[0][v] = 0.f; a1[v] = 0.f; a2[v] = 0.f; }
+  float nm = 1e30f, lsum = 0.f, dsum = 0.f, l32 = 0.f, d32 = 0.f;
+  DpShift shift;
+  const float c1 = in_vgpr(p.scale * LOG2E);
+#pragma unroll BLOCK_UNROLL
+  for (int c = 0; c < NB; ++c) {
+    f32x16 s, pa;
+    if (WB != WB_COPY) bias.get(p, w, c, lane, cz);
+    s = cz;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) pa[v] = 0.f;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
-      union { u32x4 u; uint16_t s[8]; bf16x8 v; } o;
-      o.u = dyn[ks];
-      if (p.gated) {  // dO = dY * gate, rounded as the epilogue rounds the copy that the later kernel reads
-        const u32x4 gg = *(const u32x4*)((const uint16_t*)p.G + base + (int64_t)qc * p.ss + 16 * ks + 8 * hl);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float go = (e & 1) ? __uint_as_float(dyn[ks][e >> 1] & 0xffff0000u) : __uint_as_float(dyn[ks][e >> 1] << 16);
-          const float gl = (e & 1) ? __uint_as_float(gg[e >> 1] & 0xffff0000u) : __uint_as_float(gg[e >> 1] << 16);
-          o.s[e] = f2bf(go * fast_rcp(1.f + fast_exp2(-gl * LOG2E)));
-        }
-      }
-      gf[ks] = o.v;
+      s = mfma(lds_nat<WLD>(L.t0, 32 * c + r, ks, hl), qf[ks], s);
+      pa = mfma(lds_nat<WLD>(L.t1, 32 * c + r, ks, hl), gf[ks], pa);
     }
-    __syncthreads();
-    next.store(L, tid);
-    bool masked = false;
-    int my_rid = 0;
-    if (REGION) {
-      const int* ids = p.region + (int64_t)(b % p.mask_period) * p.S;
-      masked = row_is_masked<NB>(ids, p.S, lane);
-      my_rid = ids[qc];
-      if (tid < 32 * NB) L.rid[tid] = ids[min(tid, p.S - 1)];
+    if (WB == WB_COPY) bias.get(p, w, min(c + 1, NB - 1), lane, cz);
+    if (REGION && masked) mask_regions(s, L.rid, my_rid, 32 * c, hl);
+    float rmax = s[0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) rmax = fmaxf(rmax, s[v]);
+    rmax = half_max(rmax * c1);
+    if (__builtin_amdgcn_ballot_w64(rmax + nm > 8.f) != 0) {  // raised only when exceeded by 2^8
+      const float mn = fmaxf(-nm, rmax), alpha = fast_exp2(-nm - mn);
+      nm = -mn;
+      shift.rescaled(alpha);
+      lsum *= alpha;
+      dsum *= alpha;
+      l32 *= alpha;
+      d32 *= alpha;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) { oacc[0][v] *= alpha; a1[v] *= alpha; a2[v] *= alpha; }
     }
-    __syncthreads();
-    if (b + 1 < blast) fetch(b + 1);
-    f32x16 oacc[1], a1, a2;
+    float pr[16], dp[16];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) { oacc[0][v] = 0.f; a1[v] = 0.f; a2[v] = 0.f; }
-    float m = -1e30f, lsum = 0.f, dsum = 0.f, l32 = 0.f;
-    DpShift shift;
+    for (int v = 0; v < 16; ++v) pr[v] = fast_exp2(fmaf(s[v], c1, nm));
+    l32 += sum16(pr);
+    shift.choose(pr, pa);
 #pragma unroll
-    for (int c = 0; c < NB; ++c) {
-      block_boundary(bz[c]);
-      f32x16 s, pa;
+    for (int v = 0; v < 16; ++v) dp[v] = pr[v] * (pa[v] - shift.c);
+    if (!GATED) d32 += sum16(dp);
 #pragma unroll
-      for (int v = 0; v < 16; ++v) { s[v] = 0.f; pa[v] = 0.f; }
+    for (int j = 0; j < 2; ++j) {
+      union { bf16x8 v; bf16x2 h[4]; } pf, df;
+      pf.v = pack8(&pr[8 * j]);
+      df.v = pack8(&dp[8 * j]);
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        s = mfma(lds_nat<WLD>(L.t0, 32 * c + r, ks, hl), qf[ks], s);
-        pa = mfma(lds_nat<WLD>(L.t1, 32 * c + r, ks, hl), gf[ks], pa);
+      for (int e = 0; e < 4; ++e) {  // the sums run over the rounded operands
+        lsum = __builtin_amdgcn_fdot2_f32_bf16(pf.h[e], ones2, lsum, false);
+        dsum = __builtin_amdgcn_fdot2_f32_bf16(df.h[e], ones2, dsum, false);
       }
-      bias_and_mask(s, bz[c], p.scale, masked, L.rid, my_rid, 32 * c, hl);
-      float rmax = s[0];
-#pragma unroll
-      for (int v = 1; v < 16; ++v) rmax = fmaxf(rmax, s[v]);
-      rmax = half_max(rmax * LOG2E);
-      if (__builtin_amdgcn_ballot_w64(rmax > m + 8.f) != 0) {
-        const float mn = fmaxf(m, rmax);
-        const float alpha = fast_exp2(m - mn);
-        m = mn;
-        shift.rescaled(alpha);
-        lsum *= alpha;
-        dsum *= alpha;
-        l32 *= alpha;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) { oacc[0][v] *= alpha; a1[v] *= alpha; a2[v] *= alpha; }
-      }
-      float pr[16], dp[16];
-#pragma unroll
-      for (int v = 0; v < 16; ++v) pr[v] = fast_exp2(fmaf(s[v], LOG2E, -m));
-      if (p.lse_out) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) l32 += pr[v];
-      }
-      shift.choose(pr, pa);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) dp[v] = pr[v] * (pa[v] - shift.c);
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        union { bf16x8 v; bf16x2 h[4]; } pf, df;
-        pf.v = pack8(&pr[8 * j]);
-        df.v = pack8(&dp[8 * j]);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {  // the sums run over the rounded operands
-          lsum = __builtin_amdgcn_fdot2_f32_bf16(pf.h[e], ones2, lsum, false);
-          dsum = __builtin_amdgcn_fdot2_f32_bf16(df.h[e], ones2, dsum, false);
-        }
-        const bf16x8 vt = lds_tr<WLD>(L.t1, 32 * c + 16 * j, 0, lane), kt = lds_tr<WLD>(L.t0, 32 * c + 16 * j, 0, lane);
-        oacc[0] = mfma(vt, pf.v, oacc[0]);
-        a2 = mfma(kt, pf.v, a2);
-        a1 = mfma(kt, df.v, a1);
-      }
+      const bf16x8 kt = lds_tr<WLD>(L.t0, 32 * c + 16 * j, 0, lane);
+      if (GATED) oacc[0] = mfma(lds_tr<WLD>(L.t1, 32 * c + 16 * j, 0, lane), pf.v, oacc[0]);
+      a2 = mfma(kt, pf.v, a2);
+      a1 = mfma(kt, df.v, a1);
     }
-    if (b + 1 < blast) fetch_q(b + 1);
-    if (q < p.S) {
-      const float l = half_sum(lsum), inv = 1.f / l, dmean = half_sum(dsum) * inv;
-      uint2 o[4];
+  }
+  if (q >= p.S) return;
+  const float l = half_sum(lsum), inv = 1.f / l, dmean = half_sum(dsum) * inv, lf = half_sum(l32);
+  uint2 o[4];
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
-        o[g] = pack4_bf16(fmaf(-dmean, a2[4 * g], a1[4 * g]), fmaf(-dmean, a2[4 * g + 1], a1[4 * g + 1]),
-                          fmaf(-dmean, a2[4 * g + 2], a1[4 * g + 2]), fmaf(-dmean, a2[4 * g + 3], a1[4 * g + 3]), p.scale * inv);
-      store_row32((uint16_t*)p.dQ + base + (int64_t)q * p.ss, o, hl, true);
-      fwd_epilogue_rowsum<1, true>(p, oacc, m, l, half_sum(l32), b, h, q, hl, base);
+  for (int g = 0; g < 4; ++g)
+    o[g] = pack4_bf16(fmaf(-dmean, a2[4 * g], a1[4 * g]), fmaf(-dmean, a2[4 * g + 1], a1[4 * g + 1]),
+                      fmaf(-dmean, a2[4 * g + 2], a1[4 * g + 2]), fmaf(-dmean, a2[4 * g + 3], a1[4 * g + 3]), p.scale * inv);
+  store_row32((uint16_t*)p.dQ + base + (int64_t)q * p.ss, o, hl, true);
+  if (GATED) {
+    fwd_epilogue_rowsum<1, true>(p, oacc, -nm, l, lf, b, h, q, hl, base);
+  } else {
+    const float delta = half_sum(d32) / lf + shift.c;
+    if (hl == 0) {
+      p.delta[(int64_t)(b - p.dl_b0) * p.dl_sb + (int64_t)(h - p.dl_h0) * p.dl_sh + q] = delta;
+      if (p.lse_out) p.lse_out[(int64_t)(b - p.lse_b0) * p.lse_sb + (int64_t)(h - p.lse_h0) * p.lse_sh + q] = (log2f(lf) - nm) * LN2;
     }
   }
 }
@@ -357,17 +402,28 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(3, 3)))
 // ---------------------------------------------------------------------------
 // dK, dV and the bias gradient in one walk over the queries; lane = key.  A work-group takes one group
 // of p.sm_gw consecutive global rows (or the chunk's part of it); dS is added in registers, row after
-// row, and stored as the group's partial sum, resumed when a chunk boundary cuts the group.
+// row, and stored as the group's partial sum, resumed when a chunk boundary cuts the group.  The next row's
+// operands travel global -> registers meanwhile.
 // ---------------------------------------------------------------------------
-template <int NB, bool REGION>
+template <int NB, bool REGION, int WB>
 __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(2, 2))) void win_kv_kernel(KP p) {
+#pragma clang fp contract(off)  // the variants are to give the same bits
   __shared__ __attribute__((aligned(16))) WinLds<NB> L;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 31, hl = lane >> 5;
-  const int h = p.h0 + blockIdx.y, key = 32 * w + r, kc = min(key, p.S - 1);
-  const int g = p.b0 / p.sm_gw + blockIdx.x;  // global group
+  const int h = p.h0 + blockIdx.x, key = 32 * w + r, kc = min(key, p.S - 1);
+  const int g = p.b0 / p.sm_gw + blockIdx.y;  // global group
   const int bfirst = max(g * p.sm_gw, p.b0), blast = min((g + 1) * p.sm_gw, p.b1);
   RowStage<NB> next;
   float stat = 0.f;
+  bf16x8 kf[2], vf[2];
+  auto fetch_kv = [&](int b) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const int64_t at = (int64_t)b * p.sb + (int64_t)h * p.sh + (int64_t)kc * p.ss + 16 * ks + 8 * hl;
+      kf[ks] = *(const bf16x8*)((const uint16_t*)p.K + at);
+      vf[ks] = *(const bf16x8*)((const uint16_t*)p.V + at);
+    }
+  };
   auto fetch = [&](int b) {
     const int64_t base = (int64_t)b * p.sb + (int64_t)h * p.sh;
     next.load((const uint16_t*)p.Q + base, p.ss,
@@ -378,10 +434,23 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(2, 2)))
                          : p.delta[(int64_t)(b - p.dl_b0) * p.dl_sb + (int64_t)(h - p.dl_h0) * p.dl_sh + i];
   };
   fetch(bfirst);
-  table_setup(p, h, L, tid);
-  __syncthreads();
-  uint32_t bz[NB][8];
-  gather_bias<NB, false>(p, L.table, L.cidx, h, key, hl, key >= p.S, bz);
+  fetch_kv(bfirst);
+  // which of the rows (at most 32 at a time) the region mask cuts: one look ahead, not a wait per row
+  uint32_t cut = 0;
+  auto look_ahead = [&](int b) {
+    cut = 0;
+    for (int i = 0; i < 32 && b + i < blast; ++i)
+      cut |= (uint32_t)row_is_masked<NB>(p.region + (int64_t)((b + i) % p.mask_period) * p.S, p.S, lane) << i;
+  };
+  if (WB == WB_REGS) {
+    table_setup(p, h, L, tid);
+    __syncthreads();
+  }
+  WinBias<NB, WB, true> bias;
+  bias.init(p, L, h, w, lane);
+  f32x16 cz;  // of the next block
+  if (WB == WB_COPY) bias.get(p, w, 0, lane, cz);
+  const float c1 = in_vgpr(p.scale * LOG2E);
   float acc[NB][16];
   float* part = nullptr;
   if (p.sm_partial) {
@@ -391,29 +460,21 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(2, 2)))
     for (int c = 0; c < NB; ++c)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        if ((v & 7) == 0) block_boundary(bz[c]);
         const int i = 32 * c + key_of(v, hl);
         acc[c][v] = resume && i < p.S && key < p.S ? part[i * p.S + key] : 0.f;
       }
   }
   for (int b = bfirst; b < blast; ++b) {
     const int64_t base = (int64_t)b * p.sb + (int64_t)h * p.sh;
-    bf16x8 kf[2], vf[2];
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const int64_t at = base + (int64_t)kc * p.ss + 16 * ks + 8 * hl;
-      kf[ks] = *(const bf16x8*)((const uint16_t*)p.K + at);
-      vf[ks] = *(const bf16x8*)((const uint16_t*)p.V + at);
-    }
+    if (REGION && ((b - bfirst) & 31) == 0) look_ahead(b);
+    const bool masked = REGION && ((cut >> ((b - bfirst) & 31)) & 1);
     __syncthreads();
     next.store(L, tid);
     if (tid < 32 * NB) L.lse2[tid] = -stat * LOG2E;  // negated: one fused multiply-add per score
     else L.delta[tid - 32 * NB] = stat;
-    bool masked = false;
     int my_rid = 0;
-    if (REGION) {
+    if (masked) {
       const int* ids = p.region + (int64_t)(b % p.mask_period) * p.S;
-      masked = row_is_masked<NB>(ids, p.S, lane);
       my_rid = ids[kc];
       if (tid < 32 * NB) L.rid[tid] = ids[min(tid, p.S - 1)];
     }
@@ -424,15 +485,20 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(2, 2)))
     for (int v = 0; v < 16; ++v) { dk[v] = 0.f; dv[v] = 0.f; }
 #pragma unroll
     for (int c = 0; c < NB; ++c) {
-      block_boundary(bz[c]);
+      // the blocks are unrolled (the gradient sums are registers) but meant to run one after the other
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
       f32x16 s, pa;
+      if (WB != WB_COPY) bias.get(p, w, c, lane, cz);
+      s = cz;
 #pragma unroll
-      for (int v = 0; v < 16; ++v) { s[v] = 0.f; pa[v] = 0.f; }
+      for (int v = 0; v < 16; ++v) pa[v] = 0.f;
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         s = mfma(lds_nat<WLD>(L.t0, 32 * c + r, ks, hl), kf[ks], s);
         pa = mfma(lds_nat<WLD>(L.t1, 32 * c + r, ks, hl), vf[ks], pa);
       }
+      if (WB == WB_COPY) bias.get(p, w, c + 1 < NB ? c + 1 : 0, lane, cz);
       // exponents and dP - Delta; masked pairs get -inf and 0 here, after the statistics went in, so that they contribute
       // nothing also where a query has NaN statistics
 #pragma unroll
@@ -442,11 +508,11 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(2, 2)))
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const int v = 4 * gq + e;
-          s[v] = fmaf(fmaf(s[v], p.scale, bias_of(bz[c], v)), LOG2E, l4[e]);
+          s[v] = fmaf(s[v], c1, l4[e]);
           pa[v] -= d4[e];
         }
       }
-      if (REGION && masked) {
+      if (masked) {
 #pragma unroll
         for (int gq = 0; gq < 4; ++gq) {
           const int4 rk = *(const int4*)(L.rid + 32 * c + 8 * gq + 4 * hl);
@@ -474,6 +540,7 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(2, 2)))
         dk = mfma(lds_tr<WLD>(L.t0, 32 * c + 16 * j, 0, lane), pack8(&ds[8 * j]), dk);
       }
     }
+    if (b + 1 < blast) fetch_kv(b + 1);  // under the epilogue: before, there are no registers for them
     if (key < p.S) {
       uint2 a[4], c[4];
 #pragma unroll
@@ -492,26 +559,22 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(2, 2)))
     for (int c = 0; c < NB; ++c)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        if ((v & 7) == 0) block_boundary(bz[c]);
         const int i = 32 * c + key_of(v, hl);
         if (i < p.S) part[i * p.S + at] = acc[c][v];
       }
   }
 }
 
-// Rows per work-group of the kernels that may choose freely (a row's results do not depend on it): the
-// bias gather costs about half a row, so as many rows as still leave `per_cu` work-groups per
-// compute unit, at most 8.
-inline int rows_per_wg(const KP& p, int per_cu) {
-  const int64_t units = (int64_t)(p.b1 - p.b0) * (p.h1 - p.h0), r = units / (256 * per_cu);
-  return (int)(r < 1 ? 1 : r > 8 ? 8 : r);
-}
-
 template <class F>
-hipError_t with_shape(const KP& p, F f) {
+hipError_t with_shape(const KP& p, bool copy, F f) {
   auto mask = [&](auto nb) {
-    if (p.mask_kind == 2) f(nb, std::true_type{});
-    else f(nb, std::false_type{});
+    auto source = [&](auto region) {
+      if (p.bias_kind == 0) f(nb, region, std::integral_constant<int, WB_NONE>{});
+      else if (copy) f(nb, region, std::integral_constant<int, WB_COPY>{});
+      else f(nb, region, std::integral_constant<int, WB_REGS>{});
+    };
+    if (p.mask_kind == 2) source(std::true_type{});
+    else source(std::false_type{});
   };
   if (p.S <= 96) mask(std::integral_constant<int, 3>{});
   else if (p.S <= 128) mask(std::integral_constant<int, 4>{});
@@ -522,14 +585,18 @@ hipError_t with_shape(const KP& p, F f) {
 }  // namespace
 
 hipError_t launch_win_fwd(const KP& p, hipStream_t st) {
-  const int rows = rows_per_wg(p, 3);
-  const dim3 g((p.b1 - p.b0 + rows - 1) / rows, p.h1 - p.h0);
-  return with_shape(p, [&](auto nb, auto region) { win_fwd_kernel<nb(), region()><<<g, 64 * nb(), 0, st>>>(p, rows); });
+  // rows enough for a compute unit's work-groups, three of five wavefronts, to go through twice; at most 8
+  const int64_t rounds = (int64_t)(p.b1 - p.b0) * (p.h1 - p.h0) / (2 * 256 * 3);
+  const int rows = p.bias_q ? 1 : (int)(rounds < 1 ? 1 : rounds > 8 ? 8 : rounds);
+  const dim3 g(p.h1 - p.h0, 1, (p.b1 - p.b0 + rows - 1) / rows);
+  return with_shape(p, p.bias_q != nullptr, [&](auto nb, auto region, auto wb) { win_fwd_kernel<nb(), region(), wb()><<<g, 64 * nb(), 0, st>>>(p, rows); });
 }
 hipError_t launch_win_recompute_dq(const KP& p, hipStream_t st) {
-  const int rows = rows_per_wg(p, 2);
-  const dim3 g((p.b1 - p.b0 + rows - 1) / rows, p.h1 - p.h0);
-  return with_shape(p, [&](auto nb, auto region) { win_rdq_kernel<nb(), region()><<<g, 64 * nb(), 0, st>>>(p, rows); });
+  const dim3 g(p.h1 - p.h0, 1, p.b1 - p.b0);
+  return with_shape(p, p.bias_q != nullptr, [&](auto nb, auto region, auto wb) {
+    if (p.gated) win_rdq_kernel<nb(), region(), wb(), true><<<g, 64 * nb(), 0, st>>>(p);
+    else win_rdq_kernel<nb(), region(), wb(), false><<<g, 64 * nb(), 0, st>>>(p);
+  });
 }
 hipError_t launch_win_kv(const KP& args, hipStream_t st) {
   KP p = args;
@@ -538,8 +605,8 @@ hipError_t launch_win_kv(const KP& args, hipStream_t st) {
     p.sm_gw = p.B;
     p.sm_g0 = 0; p.sm_ring = 1; p.sm_hs = p.H; p.sm_h0 = 0;
   }
-  const dim3 g((p.b1 - 1) / p.sm_gw - p.b0 / p.sm_gw + 1, p.h1 - p.h0);
-  return with_shape(p, [&](auto nb, auto region) { win_kv_kernel<nb(), region()><<<g, 64 * nb(), 0, st>>>(p); });
+  const dim3 g(p.h1 - p.h0, (p.b1 - 1) / p.sm_gw - p.b0 / p.sm_gw + 1);
+  return with_shape(p, p.bias_k != nullptr, [&](auto nb, auto region, auto wb) { win_kv_kernel<nb(), region(), wb()><<<g, 64 * nb(), 0, st>>>(p); });
 }
 
 }  // namespace ssa

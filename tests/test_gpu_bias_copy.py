@@ -1,6 +1,6 @@
-"""Pair attention with and without the library's copies of the bias in accumulator layout: shares large enough for a copy
-give the same bits in a captured graph, which does without it (and, in the forward, takes one row per wavefront
-instead of two).  And the row maximum that is raised only when a block's sum of probabilities asks for it."""
+"""Pair attention and windows with and without the library's copies of the bias in accumulator layout: shares large enough
+for a copy give the same bits in a captured graph, which does without it (the forward of pair attention then takes one row
+per wavefront instead of two, windows hold the bias in registers).  And the row maximum that is raised only when a block's sum of probabilities asks for it."""
 import numpy as np
 import pytest
 
@@ -14,9 +14,16 @@ def _cfg(B, H, S, **kw):
     return dict(dict(seed=870 + S, B=B, H=H, S=S, D=32, dtype="bf16", bias="dense", mask=None, gated=True, axis="row"), **kw)
 
 
+def _win(B, H, win, **kw):
+    return _cfg(B, H, win[0] * win[1], **dict(dict(bias="relpos", win=win, gated=False), **kw))
+
+
 # an odd number of rows; lengths that end right after a 64-key tile, after a 32-key block, and one entry short of it
 @pytest.mark.parametrize("cfg,k", [(_cfg(901, 8, 193), 3), (_cfg(301, 6, 416, layout="sbhd"), 2), (_cfg(301, 6, 415, gated=False), 1),
-                                   (_cfg(401, 5, 384, axis="head", lo=1), 2)], ids=["193", "416_sbhd", "415", "384_heads"])
+                                   (_cfg(401, 5, 384, axis="head", lo=1), 2), (_win(70, 8, (12, 12), mask="region"), 2),
+                                   (_win(130, 4, (10, 16), gated=True), 1), (_win(100, 6, (9, 9), mask="region"), 3),
+                                   (_win(90, 6, (11, 11), bias="dense", mask="region"), 2)],
+                         ids=["193", "416_sbhd", "415", "384_heads", "12x12", "10x16_gated", "9x9", "11x11_dense"])
 def test_copies_give_the_same_bits(cfg, k):
     import torch
     cfg = dict(cfg)
