@@ -100,6 +100,23 @@ __device__ inline float sum16(const float (&x)[16]) {
   for (int v = 4; v < 16; ++v) s[v & 3] += x[v];
   return (s[0] + s[1]) + (s[2] + s[3]);
 }
+// A value as the sum of three bf16 (exact: 24 bits), packed for contraction indexes 0 to 2 of a matrix instruction: with
+// `three_ones` as the other operand it adds the value to a whole row or column of an accumulator block, which costs one
+// matrix instruction instead of sixteen subtractions where the vector instructions are the scarcer ones.
+__device__ inline uint2 split3(float x) {
+  const float hi = (float)(__bf16)x, r = x - hi, mid = (float)(__bf16)r;
+  return uint2{pack2_bf16(hi, mid), pack2_bf16(r - mid, 0.f)};
+}
+__device__ inline bf16x8 split3_operand(uint2 s) {
+  union { u32x4 u; bf16x8 v; } o;
+  o.u = u32x4{s.x, s.y, 0, 0};
+  return o.v;
+}
+__device__ inline bf16x8 three_ones(int hl) {  // zeros for the half-wave of indexes 8 to 15
+  union { u32x4 u; bf16x8 v; } o;
+  o.u = u32x4{hl ? 0u : 0x3f803f80u, hl ? 0u : 0x3f80u, 0, 0};
+  return o.v;
+}
 __device__ inline f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
@@ -562,6 +579,11 @@ inline WgShape wg_shape(const KP& p) {
   return WG_2x4;
 }
 
+// The forward of the smallest shape at head size 128, causal: two query blocks per work-group of eight wavefronts where
+// that leaves blocks enough for more than one per compute unit (12 heads x 2048, 384 of them: 27.5 -> 23.9 us; 8 x 3000, 376:
+// 33.6 -> 30.3; 3 x 8000, 375: 77.6 -> 72.2; 16 x 1024, 256: 12.2 -> 13.9; 4 x 4096, 256: 29.2 -> 37.6).  Without a mask all
+// blocks are as long as the longest and the work-groups of four do better (10 x 2000: 37.0 -> 41.7).
+inline bool wave_pairs(const KP& p) { return p.mask_kind == 1 && (int64_t)((p.S + 31) / 32) * p.share_units >= 704; }
 // the forward of pair_fwd.hip: head size 32 with a dense bias, no causal mask, the large-share shape, 32-bit offsets
 inline bool pair_fwd_ok(const KP& p) {
   return fast_ok(p) && p.D == 32 && p.bias_kind == 1 && p.mask_kind == 0 && wg_shape(p) == WG_4x1 &&

@@ -59,6 +59,22 @@ __device__ __forceinline__ void w_fetch(char* tile, const void* slice, uint32_t 
   for (int t = 0; t < 8; ++t)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (w_lds_void*)(tile + t * 1024), 16, goff[t], 0, 0, 0);
 }
+// One half of it (instructions 4 half .. 4 half + 3): two wavefronts that share a tile fetch it together.
+__device__ __forceinline__ void w_fetch_half(char* tile, const void* slice, uint32_t boff, uint32_t slice_bytes,
+                                             const uint32_t (&goff)[4], int half) {
+  const __amdgpu_buffer_rsrc_t rs =
+      __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)slice + boff), 0, (int)(slice_bytes - boff), 0x00020000);
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (w_lds_void*)(tile + (4 * half + t) * 1024), 16, goff[t], 0, 0, 0);
+}
+__device__ __forceinline__ void w_lane_offsets_half(uint32_t (&goff)[4], uint32_t ss2, int lane, int half) {
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int rho = 16 * half + 4 * t + (lane >> 4);
+    goff[t] = (uint32_t)rho * ss2 + 16u * (uint32_t)((lane & 15) ^ w_sw(rho));
+  }
+}
 // LDS addresses of the operand fragments ks = 0..7 of the tile at `tile0`: row r, chunk 2 ks + hl
 __device__ __forceinline__ void w_nat_addr(uint32_t (&ka)[8], const char* tile0, int r, int hl) {
   const uint32_t a0 = (uint32_t)(size_t)(w_lds_void*)tile0 + (uint32_t)r * 256u + (uint32_t)((hl ^ w_sw(r)) << 4);
