@@ -261,13 +261,14 @@ __global__ __launch_bounds__(64 * W_NG) __attribute__((amdgpu_waves_per_eu(2, 2)
   w_merge_out<RECOMP>(p, oacc, m, l, smem, grp, lane, b, h, q, base);
 }
 
-// The same for two query blocks at a time (no bias): eight wavefronts, w and w + 4 work on the same key sub-tiles for two
+// The same for two query blocks at a time (causal, no bias): eight wavefronts, w and w + 4 work on the same key sub-tiles for two
 // neighbouring blocks of 32 queries and fetch them together, so a sub-tile serves 64 queries.  What bounds the kernel above
 // on a filled chip is the fetching: 16 KB for 32 x 32 scores, 14.6 TB/s over the chip for 12 heads x 2048 (a timing build with half
 // of the loads: 29.7 -> 21.6 us).  K and V tiles have two buffers each; one barrier per step says that the tiles of the step
 // have landed for both and that the buffers that the loads issued after it fill are free.  The order of every sum is that of
-// the kernel above: the same bits.
-template <bool CAUSAL, bool RECOMP>
+// the kernel above: the same bits.  (Two groups and two work-groups per compute unit, as the backward has them: 12 x 2048
+// 25.8 us instead of 23.9, 3 x 8000 84 instead of 72.)
+template <bool RECOMP>
 __global__ __launch_bounds__(128 * W_NG) __attribute__((amdgpu_waves_per_eu(2, 2))) void fwd_pair128_kernel(KP p) {
   constexpr int D = 128, KS = D / 16, DB = D / 32, SUB = 32, NG = W_NG;
   constexpr int TILE_B = W_TILE_B, SLOT_B = 4 * TILE_B;  // per key group: K even, K odd, V even, V odd
@@ -277,18 +278,18 @@ __global__ __launch_bounds__(128 * W_NG) __attribute__((amdgpu_waves_per_eu(2, 2
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), grp = w & 3, qs = w >> 2;
   char* sK = smem + grp * SLOT_B;
   char* sV = sK + 2 * TILE_B;
-  const BlockId blk = CAUSAL ? causal_block_id(false) : xcd_block_id();
+  const BlockId blk = causal_block_id(false);
   const int h = p.h0 + blk.y, b = p.b0 + blk.z;
   const int nsub = (p.S + SUB - 1) / SUB, npair = (nsub + 1) / 2;
-  const int pair = CAUSAL ? npair - 1 - blk.x : blk.x;  // late query blocks see the most keys under a causal mask
+  const int pair = npair - 1 - blk.x;  // late query blocks see the most keys under a causal mask
   const int qb = 2 * pair + qs, q0 = qb * SUB, q = q0 + r;
   const int64_t base = (int64_t)b * p.sb + (int64_t)h * p.sh;
   const uint16_t* Kb = (const uint16_t*)p.K + base;
   const uint16_t* Vb = (const uint16_t*)p.V + base;
   const float c1 = in_vgpr(p.scale * LOG2E);
   // key sub-tiles with a visible key: for the later block, and for this wavefront's
-  const int nj = CAUSAL ? min(nsub, 2 * pair + 2) : nsub;
-  const int mine = qb >= nsub ? 0 : CAUSAL ? min(nsub, qb + 1) : nsub;
+  const int nj = min(nsub, 2 * pair + 2);
+  const int mine = qb >= nsub ? 0 : qb + 1;
   const int n = (nj + NG - 1) / NG;  // steps, the same for all wavefronts
 
   uint32_t goff[4], ka[8], va[2][4];
@@ -346,11 +347,11 @@ __global__ __launch_bounds__(128 * W_NG) __attribute__((amdgpu_waves_per_eu(2, 2
     fetch(sV + (1 - ODD) * TILE_B, Vb, j + NG);
     if (j >= mine) return;
     w_nat_issue<(1 - ODD) * TILE_B>(fk, ka);  // after the last sub-tile: not used
-    if ((j * SUB + SUB > p.S) || (CAUSAL && j * SUB + SUB - 1 > q0)) {
+    if ((j * SUB + SUB > p.S) || (j * SUB + SUB - 1 > q0)) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const int key = j * SUB + key_of(v, hl);
-        const bool dead = key >= p.S || (CAUSAL && key > q);
+        const bool dead = key >= p.S || key > q;
         sc[v] = dead ? -INFINITY : sc[v];
       }
     }
@@ -407,8 +408,7 @@ hipError_t fwd_wave128_r(const KP& p, hipStream_t st) {
   const bool bias = p.bias_kind == 1, causal = p.mask_kind == 1;
   if (!bias && wave_pairs(p)) {
     const dim3 g2((g.x + 1) / 2, g.y, g.z);
-    if (causal) fwd_pair128_kernel<true, RECOMP><<<g2, 128 * W_NG, 0, st>>>(p);
-    else fwd_pair128_kernel<false, RECOMP><<<g2, 128 * W_NG, 0, st>>>(p);
+    fwd_pair128_kernel<RECOMP><<<g2, 128 * W_NG, 0, st>>>(p);
     return hipGetLastError();
   }
   if (bias && causal) fwd_wave128_kernel<true, true, RECOMP><<<g, 64 * W_NG, 0, st>>>(p);

@@ -584,6 +584,15 @@ inline WgShape wg_shape(const KP& p) {
 // 33.6 -> 30.3; 3 x 8000, 375: 77.6 -> 72.2; 16 x 1024, 256: 12.2 -> 13.9; 4 x 4096, 256: 29.2 -> 37.6).  Without a mask all
 // blocks are as long as the longest and the work-groups of four do better (10 x 2000: 37.0 -> 41.7).
 inline bool wave_pairs(const KP& p) { return p.mask_kind == 1 && (int64_t)((p.S + 31) / 32) * p.share_units >= 704; }
+// The backward of that shape, two blocks per work-group of four wavefronts (bwd_pair128_kernel), with the work-groups of the
+// whole share.  Causal: from a little over one round of the 512 that the chip holds (384: 28.6 -> 29.5 us; 480: 33.6 -> 32.3
+// and 56.6 -> 60.0; 576: 37.8 -> 34.8; 768: 116 -> 108; 1152: 101.8 -> 84.5, all with the recompute pass).  Without a mask
+// all work-groups are equally long: where the last round is at least half full (240: 16.3 -> 16.8; 384: 40.4 -> 35.6;
+// 480: 49.6 -> 43.9; 564: 484 -> 501; 600: 117.5 -> 127.2; 768: 66.1 -> 64.2; 960: 146 -> 138).
+inline bool wave_bwd_pairs(const KP& p) {
+  const int64_t n = 3 * (int64_t)((p.S + 63) / 64) * p.share_units;
+  return p.mask_kind == 1 ? n >= 544 : (n - 1) % 512 >= 255 && n >= 384;
+}
 // the forward of pair_fwd.hip: head size 32 with a dense bias, no causal mask, the large-share shape, 32-bit offsets
 inline bool pair_fwd_ok(const KP& p) {
   return fast_ok(p) && p.D == 32 && p.bias_kind == 1 && p.mask_kind == 0 && wg_shape(p) == WG_4x1 &&
