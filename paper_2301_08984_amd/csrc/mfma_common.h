@@ -501,7 +501,7 @@ inline bool fast_ok(const KP& p) {
 // region mask (a bf16 bias of either kind, or none; no causal mask), a positive scale
 inline bool win_ok(const KP& p) {
   if (p.D != 32 || p.S <= 64 || p.S > 160 || !(p.scale > 0.f) || p.mask_kind == 1) return false;
-  if (p.bias_kind != 0 && !p.bias_bf16) return false;
+  if (p.bias_kind != 0 && (!p.bias_bf16 || !(p.scale > 1e-9f && p.scale < 1e9f))) return false;  // bias / scale, as in fast_ok
   return p.bias_kind == 2 || p.mask_kind == 2;
 }
 

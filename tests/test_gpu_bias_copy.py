@@ -59,3 +59,18 @@ def test_maxima_that_grow_along_the_keys(S):
     print(f"growing maxima S={S}", flush=True)
     # peaked rows: one probability near 1, its bf16 rounding against V and dP of the one key; the bound of the other tests holds
     check_against_oracle(cfg, inputs=inp)
+
+
+@pytest.mark.parametrize("cfg", [_win(5, 2, (9, 9)), _cfg(3, 2, 130)], ids=["9x9", "130"])
+def test_a_scale_that_the_bias_cannot_be_divided_by(cfg):
+    """The fast kernels start a score from bias / scale, here beyond fp32 for a bias above 4: these calls go elsewhere."""
+    from oracle import attention as orc
+    from parity import AXIS, TOL, assert_close, oracle_problem
+    inp = make_inputs(**cfg)
+    inp["bias"] = round_to_bf16((inp["bias"] * (6 / np.max(np.abs(inp["bias"])))).astype(np.float32))
+    print(f"scale 1.2e-38, {cfg['S']} tokens", flush=True)
+    dc, _ = run_case(cfg, inputs=inp, scale=1.2e-38)
+    Y, _ = orc.attn_forward(oracle_problem(inp, cfg, 1.2e-38), AXIS[cfg["axis"]], 0, cfg["B"])
+    assert_close("Y", dc.host("Y"), Y, TOL["bf16"])
+    for n in ("dQ", "dK", "dV", "dBias"):
+        assert bool(getattr(dc, n).isfinite().all()), n
