@@ -469,9 +469,11 @@ hipError_t dbias_d(const KP& p, hipStream_t st) {
     if (p.sm_partial) ng = (p.b1 - 1) / p.sm_gw - p.b0 / p.sm_gw + 1;
     const int heads = p.h1 - p.h0;
     const int64_t tiles = (int64_t)((p.S + 63) / 64) * ((p.S + 63) / 64);
-    if (D == 32 && heads % 2 == 0 && p.sh == D && p.do_sh == D && tiles * (heads / 2) * ng >= 512) {
-      // neighbouring heads are 64 bytes apart: two per work-group, if that still leaves two
-      // work-groups per compute unit
+    if (D == 32 && heads % 2 == 0 && p.sh == D && p.do_sh == D && tiles * (heads / 2) * ng >= 384) {
+      // neighbouring heads are 64 bytes apart: two per work-group, if that still leaves one and a half work-groups per
+      // compute unit, of the two that fit (one head | two, us: 288 of them, 512 x 4 x 768: 173 | 199 a chunk; 338, 400 x 4 x 832:
+      // 305 | 316; 363, 300 x 6 x 700: 219 | 249; 392, 400 x 4 x 860: 185 | 170; 400, 200 x 8 x 640: 200 | 179; 450,
+      // 901 x 4 x 901: 252 | 183)
       dim3 g((p.S + 63) / 64, (p.S + 63) / 64, heads / 2 * ng);
       if (p.mask_kind == 1) dbias_tile_kernel<D <= 32 ? D : 32, true, 2><<<g, 512, 0, st>>>(p);
       else dbias_tile_kernel<D <= 32 ? D : 32, false, 2><<<g, 512, 0, st>>>(p);
