@@ -20,8 +20,8 @@
  * returns while it may still be running.  What the library holds for itself, from
  * its first use on a GPU until the process ends, is SS_LIBRARY_DEVICE_BYTES of that
  * GPU's memory: the buffer of ss_attn_bwd_static, and a buffer in which calls run
- * several chunks together or hand partial sums over (ss_attn_workspace_bytes,
- * ss_ffn.h), with an event that marks the end of the last call that used it.  It keeps
+ * several chunks together, lay a copy of the bias out or hand partial sums over
+ * (ss_attn_workspace_bytes, ss_ffn.h), with an event that marks the end of the last call that used it.  It keeps
  * no results between calls, and no other state than that, the helper stream of
  * ss_ffn_bwd and the opt-in timing instrumentation at the end of this file.
  */
