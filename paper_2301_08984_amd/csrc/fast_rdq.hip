@@ -11,7 +11,7 @@ namespace {
 // with the same scores, bias additions and exponentials.  dQ needs Delta = sum_j P_ij dP_ij, which
 // is only known after the last key; with the unnormalised probabilities p~ of the online softmax
 //     dQ_i = scale / l * ( sum_j (p~_ij dP_ij) K_j  -  Delta' * sum_j p~_ij K_j ),   l = sum_j p~_ij,
-// so two products are accumulated (A1 with p~ dP, A2 with p~; dP less one constant per query, see DpShift) and
+// so two products are accumulated (A1 with p~ dP, A2 with p~; dP less a constant per query, see DpShift) and
 // combined at the end.  The
 // two terms cancel where a row is peaked (dS -> 0), so Delta' must be the mean the matrix cores
 // actually formed: Delta' = sum_j bf16(p~ dP) / sum_j bf16(p~), both sums over the SAME rounded
@@ -79,9 +79,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
       gf[ks] = o.v;
     }
   }
-  union { uint32_t u; bf16x2 v; } one_pair;
-  one_pair.u = 0x3f803f80u;
-  const bf16x2 ones2 = one_pair.v;
   f32x16 oacc[DB], a1[DB], a2[DB];
   float lsum = 0.f, dsum = 0.f, l32 = 0.f;  // this half-wave's part of l', delta' and the fp32 row sum
   DpShift shift;
@@ -186,26 +183,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
       float pr[16], dp[16];
 #pragma unroll
       for (int v = 0; v < 16; ++v) pr[v] = fast_exp2(fmaf(sa[v], c1, nm));
-      if (p.lse_out) l32 += sum16(pr);
-      shift.choose(pr, pa);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) dp[v] = pr[v] * (pa[v] - shift.c);
       pf[0] = pack8(&pr[0]);
       pf[1] = pack8(&pr[8]);
+      const float before = lsum;  // lsum and dsum run over the rounded operands
+      lsum = sum_rounded(pf[0], lsum) + sum_rounded(pf[1], 0.f);
+      if (shift.is_due(lsum)) {
+        const float d = shift.take(pr, pa, before, lsum, dsum);
+        dsum = fmaf(d, before, dsum);
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) a1[db][v] = fmaf(d, a2[db][v], a1[db][v]);
+      }
+      if (p.lse_out) l32 += sum16(pr);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) dp[v] = pr[v] * (pa[v] - shift.c);
       df[0] = pack8(&dp[0]);
       df[1] = pack8(&dp[8]);
-    }
-    // these sums run over the rounded operands
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      union { bf16x8 v; bf16x2 h[4]; } a, c;
-      a.v = pf[j];
-      c.v = df[j];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        lsum = __builtin_amdgcn_fdot2_f32_bf16(a.h[e], ones2, lsum, false);
-        dsum = __builtin_amdgcn_fdot2_f32_bf16(c.h[e], ones2, dsum, false);
-      }
+      dsum = sum_rounded(df[1], sum_rounded(df[0], dsum));
     }
 #pragma unroll
     for (int j = 0; j < 2; ++j) {

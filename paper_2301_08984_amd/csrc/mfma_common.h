@@ -117,6 +117,16 @@ __device__ inline bf16x8 three_ones(int hl) {  // zeros for the half-wave of ind
   o.u = u32x4{hl ? 0u : 0x3f803f80u, hl ? 0u : 0x3f80u, 0, 0};
   return o.v;
 }
+// continues a sum over packed operands as they were rounded
+__device__ __forceinline__ float sum_rounded(bf16x8 x, float sum) {
+  union { uint32_t u; bf16x2 v; } ones;
+  ones.u = 0x3f803f80u;
+  union { bf16x8 v; bf16x2 h[4]; } o;
+  o.v = x;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) sum = __builtin_amdgcn_fdot2_f32_bf16(o.h[e], ones.v, sum, false);
+  return sum;
+}
 __device__ inline f32x16 mfma(bf16x8 a, bf16x8 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
 }
@@ -352,34 +362,36 @@ __device__ inline BlockId causal_block_id(bool pairs) {
 
 // The two-product form of dQ (fast_rdq.hip, win_kernels.hip) rounds p dP to bf16 before the mean of dP is taken off,
 // so what dP has in common over a query's keys (as activations and gradients with a mean of their own give
-// it) would cost its size times 2^-9.  dS does not change if one constant per query is subtracted from every
-// dP: the mean of dP over the keys that the query sees in the first block of 32 in which it sees any (a masked key
-// has no say), if it is at least twice what chance would make it, else 0 (a mean that is only noise would add to
-// the rounding error).  Relative error of the products' arithmetic, 384 tokens, V and dO offset by 0 / 0.25 / 0.5
-// / 2 standard deviations: 1.68, 1.90, 3.3, 22.3e-3 without, 1.69, 1.72, 1.70, 1.71e-3 with the constant; dS formed
-// directly: 1.73e-3 throughout.
+// it) would cost its size times 2^-9.  dS does not change if a constant per query is subtracted from every dP: the mean
+// of dP so far, weighted with the probabilities, the block at hand included.  It is taken anew on the first block in which a
+// query sees a key and whenever the weight seen has grown fourfold, for all queries of the wavefront as soon as one asks for
+// it, and the sums formed with the old constant are moved to the new one.  The bound: between two changes, a weight w < 3 W
+// of keys whose mean is off by x is rounded at the size of x, and adds at least w W / (W + w) x^2 > w x^2 / 4 to
+// the variance of dP; so the products' rounding is at most twice that of dS formed directly, however the means and the weights
+// of the keys are spread.  Relative error of dQ, 384 tokens, dO offset by 1, the products' arithmetic with no constant | with the
+// unweighted mean of the first 32 keys, kept | with this one | dS formed directly, x 1e-3: no offset in V 1.7 | 1.7 | 1.7 | 1.7; V offset by 2
+// throughout 23 | 1.7 | 1.6 | 1.7; V of the first 32 keys by 4: 2.0 | 8.2 | 3.0 | 1.8, these keys with a bias of -8 too: 1.7 | 40 | 1.6 | 1.8;
+// V and bias rising by 8 and 40 along the keys: 70 | 65 | 1.4 | 1.7.  (Twofold instead of fourfold: 2.1 instead of 3.0, and twice as many
+// changes: six instead of three of 12 blocks of normal scores, seven instead of four of 32.)
 struct DpShift {
-  float c = 0.f;      // of the lane's query
-  bool seen = false;  // chosen; until then all p, and with them the sums, are 0
-  // on every block, in order, after the row maximum was raised: a factor of 0 forgets all earlier keys
-  __device__ void rescaled(float alpha) { seen = seen && alpha != 0.f; }
-  __device__ void choose(const float (&p)[16], const f32x16& dp) {
-    if (__builtin_amdgcn_ballot_w64(!seen) == 0) return;
-    float n = 0.f, s1 = 0.f, s2 = 0.f;
+  float c = 0.f;    // of the lane's query
+  float due = 0.f;  // weight of this half-wave's keys above which c is taken anew
+  // after the row maximum was raised
+  __device__ void rescaled(float alpha) { due *= alpha; }
+  // On every block, in order, `lnew` being this half-wave's sum of p with the block's: whether the constant is taken anew ...
+  __device__ bool is_due(float lnew) const { return __builtin_amdgcn_ballot_w64(lnew > due) != 0; }
+  // ... which returns what, times the sums of p, is to be added to the sums formed with the old one.  `lsum`, `dsum`: the sums of p and
+  // p (dP - c) over the earlier blocks, rounded operands or not.
+  __device__ float take(const float (&p)[16], const f32x16& dp, float lsum, float lnew, float dsum) {
+#pragma clang fp contract(off)  // the same bits wherever this is inlined
+    float x = __builtin_fmaf(lsum - lnew, c, dsum);
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const bool visible = p[v] != 0.f;
-      const float x = visible ? dp[v] : 0.f;
-      n += visible ? 1.f : 0.f;
-      s1 += x;
-      s2 = fmaf(x, x, s2);
-    }
-    n = half_sum(n);
-    s1 = half_sum(s1);
-    s2 = half_sum(s2);
-    // mean^2 > 4 variance / n
-    if (!seen) c = s1 * s1 * (n + 4.f) > 4.f * n * s2 ? s1 * fast_rcp(n) : 0.f;
-    seen = seen || n != 0.f;
+    for (int v = 0; v < 16; ++v) x = __builtin_fmaf(p[v], dp[v], x);
+    const float w = half_sum(lnew);  // 0 if no key was seen, else at least 2^-8
+    const float d = -half_sum(x) * fast_rcp(fmaxf(w, 1e-30f));
+    c -= d;
+    due = 4.f * lnew;
+    return d;
   }
 };
 

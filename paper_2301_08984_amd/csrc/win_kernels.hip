@@ -318,9 +318,6 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(GATED |
   }
   row.store(L, tid);
   __syncthreads();
-  union { uint32_t u; bf16x2 v; } one_pair;
-  one_pair.u = 0x3f803f80u;
-  const bf16x2 ones2 = one_pair.v;
   f32x16 oacc[1], a1, a2;
 #pragma unroll
   for (int v = 0; v < 16; ++v) { oacc[0][v] = 0.f; a1[v] = 0.f; a2[v] = 0.f; }
@@ -359,25 +356,29 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(GATED |
     float pr[16], dp[16];
 #pragma unroll
     for (int v = 0; v < 16; ++v) pr[v] = fast_exp2(fmaf(s[v], c1, nm));
+    const float l32_before = l32;
     l32 += sum16(pr);
-    shift.choose(pr, pa);
+    float d = 0.f;
+    if (shift.is_due(l32)) d = shift.take(pr, pa, l32_before, l32, dsum);
+    // (in the branch above the compiler copies a1, on every block, and needs scratch)
+    if (__builtin_amdgcn_ballot_w64(d != 0.f) != 0) {
+      dsum = fmaf(d, lsum, dsum);
+      if (!GATED) d32 = fmaf(d, l32_before, d32);
+#pragma unroll
+      for (int v = 0; v < 16; ++v) a1[v] = fmaf(d, a2[v], a1[v]);
+    }
 #pragma unroll
     for (int v = 0; v < 16; ++v) dp[v] = pr[v] * (pa[v] - shift.c);
     if (!GATED) d32 += sum16(dp);
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      union { bf16x8 v; bf16x2 h[4]; } pf, df;
-      pf.v = pack8(&pr[8 * j]);
-      df.v = pack8(&dp[8 * j]);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {  // the sums run over the rounded operands
-        lsum = __builtin_amdgcn_fdot2_f32_bf16(pf.h[e], ones2, lsum, false);
-        dsum = __builtin_amdgcn_fdot2_f32_bf16(df.h[e], ones2, dsum, false);
-      }
+      const bf16x8 pf = pack8(&pr[8 * j]), df = pack8(&dp[8 * j]);
+      lsum = sum_rounded(pf, lsum);  // over the operands as they were rounded
+      dsum = sum_rounded(df, dsum);
       const bf16x8 kt = lds_tr<WLD>(L.t0, 32 * c + 16 * j, 0, lane);
-      if (GATED) oacc[0] = mfma(lds_tr<WLD>(L.t1, 32 * c + 16 * j, 0, lane), pf.v, oacc[0]);
-      a2 = mfma(kt, pf.v, a2);
-      a1 = mfma(kt, df.v, a1);
+      if (GATED) oacc[0] = mfma(lds_tr<WLD>(L.t1, 32 * c + 16 * j, 0, lane), pf, oacc[0]);
+      a2 = mfma(kt, pf, a2);
+      a1 = mfma(kt, df, a1);
     }
   }
   if (q >= p.S) return;

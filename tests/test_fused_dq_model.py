@@ -97,18 +97,60 @@ def test_one_hot_row_cancels_exactly():
 
 
 def _two_products(Q, K, V, dO, bias, scale, shifted):
-    """dQ of one (row, head) by the kernel's formula, with or without the constant that it subtracts from every dP
-    of a query: the mean of dP over the first 32 keys, where it is at least twice its standard error."""
-    x = scale * Q @ K.T + bias
-    p = np.exp(x - x.max(1, keepdims=True))
+    """dQ of one (row, head) by the kernel's formula, with or without the constant that it subtracts from every dP of a
+    query: the weighted mean of dP over the blocks of 32 keys so far, the present one included, taken anew in the first
+    block and when the weight seen by a half-wave (keys whose index has bit 2 clear, or set) has grown fourfold for
+    any of the 32 queries of a wavefront."""
+    S, D = Q.shape[0], Q.shape[1]
+    x = (scale * Q @ K.T + bias) / math.log(2)
     dP = dO @ V.T
-    if shifted:
-        first = dP[:, :32]
-        s1, s2 = first.sum(1, keepdims=True), (first ** 2).sum(1, keepdims=True)
-        dP = dP - np.where(s1 ** 2 * 36 > 4 * 32 * s2, s1 / 32, 0.0)
-    pb, wb = _bf(p), _bf(p * dP)
-    lp = pb.sum(1, keepdims=True)
-    return scale * (wb @ K - (wb.sum(1, keepdims=True) / lp) * (pb @ K)) / lp
+    out = np.zeros((S, D))
+    for q in range(0, S, 32):
+        xq, dq = x[q:q + 32], dP[q:q + 32]
+        n = xq.shape[0]
+        top, c = np.full(n, -1e30), np.zeros(n)
+        a1, a2, ls, ds, due = np.zeros((n, D)), np.zeros((n, D)), np.zeros((2, n)), np.zeros((2, n)), np.zeros((2, n))
+        for k in range(0, S, 32):
+            xb, db = xq[:, k:k + 32], dq[:, k:k + 32]
+            half = [(np.arange(xb.shape[1]) >> 2 & 1) == i for i in (0, 1)]
+            peak = xb.max(1)
+            if np.any(peak > top + 8):
+                raised = np.maximum(top, peak)
+                alpha = np.exp2(top - raised)
+                top = raised
+                a1, a2 = a1 * alpha[:, None], a2 * alpha[:, None]
+                ls, ds, due = ls * alpha, ds * alpha, due * alpha
+            p = np.exp2(xb - top[:, None])
+            pb = _bf(p)
+            weight = ls + np.stack([pb[:, h].sum(1) for h in half])
+            if shifted and np.any(weight > due):
+                seen = weight.sum(0)
+                move = (ds.sum(0) + (p * db).sum(1) - c * (weight - ls).sum(0)) / np.where(seen > 0, seen, 1.0)
+                a1 -= move[:, None] * a2
+                ds -= move * ls
+                c += move
+                due = 4 * weight
+            wb = _bf(p * (db - c[:, None]))
+            ls, ds = weight, ds + np.stack([wb[:, h].sum(1) for h in half])
+            a1 += wb @ K[k:k + 32]
+            a2 += pb @ K[k:k + 32]
+        l = ls.sum(0)[:, None]
+        out[q:q + 32] = scale * (a1 - (ds.sum(0)[:, None] / l) * a2) / l
+    return out
+
+
+def _errors(Q, K, V, dO, bias):
+    """Relative 2-norm errors of dQ: dS rounded directly, two products without and with the constant."""
+    scale = float(np.float32(1.0 / math.sqrt(Q.shape[1])))
+    x = scale * Q @ K.T + bias
+    P = np.exp(x - x.max(1, keepdims=True))
+    P /= P.sum(1, keepdims=True)
+    dP = dO @ V.T
+    dS = P * (dP - (P * dP).sum(1, keepdims=True))
+    ref = scale * dS @ K
+    err = lambda a: float(np.linalg.norm(a - ref) / np.linalg.norm(ref))
+    return tuple(err(a) for a in (scale * _bf(dS) @ K, _two_products(Q, K, V, dO, bias, scale, False),
+                                  _two_products(Q, K, V, dO, bias, scale, True)))
 
 
 @pytest.mark.parametrize("S", [144, 901])
@@ -120,18 +162,31 @@ def test_common_offset_of_values_and_gradients(offset, S):
     D = 32
     Q, K, V, dO = (_bf(g.standard_normal((S, D)) + o) for o in (0.0, 0.0, offset, offset))
     bias = _bf(g.standard_normal((S, S)))
-    scale = float(np.float32(1.0 / math.sqrt(D)))
-    x = scale * Q @ K.T + bias
-    P = np.exp(x - x.max(1, keepdims=True))
-    P /= P.sum(1, keepdims=True)
-    dP = dO @ V.T
-    dS = P * (dP - (P * dP).sum(1, keepdims=True))
-    ref = scale * dS @ K
-    err = lambda a: float(np.linalg.norm(a - ref) / np.linalg.norm(ref))
-    direct, plain, shifted = (err(a) for a in (scale * _bf(dS) @ K, _two_products(Q, K, V, dO, bias, scale, False),
-                                               _two_products(Q, K, V, dO, bias, scale, True)))
+    direct, plain, shifted = _errors(Q, K, V, dO, bias)
     print(f"S={S} offset={offset}: direct {direct:.2e}, two products {plain:.2e}, with the constant {shifted:.2e}")
     assert shifted <= 1.25 * direct + 2e-4, (direct, plain, shifted)
     assert shifted <= 1.05 * plain, (plain, shifted)   # nor does it cost anything where there is no offset
     if offset >= 1.0:
         assert plain >= 2.5 * direct, (direct, plain)  # these data do show the difference
+
+
+@pytest.mark.parametrize("S", [144, 384])
+@pytest.mark.parametrize("what", ["first", "first_-4", "first_-8", "first_-20", "first_-60", "half", "rising"])
+def test_offset_of_some_keys(what, S):
+    """V offset for some of the keys, with a bias of its own: the constant follows the weight, and the rounding of the products
+    is at most twice that of dS formed directly."""
+    g = np.random.default_rng(S + 1)
+    D, at = 32, np.arange(S)
+    Q, K, V, dO = (_bf(g.standard_normal((S, D)) + o) for o in (0.0, 0.0, 0.0, 1.0))
+    bias = _bf(g.standard_normal((S, S)))
+    if what.startswith("first"):
+        V = _bf(V + np.where(at < 32, 4.0, 0.0)[:, None])
+        bias = bias + np.where(at < 32, float(what[6:] or 0), 0.0)
+    elif what == "half":
+        V = _bf(V + np.where(at >= S // 2, 4.0, 0.0)[:, None])
+    else:
+        V = _bf(V + np.linspace(0, 8, S)[:, None])
+        bias = bias + np.linspace(0, 40, S)
+    direct, plain, shifted = _errors(Q, K, V, dO, bias)
+    print(f"S={S} {what}: direct {direct:.2e}, two products {plain:.2e}, with the constant {shifted:.2e}")
+    assert shifted <= 2.0 * direct, (direct, plain, shifted)
