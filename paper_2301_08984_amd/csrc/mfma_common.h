@@ -395,6 +395,49 @@ struct DpShift {
   }
 };
 
+// The running maxima of a kernel that forms a block's probabilities with the maximum so far and looks at the block's own only where
+// that is needed (pair_fwd.hip), NR rows per wavefront.  What tells is a half-wave's sum of 16 probabilities:
+//  up to 2^8: nothing to be done, and a score has cost no comparison;
+//  up to 2^26: the probabilities and the sums so far are scaled down by the sum's power of two (an exponent below 26 is exact to
+//    2^-20, the result's LSE is rounded to no less);
+//  beyond, infinite ones included: the block is formed again with the maxima of those queries raised.
+// After a block formed again, or scaled by 2^19 or more, these queries look first, as all do on a row's first block, until their maximum
+// grows by no more than 2^6.  A block formed again costs nearly as much as two, a scaled one or a look a quarter of one.  The lines: 2^6, 2^19 and 2^26 are
+// far enough apart for a steady growth to find its one way, and all queries of a wavefront the same (a scaled block that has a look too costs half a block; with 2^16
+// in place of 2^26 a growth of 9 or 14 bits a block took 1.4 times as long).  256 rows x 4 heads x 1024, bias less 0 | 0.03 | 0.1 | 0.2 | 0.3 | 0.5 | 1 times |i - j|,
+// us: 300 | 333 | 338 | 377 | 371 | 332 | 327, queries four times larger 329; every such block formed again 295 | 421 | 431 | 430 | 429 | 426 | 425, 396; the
+// general forward, a maximum on every block: 343 | 347 | 348 | 345 | 344 | 342 | 341, 348.
+// What a query does depends on its own scores alone, not on its company.
+template <int NR>
+struct RowMaxima {
+  static constexpr float SCALE = 1 << 8, RAISE = 1 << 26;
+  uint64_t looks[NR];  // lane masks
+  __device__ bool any() const { return (looks[0] | looks[NR - 1]) != 0; }
+  // Raises the negated maximum `nm` of row n (again: where the half-wave's `sum` asks for it); returns the factor of the sums so far.
+  __device__ __forceinline__ float raise(int n, const f32x16& s, float c1, float& nm, bool first, bool again, float sum) {
+    float rmax = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) rmax = fmaxf(rmax, s[v]);
+    rmax = half_max(rmax * c1);
+    const bool mine = again ? half_max(sum) > RAISE : __builtin_amdgcn_inverse_ballot_w64(looks[n]);
+    const float by = mine ? fmaxf(rmax + nm, 0.f) : 0.f;
+    const uint64_t more = __builtin_amdgcn_ballot_w64(by > 6.f && !first);
+    looks[n] = again ? looks[n] | more : more;
+    const float mn = by > 0.f ? rmax : -nm, alpha = fast_exp2(-nm - mn);
+    nm = -mn;
+    return alpha;
+  }
+  // the factor of row n where the sum exceeds 2^8, with `nm` set to it; else 1
+  __device__ __forceinline__ float scale(int n, float& nm, float sum) {
+    sum = half_max(sum);
+    const float by = sum > SCALE && sum < INFINITY ? (float)((int)(__float_as_uint(sum) >> 23) - 127) : 0.f;
+    looks[n] |= __builtin_amdgcn_ballot_w64(by >= 19.f);
+    const float old = nm;
+    nm -= by;
+    return fast_exp2(nm - old);  // of the difference that was taken: the subtraction may have rounded
+  }
+};
+
 __device__ inline int key_of(int v, int hl) { return 8 * (v >> 2) + 4 * hl + (v & 3); }
 
 // Forward epilogue for one 32-column block `db` of a query's output (lane = query, registers =

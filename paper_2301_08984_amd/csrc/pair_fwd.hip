@@ -45,11 +45,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS == BIA
       qf[n][ks] = *(const bf16x8*)((const uint16_t*)p.Q + base[n] + (int64_t)qc * p.ss + 16 * ks + 8 * hl);
   f32x16 oacc[NR];
   float nm[NR], l[NR];  // the negated running maximum, the row sum
+  RowMaxima<NR> maxima;
 #pragma unroll
   for (int n = 0; n < NR; ++n) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) oacc[n][v] = 0.f;
     nm[n] = 1e30f;
+    maxima.looks[n] = ~0ull;
     l[n] = 0.f;
   }
   const float c1 = in_vgpr(p.scale * LOG2E);
@@ -76,17 +78,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS == BIA
       *(u32x4*)(smem[buf][n] + BN * PLK + (tid >> 2) * PLV + (tid & 3) * 8) = pv[n];
     }
   };
-  // 32 keys.  The running maximum is taken on the first block (`look`) and after that only where a sum of probabilities
-  // says that it has grown by a lot: the probabilities are formed with the maximum so far, and if a half-wave's sum of 16 of
-  // them exceeds 2^8 for any query (infinite ones included) the block is formed again, with the maxima of those
-  // queries raised; the others go through the same arithmetic as before.  Below that the probabilities stay under 2^8,
-  // harmless in fp32 / bf16 range, and a score costs no comparison.
+  // 32 keys; the running maximum as RowMaxima says
   auto block = [&](int buf, int kb, int at) __attribute__((always_inline)) {
     f32x16 s[NR];
     float sum[NR];
-#pragma unroll
-    for (int n = 0; n < NR; ++n) sum[n] = INFINITY;
-    for (bool look = at == 0;; look = true) {
+    for (bool again = false;; again = true) {
       if (PARKED) parked_bias(bt, r, kb, hl, inv_scale, cz);
 #pragma unroll
       for (int n = 0; n < NR; ++n) {
@@ -102,15 +98,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS == BIA
 #pragma unroll
           for (int v = 0; v < 16; ++v) s[n][v] = 32 * at + key_of(v, hl) >= p.S ? -INFINITY : s[n][v];
       }
-      if (look) {
+      if (again || maxima.any()) {
 #pragma unroll
         for (int n = 0; n < NR; ++n) {
-          float rmax = -INFINITY;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) rmax = fmaxf(rmax, s[n][v]);
-          rmax = half_max(rmax * c1);
-          const float mn = half_max(sum[n]) > 256.f ? fmaxf(-nm[n], rmax) : -nm[n], alpha = fast_exp2(-nm[n] - mn);
-          nm[n] = -mn;
+          const float alpha = maxima.raise(n, s[n], c1, nm[n], at == 0, again, sum[n]);
           l[n] *= alpha;
 #pragma unroll
           for (int v = 0; v < 16; ++v) oacc[n][v] *= alpha;
@@ -123,7 +114,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS == BIA
         for (int v = 0; v < 16; ++v) x[v] = s[n][v] = fast_exp2(fmaf(s[n][v], c1, nm[n]));
         sum[n] = sum16(x);
       }
-      if (look || __builtin_amdgcn_ballot_w64(fmaxf(sum[0], sum[NR - 1]) > 256.f) == 0) break;
+      const float top = fmaxf(sum[0], sum[NR - 1]);
+      if (__builtin_amdgcn_ballot_w64(top > maxima.SCALE) == 0) break;
+      if (again || __builtin_amdgcn_ballot_w64(top > maxima.RAISE) == 0) {
+#pragma unroll
+        for (int n = 0; n < NR; ++n) {
+          const float f = maxima.scale(n, nm[n], sum[n]);
+          sum[n] *= f;
+          l[n] *= f;
+#pragma unroll
+          for (int v = 0; v < 16; ++v) { s[n][v] *= f; oacc[n][v] *= f; }
+        }
+        break;
+      }
       if (!PARKED) bc.load(cz, at);
     }
 #pragma unroll

@@ -225,7 +225,9 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB == W
     float nm = 1e30f, l = 0.f;  // the negated running maximum, the row sum
 #pragma unroll BLOCK_UNROLL
     for (int c = 0; c < NB; ++c) {
-      // the maximum is taken on blocks that raise it, see pair_fwd.hip
+      // The maximum is taken on the first block, and where a half-wave's sum of 16 probabilities says that it has grown by a lot: above
+      // 2^8 (infinite ones included) for any query the block is formed again, with the maxima of those queries raised; the
+      // others go through the same arithmetic as before.
       f32x16 s;
       float sum = INFINITY;
       for (bool look = c == 0 || masked;; look = true) {
