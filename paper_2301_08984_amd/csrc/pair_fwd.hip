@@ -83,6 +83,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS == BIA
     f32x16 s[NR];
     float sum[NR];
     for (bool again = false;; again = true) {
+      // without this the compiler keeps a block's K fragments for a second time and loads the next block's early, beyond 128 registers: 24 and 16
+      // bytes of scratch, and 1024 rows x 8 heads x 100 took 73 us (63 with it; 67 in the general forward), x 128 95 (87; 88), 1024 x 4 x 1024 1385 (1347; 1372)
+      if (PARKED) asm volatile("" ::: "memory");
       if (PARKED) parked_bias(bt, r, kb, hl, inv_scale, cz);
 #pragma unroll
       for (int n = 0; n < NR; ++n) {
