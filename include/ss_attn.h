@@ -108,9 +108,11 @@ typedef struct {
  * bias gradient, which add at most 12 MiB (or four sums over H x S x S, where those are
  * larger) to what the share needs at least, are included in the figure; to stay within
  * that it may be the figure of a finer cut than k.  A larger workspace is used to run chunks
- * together, and the chunks of a share that needs no more than 64 MiB run together in a
+ * together, and the chunks of a share that needs no more than 64 MiB, less the copy of a
+ * dense bias or table that the call lays out for its kernels, run together in a
  * buffer that the library holds on each GPU, unless another stream is using it or the
- * call is being captured into a graph; the results are the same bits.
+ * call is being captured into a graph (half of the buffer if another stream is using the
+ * other half); the results are the same bits.
  * Needs no GPU.  Returns SS_OK or a negative error. */
 int ss_attn_workspace_bytes(const ss_attn_desc* desc, size_t* fwd_bytes, size_t* bwd_bytes);
 

@@ -417,7 +417,7 @@ int run_bwd(const ss_attn_desc* d, Family fam, const WsLayout& w, const void* Q,
 
 namespace ssa {
 
-void* SharedUse::take(hipStream_t stream) {
+char* SharedUse::take(hipStream_t stream, int parts) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   int dev = -1;
   if (hipStreamIsCapturing(stream, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone ||
@@ -426,32 +426,53 @@ void* SharedUse::take(hipStream_t stream) {
     return nullptr;
   }
   Shared& x = g_shared[dev];
-  std::unique_lock<std::mutex> l(x.mu, std::try_to_lock);
-  if (!l.owns_lock()) return nullptr;
-  if (x.broken) return nullptr;
+  std::unique_lock<std::mutex> l[2];
+  for (int i = 0; i < 2; ++i) {
+    if (!(parts >> i & 1)) continue;
+    l[i] = std::unique_lock<std::mutex>(x.half[i].mu, std::try_to_lock);
+    if (!l[i].owns_lock()) return nullptr;
+  }
   // a capture under way in another thread must not see these calls as its own
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   (void)hipThreadExchangeStreamCaptureMode(&mode);
-  if (!x.ptr && (hipGetSymbolAddress(&x.ptr, HIP_SYMBOL(shared_scratch)) != hipSuccess || !x.ptr ||
-                 hipGetSymbolAddress((void**)&x.counters, HIP_SYMBOL(shared_counters)) != hipSuccess || !x.counters ||
-                 hipEventCreateWithFlags(&x.done, hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess))
-    x.broken = true;
+  bool mine;
+  {
+    std::lock_guard<std::mutex> init(x.init);
+    if (!x.ptr && !x.broken) {
+      void *ptr = nullptr, *counters = nullptr;
+      x.broken = hipGetSymbolAddress(&ptr, HIP_SYMBOL(shared_scratch)) != hipSuccess || !ptr ||
+                 hipGetSymbolAddress(&counters, HIP_SYMBOL(shared_counters)) != hipSuccess || !counters;
+      for (int e = SHARED_FIRST; e <= SHARED_BOTH && !x.broken; ++e)
+        x.broken = hipEventCreateWithFlags(&x.done[e], hipEventDisableTiming | hipEventDisableSystemFence) != hipSuccess;
+      x.ptr = (char*)ptr;
+      x.counters = (unsigned*)counters;
+    }
+    mine = !x.broken;
+  }
   // (the wait on what should be the same stream is for a handle that was destroyed and handed out again)
-  const bool mine = !x.broken && (!x.used || (x.stream == stream ? hipStreamWaitEvent(stream, x.done, 0)
-                                                                 : hipEventQuery(x.done)) == hipSuccess);
+  for (int i = 0; i < 2 && mine; ++i) {
+    const Shared::Half& h = x.half[i];
+    if (!(parts >> i & 1) || h.last == 0 || (i == 1 && parts == SHARED_BOTH && h.last == x.half[0].last)) continue;
+    mine = (h.stream == stream ? hipStreamWaitEvent(stream, x.done[h.last], 0) : hipEventQuery(x.done[h.last])) == hipSuccess;
+  }
   if (!mine) (void)hipGetLastError();
   (void)hipThreadExchangeStreamCaptureMode(&mode);
   if (!mine) return nullptr;
-  x.used = true;
-  x.stream = stream;
+  for (int i = 0; i < 2; ++i) {
+    if (!(parts >> i & 1)) continue;
+    x.half[i].last = parts;
+    x.half[i].stream = stream;
+    lock_[i] = std::move(l[i]);
+  }
   s_ = &x;
   st_ = stream;
-  lock_ = std::move(l);
-  return x.ptr;
+  parts_ = parts;
+  return x.ptr + (parts & SHARED_FIRST ? 0 : SHARED_HALF);
 }
 
 SharedUse::~SharedUse() {
-  if (s_ && hipEventRecord(s_->done, st_) != hipSuccess) {  // nobody could tell when this call's work ends
+  if (s_ && hipEventRecord(s_->done[parts_], st_) != hipSuccess) {  // nobody could tell when this call's work ends
+    std::lock_guard<std::mutex> init(s_->init);
     s_->broken = true;
     (void)hipGetLastError();
   }
@@ -560,7 +581,8 @@ int ss_attn_fwd(const ss_attn_desc* d, const void* Q, const void* K, const void*
   ssa::SharedUse shared;
   if (fam == FAM_MFMA) {
     const size_t bytes = ssa::bias_copy_bytes_for(p, false, p.b1 - p.b0, p.h1 - p.h0);
-    float* copy = bytes > 0 && bytes <= ssa::SHARED_BYTES ? (float*)shared.take(st) : nullptr;
+    float* copy = bytes > 0 && bytes <= ssa::SHARED_BYTES
+                      ? (float*)shared.take(st, bytes <= ssa::SHARED_HALF ? ssa::SHARED_FIRST : ssa::SHARED_BOTH) : nullptr;
     if (copy) {
       SS_LAUNCH(SS_K_TABLE_REDUCE, ssa::launch_bias_copies(p, copy, false, p.h0, p.h1, st), "bias copy");
     }
@@ -610,25 +632,42 @@ int ss_attn_bwd(const ss_attn_desc* d, const void* Q, const void* K, const void*
   if (!workspace || workspace_bytes < w.total || ((uintptr_t)workspace % ALIGN)) return SS_ERR_WORKSPACE;
   hipStream_t st = (hipStream_t)hip_stream;
   char* ws = (char*)workspace;
-  // Copies of the bias in accumulator layout go into the library's buffer, behind the scratch of the chunks if that goes
-  // there too.
-  const KP p = base_params(&run);
-  const int rows = d->shard_axis == SS_AXIS_ROW ? d->hi - d->lo : d->B, heads = d->shard_axis == SS_AXIS_HEAD ? d->hi - d->lo : d->H;
-  size_t copy_bytes = fam == FAM_MFMA ? ssa::bias_copy_bytes_for(p, true, rows, heads) : 0;
-  if (copy_bytes > ssa::SHARED_BYTES) copy_bytes = 0;
-  const size_t room = ssa::SHARED_BYTES - copy_bytes;
   // Chunks of a small share cannot fill the chip (a launch of 4 rows x 1 head takes as long as one of
   // 4 rows x 6), and what keeps them apart is only that they reuse one chunk's scratch.  The results
   // do not depend on k: run the fewest chunks whose scratch fits what the caller handed over, or
   // else the library's buffer.  Backward of 4 rows x 6 heads x 215 queries, D = 128, k = 4: 131 -> 36 us;
   // pair attention of 18 rows x 8 heads x 472, k = 16, forward and backward: 729 -> 113 us.
+  // Copies of the bias in accumulator layout go there too, behind the scratch.
+  const KP p = base_params(&run);
+  const int rows = d->shard_axis == SS_AXIS_ROW ? d->hi - d->lo : d->B, heads = d->shard_axis == SS_AXIS_HEAD ? d->hi - d->lo : d->H;
+  const size_t copies = fam == FAM_MFMA ? ssa::bias_copy_bytes_for(p, true, rows, heads) : 0;
   const int kw = fewest_chunks(&run, gw, workspace_bytes);
-  const int ks = run.k > 1 && layout_with(&run, gw).total <= room ? fewest_chunks(&run, gw, room) : kw;
+  struct Use {
+    size_t copies, bytes;  // of the copies, and all
+    int k;
+  };
+  auto use_of = [&](size_t room) {
+    Use u{copies <= room ? copies : 0, 0, kw};
+    ss_attn_desc t = run;
+    if (run.k > 1 && layout_with(&run, gw).total <= room - u.copies) t.k = fewest_chunks(&run, gw, room - u.copies);
+    if (t.k < kw) u.k = t.k;
+    u.bytes = u.copies + (u.k < kw ? layout_with(&t, gw).total : 0);
+    return u;
+  };
+  Use u = use_of(ssa::SHARED_BYTES);
   ssa::SharedUse shared;
-  char* own = copy_bytes > 0 || ks < kw ? (char*)shared.take(st) : nullptr;
-  float* copy = own && copy_bytes > 0 ? (float*)(own + room) : nullptr;
-  if (own && ks < kw) ws = own;
-  run.k = own && ks < kw ? ks : kw;
+  char* own = u.bytes > ssa::SHARED_HALF ? shared.take(st) : nullptr;
+  if (!own) {
+    u = use_of(ssa::SHARED_HALF);
+    if (u.bytes > 0) own = shared.take(st, ssa::SHARED_FIRST);
+    if (u.bytes > 0 && !own) own = shared.take(st, ssa::SHARED_SECOND);
+  }
+  float* copy = own && u.copies > 0 ? (float*)(own + (u.bytes - u.copies)) : nullptr;
+  run.k = kw;
+  if (own && u.k < kw) {
+    ws = own;
+    run.k = u.k;
+  }
   w = layout_with(&run, gw);
   return run_bwd(&run, fam, w, Q, K, V, bias, region_ids, G, dY, lse, dQ, dK, dV, dBias, dG, ws, copy, st);
 }

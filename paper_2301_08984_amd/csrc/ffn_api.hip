@@ -159,22 +159,26 @@ ssa::GemmArgs gemm(const void* A, int64_t lda, const void* B, int64_t ldb, int M
   return g;
 }
 
-// Scratch beyond one chunk's hidden activations, the library's if nobody else is using it: for split contractions (one half of SPLIT_BYTES for the caller's stream, one for
-// the helper stream) and for the hidden activations of a whole small share.
+// Scratch beyond one chunk's hidden activations, the library's if nobody else is using it: its first half for the hidden activations of a
+// whole small share, its second for split contractions (SPLIT_BYTES for the caller's stream, as many for the helper stream).
 constexpr size_t HIDDEN_BYTES = 32u << 20;
-static_assert(HIDDEN_BYTES + 2 * ssa::SPLIT_BYTES <= ssa::SHARED_BYTES && 2 * ssa::SPLIT_TILES <= ssa::SHARED_COUNTERS, "library scratch");
+static_assert(HIDDEN_BYTES <= ssa::SHARED_HALF && 2 * ssa::SPLIT_BYTES <= ssa::SHARED_HALF && 2 * ssa::SPLIT_TILES <= ssa::SHARED_COUNTERS, "library scratch");
 constexpr size_t COUNTER_BYTES = 2 * ssa::SPLIT_TILES * sizeof(unsigned);
 static_assert(SS_FFN_PARTS_BYTES == COUNTER_BYTES + 2 * ssa::SPLIT_BYTES, "as documented");
 struct Scratch {
   ssa::SharedUse use;
-  char* base = nullptr;                    // the library's, if this call has it
+  char* base = nullptr;                    // the library's first half, if this call has it
   char* parts = nullptr;                   // of the split contractions: the library's, or at the end of the caller's workspace
   unsigned* counters = nullptr;
   // `spare`, `bytes`: the caller's workspace beyond what the call needs
   Scratch(hipStream_t st, bool merge, bool split, char* spare, size_t bytes) {
-    if (merge || split) base = (char*)use.take(st);
-    if (base) {
-      parts = base + HIDDEN_BYTES;
+    int got = (merge ? ssa::SHARED_FIRST : 0) | (split ? ssa::SHARED_SECOND : 0);
+    char* own = got ? use.take(st, got) : nullptr;
+    if (!own && got == ssa::SHARED_BOTH) own = use.take(st, got = ssa::SHARED_SECOND);
+    if (!own && merge && split) own = use.take(st, got = ssa::SHARED_FIRST);
+    if (own && got & ssa::SHARED_FIRST) base = own;
+    if (own && got & ssa::SHARED_SECOND) {
+      parts = own + (got & ssa::SHARED_FIRST ? ssa::SHARED_HALF : 0);
       counters = use.counters();
     } else if (split && bytes >= SS_FFN_PARTS_BYTES) {
       // a kernel of its own sets the counters to zero (3 us), which is how the products leave them

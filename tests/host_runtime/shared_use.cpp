@@ -63,6 +63,24 @@ int main() {
   { ssa::SharedUse a; CHECK(a.take(s2) == nullptr); }
   g_done = true;
   { ssa::SharedUse a; CHECK(a.take(s2) != nullptr); }
+  {  // halves: a user each, and none for a call that wants both
+    ssa::SharedUse a, b, c;
+    char* first = a.take(s1, ssa::SHARED_FIRST);
+    CHECK(first != nullptr && a.counters() == nullptr);
+    std::thread([&] {
+      CHECK(c.take(s2) == nullptr && c.take(s2, ssa::SHARED_FIRST) == nullptr);
+      CHECK(b.take(s2, ssa::SHARED_SECOND) == first + ssa::SHARED_HALF && b.counters() != nullptr);
+    }).join();
+  }
+  g_done = false;  // a half that another stream's call used last keeps the other one free, and one's own stream has it
+  { ssa::SharedUse a; CHECK(a.take(s1) == nullptr); }
+  { ssa::SharedUse a; CHECK(a.take(s1, ssa::SHARED_FIRST) != nullptr); }
+  { ssa::SharedUse a; CHECK(a.take(s2, ssa::SHARED_FIRST) == nullptr && a.take(s2, ssa::SHARED_SECOND) != nullptr); }
+  g_done = true;
+  { ssa::SharedUse a; CHECK(a.take(s1) != nullptr); }
+  g_done = false;
+  { ssa::SharedUse a; CHECK(a.take(s2, ssa::SHARED_SECOND) == nullptr); }
+  g_done = true;
   g_capturing = true;
   { ssa::SharedUse a; CHECK(a.take(s2) == nullptr); }
   g_capturing = false;

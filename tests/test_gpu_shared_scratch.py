@@ -90,3 +90,34 @@ def test_two_host_threads_on_two_streams(name, k):
             ref = getattr(cases[2], n)
             if ref is not None:
                 assert torch.equal(torch.nan_to_num(getattr(cases[i], n), nan=12345.0), torch.nan_to_num(ref, nan=12345.0)), (i, n)
+
+
+def test_a_forward_leaves_room_for_the_chunks_of_another_stream():
+    """Beside a forward of pair attention (about 300 us), whose copy of the bias is in the library's buffer, the 16 chunks of a small share
+    still run together."""
+    import torch
+    from paper_2301_08984_amd import binding as ss
+    from paper_2301_08984_amd.runner import DeviceCase
+    from paper_2301_08984_amd.workloads import make_inputs
+    print("attention beside a forward", flush=True)
+    cases = [DeviceCase(make_inputs(B=B, H=H, S=S, D=32, dtype="bf16", bias="dense", gated=True, seed=S), dtype="bf16", bias="dense", gated=True)
+             for B, H, S in ((256, 4, 1024), (18, 8, 200))]
+    long, small = cases[0].desc("row", 0, 256, 1), cases[1].desc("row", 0, 18, 16)
+    side = torch.cuda.Stream()
+    cases[1].workspace(small)
+    for _ in range(2):  # what a first call does once
+        cases[0].fwd(long)
+        cases[1].bwd(small)
+        torch.cuda.synchronize()
+    alone = {n: getattr(cases[1], n).clone() for n in OUTS if getattr(cases[1], n) is not None}
+    cases[0].fwd(long)
+    cases[0].fwd(long)
+    ss.ss_attn_profile_enable(True)
+    with torch.cuda.stream(side):
+        cases[1].bwd(small)
+    torch.cuda.synchronize()
+    ss.ss_attn_profile_enable(False)
+    launches = {n: ss.ss_attn_profile_read(i)[1] for i, n in enumerate(ss.KERNEL_NAMES)}
+    assert launches["dkdv"] + launches["dq_dkdv"] == 1, launches
+    for n, ref in alone.items():
+        assert torch.equal(getattr(cases[1], n), ref), n
