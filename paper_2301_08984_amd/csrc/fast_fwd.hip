@@ -330,8 +330,15 @@ void fwd_fast_launch(const KP& p, hipStream_t st) {
   const bool slice32 = ((int64_t)(p.S - 1) * p.ss + D) * 2 < (1ll << 31);
   const int together = p.bias_kind ? heads_together(p.h1 - p.h0, p.S, 2) : 0;
   dispatch_bias(p, [&](auto bias, auto causal) {
-    if (slice32) fwd_fast_kernel<D, bias(), causal(), RECOMP, QW, NG, true><<<g, 64 * QW * NG, 0, st>>>(p, together);
-    else fwd_fast_kernel<D, bias(), causal(), RECOMP, QW, NG, false><<<g, 64 * QW * NG, 0, st>>>(p, together);
+    // head size 32, large shares: the backward's pass (rdq_ok) and unmasked forwards with a bias (pair_fwd_ok) are other kernels' then
+    constexpr bool elsewhere = D == 32 && NG == 1 && (RECOMP || (bias() && !causal()));
+    if constexpr (!elsewhere) {
+      if (slice32) {
+        fwd_fast_kernel<D, bias(), causal(), RECOMP, QW, NG, true><<<g, 64 * QW * NG, 0, st>>>(p, together);
+        return;
+      }
+    }
+    fwd_fast_kernel<D, bias(), causal(), RECOMP, QW, NG, false><<<g, 64 * QW * NG, 0, st>>>(p, together);
   });
 }
 

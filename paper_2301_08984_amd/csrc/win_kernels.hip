@@ -592,7 +592,10 @@ hipError_t launch_win_fwd(const KP& p, hipStream_t st) {
   const int64_t rounds = (int64_t)(p.b1 - p.b0) * (p.h1 - p.h0) / (2 * 256 * 3);
   const int rows = p.bias_q ? 1 : (int)(rounds < 1 ? 1 : rounds > 8 ? 8 : rounds);
   const dim3 g(p.h1 - p.h0, 1, (p.b1 - p.b0 + rows - 1) / rows);
-  return with_shape(p, p.bias_q != nullptr, [&](auto nb, auto region, auto wb) { win_fwd_kernel<nb(), region(), wb()><<<g, 64 * nb(), 0, st>>>(p, rows); });
+  return with_shape(p, p.bias_q != nullptr, [&](auto nb, auto region, auto wb) {
+    constexpr int WB = wb() == WB_COPY && nb() < 5 ? WB_REGS : wb();  // no copy up to 128 tokens (bias_copy_bytes_for)
+    win_fwd_kernel<nb(), region(), WB><<<g, 64 * nb(), 0, st>>>(p, rows);
+  });
 }
 hipError_t launch_win_recompute_dq(const KP& p, hipStream_t st) {
   const dim3 g(p.h1 - p.h0, 1, p.b1 - p.b0);
