@@ -1,5 +1,5 @@
-"""Windows of 65 to 160 tokens (head size 32): the kernels that keep a strip of the bias in registers and walk
-the rows of a head.  Sizes at the edges of the 32-token blocks, every bias kind with and without the
+"""Windows of 65 to 160 tokens (head size 32): kernels whose scores start from the bias, here (small shares) a strip of it held in
+registers; from a copy in accumulator layout see test_gpu_bias_copy.py.  Sizes at the edges of the 32-token blocks, every bias kind with and without the
 region mask, gating, both split axes and transposed storage, against the oracle; bit for bit across k,
 with row groups of the bias gradient that a chunk boundary cuts."""
 import numpy as np
