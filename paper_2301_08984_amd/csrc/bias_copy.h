@@ -14,10 +14,13 @@ namespace {
 // Backward: dK / dV 9 % shorter (1024 x 4 x 1024: 2037 -> 1850 us), and the copy replaces the transposed bf16 one; the
 // recompute + dQ kernel gains nothing from a copy of its own (2469 | 2510).
 // Windows (win_kernels.hip; the backward takes both copies): without one a work-group gathers the bias from the table in
-// LDS and holds it in registers.
+// LDS and holds it in registers.  Without | with, us, rows x heads of 256, 512, 1024, 2048 (8 heads, region mask): 12 x 12 tokens forward
+// 10.3 | 13.7, 17.5 | 16.0, 31.8 | 25.9, 64.0 | 37.6; backward of 32, 64, 128, 256: 39.3 | 39.0, 41.9 | 41.9, 48.7 | 46.9, 56.9 | 54.5 (4 heads: 44.3 | 43.5 at 64);
+// backward of 9 x 9: 36.6 | 39.2, 42.2 | 43.8, 51.9 | 50.9, 70.9 | 67.6, of 11 x 11: 47.4 | 47.0, 54.1 | 54.7, 68.1 | 65.7, 93.6 | 90.2; forward of 9 x 9:
+// 7.9 | 12.5, 7.9 | 12.4, 9.6 | 14.1, 19.2 | 19.8, of 11 x 11: 8.5 | 12.4, 9.4 | 13.8, 15.7 | 17.0, 26.4 | 25.6.
 inline size_t bias_copy_bytes_for(const KP& p, bool backward, int64_t rows, int heads) {
   if (win_ok(p)) {
-    if (p.bias_kind == 0 || (backward ? rows * heads < (p.S <= 128 ? 256 : 64) : p.S <= 128 || rows * heads < 512)) return 0;
+    if (p.bias_kind == 0 || (backward ? rows * heads < (p.S <= 128 ? 1024 : 64) : p.S <= 128 || rows * heads < 512)) return 0;
     return (size_t)bias_copy_bytes(p.S, heads) * (backward ? 2 : 1);
   }
   if (!pair_fwd_ok(p) || p.S > 16384) return 0;

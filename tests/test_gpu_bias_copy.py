@@ -66,8 +66,8 @@ def _eager_and_captured(cfg, lo, k, inputs=None):
 # at another head than the first
 @pytest.mark.parametrize("cfg,k", [(_cfg(901, 8, 193), 3), (_cfg(301, 6, 416, layout="sbhd"), 2), (_cfg(301, 6, 415, gated=False), 1),
                                    (_cfg(457, 5, 384, axis="head", lo=1), 2), (_win(70, 8, (12, 12), mask="region"), 2),
-                                   (_win(130, 4, (10, 16), gated=True), 1), (_win(100, 6, (9, 9), mask="region"), 3),
-                                   (_win(90, 6, (11, 11), bias="dense", mask="region"), 2),
+                                   (_win(130, 4, (10, 16), gated=True), 1), (_win(180, 6, (9, 9), mask="region"), 3),
+                                   (_win(175, 6, (11, 11), bias="dense", mask="region"), 2),
                                    (_win(130, 5, (12, 12), mask="region", axis="head", lo=1), 2)],
                          ids=["193", "416_sbhd", "415", "384_heads", "12x12", "10x16_gated", "9x9", "11x11_dense", "12x12_heads"])
 def test_copies_give_the_same_bits(cfg, k):
