@@ -211,13 +211,14 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB == W
 #pragma unroll
       for (int c = 0; c < (NB + 1) / 2; ++c) other |= ids_n[c] ^ id0;
       masked = __builtin_amdgcn_ballot_w64(other != 0) != 0;
-      if (masked) {
-        const int* ids = p.region + (int64_t)(b % p.mask_period) * p.S;
-        my_rid = ids[qc];
-        if (tid < 32 * NB) L.rid[tid] = ids[min(tid, p.S - 1)];
+      if (masked && w == 0) {  // every wavefront has all ids; loading them here instead would be a wait of its own
+#pragma unroll
+        for (int c = 0; c < (NB + 1) / 2; ++c)
+          if (lane + 64 * c < 32 * NB) L.rid[lane + 64 * c] = ids_n[c];
       }
     }
     __syncthreads();
+    if (masked) my_rid = L.rid[q];
     if (RUN && b + 1 < blast) fetch(b + 1);
     f32x16 oacc[1];
 #pragma unroll
