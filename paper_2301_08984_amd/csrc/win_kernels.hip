@@ -589,9 +589,17 @@ hipError_t with_shape(const KP& p, bool copy, F f) {
 }  // namespace
 
 hipError_t launch_win_fwd(const KP& p, hipStream_t st) {
-  // rows enough for a compute unit's work-groups, three of five wavefronts, to go through twice; at most 8
-  const int64_t rounds = (int64_t)(p.b1 - p.b0) * (p.h1 - p.h0) / (2 * 256 * 3);
-  const int rows = p.bias_q ? 1 : (int)(rounds < 1 ? 1 : rounds > 8 ? 8 : rounds);
+  // Rows per work-group.  With the bias in registers, gathered once per work-group: as many as let the launch fit the chip in one round (4, 3 and 1
+  // work-groups of 3, 4 and 5 wavefronts per compute unit: two of 5 take as long as one after the other), at most 8; beyond that rounds of at most 6, or 8 of
+  // 5 wavefronts.  8 heads, region mask, us, rows x heads of 1536, 2048, 3072, 4096, 6144, 8192, with one row | a row for every 1536 of them | this rule:
+  // 9 x 9 tokens 14.4 | 14.4 | 12.0, 19.2 | 19.2 | 14.1, 25.3 | 21.7 | 18.4, 31.1 | 27.2 | 22.8, 42.6 | 33.2 | 30.5, 54.1 | 41.9 | 39.6; 11 x 11: 19.8 | 19.8 | 16.7,
+  // 25.7 | 25.8 | 21.9, 34.6 | 29.2 | 26.1, 43.5 | 36.5 | 35.5, 61.4 | 46.1 | 46.0, 78.7 | 61.2 | 61.5; 12 x 12 without the copy (captured): 47.3 | 47.3 | 30.2,
+  // 63.8 | 63.8 | 43.6, 92.8 | 71.7 | 60.4, 121 | 93.3 | 77.7, 179 | 116 | 111, 255 | 162 | 168.  One row where there is nothing to gather (no bias, 9 x 9: 2048
+  // 12.4 us, two rows 13.2, 8192 33.0 | 35.1; 11 x 11: 17.1 | 19.2, 50.5 | 51.6; 12 x 12: 30.2 | 35.5, 110 | 111) or to hold (the copy).
+  const int per_cu = p.S <= 96 ? 4 : p.S <= 128 ? 3 : 1;
+  const int64_t slots = 256 * per_cu, units = (int64_t)(p.b1 - p.b0) * (p.h1 - p.h0), once = (units + slots - 1) / slots;
+  const int64_t most = per_cu == 1 ? 8 : 6, rounds = once <= 8 ? 1 : (once + most - 1) / most;
+  const int rows = p.bias_q || p.bias_kind == 0 ? 1 : (int)((units + slots * rounds - 1) / (slots * rounds));
   const dim3 g(p.h1 - p.h0, 1, (p.b1 - p.b0 + rows - 1) / rows);
   return with_shape(p, p.bias_q != nullptr, [&](auto nb, auto region, auto wb) {
     constexpr int WB = wb() == WB_COPY && nb() < 5 ? WB_REGS : wb();  // no copy up to 128 tokens (bias_copy_bytes_for)
