@@ -596,10 +596,12 @@ hipError_t launch_win_fwd(const KP& p, hipStream_t st) {
   // 25.7 | 25.8 | 21.9, 34.6 | 29.2 | 26.1, 43.5 | 36.5 | 35.5, 61.4 | 46.1 | 46.0, 78.7 | 61.2 | 61.5; 12 x 12 without the copy (captured): 47.3 | 47.3 | 30.2,
   // 63.8 | 63.8 | 43.6, 92.8 | 71.7 | 60.4, 121 | 93.3 | 77.7, 179 | 116 | 111, 255 | 162 | 168.  One row where there is nothing to gather (no bias, 9 x 9: 2048
   // 12.4 us, two rows 13.2, 8192 33.0 | 35.1; 11 x 11: 17.1 | 19.2, 50.5 | 51.6; 12 x 12: 30.2 | 35.5, 110 | 111) or to hold (the copy).
+  // (Work-groups of one head, not rows x heads through rows: 24 heads x 128 rows of 9 x 9 tokens are 1032 work-groups of three rows, 20.7 us, or 768 of four, 17.9.)
   const int per_cu = p.S <= 96 ? 4 : p.S <= 128 ? 3 : 1;
-  const int64_t slots = 256 * per_cu, units = (int64_t)(p.b1 - p.b0) * (p.h1 - p.h0), once = (units + slots - 1) / slots;
+  const int64_t slots = 256 * per_cu, nrows = p.b1 - p.b0, heads = p.h1 - p.h0, once = (nrows * heads + slots - 1) / slots;
   const int64_t most = per_cu == 1 ? 8 : 6, rounds = once <= 8 ? 1 : (once + most - 1) / most;
-  const int rows = p.bias_q || p.bias_kind == 0 ? 1 : (int)((units + slots * rounds - 1) / (slots * rounds));
+  const int64_t of_head = slots * rounds / heads > 1 ? slots * rounds / heads : 1;
+  const int rows = p.bias_q || p.bias_kind == 0 ? 1 : (int)((nrows + of_head - 1) / of_head);
   const dim3 g(p.h1 - p.h0, 1, (p.b1 - p.b0 + rows - 1) / rows);
   return with_shape(p, p.bias_q != nullptr, [&](auto nb, auto region, auto wb) {
     constexpr int WB = wb() == WB_COPY && nb() < 5 ? WB_REGS : wb();  // no copy up to 128 tokens (bias_copy_bytes_for)
