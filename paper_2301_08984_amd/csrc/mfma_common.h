@@ -636,9 +636,13 @@ inline WgShape wg_shape(const KP& p) {
 
 // The forward of the smallest shape at head size 128, causal: two query blocks per work-group of eight wavefronts where
 // that leaves blocks enough for more than one per compute unit (12 heads x 2048, 384 of them: 27.5 -> 23.9 us; 8 x 3000, 376:
-// 33.6 -> 30.3; 3 x 8000, 375: 77.6 -> 72.2; 16 x 1024, 256: 12.2 -> 13.9; 4 x 4096, 256: 29.2 -> 37.6).  Without a mask all
-// blocks are as long as the longest and the work-groups of four do better (10 x 2000: 37.0 -> 41.7).
-inline bool wave_pairs(const KP& p) { return p.mask_kind == 1 && (int64_t)((p.S + 31) / 32) * p.share_units >= 704; }
+// 33.6 -> 30.3; 3 x 8000, 375: 77.6 -> 72.2; 16 x 1024, 256: 12.2 -> 13.9; 4 x 4096, 256: 29.2 -> 37.6) and no more than two (16 x 2048, 512:
+// 30.1 -> 26.9; 50 x 617, 500: 17.4 -> 17.3; but 40 x 800, 520: 18.7 -> 22.0, 52 x 617, 520: 19.6 -> 21.4, 27 x 1400, 594: 29.7 -> 31.5, 60 x 617, 600: 20.7 -> 22.3).
+// Without a mask all blocks are as long as the longest and the work-groups of four do better (10 x 2000: 37.0 -> 41.7).
+inline bool wave_pairs(const KP& p) {
+  const int64_t blocks = (int64_t)((p.S + 31) / 32) * p.share_units, pairs = (int64_t)((p.S + 63) / 64) * p.share_units;
+  return p.mask_kind == 1 && blocks >= 704 && pairs <= 512;
+}
 // The backward of that shape, two blocks per work-group of four wavefronts (bwd_pair128_kernel), with the work-groups of the
 // whole share.  Causal: from a little over one round of the 512 that the chip holds (384: 28.6 -> 29.5 us; 480: 33.6 -> 32.3
 // and 56.6 -> 60.0; 576: 37.8 -> 34.8; 768: 116 -> 108; 1152: 101.8 -> 84.5, all with the recompute pass).  Without a mask
