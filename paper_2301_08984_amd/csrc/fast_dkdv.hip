@@ -6,6 +6,19 @@
 namespace ssa {
 namespace {
 
+// Four scaled values as packed bf16 with integer arithmetic (round to nearest even).  Not the hardware's conversion at head sizes 64 and 128: where the
+// accumulators end in it, the compiler keeps more of them in the accumulation file through the whole loop, 64 moves to and from it a tile at D = 64 instead of 32.
+// 25 heads x 2048 x 64, no mask, us: hardware conversion and head groups as an argument 124, integer arithmetic 112 - 115, and a constant 105; 14 heads 63 | 57 | 53.
+template <int D>
+__device__ inline uint2 pack4_acc(float a, float b, float c, float d, float s) {
+  if (D <= 32) return pack4_bf16(a, b, c, d, s);
+  auto bits = [](float f) {
+    const uint32_t u = __float_as_uint(f);
+    return (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
+  };
+  return uint2{bits(a * s) | (bits(b * s) << 16), bits(c * s) | (bits(d * s) << 16)};
+}
+
 // ---------------------------------------------------------------------------
 // dK, dV (optional dense bf16 bias read from its transposed copy, optional causal mask).  Each wavefront
 // keeps a 32-key block of K and V and both gradient accumulators in registers and
@@ -28,7 +41,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 32
   __shared__ __attribute__((aligned(16))) float sD[2][SPLIT ? 2 * BN : BN];
   __shared__ __attribute__((aligned(16))) uint16_t sBias[BIAS == BIAS_EVEN || BIAS == BIAS_ODD ? NW * BIAS_TILE_ELEMS : 8];  // one parked tile per wavefront
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 31, hl = lane >> 5;
-  const BlockId blk = CAUSAL && !BIAS ? causal_block_id(false) : xcd_block_id(together);
+  // (a constant without a bias: the argument, 0 then, moved the schedule of the whole loop, see pack4_acc)
+  const BlockId blk = CAUSAL && !BIAS ? causal_block_id(false) : xcd_block_id(BIAS ? together : 0);
   const int h = p.h0 + blk.y, b = p.b0 + blk.z;
   const int kblk = blk.x * BK;  // early key blocks see the most queries under a causal mask
   const int k0 = kblk + 32 * w, key = k0 + r;
@@ -274,8 +288,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 32
     uint2 a[4], c[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      a[g] = pack4_bf16(dk[db][4 * g], dk[db][4 * g + 1], dk[db][4 * g + 2], dk[db][4 * g + 3], p.scale);
-      c[g] = pack4_bf16(dv[db][4 * g], dv[db][4 * g + 1], dv[db][4 * g + 2], dv[db][4 * g + 3], 1.f);
+      a[g] = pack4_acc<D>(dk[db][4 * g], dk[db][4 * g + 1], dk[db][4 * g + 2], dk[db][4 * g + 3], p.scale);
+      c[g] = pack4_acc<D>(dv[db][4 * g], dv[db][4 * g + 1], dv[db][4 * g + 2], dv[db][4 * g + 3], 1.f);
     }
     store_row32(oK + 32 * db, a, hl, true);
     store_row32(oV + 32 * db, c, hl, true);

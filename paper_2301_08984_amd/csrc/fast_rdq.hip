@@ -42,7 +42,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(BIAS && CAU
   __shared__ __attribute__((aligned(16))) uint16_t smem[KV_ELEMS + BIAS_ELEMS];
   const int tid = threadIdx.x;
   const int lane = tid & 63, w = tid >> 6, r = lane & 31, hl = lane >> 5;
-  const BlockId blk = CAUSAL && !BIAS ? causal_block_id(false) : xcd_block_id(together);
+  const BlockId blk = CAUSAL && !BIAS ? causal_block_id(false) : xcd_block_id(BIAS ? together : 0);
   const int h = p.h0 + blk.y, b = p.b0 + blk.z;
   const int qblk = (gridDim.x - 1 - blk.x) * BM;  // long (late) causal blocks first
   const int q0 = qblk + 32 * w, q = q0 + r;
