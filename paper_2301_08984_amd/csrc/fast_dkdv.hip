@@ -310,25 +310,20 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(D <= 32
 // At D = 32 four work-groups fill a compute unit exactly (4 x 40 KB of LDS, 128 registers per lane),
 // which is also what a 1024 x 1024 head needs for all its tiles to be resident at once; the per-row
 // statistics therefore live in the padding of the Q tile's rows instead of arrays of their own.
-// HP = 2 (D = 32, heads side by side in memory): eight wavefronts cover the same tile of two
-// neighbouring heads, whose row slices are fetched together as 128 contiguous bytes: whole cache
-// lines instead of halves, at twice the bytes per cycle through the load path.
 typedef f32x4 f32x4_u __attribute__((aligned(4)));  // rows of S floats start anywhere
-template <int D, bool CAUSAL, int HP>
-__global__ __launch_bounds__(256 * HP)
+template <int D, bool CAUSAL>
+__global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu(D <= 32 ? 4 : 1, D <= 32 ? 4 : (D <= 64 ? 2 : 1))))
 void dbias_tile_kernel(KP p) {
   constexpr int KS = D / 16, LD = D + 8, CPR = D / 8;
   constexpr int CPT = 64 * CPR / 256;  // 16-byte chunks per thread per tensor tile
-  static_assert(HP == 1 || CPT == 1, "two heads per work-group: D = 32 only");
-  __shared__ __attribute__((aligned(16))) uint16_t sT[2][4][HP][64 * LD];  // Q, dO, K, V
-  const int tid = threadIdx.x, lane = tid & 63, w = (tid >> 6) & 3, hsel = tid >> 8, r = lane & 31, hl = lane >> 5;
-  const int Hc = (p.h1 - p.h0) / HP;  // head groups
+  __shared__ __attribute__((aligned(16))) uint16_t sT[2][4][64 * LD];  // Q, dO, K, V
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 31, hl = lane >> 5;
+  const int Hc = p.h1 - p.h0;
   // consecutive tiles (same head, neighbouring query tiles, all key tiles) run on one XCD, so a
   // row's Q/dO/K/V slices are fetched into few L2s instead of all eight
   const BlockId blk = xcd_block_id();
-  const int hA = p.h0 + (blk.z % Hc) * HP;  // first head of the work-group
-  const int h = hA + hsel;
+  const int h = p.h0 + blk.z % Hc;
   const int q0t = blk.y * 64, k0t = blk.x * 64;
   const int wq = w >> 1, wk = w & 1;
   const int q0 = q0t + 32 * wq, k0 = k0t + 32 * wk;
@@ -362,44 +357,33 @@ void dbias_tile_kernel(KP p) {
     // staging: thread -> (tensor-tile row, 16-byte chunk); Q/dO rows q0t.., K/V rows k0t..
     u32x4 pre[4][CPT];
     float pstat = 0.f;
-    // HP = 1: thread t takes the chunks t, t + 256, ... of its head's tile rows.  HP = 2: the two heads'
-    // slices of a row are 2 * CPR consecutive chunks (stride_h == D); thread t takes chunk t of them.
-    auto chunk = [&](int c, int& hh, int& row, int& col) {
-      const int idx = HP == 1 ? tid + c * 256 : tid;
-      row = idx / (CPR * HP);
-      hh = HP == 1 ? 0 : (idx % (CPR * HP)) / CPR;
-      col = (idx % CPR) * 8;
-    };
     auto gload = [&](int b) {
 #pragma unroll
       for (int c = 0; c < CPT; ++c) {
-        int hh, row, col;
-        chunk(c, hh, row, col);
+        const int idx = tid + c * 256, row = idx / CPR, col = (idx % CPR) * 8;
         const int rq = min(q0t + row, p.S - 1), rk = min(k0t + row, p.S - 1);
-        const int hc = HP == 1 ? h : hA;  // HP = 2: addressed from the first head, hh * D columns on
-        const int64_t ba = (int64_t)b * p.sb + (int64_t)hc * p.sh + hh * D + col;
+        const int64_t ba = (int64_t)b * p.sb + (int64_t)h * p.sh + col;
         pre[0][c] = *(const u32x4*)((const uint16_t*)p.Q + ba + (int64_t)rq * p.ss);
-        pre[1][c] = *(const u32x4*)((const uint16_t*)p.dO + (int64_t)(b - p.do_b0) * p.do_sb + (int64_t)(hc - p.do_h0) * p.do_sh + (int64_t)rq * p.do_ss + hh * D + col);
+        pre[1][c] = *(const u32x4*)((const uint16_t*)p.dO + (int64_t)(b - p.do_b0) * p.do_sb + (int64_t)(h - p.do_h0) * p.do_sh + (int64_t)rq * p.do_ss + col);
         pre[2][c] = *(const u32x4*)((const uint16_t*)p.K + ba + (int64_t)rk * p.ss);
         pre[3][c] = *(const u32x4*)((const uint16_t*)p.V + ba + (int64_t)rk * p.ss);
       }
-      if (tid < 128 * HP) {
-        const int hs = hA + tid / 128, i = min(q0t + (tid & 63), p.S - 1);
-        pstat = (tid & 64) == 0 ? p.lse[(int64_t)(b - p.lse_b0) * p.lse_sb + (int64_t)(hs - p.lse_h0) * p.lse_sh + i]
-                                : p.delta[(int64_t)(b - p.dl_b0) * p.dl_sb + (int64_t)(hs - p.dl_h0) * p.dl_sh + i];
+      if (tid < 128) {
+        const int i = min(q0t + (tid & 63), p.S - 1);
+        pstat = (tid & 64) == 0 ? p.lse[(int64_t)(b - p.lse_b0) * p.lse_sb + (int64_t)(h - p.lse_h0) * p.lse_sh + i]
+                                : p.delta[(int64_t)(b - p.dl_b0) * p.dl_sb + (int64_t)(h - p.dl_h0) * p.dl_sh + i];
       }
     };
     auto lstore = [&](int buf) {
 #pragma unroll
       for (int c = 0; c < CPT; ++c) {
-        int hh, row, col;
-        chunk(c, hh, row, col);
+        const int idx = tid + c * 256, row = idx / CPR, col = (idx % CPR) * 8;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) *(u32x4*)(&sT[buf][t][hh][row * LD + col]) = pre[t][c];
+        for (int t = 0; t < 4; ++t) *(u32x4*)(&sT[buf][t][row * LD + col]) = pre[t][c];
       }
       // -LSE (base 2) and Delta of query i: the two floats after the D elements of row i of the Q tile
-      if (tid < 128 * HP) {
-        float* st = (float*)(&sT[buf][0][tid / 128][(tid & 63) * LD + D]);
+      if (tid < 128) {
+        float* st = (float*)(&sT[buf][0][(tid & 63) * LD + D]);
         if ((tid & 64) == 0) st[0] = -pstat * LOG2E;
         else st[1] = pstat;
       }
@@ -412,20 +396,20 @@ void dbias_tile_kernel(KP p) {
       __syncthreads();
       if (b + 1 < blast) lstore(buf ^ 1);
       if (b + 2 < blast) gload(b + 2);
-      f32x16 sa = bz, pa;  // the scores start from bias / scale
+      const float2 st2 = *(const float2*)(&sT[buf][0][(32 * wq + r) * LD + D]);
+      const float nlse2 = st2.x;
+      f32x16 sa = bz, pa;  // the scores start from bias / scale, dP from -Delta: the same operations as in pair_dbias.hip, the same bits
 #pragma unroll
-      for (int v = 0; v < 16; ++v) pa[v] = 0.f;
+      for (int v = 0; v < 16; ++v) pa[v] = -st2.y;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
-        sa = mfma(lds_nat<LD>(sT[buf][2][hsel], 32 * wk + r, ks, hl), lds_nat<LD>(sT[buf][0][hsel], 32 * wq + r, ks, hl), sa);
-        pa = mfma(lds_nat<LD>(sT[buf][3][hsel], 32 * wk + r, ks, hl), lds_nat<LD>(sT[buf][1][hsel], 32 * wq + r, ks, hl), pa);
+        sa = mfma(lds_nat<LD>(sT[buf][2], 32 * wk + r, ks, hl), lds_nat<LD>(sT[buf][0], 32 * wq + r, ks, hl), sa);
+        pa = mfma(lds_nat<LD>(sT[buf][3], 32 * wk + r, ks, hl), lds_nat<LD>(sT[buf][1], 32 * wq + r, ks, hl), pa);
       }
-      const float2 st2 = *(const float2*)(&sT[buf][0][hsel][(32 * wq + r) * LD + D]);
-      const float nlse2 = st2.x, dlt = st2.y;
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const float e = fast_exp2(fmaf(sa[v], c1, nlse2));
-        float t = pa[v] - dlt;
+        float t = pa[v];
         if (CAUSAL) t = k0 + key_of(v, hl) > q ? 0.f : t;
         acc[v] = __builtin_fmaf(e, t, acc[v]);
       }
@@ -478,26 +462,19 @@ hipError_t dkdv_d(const KP& p, hipStream_t st) {
 }
 template <int D>
 hipError_t dbias_d(const KP& p, hipStream_t st) {
-  {  // callers guarantee S > 64 (fast_ok)
-    int ng = 1;
-    if (p.sm_partial) ng = (p.b1 - 1) / p.sm_gw - p.b0 / p.sm_gw + 1;
-    const int heads = p.h1 - p.h0;
-    const int64_t tiles = (int64_t)((p.S + 63) / 64) * ((p.S + 63) / 64);
-    if (D == 32 && heads % 2 == 0 && p.sh == D && p.do_sh == D && tiles * (heads / 2) * ng >= 384) {
-      // neighbouring heads are 64 bytes apart: two per work-group, if that still leaves one and a half work-groups per
-      // compute unit, of the two that fit (one head | two, us: 288 of them, 512 x 4 x 768: 173 | 199 a chunk; 338, 400 x 4 x 832:
-      // 305 | 316; 363, 300 x 6 x 700: 219 | 249; 392, 400 x 4 x 860: 185 | 170; 400, 200 x 8 x 640: 200 | 179; 450,
-      // 901 x 4 x 901: 252 | 183)
-      dim3 g((p.S + 63) / 64, (p.S + 63) / 64, heads / 2 * ng);
-      if (p.mask_kind == 1) dbias_tile_kernel<D <= 32 ? D : 32, true, 2><<<g, 512, 0, st>>>(p);
-      else dbias_tile_kernel<D <= 32 ? D : 32, false, 2><<<g, 512, 0, st>>>(p);
-      return hipGetLastError();
-    }
-    dim3 g((p.S + 63) / 64, (p.S + 63) / 64, heads * ng);
-    if (p.mask_kind == 1) dbias_tile_kernel<D, true, 1><<<g, 256, 0, st>>>(p);
-    else dbias_tile_kernel<D, false, 1><<<g, 256, 0, st>>>(p);
-    return hipGetLastError();
-  }
+  // callers guarantee S > 64 (fast_ok)
+  const int ng = p.sm_partial ? (p.b1 - 1) / p.sm_gw - p.b0 / p.sm_gw + 1 : 1, heads = p.h1 - p.h0, tiles = (p.S + 63) / 64;
+  const int64_t lim = 1ll << 30;
+  // Neighbouring heads 64 bytes apart: two per work-group (pair_dbias.hip), whose start takes longer, where that leaves a work-group for every compute
+  // unit (one head | two, us: 16 of them, 16 rows x 4 heads x 100: 11.3 | 13.1; 128, 16 x 8 x 200: 12.3 | 13.3; 256, 18 x 8 x 472: 22.6 | 22.3; 300, 46 x 4 x
+  // 295: 20.6 | 18.5; 400, 100 x 4 x 512: 53.6 | 40.6; 576, 128 rows of 8 x 384: 79 | 65)
+  if (D == 32 && heads % 2 == 0 && p.sh == D && p.do_sh == D && (int64_t)tiles * tiles * (heads / 2) * ng >= 256 &&
+      ((int64_t)(p.S - 1) * p.ss + 2 * D) * 2 < lim && ((int64_t)(p.S - 1) * p.do_ss + 2 * D) * 2 < lim)
+    return launch_pair_dbias(p, st);
+  const dim3 g(tiles, tiles, heads * ng);
+  if (p.mask_kind == 1) dbias_tile_kernel<D, true><<<g, 256, 0, st>>>(p);
+  else dbias_tile_kernel<D, false><<<g, 256, 0, st>>>(p);
+  return hipGetLastError();
 }
 
 }  // namespace

@@ -680,6 +680,7 @@ hipError_t launch_fast_fwd_wave128(const KP& p, bool recompute, hipStream_t st);
 hipError_t launch_fast_bwd_wave(const KP& p, hipStream_t st);
 hipError_t launch_fast_bwd_wave3(const KP& p, hipStream_t st);
 hipError_t launch_fast_dbias(const KP& p, hipStream_t st);
+hipError_t launch_pair_dbias(const KP& p, hipStream_t st);
 hipError_t launch_win_fwd(const KP& p, hipStream_t st);
 hipError_t launch_win_recompute_dq(const KP& p, hipStream_t st);
 hipError_t launch_win_kv(const KP& p, hipStream_t st);  // with the bias gradient's group partials
