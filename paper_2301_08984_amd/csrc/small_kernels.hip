@@ -91,10 +91,25 @@ __device__ inline void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// scores of query block qb against both key blocks, lane = query: x = s*c1 + bias*log2e, masked -> -inf
-template <bool REGION>
+// What a score costs in vector instructions: the logit t = s * scale + bias (one unpacking and one fused instruction; the bias is added in its own
+// units, so that it needs no factor of its own), the exponential of t * log2(e) less the row's constant (a fused instruction and a
+// quarter-rate one).  Registers that hold nothing but padding are left out: KG is the number of groups of 8 tokens of the second block of 32
+// that hold any, 3 for up to 56 tokens.  Step of 300 windows of 7 x 7 x 12 heads 71.1 -> 69.2 us, 64 x 4, region mask, 37.7 -> 36.8, 1024 of 8 x 8 x 8
+// 135.6 -> 134.0; of 4096 x 16, bound by memory, 683 -> 677.  (A transposed copy of the bias tile for the backward, 16 reads of 8 bytes instead of 64 of 2:
+// no change at 7 x 7, 76 -> 83 at 8 x 8.)
+template <int KG>
+constexpr int live(int blk) { return blk == 0 ? 16 : 4 * KG; }  // registers of a block
+__device__ inline void unpack4(uint2 u, float (&x)[4]) {
+  x[0] = __uint_as_float(u.x << 16);
+  x[1] = __uint_as_float(u.x & 0xffff0000u);
+  x[2] = __uint_as_float(u.y << 16);
+  x[3] = __uint_as_float(u.y & 0xffff0000u);
+}
+
+// logits of query block qb against both key blocks, lane = query, masked -> -inf
+template <bool REGION, int KG>
 __device__ inline void scores_by_query(const KP& p, const bf16x8 (&kf)[2][2], const bf16x8 (&qf)[2][2], int qb,
-                                       const uint16_t* bias_tile, const int* rid, int q, int hl, float c1,
+                                       const uint16_t* bias_tile, const int* rid, int q, int hl, float scale,
                                        float (&x)[2][16]) {
   const int my_rid = REGION ? rid[q] : 0;
 #pragma unroll
@@ -105,22 +120,40 @@ __device__ inline void scores_by_query(const KP& p, const bf16x8 (&kf)[2][2], co
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) sa = mfma(kf[kb][ks], qf[qb][ks], sa);
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
+    for (int g = 0; g < live<KG>(kb) / 4; ++g) {
       const int kbase = 32 * kb + 8 * g + 4 * hl;
-      const uint2 u = *(const uint2*)(bias_tile + q * BLD + kbase);
-      const float bl[4] = {__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u),
-                           __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u)};
+      float bl[4];
+      unpack4(*(const uint2*)(bias_tile + q * BLD + kbase), bl);
       int4 rk = {0, 0, 0, 0};
       if (REGION) rk = *(const int4*)(rid + kbase);
       const int rks[4] = {rk.x, rk.y, rk.z, rk.w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        float t = fmaf(sa[4 * g + e], c1, bl[e] * LOG2E);
+        float t = fmaf(sa[4 * g + e], scale, bl[e]);
         if (REGION) t = rks[e] != my_rid ? -INFINITY : t;
         x[kb][4 * g + e] = t;
       }
     }
   }
+}
+// the same turned into probabilities (not normalised; 0 in registers of padding): the row maximum in base-2 units in `m`, their sum
+template <int KG>
+__device__ inline float exponentials(float (&x)[2][16], float log2e, float& m) {
+  m = -1e30f;
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int v = 0; v < live<KG>(kb); ++v) m = fmaxf(m, x[kb][v]);
+  m = half_max(m) * log2e;
+  float l = 0.f;
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      x[kb][v] = v < live<KG>(kb) ? fast_exp2(fmaf(x[kb][v], log2e, -m)) : 0.f;
+      if (v < live<KG>(kb)) l += x[kb][v];
+    }
+  return half_sum(l);
 }
 
 // ---------------------------------------------------------------------------
@@ -131,7 +164,7 @@ __device__ inline void scores_by_query(const KP& p, const bf16x8 (&kf)[2][2], co
 // (one lane = one row, 16 bytes) costs four cache-line lookups per four lanes instead of one, and the
 // short-sequence kernels are bound by exactly that.
 // ---------------------------------------------------------------------------
-template <bool REGION>
+template <bool REGION, int KG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void small_fwd_kernel(KP p, int rows_per_wave) {
   __shared__ __attribute__((aligned(16))) uint16_t bias_tile[64 * BLD];
   __shared__ __attribute__((aligned(16))) WaveLds wl[4];
@@ -140,7 +173,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   build_bias_tile(p, h, bias_tile, tid);
   __syncthreads();
   WaveLds& L = wl[w];
-  const float c1 = p.scale * LOG2E;
+  const float scale = in_vgpr(p.scale), log2e = in_vgpr(LOG2E);
   const int bfirst = p.b0 + (blockIdx.x * 4 + w) * rows_per_wave;
   const int blast = min(bfirst + rows_per_wave, p.b1);
   // the operands of row b + 1 are fetched while row b is computed
@@ -180,22 +213,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int qb = 0; qb < 2; ++qb) {
       const int q = 32 * qb + r;
       float x[2][16];
-      if (masked) scores_by_query<true>(p, kf, qf, qb, bias_tile, L.rid, q, hl, c1, x);
-      else scores_by_query<false>(p, kf, qf, qb, bias_tile, L.rid, q, hl, c1, x);
-      float m = -1e30f;
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) m = fmaxf(m, x[kb][v]);
-      m = half_max(m);
-      float l = 0.f;
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          x[kb][v] = fast_exp2(x[kb][v] - m);
-          l += x[kb][v];
-        }
+      if (masked) scores_by_query<true, KG>(p, kf, qf, qb, bias_tile, L.rid, q, hl, scale, x);
+      else scores_by_query<false, KG>(p, kf, qf, qb, bias_tile, L.rid, q, hl, scale, x);
+      float m;
+      const float l = exponentials<KG>(x, log2e, m);
       f32x16 oacc;
 #pragma unroll
       for (int v = 0; v < 16; ++v) oacc[v] = 0.f;
@@ -205,7 +226,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int hb = 0; hb < 2; ++hb)
           oacc = mfma(lds_tr<SLD>(L.t0, 32 * kb + 16 * hb, 0, lane), pack8(&x[kb][8 * hb]), oacc);
       // normalise; the block's output row goes to the (consumed) Q tile, LSE straight to memory
-      l = half_sum(l);
       const float inv = 1.f / l;
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
@@ -235,7 +255,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 // ---------------------------------------------------------------------------
 // backward: grid (ceil(groups/4), heads); each wavefront takes one group of rows
 // ---------------------------------------------------------------------------
-template <bool REGION>
+template <bool REGION, int KG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void small_bwd_kernel(KP p) {
   __shared__ __attribute__((aligned(16))) uint16_t bias_tile[64 * BLD];
   __shared__ __attribute__((aligned(16))) WaveLds wl[4];
@@ -244,13 +264,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   build_bias_tile(p, h, bias_tile, tid);
   __syncthreads();
   WaveLds& L = wl[w];
-  const float c1 = p.scale * LOG2E;
+  const float scale = in_vgpr(p.scale), log2e = in_vgpr(LOG2E);
   const int g = p.b0 / p.sm_gw + blockIdx.x * 4 + w;  // global group index
   const int bfirst = max(g * p.sm_gw, p.b0);
   const int blast = min((g + 1) * p.sm_gw, p.b1);
   if (bfirst >= blast) return;
   // bias-gradient accumulators, lane = key: acc[qb][kb][v] for query 32*qb + key_of(v), key 32*kb + r
-  float acc[2][2][16];
+  float acc[2][2][16];  // (those of padding are never used)
   float* part = nullptr;
   if (p.sm_partial) {
     part = p.sm_partial + ((int64_t)((g - p.sm_g0) % p.sm_ring) * p.sm_hs + (h - p.sm_h0)) * p.S * p.S;
@@ -260,7 +280,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
+        for (int v = 0; v < live<KG>(qb); ++v) {
           const int q = 32 * qb + key_of(v, hl), k = 32 * kb + r;
           acc[qb][kb][v] = (resume && q < p.S && k < p.S) ? part[q * p.S + k] : 0.f;
         }
@@ -313,24 +333,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           qf[qb][ks] = tile_nat(L.t2, qb, ks, r, hl);
           gq_[ks] = tile_nat(L.t1, qb, ks, r, hl);
         }
-        if (masked) scores_by_query<true>(p, kf, qf, qb, bias_tile, L.rid, q, hl, c1, x);
-        else scores_by_query<false>(p, kf, qf, qb, bias_tile, L.rid, q, hl, c1, x);
+        if (masked) scores_by_query<true, KG>(p, kf, qf, qb, bias_tile, L.rid, q, hl, scale, x);
+        else scores_by_query<false, KG>(p, kf, qf, qb, bias_tile, L.rid, q, hl, scale, x);
       }
-      float m = -1e30f;
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) m = fmaxf(m, x[kb][v]);
-      m = half_max(m);
-      float l = 0.f;
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          x[kb][v] = fast_exp2(x[kb][v] - m);
-          l += x[kb][v];
-        }
-      l = half_sum(l);
+      float m, l = exponentials<KG>(x, log2e, m);
       l = q < p.S ? l : 1.f;  // padded queries: keep the statistics finite
       const float inv = 1.f / l;
       f32x16 pa[2];
@@ -345,7 +351,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
+        for (int v = 0; v < live<KG>(kb); ++v) {
           x[kb][v] *= inv;
           dl = fmaf(x[kb][v], pa[kb][v], dl);
         }
@@ -360,7 +366,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) x[kb][v] *= (pa[kb][v] - dl);
+        for (int v = 0; v < live<KG>(kb); ++v) x[kb][v] *= (pa[kb][v] - dl);
 #pragma unroll
         for (int hb = 0; hb < 2; ++hb)
           dq = mfma(lds_tr<SLD>(L.t0, 32 * kb + 16 * hb, 0, lane), pack8(&x[kb][8 * hb]), dq);
@@ -396,20 +402,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
           pa = mfma(tile_nat(L.t1, qb, ks, r, hl), vf[kb][ks], pa);
         }
         float pr[16], ds[16];
+#pragma unroll
+        for (int v = live<KG>(qb); v < 16; ++v) pr[v] = ds[v] = 0.f;
         auto probs = [&](auto masked_tag) {
           constexpr bool MASKED = decltype(masked_tag)::value;
 #pragma unroll
-          for (int gq = 0; gq < 4; ++gq) {
+          for (int gq = 0; gq < live<KG>(qb) / 4; ++gq) {
             const int qbase = 32 * qb + 8 * gq + 4 * hl;
             const f32x4 l4 = *(const f32x4*)(L.lse2 + qbase);
             const f32x4 d4 = *(const f32x4*)(L.delta + qbase);
             int4 rq = {0, 0, 0, 0};
             if (MASKED) rq = *(const int4*)(L.rid + qbase);
             const int rqs[4] = {rq.x, rq.y, rq.z, rq.w};
+            float bl[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bl[e] = bf2f(bias_tile[(qbase + e) * BLD + key]);
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-              const float bl = bf2f(bias_tile[(qbase + e) * BLD + key]) * LOG2E;
-              float t = fmaf(sa[4 * gq + e], c1, bl) - l4[e];
+              float t = fmaf(fmaf(sa[4 * gq + e], scale, bl[e]), log2e, -l4[e]);
               if (MASKED) t = rqs[e] != my_rid ? -INFINITY : t;
               const float pe = fast_exp2(t);
               pr[4 * gq + e] = pe;
@@ -421,7 +431,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         else probs(std::false_type{});
         if (part) {
 #pragma unroll
-          for (int v = 0; v < 16; ++v) acc[qb][kb][v] += ds[v];
+          for (int v = 0; v < live<KG>(qb); ++v) acc[qb][kb][v] += ds[v];
         }
 #pragma unroll
         for (int hb = 0; hb < 2; ++hb) {
@@ -451,7 +461,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
+        for (int v = 0; v < live<KG>(qb); ++v) {
           const int q = 32 * qb + key_of(v, hl), k = 32 * kb + r;
           if (q < p.S && k < p.S) part[q * p.S + k] = acc[qb][kb][v];
         }
@@ -501,6 +511,17 @@ __global__ __launch_bounds__(256) void group_reduce_kernel(const float* partial,
   *out = a;
 }
 
+template <class F>
+hipError_t with_variant(const KP& p, F f) {
+  auto tokens = [&](auto region) {
+    if (p.S <= 56) f(region, std::integral_constant<int, 3>{});
+    else f(region, std::integral_constant<int, 4>{});
+  };
+  if (p.mask_kind == 2) tokens(std::true_type{});
+  else tokens(std::false_type{});
+  return hipGetLastError();
+}
+
 }  // namespace
 
 bool small_supported(const KP& p, bool bf16) {
@@ -512,17 +533,13 @@ hipError_t launch_small_fwd(const KP& p, hipStream_t st) {
   // the launch fit the 2048 wavefronts that the chip holds, up to 8.  Forward of 17 rows x 8 heads x 49: 23 -> 10 us.
   const int rows = p.b1 - p.b0, even = (rows * (p.h1 - p.h0) + 2047) / 2048, rows_per_wave = even > 8 ? 8 : even;
   dim3 g((rows + 4 * rows_per_wave - 1) / (4 * rows_per_wave), p.h1 - p.h0);
-  if (p.mask_kind == 2) small_fwd_kernel<true><<<g, 256, 0, st>>>(p, rows_per_wave);
-  else small_fwd_kernel<false><<<g, 256, 0, st>>>(p, rows_per_wave);
-  return hipGetLastError();
+  return with_variant(p, [&](auto region, auto kg) { small_fwd_kernel<region(), kg()><<<g, 256, 0, st>>>(p, rows_per_wave); });
 }
 
 hipError_t launch_small_bwd(const KP& p, hipStream_t st) {
   const int ng = (p.b1 - 1) / p.sm_gw - p.b0 / p.sm_gw + 1;
   dim3 g((ng + 3) / 4, p.h1 - p.h0);
-  if (p.mask_kind == 2) small_bwd_kernel<true><<<g, 256, 0, st>>>(p);
-  else small_bwd_kernel<false><<<g, 256, 0, st>>>(p);
-  return hipGetLastError();
+  return with_variant(p, [&](auto region, auto kg) { small_bwd_kernel<region(), kg()><<<g, 256, 0, st>>>(p); });
 }
 
 hipError_t launch_group_fold(float* partial, float* dense, int ring, int hs, int hd0, int nh, int S, int slice,
