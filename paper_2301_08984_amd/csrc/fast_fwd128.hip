@@ -1,4 +1,4 @@
-// Forward / recompute kernel for large shares at head size 128 without a bias: the 128-query
+// Forward kernel, and with a gate the recompute pass (without: fast_stat128.hip), for large shares at head size 128 without a bias: the 128-query
 // work-group of fast_fwd.hip (four wavefronts of 32 queries that share every 64-key K / V tile) with
 // the tiles fetched from memory straight into LDS (wave_dma.h).
 //

@@ -670,6 +670,7 @@ inline bool rdq_ok(const KP& p) {
 hipError_t launch_fast_fwd(const KP& p, bool recompute, hipStream_t st);
 hipError_t launch_pair_fwd(const KP& p, hipStream_t st);
 hipError_t launch_fast_fwd128(const KP& p, bool recompute, hipStream_t st);
+hipError_t launch_fast_stat128(const KP& p, hipStream_t st);  // the recompute pass without a gate
 hipError_t launch_fast_dq(const KP& p, hipStream_t st);
 hipError_t launch_fast_dq128(const KP& p, hipStream_t st);
 hipError_t launch_fast_recompute_dq(const KP& p, hipStream_t st);
