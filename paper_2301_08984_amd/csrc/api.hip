@@ -374,7 +374,10 @@ int run_bwd(const ss_attn_desc* d, Family fam, const WsLayout& w, const void* Q,
         set_groups(p);
       }
       p.sm_gw = w.gw > 0 ? w.gw : 8;
-      if (ssa::mfma_fuses_recompute_dq(p)) {
+      const bool one = ssa::win_ok(p);  // every gradient in one launch
+      if (one) {
+        SS_LAUNCH(SS_K_DQ_DKDV, ssa::launch_mfma_recompute_dq(p, st), "backward (windows)");
+      } else if (ssa::mfma_fuses_recompute_dq(p)) {
         SS_LAUNCH(SS_K_RECOMPUTE_DQ, ssa::launch_mfma_recompute_dq(p, st), "recompute + dQ");
         SS_LAUNCH(SS_K_DKDV, ssa::launch_mfma_dkdv(p, st), "dK/dV");
       } else {
@@ -387,7 +390,7 @@ int run_bwd(const ss_attn_desc* d, Family fam, const WsLayout& w, const void* Q,
         }
       }
       if (want_dbias) {
-        SS_LAUNCH(SS_K_DBIAS, ssa::launch_mfma_dbias(p, st), "dBias");
+        if (!one) SS_LAUNCH(SS_K_DBIAS, ssa::launch_mfma_dbias(p, st), "dBias");
         if (w.gw > 0) {
           const int rf = fold_groups(p, c);
           if (rf != SS_OK) return rf;

@@ -13,15 +13,15 @@ namespace {
 // 256 rows 373 | 329; odd lengths, whose parked tiles are loaded unaligned: 64 x 8 x 501: 58.0 | 58.3, 512 x 4 x 301: 107 | 92.
 // Backward: dK / dV 9 % shorter (1024 x 4 x 1024: 2037 -> 1850 us), and the copy replaces the transposed bf16 one; the
 // recompute + dQ kernel gains nothing from a copy of its own (2469 | 2510).
-// Windows (win_kernels.hip; the backward takes both copies): without one a work-group gathers the bias from the table in
-// LDS and holds it in registers.  Without | with, us, rows x heads of 256, 512, 1024, 2048 (8 heads, region mask): 12 x 12 tokens forward
-// 10.3 | 13.7, 17.5 | 16.0, 31.8 | 25.9, 64.0 | 37.6; backward of 32, 64, 128, 256: 39.3 | 39.0, 41.9 | 41.9, 48.7 | 46.9, 56.9 | 54.5 (4 heads: 44.3 | 43.5 at 64);
-// backward of 9 x 9: 36.6 | 39.2, 42.2 | 43.8, 51.9 | 50.9, 70.9 | 67.6, of 11 x 11: 47.4 | 47.0, 54.1 | 54.7, 68.1 | 65.7, 93.6 | 90.2; forward of 9 x 9:
-// 7.9 | 12.5, 7.9 | 12.4, 9.6 | 14.1, 19.2 | 19.8, of 11 x 11: 8.5 | 12.4, 9.4 | 13.8, 15.7 | 17.0, 26.4 | 25.6.
+// Windows (win_kernels.hip; the backward, win_bwd.hip, takes packed bf16): without one a work-group gathers the bias from the table in
+// LDS and holds it in registers.  Without | with, us, rows x heads of 256, 512, 1024, 2048 (8 heads, region mask): forward of 12 x 12 tokens
+// 10.3 | 13.7, 17.5 | 16.0, 31.8 | 25.9, 64.0 | 37.6; of 9 x 9 7.9 | 12.5, 7.9 | 12.4, 9.6 | 14.1, 19.2 | 19.8, of 11 x 11 8.5 | 12.4, 9.4 | 13.8, 15.7 | 17.0,
+// 26.4 | 25.6.  Backward with a dense bias: 12 x 12 tokens, 64 rows x 8 heads 44.3 | 40.5, 512 x 8 128 | 126; 11 x 11, 512 x 8 90 | 92.
+inline int64_t win_packed_bytes(int S, int heads) { return (int64_t)heads * ((S + 15) / 16) * ((S + 15) / 16) * 512; }
 inline size_t bias_copy_bytes_for(const KP& p, bool backward, int64_t rows, int heads) {
   if (win_ok(p)) {
     if (p.bias_kind == 0 || (backward ? rows * heads < (p.S <= 128 ? 1024 : 64) : p.S <= 128 || rows * heads < 512)) return 0;
-    return (size_t)bias_copy_bytes(p.S, heads) * (backward ? 2 : 1);
+    return backward ? (size_t)win_packed_bytes(p.S, heads) : (size_t)bias_copy_bytes(p.S, heads);
   }
   if (!pair_fwd_ok(p) || p.S > 16384) return 0;
   const int64_t row_stride = p.ss > (int64_t)p.H * p.D ? p.ss : (int64_t)p.H * p.D;
@@ -50,43 +50,50 @@ __global__ __launch_bounds__(256) void bias_copy_kernel(const uint16_t* src, flo
     out[64 * g] = x;
   }
 }
-// The same of a window's bias, from the relative-position table or the dense matrix; z = head, then the copy.
-__global__ __launch_bounds__(256) void win_bias_copy_kernel(KP p, float* dst, int heads) {
+// an entry of a window's bias, from the relative-position table or the dense matrix: query i, key j
+__device__ inline uint16_t win_bias_entry(const KP& p, int h, int i, int j) {
+  const uint16_t* b = (const uint16_t*)p.bias;
+  if (p.bias_kind != 2) return b[((int64_t)h * p.S + i) * p.S + j];
+  const int rowlen = 2 * p.win_w - 1, dy = i / p.win_w - j / p.win_w + p.win_h - 1, dx = i % p.win_w - j % p.win_w + p.win_w - 1;
+  return b[(int64_t)h * ((2 * p.win_h - 1) * rowlen) + dy * rowlen + dx];
+}
+// The same of a window's bias.
+__global__ __launch_bounds__(256) void win_bias_copy_kernel(KP p, float* dst) {
   const int lane = threadIdx.x & 63, block = blockIdx.x * 4 + (threadIdx.x >> 6), strip = blockIdx.y, S = p.S;
   if (block >= bias_copy_blocks(S)) return;
-  const int head = blockIdx.z % heads, by_key = blockIdx.z / heads, h = p.bc_h0 + head;
-  const int R = (2 * p.win_h - 1) * (2 * p.win_w - 1);
-  const uint16_t* from = (const uint16_t*)p.bias + (p.bias_kind == 2 ? (int64_t)h * R : (int64_t)h * S * S);
   f32x4* out = (f32x4*)dst + ((blockIdx.z * bias_copy_strips(S) + strip) * bias_copy_blocks(S) + block) * 256 + lane;
-  const int row = 32 * strip + (lane & 31), col = 32 * block + 4 * (lane >> 5), rc = min(row, S - 1);
-  const int ry = rc / p.win_w, rx = rc % p.win_w;
+  const int row = 32 * strip + (lane & 31), col = 32 * block + 4 * (lane >> 5);
 #pragma unroll
   for (int g = 0; g < 4; ++g) {
     f32x4 x;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int c = col + 8 * g + e, cc = min(c, S - 1);
-      int at;
-      if (p.bias_kind == 2) {
-        const int cy = cc / p.win_w, cx = cc % p.win_w, sign = by_key ? -1 : 1;  // query minus key
-        at = (sign * (ry - cy) + p.win_h - 1) * (2 * p.win_w - 1) + sign * (rx - cx) + p.win_w - 1;
-      } else {
-        at = by_key ? cc * S + rc : rc * S + cc;
-      }
-      x[e] = row < S && c < S ? bf2f(from[at]) * p.inv_scale : -INFINITY;
+      const int c = col + 8 * g + e;
+      const float b = bf2f(win_bias_entry(p, p.bc_h0 + blockIdx.z, min(row, S - 1), min(c, S - 1)));
+      x[e] = row < S && c < S ? b * p.inv_scale : -INFINITY;
     }
     out[64 * g] = x;
   }
 }
-// Makes the copies that bias_copy_bytes_for asks for, of the heads [h0, h1), and points `p` at them.
+// What the backward of windows reads (win_bwd.hip): bf16, blocks of 16 queries x 16 keys, lane l the query l % 16 and four keys from 4 (l / 16) on; -inf
+// past the last key.  x = block of keys, y = block of queries, z = head.
+__global__ __launch_bounds__(64) void win_bias_pack_kernel(KP p, uint2* dst) {
+  const int lane = threadIdx.x, i = min(16 * (int)blockIdx.y + (lane & 15), p.S - 1), j0 = 16 * blockIdx.x + 4 * (lane >> 4);
+  uint32_t x[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) x[e] = j0 + e < p.S ? win_bias_entry(p, p.bc_h0 + blockIdx.z, i, min(j0 + e, p.S - 1)) : 0xff80u;
+  dst[((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 64 + lane] = uint2{x[0] | x[1] << 16, x[2] | x[3] << 16};
+}
+// Makes the copy that bias_copy_bytes_for asks for, of the heads [h0, h1), and points `p` at it.
 inline hipError_t launch_bias_copies(KP& p, float* copy, bool backward, int h0, int h1, hipStream_t st) {
-  const int heads = h1 - h0, kinds = win_ok(p) && backward ? 2 : 1;
+  const int heads = h1 - h0;
   p.bc_h0 = h0;
-  const dim3 g((unsigned)((bias_copy_blocks(p.S) + 3) / 4), (unsigned)bias_copy_strips(p.S), heads * kinds);
-  if (win_ok(p)) win_bias_copy_kernel<<<g, 256, 0, st>>>(p, copy, heads);
+  const dim3 g((unsigned)((bias_copy_blocks(p.S) + 3) / 4), (unsigned)bias_copy_strips(p.S), heads);
+  if (win_ok(p) && backward) win_bias_pack_kernel<<<dim3((p.S + 15) / 16, (p.S + 15) / 16, heads), 64, 0, st>>>(p, (uint2*)copy);
+  else if (win_ok(p)) win_bias_copy_kernel<<<g, 256, 0, st>>>(p, copy);
   else bias_copy_kernel<<<g, 256, 0, st>>>((const uint16_t*)p.bias, copy, p.S, h0, backward ? 1 : 0, p.inv_scale);
-  if (!backward || kinds == 2) p.bias_q = copy;
-  if (backward) p.bias_k = copy + (kinds - 1) * bias_copy_bytes(p.S, heads) / 4;
+  if (backward) p.bias_k = copy;
+  else p.bias_q = copy;
   return hipGetLastError();
 }
 

@@ -46,7 +46,7 @@ struct KP {
   int share_b0;     // first row of the whole share
   int share_units;  // (row, head) pairs in the whole share [lo,hi): kernel-shape choices use this, never the chunk
   // copies of a dense bias in accumulator layout (BiasCopy in mfma_common.h) from head bc_h0 on, or nullptr: a row of
-  // the copy is a query, a key
+  // the copy is a query, a key (windows: packed bf16, see win_bias_pack_kernel in bias_copy.h)
   const float *bias_q, *bias_k;
   int bc_h0;
   float scale, inv_scale;
@@ -83,7 +83,7 @@ hipError_t launch_mfma_dbias(const KP& p, hipStream_t st);
 bool mfma_fuses_dq_dkdv(const KP& p);
 hipError_t launch_mfma_dq_dkdv(const KP& p, hipStream_t st);
 bool mfma_fuses_recompute_dq(const KP& p);
-hipError_t launch_mfma_recompute_dq(const KP& p, hipStream_t st);
+hipError_t launch_mfma_recompute_dq(const KP& p, hipStream_t st);  // windows: the whole backward
 bool mfma_wants_bias_transpose(const KP& p);    // the backward kernels read a transposed bias copy
 int mfma_dbias_group_rows(const KP& p);         // rows per group of the grouped bias-gradient sum that fills the chip; 0: no groups
 hipError_t launch_bias_transpose(const void* bias, void* biasT, int S, int h0, int h1, hipStream_t st);

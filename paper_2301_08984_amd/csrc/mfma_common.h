@@ -360,7 +360,7 @@ __device__ inline BlockId causal_block_id(bool pairs) {
   return b;
 }
 
-// The two-product form of dQ (fast_rdq.hip, win_kernels.hip) rounds p dP to bf16 before the mean of dP is taken off,
+// The two-product form of dQ (fast_rdq.hip) rounds p dP to bf16 before the mean of dP is taken off,
 // so what dP has in common over a query's keys (as activations and gradients with a mean of their own give
 // it) would cost its size times 2^-9.  dS does not change if a constant per query is subtracted from every dP: the mean
 // of dP so far, weighted with the probabilities, the block at hand included.  It is taken anew on the first block in which a
@@ -552,7 +552,7 @@ inline bool fast_ok(const KP& p) {
   return true;
 }
 
-// the window kernels (win_kernels.hip) serve: head size 32, 65 to 160 tokens, a relative-position bias or a
+// the window kernels (win_kernels.hip, win_bwd.hip) serve: head size 32, 65 to 160 tokens, a relative-position bias or a
 // region mask (a bf16 bias of either kind, or none; no causal mask), a positive scale
 inline bool win_ok(const KP& p) {
   if (p.D != 32 || p.S <= 64 || p.S > 160 || !(p.scale > 0.f) || p.mask_kind == 1) return false;
@@ -570,8 +570,8 @@ inline bool win_ok(const KP& p) {
 // otherwise the share's rows are cut into groups so that about two work-groups per compute unit exist.
 inline int dbias_group_rows(const KP& p) {
   if (win_ok(p)) {
-    // one work-group per group and head, all of them at one time: 256 of five wavefronts, 512 of four or three
-    const int most = p.S > 128 ? 256 : 512;
+    // one work-group per group and head, all of them at one time: two on a compute unit of up to 112 tokens, one of more (win_bwd.hip)
+    const int most = p.S > 112 ? 256 : 512;
     return p.bias_kind != 0 ? (p.share_units + most - 1) / most : 0;
   }
   if (p.bias_kind != 1 || !fast_ok(p)) return 0;
@@ -683,7 +683,6 @@ hipError_t launch_fast_bwd_wave3(const KP& p, hipStream_t st);
 hipError_t launch_fast_dbias(const KP& p, hipStream_t st);
 hipError_t launch_pair_dbias(const KP& p, hipStream_t st);
 hipError_t launch_win_fwd(const KP& p, hipStream_t st);
-hipError_t launch_win_recompute_dq(const KP& p, hipStream_t st);
-hipError_t launch_win_kv(const KP& p, hipStream_t st);  // with the bias gradient's group partials
+hipError_t launch_win_bwd(const KP& p, hipStream_t st);  // all gradients, the bias gradient's group partials among them
 
 }  // namespace ssa

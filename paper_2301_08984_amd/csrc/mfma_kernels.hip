@@ -626,12 +626,10 @@ hipError_t launch_mfma_dq(const KP& p, hipStream_t st) {
   SS_DISPATCH_D(dq_d, p, st)
 }
 hipError_t launch_mfma_dkdv(const KP& p, hipStream_t st) {
-  if (win_ok(p)) return launch_win_kv(p, st);
   if (fast_ok(p)) return launch_fast_dkdv(p, st);
   SS_DISPATCH_D(dkdv_d, p, st)
 }
 hipError_t launch_mfma_dbias(const KP& p, hipStream_t st) {
-  if (win_ok(p)) return hipSuccess;  // the window kernels' dK/dV launch leaves the group partials of the bias gradient too
   if (fast_ok(p) && p.bias_kind == 1) return launch_fast_dbias(p, st);
   SS_DISPATCH_D(dbias_d, p, st)
 }
@@ -644,11 +642,9 @@ hipError_t launch_mfma_dq_dkdv(const KP& p, hipStream_t st) {
   if (p.D == 128 && p.bias_kind == 0) return launch_fast_bwd_wave3(p, st);
   return launch_fast_bwd_wave(p, st);
 }
-bool mfma_fuses_recompute_dq(const KP& p) {
-  return win_ok(p) || rdq_ok(p);
-}
+bool mfma_fuses_recompute_dq(const KP& p) { return rdq_ok(p); }
 hipError_t launch_mfma_recompute_dq(const KP& p, hipStream_t st) {
-  return win_ok(p) ? launch_win_recompute_dq(p, st) : launch_fast_recompute_dq(p, st);
+  return win_ok(p) ? launch_win_bwd(p, st) : launch_fast_recompute_dq(p, st);
 }
 int mfma_dbias_group_rows(const KP& p) { return dbias_group_rows(p); }
 

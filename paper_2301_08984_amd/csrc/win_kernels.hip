@@ -1,16 +1,14 @@
-// Attention over windows of 65 to 160 tokens with head size 32, bf16: a whole row (b, h) is small
-// enough to share one work-group, too large for one wavefront (small_kernels.hip ends at 64 tokens).
+// Forward of attention over windows of 65 to 160 tokens with head size 32, bf16: a whole row (b, h) is small
+// enough to share one work-group, too large for one wavefront (small_kernels.hip ends at 64 tokens; the backward is win_bwd.hip).
 //
-// A work-group has one wavefront per 32-token block (NB = 3, 4 or 5); K and V (or Q and dO) of the row are staged in LDS
-// once for all of them.  The scores start from the bias (BiasCopy in mfma_common.h): large shares read it in accumulator
-// layout, expanded from the relative-position table once per call into the library's buffer; others, captured calls and
-// forwards of up to 128 tokens gather it once per work-group and keep it in registers, packed bf16, with the same values.
+// A work-group has one wavefront per 32-token block (NB = 3, 4 or 5); K and V of the row are staged in LDS
+// once for all of them.  The scores start from the bias (BiasCopy in mfma_common.h): of more than 128 tokens large shares read it in accumulator
+// layout, expanded from the relative-position table once per call into the library's buffer; others and captured calls
+// gather it once per work-group and keep it in registers, packed bf16, with the same values.
 //
 // What bounds it: the chain of loads, matrix steps and vector arithmetic of the few wavefronts that fit a compute unit.
-// The bias held in registers by every wavefront (40 of them at NB = 5) left one or two work-groups per compute unit and
-// spills in the recompute + dQ kernel; loaded block by block, and without the sum for O, which nobody needs without a gate, that
-// kernel fits 128 registers, three work-groups.  512 windows of 12 x 12 tokens, 8 heads, us: forward 100 -> 71, recompute +
-// dQ 258 -> 96, dK / dV and the bias gradient 148 -> 129, copies 11, step 518 -> 306; 1024 x 16 x 9 x 9 backward 560 -> 367.
+// The bias held in registers by every wavefront (40 of them at NB = 5) left one or two work-groups per compute unit.
+// 512 windows of 12 x 12 tokens, 8 heads: 100 -> 71 us.
 #include "mfma_common.h"
 
 namespace ssa {
@@ -24,9 +22,8 @@ enum { WB_NONE = 0, WB_COPY = 1, WB_REGS = 2 };
 
 template <int NB>
 struct WinLds {
-  uint16_t t0[32 * NB * WLD];  // forward, dQ: K; dK/dV: Q
-  uint16_t t1[32 * NB * WLD];  // forward, dQ: V; dK/dV: dO
-  alignas(16) float lse2[32 * NB], delta[32 * NB];
+  uint16_t t0[32 * NB * WLD];  // K
+  uint16_t t1[32 * NB * WLD];  // V
   alignas(16) int rid[32 * NB];
   alignas(16) int cidx[32 * NB];
   uint16_t table[MAX_RELPOS_R];
@@ -45,21 +42,21 @@ __device__ inline void table_setup(const KP& p, int h, WinLds<NB>& L, int tid) {
 }
 
 // What the scores of a block start from: element v is the pair (lane's row, column 32 c + key_of(v, hl)), bias / scale,
-// -inf where either lies outside the window.  KEYS: the lane's row is a key and the columns are queries.
+// -inf where either lies outside the window.
 //  WB_COPY: loaded from the copy in accumulator layout;
 //  WB_REGS: gathered once per work-group and kept in registers, packed bf16, 8 per block (the caller unrolls the blocks).
-template <int NB, int WB, bool KEYS>
+template <int NB, int WB>
 struct WinBias {
   BiasCopy bc;
   uint32_t bz[WB == WB_REGS ? NB : 1][8];
   // WB_REGS: the table and the coordinates are in LDS and visible
   __device__ void init(const KP& p, const WinLds<NB>& L, int h, int w, int lane) {
-    if (WB == WB_COPY) bc.init(KEYS ? p.bias_k : p.bias_q, h - p.bc_h0, 32 * w, p.S, lane);
+    if (WB == WB_COPY) bc.init(p.bias_q, h - p.bc_h0, 32 * w, p.S, lane);
     if (WB != WB_REGS) return;
     const int row = 32 * w + (lane & 31), hl = lane >> 5, rc = min(row, p.S - 1);
     const int c0 = (p.win_h - 1) * (2 * p.win_w - 1) + (p.win_w - 1);
     const uint16_t* m = (const uint16_t*)p.bias + (int64_t)h * p.S * p.S;
-    const int cr = p.bias_kind == 2 ? L.cidx[rc] + (KEYS ? -c0 : c0) : 0;
+    const int cr = p.bias_kind == 2 ? L.cidx[rc] + c0 : 0;
 #pragma unroll
     for (int c = 0; c < NB; ++c) {
 #pragma unroll
@@ -68,16 +65,13 @@ struct WinBias {
         uint32_t x[4];
         if (p.bias_kind == 2) {
           const int4 ck = *(const int4*)(L.cidx + k);
-          x[0] = L.table[KEYS ? ck.x - cr : cr - ck.x];
-          x[1] = L.table[KEYS ? ck.y - cr : cr - ck.y];
-          x[2] = L.table[KEYS ? ck.z - cr : cr - ck.z];
-          x[3] = L.table[KEYS ? ck.w - cr : cr - ck.w];
+          x[0] = L.table[cr - ck.x];
+          x[1] = L.table[cr - ck.y];
+          x[2] = L.table[cr - ck.z];
+          x[3] = L.table[cr - ck.w];
         } else {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int kc = min(k + e, p.S - 1);
-            x[e] = m[KEYS ? kc * p.S + rc : rc * p.S + kc];
-          }
+          for (int e = 0; e < 4; ++e) x[e] = m[rc * p.S + min(k + e, p.S - 1)];
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[e] = row < p.S && k + e < p.S ? x[e] : 0xff80u;  // -inf
@@ -134,17 +128,6 @@ struct RowStage {
   }
 };
 
-// does the row's region mask mask anything at all?  Most windows of a shifted map lie inside one region;
-// their rows take the code without the comparison (uniform)
-template <int NB>
-__device__ inline bool row_is_masked(const int* ids, int S, int lane) {
-  const int first = ids[0];
-  int other = 0;  // all loads in flight together
-#pragma unroll
-  for (int c = 0; c < (NB + 1) / 2; ++c) other |= ids[min(lane + 64 * c, S - 1)] ^ first;
-  return __builtin_amdgcn_ballot_w64(other != 0) != 0;
-}
-
 // pairs of different regions: -inf
 __device__ inline void mask_regions(f32x16& s, const int* rid, int my_rid, int k0, int hl) {
 #pragma unroll
@@ -194,7 +177,7 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB == W
     table_setup(p, h, L, tid);
     __syncthreads();
   }
-  WinBias<NB, WB, false> bias;
+  WinBias<NB, WB> bias;
   bias.init(p, L, h, w, lane);
   f32x16 cz;  // of the block, then of the next one
   if (AHEAD) bias.get(p, w, 0, lane, cz);
@@ -269,306 +252,6 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB == W
   }
 }
 
-// ---------------------------------------------------------------------------
-// recompute pass and dQ in one walk over the keys (the two-product form of fast_rdq.hip): statistics, Delta, dQ; lane =
-// query.  GATED: dG and the pre-gated dO too, for which O is summed up; without a gate nobody needs O, and Delta is
-// sum_j p (dP - c) / sum_j p + c with both sums in fp32.
-// ---------------------------------------------------------------------------
-template <int NB, bool REGION, int WB, bool GATED>
-__global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(GATED || WB == WB_REGS ? 3 : 4, GATED || WB == WB_REGS ? 3 : 4))) void win_rdq_kernel(KP p) {
-#pragma clang fp contract(off)  // the variants are to give the same bits
-  __shared__ __attribute__((aligned(16))) WinLds<NB> L;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 31, hl = lane >> 5;
-  constexpr int BLOCK_UNROLL = WB == WB_REGS ? NB : 1;
-  const BlockId blk = xcd_block_id();
-  const int h = p.h0 + blk.x, b = p.b0 + blk.z, q = 32 * w + r, qc = min(q, p.S - 1);
-  const int64_t base = (int64_t)b * p.sb + (int64_t)h * p.sh;
-  RowStage<NB> row;
-  row.load((const uint16_t*)p.K + base, p.ss, (const uint16_t*)p.V + base, p.ss, p.S, tid);
-  bf16x8 qf[2], gf[2];
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks) {
-    const int64_t at = base + (int64_t)qc * p.ss + 16 * ks + 8 * hl;
-    qf[ks] = *(const bf16x8*)((const uint16_t*)p.Q + at);
-    union { u32x4 u; uint32_t w[4]; bf16x8 v; } o;
-    o.u = *(const u32x4*)((const uint16_t*)p.dY + at);
-    if (GATED) {  // dO = dY * gate, rounded as the epilogue rounds the copy that the later kernel reads
-      const u32x4 gg = *(const u32x4*)((const uint16_t*)p.G + at);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float g0 = __uint_as_float(gg[e] << 16), g1 = __uint_as_float(gg[e] & 0xffff0000u);
-        o.w[e] = pack2_bf16(__uint_as_float(o.w[e] << 16) * fast_rcp(1.f + fast_exp2(-g0 * LOG2E)),
-                            __uint_as_float(o.w[e] & 0xffff0000u) * fast_rcp(1.f + fast_exp2(-g1 * LOG2E)));
-      }
-    }
-    gf[ks] = o.v;
-  }
-  if (WB == WB_REGS) {
-    table_setup(p, h, L, tid);
-    __syncthreads();
-  }
-  WinBias<NB, WB, false> bias;
-  bias.init(p, L, h, w, lane);
-  f32x16 cz;  // of the block, then of the next one
-  if (WB == WB_COPY) bias.get(p, w, 0, lane, cz);
-  bool masked = false;
-  int my_rid = 0;
-  if (REGION) {
-    const int* ids = p.region + (int64_t)(b % p.mask_period) * p.S;
-    masked = row_is_masked<NB>(ids, p.S, lane);
-    my_rid = ids[qc];
-    if (tid < 32 * NB) L.rid[tid] = ids[min(tid, p.S - 1)];
-  }
-  row.store(L, tid);
-  __syncthreads();
-  f32x16 oacc[1], a1, a2;
-#pragma unroll
-  for (int v = 0; v < 16; ++v) { oacc[0][v] = 0.f; a1[v] = 0.f; a2[v] = 0.f; }
-  float nm = 1e30f, lsum = 0.f, dsum = 0.f, l32 = 0.f, d32 = 0.f;
-  DpShift shift;
-  const float c1 = in_vgpr(p.scale * LOG2E);
-#pragma unroll BLOCK_UNROLL
-  for (int c = 0; c < NB; ++c) {
-    f32x16 s, pa;
-    if (WB != WB_COPY) bias.get(p, w, c, lane, cz);
-    s = cz;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) pa[v] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      s = mfma(lds_nat<WLD>(L.t0, 32 * c + r, ks, hl), qf[ks], s);
-      pa = mfma(lds_nat<WLD>(L.t1, 32 * c + r, ks, hl), gf[ks], pa);
-    }
-    if (WB == WB_COPY) bias.get(p, w, min(c + 1, NB - 1), lane, cz);
-    if (REGION && masked) mask_regions(s, L.rid, my_rid, 32 * c, hl);
-    float rmax = s[0];
-#pragma unroll
-    for (int v = 1; v < 16; ++v) rmax = fmaxf(rmax, s[v]);
-    rmax = half_max(rmax * c1);
-    if (__builtin_amdgcn_ballot_w64(rmax + nm > 8.f) != 0) {  // raised only when exceeded by 2^8
-      const float mn = fmaxf(-nm, rmax), alpha = fast_exp2(-nm - mn);
-      nm = -mn;
-      shift.rescaled(alpha);
-      lsum *= alpha;
-      dsum *= alpha;
-      l32 *= alpha;
-      d32 *= alpha;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) { oacc[0][v] *= alpha; a1[v] *= alpha; a2[v] *= alpha; }
-    }
-    float pr[16], dp[16];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) pr[v] = fast_exp2(fmaf(s[v], c1, nm));
-    const float l32_before = l32;
-    l32 += sum16(pr);
-    float d = 0.f;
-    if (shift.is_due(l32)) d = shift.take(pr, pa, l32_before, l32, dsum);
-    // (in the branch above the compiler copies a1, on every block, and needs scratch)
-    if (__builtin_amdgcn_ballot_w64(d != 0.f) != 0) {
-      dsum = fmaf(d, lsum, dsum);
-      if (!GATED) d32 = fmaf(d, l32_before, d32);
-#pragma unroll
-      for (int v = 0; v < 16; ++v) a1[v] = fmaf(d, a2[v], a1[v]);
-    }
-#pragma unroll
-    for (int v = 0; v < 16; ++v) dp[v] = pr[v] * (pa[v] - shift.c);
-    if (!GATED) d32 += sum16(dp);
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const bf16x8 pf = pack8(&pr[8 * j]), df = pack8(&dp[8 * j]);
-      lsum = sum_rounded(pf, lsum);  // over the operands as they were rounded
-      dsum = sum_rounded(df, dsum);
-      const bf16x8 kt = lds_tr<WLD>(L.t0, 32 * c + 16 * j, 0, lane);
-      if (GATED) oacc[0] = mfma(lds_tr<WLD>(L.t1, 32 * c + 16 * j, 0, lane), pf, oacc[0]);
-      a2 = mfma(kt, pf, a2);
-      a1 = mfma(kt, df, a1);
-    }
-  }
-  if (q >= p.S) return;
-  const float l = half_sum(lsum), inv = 1.f / l, dmean = half_sum(dsum) * inv, lf = half_sum(l32);
-  uint2 o[4];
-#pragma unroll
-  for (int g = 0; g < 4; ++g)
-    o[g] = pack4_bf16(fmaf(-dmean, a2[4 * g], a1[4 * g]), fmaf(-dmean, a2[4 * g + 1], a1[4 * g + 1]),
-                      fmaf(-dmean, a2[4 * g + 2], a1[4 * g + 2]), fmaf(-dmean, a2[4 * g + 3], a1[4 * g + 3]), p.scale * inv);
-  store_row32((uint16_t*)p.dQ + base + (int64_t)q * p.ss, o, hl, true);
-  if (GATED) {
-    fwd_epilogue_rowsum<1, true>(p, oacc, -nm, l, lf, b, h, q, hl, base);
-  } else {
-    const float delta = half_sum(d32) / lf + shift.c;
-    if (hl == 0) {
-      p.delta[(int64_t)(b - p.dl_b0) * p.dl_sb + (int64_t)(h - p.dl_h0) * p.dl_sh + q] = delta;
-      if (p.lse_out) p.lse_out[(int64_t)(b - p.lse_b0) * p.lse_sb + (int64_t)(h - p.lse_h0) * p.lse_sh + q] = (log2f(lf) - nm) * LN2;
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// dK, dV and the bias gradient in one walk over the queries; lane = key.  A work-group takes one group
-// of p.sm_gw consecutive global rows (or the chunk's part of it); dS is added in registers, row after
-// row, and stored as the group's partial sum, resumed when a chunk boundary cuts the group.  The next row's
-// operands travel global -> registers meanwhile.
-// ---------------------------------------------------------------------------
-template <int NB, bool REGION, int WB>
-__global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(2, 2))) void win_kv_kernel(KP p) {
-#pragma clang fp contract(off)  // the variants are to give the same bits
-  __shared__ __attribute__((aligned(16))) WinLds<NB> L;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, r = lane & 31, hl = lane >> 5;
-  const int h = p.h0 + blockIdx.x, key = 32 * w + r, kc = min(key, p.S - 1);
-  const int g = p.b0 / p.sm_gw + blockIdx.y;  // global group
-  const int bfirst = max(g * p.sm_gw, p.b0), blast = min((g + 1) * p.sm_gw, p.b1);
-  RowStage<NB> next;
-  float stat = 0.f;
-  bf16x8 kf[2], vf[2];
-  auto fetch_kv = [&](int b) {
-#pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
-      const int64_t at = (int64_t)b * p.sb + (int64_t)h * p.sh + (int64_t)kc * p.ss + 16 * ks + 8 * hl;
-      kf[ks] = *(const bf16x8*)((const uint16_t*)p.K + at);
-      vf[ks] = *(const bf16x8*)((const uint16_t*)p.V + at);
-    }
-  };
-  auto fetch = [&](int b) {
-    const int64_t base = (int64_t)b * p.sb + (int64_t)h * p.sh;
-    next.load((const uint16_t*)p.Q + base, p.ss,
-              (const uint16_t*)p.dO + (int64_t)(b - p.do_b0) * p.do_sb + (int64_t)(h - p.do_h0) * p.do_sh, p.do_ss, p.S, tid);
-    // 64 NB threads, two statistics for 32 NB queries
-    const int i = min(tid < 32 * NB ? tid : tid - 32 * NB, p.S - 1);
-    stat = tid < 32 * NB ? p.lse[(int64_t)(b - p.lse_b0) * p.lse_sb + (int64_t)(h - p.lse_h0) * p.lse_sh + i]
-                         : p.delta[(int64_t)(b - p.dl_b0) * p.dl_sb + (int64_t)(h - p.dl_h0) * p.dl_sh + i];
-  };
-  fetch(bfirst);
-  fetch_kv(bfirst);
-  // which of the rows (at most 32 at a time) the region mask cuts: one look ahead, not a wait per row
-  uint32_t cut = 0;
-  auto look_ahead = [&](int b) {
-    cut = 0;
-    for (int i = 0; i < 32 && b + i < blast; ++i)
-      cut |= (uint32_t)row_is_masked<NB>(p.region + (int64_t)((b + i) % p.mask_period) * p.S, p.S, lane) << i;
-  };
-  if (WB == WB_REGS) {
-    table_setup(p, h, L, tid);
-    __syncthreads();
-  }
-  WinBias<NB, WB, true> bias;
-  bias.init(p, L, h, w, lane);
-  f32x16 cz;  // of the next block
-  if (WB == WB_COPY) bias.get(p, w, 0, lane, cz);
-  const float c1 = in_vgpr(p.scale * LOG2E);
-  float acc[NB][16];
-  float* part = nullptr;
-  if (p.sm_partial) {
-    part = p.sm_partial + ((int64_t)((g - p.sm_g0) % p.sm_ring) * p.sm_hs + (h - p.sm_h0)) * p.S * p.S;
-    const bool resume = max(g * p.sm_gw, p.share_b0) < p.b0;  // an earlier chunk started this group
-#pragma unroll
-    for (int c = 0; c < NB; ++c)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int i = 32 * c + key_of(v, hl);
-        acc[c][v] = resume && i < p.S && key < p.S ? part[i * p.S + key] : 0.f;
-      }
-  }
-  for (int b = bfirst; b < blast; ++b) {
-    const int64_t base = (int64_t)b * p.sb + (int64_t)h * p.sh;
-    if (REGION && ((b - bfirst) & 31) == 0) look_ahead(b);
-    const bool masked = REGION && ((cut >> ((b - bfirst) & 31)) & 1);
-    __syncthreads();
-    next.store(L, tid);
-    if (tid < 32 * NB) L.lse2[tid] = -stat * LOG2E;  // negated: one fused multiply-add per score
-    else L.delta[tid - 32 * NB] = stat;
-    int my_rid = 0;
-    if (masked) {
-      const int* ids = p.region + (int64_t)(b % p.mask_period) * p.S;
-      my_rid = ids[kc];
-      if (tid < 32 * NB) L.rid[tid] = ids[min(tid, p.S - 1)];
-    }
-    __syncthreads();
-    if (b + 1 < blast) fetch(b + 1);
-    f32x16 dk, dv;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) { dk[v] = 0.f; dv[v] = 0.f; }
-#pragma unroll
-    for (int c = 0; c < NB; ++c) {
-      // the blocks are unrolled (the gradient sums are registers) but meant to run one after the other
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_sched_barrier(0);
-      f32x16 s, pa;
-      if (WB != WB_COPY) bias.get(p, w, c, lane, cz);
-      s = cz;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) pa[v] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        s = mfma(lds_nat<WLD>(L.t0, 32 * c + r, ks, hl), kf[ks], s);
-        pa = mfma(lds_nat<WLD>(L.t1, 32 * c + r, ks, hl), vf[ks], pa);
-      }
-      if (WB == WB_COPY) bias.get(p, w, c + 1 < NB ? c + 1 : 0, lane, cz);
-      // exponents and dP - Delta; masked pairs get -inf and 0 here, after the statistics went in, so that they contribute
-      // nothing also where a query has NaN statistics
-#pragma unroll
-      for (int gq = 0; gq < 4; ++gq) {
-        const f32x4 l4 = *(const f32x4*)(L.lse2 + 32 * c + 8 * gq + 4 * hl);
-        const f32x4 d4 = *(const f32x4*)(L.delta + 32 * c + 8 * gq + 4 * hl);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int v = 4 * gq + e;
-          s[v] = fmaf(s[v], c1, l4[e]);
-          pa[v] -= d4[e];
-        }
-      }
-      if (masked) {
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-          const int4 rk = *(const int4*)(L.rid + 32 * c + 8 * gq + 4 * hl);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const bool dead = (e == 0 ? rk.x : e == 1 ? rk.y : e == 2 ? rk.z : rk.w) != my_rid;
-            s[4 * gq + e] = dead ? -INFINITY : s[4 * gq + e];
-            pa[4 * gq + e] = dead ? 0.f : pa[4 * gq + e];
-          }
-        }
-      }
-      float pr[16], ds[16];
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        pr[v] = fast_exp2(s[v]);
-        ds[v] = pr[v] * pa[v];
-      }
-      if (part) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[c][v] += ds[v];
-      }
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        dv = mfma(lds_tr<WLD>(L.t1, 32 * c + 16 * j, 0, lane), pack8(&pr[8 * j]), dv);
-        dk = mfma(lds_tr<WLD>(L.t0, 32 * c + 16 * j, 0, lane), pack8(&ds[8 * j]), dk);
-      }
-    }
-    if (b + 1 < blast) fetch_kv(b + 1);  // under the epilogue: before, there are no registers for them
-    if (key < p.S) {
-      uint2 a[4], c[4];
-#pragma unroll
-      for (int gd = 0; gd < 4; ++gd) {
-        a[gd] = pack4_bf16(dk[4 * gd], dk[4 * gd + 1], dk[4 * gd + 2], dk[4 * gd + 3], p.scale);
-        c[gd] = pack4_bf16(dv[4 * gd], dv[4 * gd + 1], dv[4 * gd + 2], dv[4 * gd + 3], 1.f);
-      }
-      store_row32((uint16_t*)p.dK + base + (int64_t)key * p.ss, a, hl, true);
-      store_row32((uint16_t*)p.dV + base + (int64_t)key * p.ss, c, hl, true);
-    }
-  }
-  if (part && key < p.S) {
-    int at = key;  // opaque: the addresses are not to be kept in registers from the load of the partial sum on
-    asm volatile("" : "+v"(at));
-#pragma unroll
-    for (int c = 0; c < NB; ++c)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int i = 32 * c + key_of(v, hl);
-        if (i < p.S) part[i * p.S + at] = acc[c][v];
-      }
-  }
-}
-
 template <class F>
 hipError_t with_shape(const KP& p, bool copy, F f) {
   auto mask = [&](auto nb) {
@@ -608,22 +291,4 @@ hipError_t launch_win_fwd(const KP& p, hipStream_t st) {
     win_fwd_kernel<nb(), region(), WB><<<g, 64 * nb(), 0, st>>>(p, rows);
   });
 }
-hipError_t launch_win_recompute_dq(const KP& p, hipStream_t st) {
-  const dim3 g(p.h1 - p.h0, 1, p.b1 - p.b0);
-  return with_shape(p, p.bias_q != nullptr, [&](auto nb, auto region, auto wb) {
-    if (p.gated) win_rdq_kernel<nb(), region(), wb(), true><<<g, 64 * nb(), 0, st>>>(p);
-    else win_rdq_kernel<nb(), region(), wb(), false><<<g, 64 * nb(), 0, st>>>(p);
-  });
-}
-hipError_t launch_win_kv(const KP& args, hipStream_t st) {
-  KP p = args;
-  if (p.dbias_acc && !p.sm_partial) {  // no partial sums: all rows are one group, which sums in the result itself
-    p.sm_partial = p.dbias_acc;
-    p.sm_gw = p.B;
-    p.sm_g0 = 0; p.sm_ring = 1; p.sm_hs = p.H; p.sm_h0 = 0;
-  }
-  const dim3 g(p.h1 - p.h0, (p.b1 - 1) / p.sm_gw - p.b0 / p.sm_gw + 1);
-  return with_shape(p, p.bias_k != nullptr, [&](auto nb, auto region, auto wb) { win_kv_kernel<nb(), region(), wb()><<<g, 64 * nb(), 0, st>>>(p); });
-}
-
 }  // namespace ssa
