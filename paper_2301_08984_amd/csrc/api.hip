@@ -4,6 +4,7 @@
 // workspace (co-shard, Section 2 of the paper).
 #include "../../include/ss_attn.h"
 #include "bias_copy.h"
+#include "table_fold.h"
 #include "f32_kernels.h"
 #include "kparams.h"
 #include "mfma_common.h"
@@ -320,6 +321,15 @@ int run_bwd(const ss_attn_desc* d, Family fam, const WsLayout& w, const void* Q,
       slices_done = s1;
     }
     if (s1 <= s0) return SS_OK;
+    if (d->bias_kind == SS_BIAS_RELPOS) {
+      SS_LAUNCH(SS_K_TABLE_REDUCE,
+                ssa::launch_table_slices(q.sm_partial, w.ring, w.hs, nh, d->S, w.slice, s0, s1, w.ngroups, d->win_h, d->win_w, st),
+                "relative-position tables of the slices");
+      SS_LAUNCH(SS_K_TABLE_REDUCE,
+                ssa::launch_table_sum(q.sm_partial, dBias, w.ring, w.hs, hd0, nh, d->S, w.slice, s0, s1, d->win_h, d->win_w, s0 == 0, st),
+                "sum of the slices' tables");
+      return SS_OK;
+    }
     SS_LAUNCH(SS_K_DBIAS_FOLD,
               ssa::launch_group_fold(q.sm_partial, dense, w.ring, w.hs, hd0, nh, d->S, w.slice, s0, s1, w.ngroups,
                                      s0 == 0, st),
@@ -358,13 +368,6 @@ int run_bwd(const ss_attn_desc* d, Family fam, const WsLayout& w, const void* Q,
       if (want_dbias) {
         const int rf = fold_groups(p, c);
         if (rf != SS_OK) return rf;
-        if (d->bias_kind == SS_BIAS_RELPOS && (d->shard_axis == SS_AXIS_HEAD || c == d->k - 1)) {
-          const int h0 = d->shard_axis == SS_AXIS_HEAD ? p.h0 : 0;
-          const int h1 = d->shard_axis == SS_AXIS_HEAD ? p.h1 : d->H;
-          SS_LAUNCH(SS_K_TABLE_REDUCE,
-                    ssa::launch_relpos_reduce(dense, dBias, h0, h1, d->S, d->win_h, d->win_w, st),
-                    "relative-position table reduce");
-        }
       }
       continue;
     }
@@ -405,7 +408,7 @@ int run_bwd(const ss_attn_desc* d, Family fam, const WsLayout& w, const void* Q,
       SS_LAUNCH(SS_K_DKDV, ssa::launch_generic_dkdv(p, bf16, st), "dK/dV (generic)");
       if (want_dbias) SS_LAUNCH(SS_K_DBIAS, ssa::launch_generic_dbias(p, bf16, st), "dBias (generic)");
     }
-    if (want_dbias && d->bias_kind == SS_BIAS_RELPOS &&
+    if (want_dbias && d->bias_kind == SS_BIAS_RELPOS && p.sm_partial == nullptr &&
         (d->shard_axis == SS_AXIS_HEAD || c == d->k - 1)) {
       const int h0 = d->shard_axis == SS_AXIS_HEAD ? p.h0 : 0;
       const int h1 = d->shard_axis == SS_AXIS_HEAD ? p.h1 : d->H;

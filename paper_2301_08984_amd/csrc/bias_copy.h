@@ -16,11 +16,12 @@ namespace {
 // Windows (win_kernels.hip; the backward, win_bwd.hip, takes packed bf16): without one a work-group gathers the bias from the table in
 // LDS and holds it in registers.  Without | with, us, rows x heads of 256, 512, 1024, 2048 (8 heads, region mask): forward of 12 x 12 tokens
 // 10.3 | 13.7, 17.5 | 16.0, 31.8 | 25.9, 64.0 | 37.6; of 9 x 9 7.9 | 12.5, 7.9 | 12.4, 9.6 | 14.1, 19.2 | 19.8, of 11 x 11 8.5 | 12.4, 9.4 | 13.8, 15.7 | 17.0,
-// 26.4 | 25.6.  Backward with a dense bias: 12 x 12 tokens, 64 rows x 8 heads 44.3 | 40.5, 512 x 8 128 | 126; 11 x 11, 512 x 8 90 | 92.
+// 26.4 | 25.6.  Backward: gathered from the table, 3 us shorter than
+// with a launch that does it; from a dense matrix, 12 x 12 tokens, 64 rows x 8 heads 44.3 | 40.5, 512 x 8 128 | 126; 11 x 11, 512 x 8 90 | 92.
 inline int64_t win_packed_bytes(int S, int heads) { return (int64_t)heads * ((S + 15) / 16) * ((S + 15) / 16) * 512; }
 inline size_t bias_copy_bytes_for(const KP& p, bool backward, int64_t rows, int heads) {
   if (win_ok(p)) {
-    if (p.bias_kind == 0 || (backward ? rows * heads < (p.S <= 128 ? 1024 : 64) : p.S <= 128 || rows * heads < 512)) return 0;
+    if (p.bias_kind == 0 || (backward ? p.bias_kind == 2 || rows * heads < (p.S <= 128 ? 1024 : 64) : p.S <= 128 || rows * heads < 512)) return 0;
     return backward ? (size_t)win_packed_bytes(p.S, heads) : (size_t)bias_copy_bytes(p.S, heads);
   }
   if (!pair_fwd_ok(p) || p.S > 16384) return 0;
