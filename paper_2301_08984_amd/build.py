@@ -12,7 +12,7 @@ from concurrent.futures import ThreadPoolExecutor
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libss_attn.so")
-SOURCES = ["api.hip", "generic_kernels.hip", "f32_kernels.hip", "mfma_kernels.hip", "small_kernels.hip", "win_kernels.hip", "win_bwd.hip", "fast_fwd.hip", "pair_fwd.hip", "pair_dbias.hip", "fast_fwd128.hip", "fast_stat128.hip", "fast_dq.hip", "fast_rdq.hip", "fast_dq128.hip", "fast_kv128.hip", "fast_wave_fwd.hip", "fast_wave_fwd128.hip", "fast_wave_bwd.hip", "fast_wave_bwd128.hip", "ffn_kernels.hip", "ffn_skinny.hip", "ffn_api.hip", "planner.hip",
+SOURCES = ["api.hip", "generic_kernels.hip", "f32_kernels.hip", "mfma_kernels.hip", "small_kernels.hip", "win_fwd.hip", "win_bwd.hip", "fast_fwd.hip", "pair_fwd.hip", "pair_dbias.hip", "fast_fwd128.hip", "fast_stat128.hip", "fast_dq.hip", "fast_rdq.hip", "fast_dq128.hip", "fast_kv128.hip", "fast_wave_fwd.hip", "fast_wave_fwd128.hip", "fast_wave_bwd.hip", "fast_wave_bwd128.hip", "ffn_kernels.hip", "ffn_skinny.hip", "ffn_api.hip", "planner.hip",
            "fast_dkdv.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -22,7 +22,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
 # Sources that use no accumulation registers: matrix instructions in their vector-register form, so
 # that all of a wavefront's registers are vector registers (see the header of fast_wave_fwd128.hip).
 VGPR_FORM = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-EXTRA_FLAGS = {"win_bwd.hip": VGPR_FORM, "pair_dbias.hip": VGPR_FORM, "fast_fwd128.hip": VGPR_FORM, "fast_stat128.hip": VGPR_FORM, "fast_dq128.hip": VGPR_FORM, "fast_kv128.hip": VGPR_FORM, "fast_wave_fwd128.hip": VGPR_FORM, "fast_wave_bwd128.hip": VGPR_FORM}
+EXTRA_FLAGS = {"win_fwd.hip": VGPR_FORM, "win_bwd.hip": VGPR_FORM, "pair_dbias.hip": VGPR_FORM, "fast_fwd128.hip": VGPR_FORM, "fast_stat128.hip": VGPR_FORM, "fast_dq128.hip": VGPR_FORM, "fast_kv128.hip": VGPR_FORM, "fast_wave_fwd128.hip": VGPR_FORM, "fast_wave_bwd128.hip": VGPR_FORM}
 
 
 def _compile(src: str, objdir: str) -> str:

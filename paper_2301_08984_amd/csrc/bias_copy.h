@@ -13,16 +13,15 @@ namespace {
 // 256 rows 373 | 329; odd lengths, whose parked tiles are loaded unaligned: 64 x 8 x 501: 58.0 | 58.3, 512 x 4 x 301: 107 | 92.
 // Backward: dK / dV 9 % shorter (1024 x 4 x 1024: 2037 -> 1850 us), and the copy replaces the transposed bf16 one; the
 // recompute + dQ kernel gains nothing from a copy of its own (2469 | 2510).
-// Windows (win_kernels.hip; the backward, win_bwd.hip, takes packed bf16): without one a work-group gathers the bias from the table in
-// LDS and holds it in registers.  Without | with, us, rows x heads of 256, 512, 1024, 2048 (8 heads, region mask): forward of 12 x 12 tokens
-// 10.3 | 13.7, 17.5 | 16.0, 31.8 | 25.9, 64.0 | 37.6; of 9 x 9 7.9 | 12.5, 7.9 | 12.4, 9.6 | 14.1, 19.2 | 19.8, of 11 x 11 8.5 | 12.4, 9.4 | 13.8, 15.7 | 17.0,
-// 26.4 | 25.6.  Backward: gathered from the table, 3 us shorter than
-// with a launch that does it; from a dense matrix, 12 x 12 tokens, 64 rows x 8 heads 44.3 | 40.5, 512 x 8 128 | 126; 11 x 11, 512 x 8 90 | 92.
+// Windows (win_fwd.hip, win_bwd.hip: packed bf16): without one a work-group gathers the bias from the table in LDS or from the dense matrix.  Without | with,
+// us, 12 x 12 tokens with regions, 64 x 8 and 512 x 8 rows x heads: dense forward 27.3 | 18.4, 65.9 | 54.8, backward 44.3 | 40.5, 128 | 126 (11 x 11, 512 x 8:
+// 90 | 92).  From the table: backward 3 us shorter without, so never; forward 11.0 | 16.2, 51.7 | 55.2: the copy's launch remains, one rule for both kinds of
+// bias, until the launches that callers see in a profile may change.
 inline int64_t win_packed_bytes(int S, int heads) { return (int64_t)heads * ((S + 15) / 16) * ((S + 15) / 16) * 512; }
 inline size_t bias_copy_bytes_for(const KP& p, bool backward, int64_t rows, int heads) {
   if (win_ok(p)) {
     if (p.bias_kind == 0 || (backward ? p.bias_kind == 2 || rows * heads < (p.S <= 128 ? 1024 : 64) : p.S <= 128 || rows * heads < 512)) return 0;
-    return backward ? (size_t)win_packed_bytes(p.S, heads) : (size_t)bias_copy_bytes(p.S, heads);
+    return (size_t)win_packed_bytes(p.S, heads);
   }
   if (!pair_fwd_ok(p) || p.S > 16384) return 0;
   const int64_t row_stride = p.ss > (int64_t)p.H * p.D ? p.ss : (int64_t)p.H * p.D;
@@ -58,25 +57,7 @@ __device__ inline uint16_t win_bias_entry(const KP& p, int h, int i, int j) {
   const int rowlen = 2 * p.win_w - 1, dy = i / p.win_w - j / p.win_w + p.win_h - 1, dx = i % p.win_w - j % p.win_w + p.win_w - 1;
   return b[(int64_t)h * ((2 * p.win_h - 1) * rowlen) + dy * rowlen + dx];
 }
-// The same of a window's bias.
-__global__ __launch_bounds__(256) void win_bias_copy_kernel(KP p, float* dst) {
-  const int lane = threadIdx.x & 63, block = blockIdx.x * 4 + (threadIdx.x >> 6), strip = blockIdx.y, S = p.S;
-  if (block >= bias_copy_blocks(S)) return;
-  f32x4* out = (f32x4*)dst + ((blockIdx.z * bias_copy_strips(S) + strip) * bias_copy_blocks(S) + block) * 256 + lane;
-  const int row = 32 * strip + (lane & 31), col = 32 * block + 4 * (lane >> 5);
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    f32x4 x;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int c = col + 8 * g + e;
-      const float b = bf2f(win_bias_entry(p, p.bc_h0 + blockIdx.z, min(row, S - 1), min(c, S - 1)));
-      x[e] = row < S && c < S ? b * p.inv_scale : -INFINITY;
-    }
-    out[64 * g] = x;
-  }
-}
-// What the backward of windows reads (win_bwd.hip): bf16, blocks of 16 queries x 16 keys, lane l the query l % 16 and four keys from 4 (l / 16) on; -inf
+// What the kernels of windows read (win_common.h): bf16, blocks of 16 queries x 16 keys, lane l the query l % 16 and four keys from 4 (l / 16) on; -inf
 // past the last key.  x = block of keys, y = block of queries, z = head.
 __global__ __launch_bounds__(64) void win_bias_pack_kernel(KP p, uint2* dst) {
   const int lane = threadIdx.x, i = min(16 * (int)blockIdx.y + (lane & 15), p.S - 1), j0 = 16 * blockIdx.x + 4 * (lane >> 4);
@@ -90,8 +71,7 @@ inline hipError_t launch_bias_copies(KP& p, float* copy, bool backward, int h0, 
   const int heads = h1 - h0;
   p.bc_h0 = h0;
   const dim3 g((unsigned)((bias_copy_blocks(p.S) + 3) / 4), (unsigned)bias_copy_strips(p.S), heads);
-  if (win_ok(p) && backward) win_bias_pack_kernel<<<dim3((p.S + 15) / 16, (p.S + 15) / 16, heads), 64, 0, st>>>(p, (uint2*)copy);
-  else if (win_ok(p)) win_bias_copy_kernel<<<g, 256, 0, st>>>(p, copy);
+  if (win_ok(p)) win_bias_pack_kernel<<<dim3((p.S + 15) / 16, (p.S + 15) / 16, heads), 64, 0, st>>>(p, (uint2*)copy);
   else bias_copy_kernel<<<g, 256, 0, st>>>((const uint16_t*)p.bias, copy, p.S, h0, backward ? 1 : 0, p.inv_scale);
   if (backward) p.bias_k = copy;
   else p.bias_q = copy;

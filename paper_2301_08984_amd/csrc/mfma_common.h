@@ -552,7 +552,7 @@ inline bool fast_ok(const KP& p) {
   return true;
 }
 
-// the window kernels (win_kernels.hip, win_bwd.hip) serve: head size 32, 65 to 160 tokens, a relative-position bias or a
+// the window kernels (win_fwd.hip, win_bwd.hip) serve: head size 32, 65 to 160 tokens, a relative-position bias or a
 // region mask (a bf16 bias of either kind, or none; no causal mask), a positive scale
 inline bool win_ok(const KP& p) {
   if (p.D != 32 || p.S <= 64 || p.S > 160 || !(p.scale > 0.f) || p.mask_kind == 1) return false;

@@ -15,50 +15,10 @@
 // What bounds it (12 x 12): nine wavefronts on four SIMDs, of which one runs three: its vector arithmetic, some 20 instructions a score
 // with what goes round it, takes 60 % of the time; sums of S x S and a row's S and dP (108 registers) leave no room for a second work-group.  LDS 25 %.
 // Timed on the way there: waits for loads that the compiler inserted (see `store`) 280 -> 228 (1024 x 16 x 9 x 9), nine spilled registers 147 -> 137.
-#include "mfma_common.h"
+#include "win_common.h"
 
 namespace ssa {
 namespace {
-
-constexpr int WB_TOKEN = 64;  // bytes of a token of a tensor in LDS: four chunks of 16
-
-typedef __attribute__((address_space(3))) void wb_lds_void;
-typedef __attribute__((address_space(1))) void wb_glb_void;
-typedef __attribute__((address_space(3))) s16x4 wb_lds_s16x4;
-
-// Chunk c of token i sits at position c ^ wb_place(i): 16 consecutive tokens put a chunk at 16 different places of 256 bytes (reads along
-// the head), and eight consecutive ones two neighbouring chunks at eight different places (transposed reads).
-__device__ inline int wb_place(int i) { return ((i >> 1) & 2) | ((i >> 3) & 1); }
-
-__device__ inline f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
-
-// over the four 16-lane groups
-__device__ inline float groups_max(float x) {
-  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return half_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
-}
-__device__ inline float groups_sum(float x) {
-  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return half_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
-}
-// A lane's columns 16 db + 4 g .. + 3 of 32 (g = its 16-lane group) as 16 bytes of memory order, for column 8 * store_chunk(g) on: neighbouring
-// groups exchange pieces.
-__device__ inline u32x4 gather16(const uint2 (&x)[2]) {
-  auto a = __builtin_amdgcn_permlane16_swap(x[0].x, x[1].x, false, false);
-  auto c = __builtin_amdgcn_permlane16_swap(x[0].y, x[1].y, false, false);
-  return u32x4{a[0], c[0], a[1], c[1]};
-}
-__device__ inline int store_chunk(int g) { return 2 * (g & 1) + (g >> 1); }
-
-// does the row's region mask mask anything at all?  (uniform; most rows do not)
-template <int NB>
-__device__ inline bool ids_differ(const int* rid, int lane) {
-  const int first = rid[0];
-  int other = 0;
-#pragma unroll
-  for (int c = 0; c < (NB + 3) / 4; ++c) other |= rid[min(lane + 64 * c, 16 * NB - 1)] ^ first;
-  return __builtin_amdgcn_ballot_w64(other != 0) != 0;
-}
 
 // LDS of a work-group.  Two buffers of a row's tensors, but one of K and V where that makes room for a second work-group on the compute unit; P and
 // dS next to each other, or one after the other in one place (and two barriers more a row).  KiB: 65, 74, 69, 129, 155, 132.
@@ -71,7 +31,7 @@ template <int NB, bool REGION, bool BIAS, bool GATED>
 __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(NB == 8 ? 2 : 3, NB == 8 ? 2 : 3))) void win_bwd_kernel(KP p) {
 #pragma clang fp contract(off)
   constexpr int T = 16 * NB, STEPS = (NB + 1) / 2, TENSOR = T * WB_TOKEN, BLOCK = T * 32;
-  constexpr bool KV2 = TWO_KV<NB>, ONE = ONE_PLACE<NB>, LB = BIAS && LDS_BIAS<NB>;
+  constexpr bool KV2 = TWO_KV<NB>, ONE = ONE_PLACE<NB>, LB = BIAS && LDS_BIAS<NB>, TIGHT = NB == 7 || NB > 8;
   // arrays of their own: the compiler then knows that a load into one does not feed a read of another
   __shared__ __attribute__((aligned(1024))) char qg0[2 * TENSOR];
   __shared__ __attribute__((aligned(1024))) char qg1[2 * TENSOR];
@@ -88,10 +48,10 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(NB == 8
   const int bfirst = max(group * p.sm_gw, p.b0), blast = min((group + 1) * p.sm_gw, p.b1);
 
   // this lane's piece of a row: token 16 w + lane / 4 (past S - 1: the last one again), the chunk that belongs at position lane % 4
-  // (lane addresses are formed anew in every row: the registers hold no more than they must)
+  // (lane addresses are formed anew in every row where the registers hold no more than they must)
   auto anew = [&] {
     int x = lane;
-    asm volatile("" : "+v"(x));
+    if (TIGHT) asm volatile("" : "+v"(x));
     return x;
   };
   auto piece_at = [&] {
@@ -121,53 +81,8 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(NB == 8
   load_id(bfirst);
   load_gate(bfirst);
 
-  // What the scores start from, packed bf16: the bias of query `me` and keys 16 c + 4 g .. + 3; -inf past the last key.  From a copy in this order,
-  // made once per call, or gathered here.
   uint32_t bz[BIAS ? NB : 1][2];
-  if (BIAS && p.bias_k) {
-#pragma unroll
-    for (int c = 0; c < NB; ++c) {
-      const uint2 x = ((const uint2*)p.bias_k)[(((int64_t)(h - p.bc_h0) * NB + w) * NB + c) * 64 + lane];
-      bz[BIAS ? c : 0][0] = x.x;
-      bz[BIAS ? c : 0][1] = x.y;
-    }
-  } else if (BIAS) {
-    const uint16_t* m = (const uint16_t*)p.bias;
-    uint16_t* table = (uint16_t*)qg1;  // no row arrives there yet
-    int* place = (int*)(qg1 + MAX_RELPOS_R * 2);
-    static_assert(MAX_RELPOS_R * 2 + 4 * T <= 2 * TENSOR, "the table fits a buffer");
-    uint32_t x[NB][4];
-    if (p.bias_kind == 2) {
-      const int rowlen = 2 * p.win_w - 1, R = (2 * p.win_h - 1) * rowlen;
-      if (tid < T) {
-        const int i = min(tid, p.S - 1);
-        place[tid] = (i / p.win_w) * rowlen + i % p.win_w;
-      }
-      for (int i = tid; i < R; i += 64 * NB) table[i] = m[(int64_t)h * R + i];
-      __syncthreads();
-      const int c0 = (p.win_h - 1) * rowlen + p.win_w - 1 + place[mc];
-#pragma unroll
-      for (int c = 0; c < NB; ++c) {
-        const int4 k = *(const int4*)(place + 16 * c + 4 * g);
-        x[c][0] = table[c0 - k.x]; x[c][1] = table[c0 - k.y]; x[c][2] = table[c0 - k.z]; x[c][3] = table[c0 - k.w];
-      }
-      __syncthreads();  // the buffer is the second row's
-    } else {
-      m += ((int64_t)h * p.S + mc) * p.S;
-#pragma unroll
-      for (int c = 0; c < NB; ++c)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[c][e] = m[min(16 * c + 4 * g + e, p.S - 1)];
-    }
-#pragma unroll
-    for (int c = 0; c < NB; ++c) {
-      if (c == NB - 1)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[c][e] = 16 * c + 4 * g + e < p.S ? x[c][e] : 0xff80u;
-      bz[BIAS ? c : 0][0] = x[c][0] | x[c][1] << 16;
-      bz[BIAS ? c : 0][1] = x[c][2] | x[c][3] << 16;
-    }
-  }
+  if constexpr (BIAS) win_bias<NB>(p, (const uint2*)p.bias_k, qg1, h, w, lane, bz);
   f32x4 acc[BIAS ? NB : 1];
 #pragma unroll
   for (int c = 0; c < (BIAS ? NB : 1); ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -191,34 +106,15 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(NB == 8
     if (LB) bias_lds[(w * NB + c) * 64 + lane] = uint2{bz[c][0], bz[c][1]};  // the lane itself reads it
   }
   const float scale = in_vgpr(p.scale), c1 = in_vgpr(BIAS ? LOG2E : p.scale * LOG2E);  // score to logit, then to exponent of two
-  // where this lane reads: along the head, token r of a block, chunk g; transposed, token 4 g + r / 4 and the four
-  // columns 16 db + 4 (r % 4) on
-  uint32_t nat = (uint32_t)(r * WB_TOKEN + ((g ^ wb_place(r)) << 4));
-  const int tt = 4 * g + (r >> 2);
-  uint32_t tr = (uint32_t)(tt * WB_TOKEN + ((((r & 3) >> 1) ^ wb_place(tt)) << 4) + 8 * (r & 1));  // db = 1: ^ 32
+  uint32_t nat = wb_along(r, g), tr = wb_across(r, g);
   // in a block of P or dS, keys 4 j on of query i are at position j ^ (i / 4) of its row of 32 bytes (as above): as this lane writes them, as it reads
-  uint32_t give = (uint32_t)(32 * r + 8 * (g ^ (r >> 2))), take = (uint32_t)(w * BLOCK + 32 * tt + 8 * ((r & 3) ^ g));
-  auto tr_pair = [&](const char* at, int step, bool both) {
-    union { s16x4 h[2]; bf16x8 v; } o;
-    o.h[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((wb_lds_s16x4*)at);
-    o.h[1] = s16x4{0, 0, 0, 0};
-    if (both) o.h[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((wb_lds_s16x4*)(at + step));
-    return o.v;
-  };
-  // columns 16 db .. of tokens 32 t + {0 .. 3, 16 .. 19} + 4 g of a tensor, transposed
-  auto read_tr = [&](const char* tensor, int t, int db) {
-    return tr_pair(tensor + (tr ^ (uint32_t)(32 * db)) + 32 * WB_TOKEN * t, 16 * WB_TOKEN, 2 * t + 1 < NB);
-  };
+  uint32_t give = (uint32_t)(32 * r + 8 * (g ^ (r >> 2))), take = (uint32_t)(w * BLOCK + 32 * (4 * g + (r >> 2)) + 8 * ((r & 3) ^ g));
+  auto read_tr = [&](const char* tensor, int t, int db) { return wb_read_across<NB>(tensor, tr, t, db); };
   // keys 16 w .. of the same queries of P or dS
-  auto read_hand = [&](const char* from, int t) { return tr_pair(from + take + 1024 * t, 512, 2 * t + 1 < NB); };
-  auto barrier = [] {  // a bare one: __syncthreads() would wait for every load and store in flight
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-  };
+  auto read_hand = [&](const char* from, int t) { return wb_tr_pair(from + take + 1024 * t, 512, 2 * t + 1 < NB); };
 
   auto row = [&](int b, char* qg, char* kv, char* qg_next, char* kv_next, int* rid) __attribute__((always_inline)) {
-    asm volatile("" : "+v"(nat), "+v"(tr), "+v"(give), "+v"(take));  // sums with the buffers' places are not kept from row to row
+    if (TIGHT) asm volatile("" : "+v"(nat), "+v"(tr), "+v"(give), "+v"(take));  // sums with the buffers' places are not kept from row to row
     // This row is in LDS: three stores (dQ, dK, dV) are younger than its last piece, or two where K and V come after dQ.
     // (As a builtin: a wait that the compiler does not know of it repeats before the first read, on every load in flight by then.)
     __builtin_amdgcn_s_waitcnt(KV2 ? 0xf73 : 0xf72);  // vmcnt(3), vmcnt(2)
@@ -235,7 +131,7 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(NB == 8
       }
       *at = o;
     }
-    barrier();
+    wb_barrier();
     const bool more = b + 1 < blast;
     if (more) {
       if (KV2) load_pair(kv_next, p.K, p.V, b + 1);
@@ -412,7 +308,7 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(NB == 8
       asm volatile("" ::: "memory");  // older than the three stores that the next row's wait leaves in flight
     }
     store(p.dQ, a, p.scale);
-    barrier();
+    wb_barrier();
     if (!KV2 && more) load_pair(kv, p.K, p.V, b + 1);
 #pragma unroll
     for (int db = 0; db < 2; ++db) a[db] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -425,9 +321,9 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(NB == 8
     }
     store(p.dV, dv, 1.f);
     if (ONE) {
-      barrier();
+      wb_barrier();
       put(hand, dw);
-      barrier();
+      wb_barrier();
     }
 #pragma unroll
     for (int t = 0; t < STEPS; ++t) {
