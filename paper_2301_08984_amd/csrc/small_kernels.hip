@@ -1,5 +1,5 @@
 // Whole-sequence-in-registers attention kernels for short sequences (S <= 64) with
-// head size 32, bf16: the shape of window attention (7x7 = 49 tokens per window).
+// head size 32, bf16, that win_fwd.hip and win_bwd.hip do not serve: the causal mask, a bias in fp32, up to 16 tokens.
 //
 // One wavefront owns one (row b, head h) pair at a time and keeps its entire
 // padded 64x64 score matrix in MFMA accumulators, so the softmax is exact in one
@@ -524,11 +524,18 @@ hipError_t with_variant(const KP& p, F f) {
 
 }  // namespace
 
+// A wavefront per 16 tokens instead of one per row (win_fwd.hip, win_bwd.hip): more than one of them, a bf16 bias or none, no causal mask.  A wavefront here
+// pads every row to 64 tokens, forms scores and exponentials twice in the backward and waits for a row's loads; two of them fit a SIMD.  Forward, backward, us,
+// here | there: 4096 windows of 7 x 7 x 16 heads, regions 203 | 177, 473 | 387; 300 x 12 20.9 | 11.4, 50.8 | 36.9; 64 x 4 9.6 | 9.0, 27.0 | 16.9; 1024 of 8 x 8 x 8
+// 29.9 | 26.0, 91.5 | 75.5; 2048 x 3 of 7 x 7 32.3 | 15.2, 73.0 | 42.4; 1000 x 6 of 6 x 6 24.5 | 12.7, 66.3 | 38.5; 500 x 6 of 5 x 5 14.5 | 9.0, 45.6 | 21.9.
+static bool blocks_ok(const KP& p) { return p.S > 16 && p.mask_kind != 1 && (p.bias_kind == 0 || p.bias_bf16); }
+
 bool small_supported(const KP& p, bool bf16) {
   return bf16 && p.D == SD && p.S <= 64 && !p.gated && p.scale > 0.f;
 }
 
 hipError_t launch_small_fwd(const KP& p, hipStream_t st) {
+  if (blocks_ok(p)) return launch_win_fwd(p, st);
   // A wavefront's rows share its bias tile (a row's results do not depend on how many there are): as many as let
   // the launch fit the 2048 wavefronts that the chip holds, up to 8.  Forward of 17 rows x 8 heads x 49: 23 -> 10 us.
   const int rows = p.b1 - p.b0, even = (rows * (p.h1 - p.h0) + 2047) / 2048, rows_per_wave = even > 8 ? 8 : even;
@@ -537,6 +544,7 @@ hipError_t launch_small_fwd(const KP& p, hipStream_t st) {
 }
 
 hipError_t launch_small_bwd(const KP& p, hipStream_t st) {
+  if (blocks_ok(p)) return launch_win_bwd(p, st);
   const int ng = (p.b1 - 1) / p.sm_gw - p.b0 / p.sm_gw + 1;
   dim3 g((ng + 3) / 4, p.h1 - p.h0);
   return with_variant(p, [&](auto region, auto kg) { small_bwd_kernel<region(), kg()><<<g, 256, 0, st>>>(p); });

@@ -1,7 +1,7 @@
-// Backward of windows of 65 to 160 tokens with head size 32, bf16, in one kernel: dQ, dK, dV, dG and the bias gradient.
+// Backward of windows of 17 to 160 tokens with head size 32, bf16, in one kernel: dQ, dK, dV, dG and the bias gradient.
 //
 // A work-group takes one head and one group of p.sm_gw consecutive global rows (or the chunk's part of it), a wavefront 16 tokens
-// (NB = 5 to 10 wavefronts).  For a row, a wavefront holds the scores and dP of its 16 queries with all keys in registers (lane = query), so
+// (NB = 2 to 10 wavefronts).  For a row, a wavefront holds the scores and dP of its 16 queries with all keys in registers (lane = query), so
 // that the softmax needs no second look at them: maximum, sum and Delta, then P and dS, dQ, and the sum of dS over the rows, which stays in
 // registers and is stored as the group's partial sum, resumed when a chunk boundary cuts the group.  P and dS are handed over through LDS,
 // rounded to bf16, to the wavefronts of the keys (lane = key), which sum dV and dK.  The row's Q, dO, K and V travel straight into
@@ -14,6 +14,8 @@
 //
 // What bounds it (12 x 12): nine wavefronts on four SIMDs, of which one runs three: its vector arithmetic, some 20 instructions a score
 // with what goes round it, takes 60 % of the time; sums of S x S and a row's S and dP (108 registers) leave no room for a second work-group.  LDS 25 %.
+// 4096 x 16 heads of 7 x 7 (memory: 248): 387 with a work-group for every 8 rows, 462 with as many as the chip holds and several groups each, whose heads drift
+// apart and no longer share cache lines; two buffers of K and V, three work-groups a compute unit instead of four, 406.
 // Timed on the way there: waits for loads that the compiler inserted (see `store`) 280 -> 228 (1024 x 16 x 9 x 9), nine spilled registers 147 -> 137.
 #include "win_common.h"
 
@@ -21,14 +23,16 @@ namespace ssa {
 namespace {
 
 // LDS of a work-group.  Two buffers of a row's tensors, but one of K and V where that makes room for a second work-group on the compute unit; P and
-// dS next to each other, or one after the other in one place (and two barriers more a row).  KiB: 65, 74, 69, 129, 155, 132.
-template <int NB> constexpr bool TWO_KV = NB != 6 && NB != 7;
-template <int NB> constexpr bool ONE_PLACE = NB == 7 || NB == 9 || NB == 10;
+// dS next to each other, or one after the other in one place (and two barriers more a row).  KiB from NB = 2 on: 14, 23, 33, 65, 74, 69, 129, 155, 132.
+template <int NB> constexpr bool TWO_KV = NB > 4 && NB != 6 && NB != 7;
+template <int NB> constexpr bool ONE_PLACE = NB <= 4 || NB == 7 || NB == 9 || NB == 10;
+// wavefronts on a SIMD that LDS then allows
+template <int NB> constexpr int WB_WAVES = NB <= 4 ? 4 : NB == 8 ? 2 : 3;
 // the bias in LDS where the registers do not hold it (of ten wavefronts LDS does not, either)
 template <int NB> constexpr bool LDS_BIAS = NB == 9;
 
 template <int NB, bool REGION, bool BIAS, bool GATED>
-__global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(NB == 8 ? 2 : 3, NB == 8 ? 2 : 3))) void win_bwd_kernel(KP p) {
+__global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVES<NB>, WB_WAVES<NB>))) void win_bwd_kernel(KP p) {
 #pragma clang fp contract(off)
   constexpr int T = 16 * NB, STEPS = (NB + 1) / 2, TENSOR = T * WB_TOKEN, BLOCK = T * 32;
   constexpr bool KV2 = TWO_KV<NB>, ONE = ONE_PLACE<NB>, LB = BIAS && LDS_BIAS<NB>, TIGHT = NB == 7 || NB > 8;
@@ -351,11 +355,14 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(NB == 8
 }
 
 template <int NB>
-void launch_blocks(const KP& p, dim3 grid, hipStream_t st) {
+void launch_blocks(const KP& p, hipStream_t st) {
+  const dim3 grid(p.h1 - p.h0, (p.b1 - 1) / p.sm_gw - p.b0 / p.sm_gw + 1);
   auto go = [&](auto region, auto bias, auto gated) { win_bwd_kernel<NB, region(), bias(), gated()><<<grid, 64 * NB, 0, st>>>(p); };
   auto with_bias = [&](auto region, auto bias) {
-    if (p.gated) go(region, bias, std::true_type{});
-    else go(region, bias, std::false_type{});
+    if constexpr (NB > 4) {
+      if (p.gated) return go(region, bias, std::true_type{});
+    }
+    go(region, bias, std::false_type{});
   };
   auto with_mask = [&](auto region) {
     if (p.bias_kind) with_bias(region, std::true_type{});
@@ -374,14 +381,16 @@ hipError_t launch_win_bwd(const KP& args, hipStream_t st) {
     p.sm_gw = p.B;
     p.sm_g0 = 0; p.sm_ring = 1; p.sm_hs = p.H; p.sm_h0 = 0;
   }
-  const dim3 grid(p.h1 - p.h0, (p.b1 - 1) / p.sm_gw - p.b0 / p.sm_gw + 1);
   switch ((p.S + 15) / 16) {
-    case 5: launch_blocks<5>(p, grid, st); break;
-    case 6: launch_blocks<6>(p, grid, st); break;
-    case 7: launch_blocks<7>(p, grid, st); break;
-    case 8: launch_blocks<8>(p, grid, st); break;
-    case 9: launch_blocks<9>(p, grid, st); break;
-    case 10: launch_blocks<10>(p, grid, st); break;
+    case 2: launch_blocks<2>(p, st); break;
+    case 3: launch_blocks<3>(p, st); break;
+    case 4: launch_blocks<4>(p, st); break;
+    case 5: launch_blocks<5>(p, st); break;
+    case 6: launch_blocks<6>(p, st); break;
+    case 7: launch_blocks<7>(p, st); break;
+    case 8: launch_blocks<8>(p, st); break;
+    case 9: launch_blocks<9>(p, st); break;
+    case 10: launch_blocks<10>(p, st); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

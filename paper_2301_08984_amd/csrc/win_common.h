@@ -1,4 +1,4 @@
-// What the kernels of windows of 65 to 160 tokens share (win_fwd.hip, win_bwd.hip): a wavefront per block of 16 tokens, tensors of 32 columns in LDS.
+// What the kernels of windows of 17 to 160 tokens share (win_fwd.hip, win_bwd.hip): a wavefront per block of 16 tokens, tensors of 32 columns in LDS.
 #pragma once
 #include "mfma_common.h"
 

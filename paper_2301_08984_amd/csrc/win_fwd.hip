@@ -1,7 +1,7 @@
-// Forward of attention over windows of 65 to 160 tokens with head size 32, bf16: a whole row (b, h) is small
-// enough to share one work-group, too large for one wavefront (small_kernels.hip ends at 64 tokens; the backward is win_bwd.hip).
+// Forward of attention over windows of 17 to 160 tokens with head size 32, bf16: a whole row (b, h) is small
+// enough to share one work-group (the backward is win_bwd.hip).
 //
-// A work-group takes a run of rows of one head, a wavefront 16 queries (NB = 5 to 10 wavefronts), lane = query.  K and V of a row travel straight into
+// A work-group takes a run of rows of one head, a wavefront 16 queries (NB = 2 to 10 wavefronts), lane = query.  K and V of a row travel straight into
 // one of two LDS buffers, a row ahead; the scores with all keys are held in registers, so that the maximum is known before the first exponential, and
 // the probabilities are the operand of the second product as they are.  One barrier a row.  The bias is fetched or gathered once per work-group.
 //
@@ -15,7 +15,7 @@ namespace ssa {
 namespace {
 
 // work-groups on a compute unit, wavefronts on a SIMD that this takes; the bias in LDS where the registers of that many do not hold it
-template <int NB> constexpr int WF_GROUPS = NB == 5 ? 4 : NB == 6 ? 4 : NB == 10 ? 1 : 2;
+template <int NB> constexpr int WF_GROUPS = NB == 2 ? 12 : NB == 3 ? 8 : NB == 4 ? 6 : NB == 5 ? 4 : NB == 6 ? 4 : NB == 10 ? 1 : 2;
 template <int NB> constexpr int WF_WAVES = (WF_GROUPS<NB> * NB + 3) / 4;
 template <int NB> constexpr bool WF_LDS_BIAS = NB == 9;
 
@@ -176,7 +176,7 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WF_WAVE
 template <int NB>
 void launch_blocks(const KP& p, hipStream_t st) {
   // A run of rows for as many work-groups as the chip holds at a time; of up to 96 tokens, whose fetches would fill the L2s, rounds of at most 6 rows where
-  // that would be more than 8 (1024 x 16 heads of 9 x 9: 98 us in one round, 95 so, before the lane addresses were kept; 256 x 24 of 12 x 12: 85 so, 77 in one).
+  // that would be more than 8 (4096 x 16 heads of 7 x 7: 177 us, rounds of 4 the same, of 12 187; 1024 x 16 heads of 9 x 9: 98 us in one round, 95 so, before the lane addresses were kept; 256 x 24 of 12 x 12: 85 so, 77 in one).
   const int64_t rows = p.b1 - p.b0, heads = p.h1 - p.h0, slots = 256 * WF_GROUPS<NB>;
   const int64_t once = (rows * heads + slots - 1) / slots, rounds = NB > 6 || once <= 8 ? 1 : (once + 5) / 6;
   const int64_t of_head = slots * rounds / heads > 1 ? slots * rounds / heads : 1;
@@ -199,6 +199,9 @@ void launch_blocks(const KP& p, hipStream_t st) {
 
 hipError_t launch_win_fwd(const KP& p, hipStream_t st) {
   switch ((p.S + 15) / 16) {
+    case 2: launch_blocks<2>(p, st); break;
+    case 3: launch_blocks<3>(p, st); break;
+    case 4: launch_blocks<4>(p, st); break;
     case 5: launch_blocks<5>(p, st); break;
     case 6: launch_blocks<6>(p, st); break;
     case 7: launch_blocks<7>(p, st); break;

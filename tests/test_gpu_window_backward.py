@@ -8,8 +8,8 @@ from parity import check_against_oracle
 
 pytestmark = pytest.mark.gpu
 
-# windows of 66, 80, 84, 96, 98, 112, 114, 128, 130, 144, 147, 160 tokens: 5 to 10 wavefronts
-WINS = [(6, 11), (8, 10), (7, 12), (8, 12), (7, 14), (8, 14), (6, 19), (8, 16), (10, 13), (9, 16), (7, 21), (10, 16)]
+# windows of 17, 32, 33, 48, 49, 64, 66, 80, 84, 96, 98, 112, 114, 128, 130, 144, 147, 160 tokens: 2 to 10 wavefronts
+WINS = [(1, 17), (4, 8), (3, 11), (6, 8), (7, 7), (8, 8), (6, 11), (8, 10), (7, 12), (8, 12), (7, 14), (8, 14), (6, 19), (8, 16), (10, 13), (9, 16), (7, 21), (10, 16)]
 
 
 @pytest.mark.parametrize("win", WINS, ids=lambda w: f"{w[0]}x{w[1]}")
@@ -31,3 +31,11 @@ def test_groups_of_several_rows_with_tokens_past_the_end():
     cfg = dict(seed=1300, B=333, H=8, S=130, D=32, dtype="bf16", bias="relpos", win=(10, 13), mask=None, axis="row")
     print("window backward, many rows", flush=True)
     check_against_oracle(cfg, k=1)
+
+
+def test_short_rows_with_a_dense_bias_and_cut_groups():
+    """Dense bias of up to 64 tokens, groups of rows that chunk boundaries cut."""
+    for S, k in ((17, 3), (50, 4), (64, 5)):
+        cfg = dict(seed=1500 + S, B=611, H=5, S=S, D=32, dtype="bf16", bias="dense", mask=None, axis="row")
+        print(f"short rows {S}", flush=True)
+        check_against_oracle(cfg, lo=3, hi=600, k=k)
