@@ -377,7 +377,7 @@ int run_bwd(const ss_attn_desc* d, Family fam, const WsLayout& w, const void* Q,
         set_groups(p);
       }
       p.sm_gw = w.gw > 0 ? w.gw : 8;
-      const bool one = ssa::win_ok(p);  // every gradient in one launch
+      const bool one = ssa::row_ok(p, false);  // every gradient in one launch
       if (one) {
         SS_LAUNCH(SS_K_DQ_DKDV, ssa::launch_mfma_recompute_dq(p, st), "backward (windows)");
       } else if (ssa::mfma_fuses_recompute_dq(p)) {

@@ -23,7 +23,7 @@ inline size_t bias_copy_bytes_for(const KP& p, bool backward, int64_t rows, int 
     if (p.bias_kind == 0 || (backward ? p.bias_kind == 2 || rows * heads < (p.S <= 128 ? 1024 : 64) : p.S <= 128 || rows * heads < 512)) return 0;
     return (size_t)win_packed_bytes(p.S, heads);
   }
-  if (!pair_fwd_ok(p) || p.S > 16384) return 0;
+  if (row_ok(p, !backward) || !pair_fwd_ok(p) || p.S > 16384) return 0;
   const int64_t row_stride = p.ss > (int64_t)p.H * p.D ? p.ss : (int64_t)p.H * p.D;
   if (((int64_t)(p.S - 1) * row_stride + p.D) * 2 >= (1ll << 31)) return 0;
   const int64_t entries = (int64_t)heads * p.S * p.S;

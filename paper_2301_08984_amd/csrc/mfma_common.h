@@ -552,12 +552,22 @@ inline bool fast_ok(const KP& p) {
   return true;
 }
 
-// the window kernels (win_fwd.hip, win_bwd.hip) serve: head size 32, 65 to 160 tokens, a relative-position bias or a
+// the window kernels (win_fwd.hip, win_bwd.hip) serve, beside what row_ok adds: head size 32, 65 to 160 tokens, a relative-position bias or a
 // region mask (a bf16 bias of either kind, or none; no causal mask), a positive scale
 inline bool win_ok(const KP& p) {
   if (p.D != 32 || p.S <= 64 || p.S > 160 || !(p.scale > 0.f) || p.mask_kind == 1) return false;
   if (p.bias_kind != 0 && (!p.bias_bf16 || !(p.scale > 1e-9f && p.scale < 1e9f))) return false;  // bias / scale, as in fast_ok
   return p.bias_kind == 2 || p.mask_kind == 2;
+}
+// Rows of pair attention take the same kernels, head size 32, no mask, a dense bf16 bias or none: the backward of 65 to 160 tokens, with a gate up to 144, beyond
+// which it spills (1000 rows x 8 heads x 160, step: 800 us with the tiled kernels, 1109 with this one); the forward of 129 to 160.  Us, gated, dense bias, tiled
+// kernels | these: backward, 16 x 4 x 100 30.4 | 16.5, 100 x 4 x 128 40.9 | 34.2, 64 x 8 x 128 41.1 | 34.6, 1000 x 8 x 112 339 | 221; without a bias 64 x 4 x 128
+// 16.2 | 9.9, 1000 x 8 x 144 407 | 245; without a gate 300 x 8 x 160 177 | 112.  Forward, 60 x 8 x 155 14.4 | 12.3, 120 x 8 x 140 23.6 | 18.9, 1000 x 8 x 160
+// 163 | 121; 100 x 8 x 128 11.7 | 15.0, 500 x 4 x 128 20.2 | 23.9, 150 x 8 x 100 14.4 | 15.1, 200 x 4 x 96 10.4 | 11.9.
+inline bool row_ok(const KP& p, bool forward) {
+  if (win_ok(p)) return true;
+  return p.D == 32 && p.S > 64 && p.S <= 160 && p.scale > 0.f && p.mask_kind == 0 && (p.bias_kind == 0 || (p.bias_kind == 1 && p.bias_bf16)) &&
+         (forward ? p.S > 128 : !p.gated || p.S <= 144);
 }
 
 // Work-group shape of the forward / dQ kernels: query wavefronts x key-tile groups.  Large shares
@@ -568,12 +578,7 @@ inline bool win_ok(const KP& p) {
 // Decided from the share, never from the chunk.
 // Rows per group of the tiled bias-gradient kernel: 0 = one group (the sum continues in the output);
 // otherwise the share's rows are cut into groups so that about two work-groups per compute unit exist.
-inline int dbias_group_rows(const KP& p) {
-  if (win_ok(p)) {
-    // one work-group per group and head, all of them at one time: two on a compute unit of up to 112 tokens, one of more (win_bwd.hip)
-    const int most = p.S > 112 ? 256 : 512;
-    return p.bias_kind != 0 ? (p.share_units + most - 1) / most : 0;
-  }
+inline int tiled_group_rows(const KP& p) {
   if (p.bias_kind != 1 || !fast_ok(p)) return 0;
   const int64_t tiles = (int64_t)((p.S + 63) / 64) * ((p.S + 63) / 64);
   if (tiles * p.H >= 512) return 0;
@@ -585,9 +590,20 @@ inline int dbias_group_rows(const KP& p) {
   return gw;
 }
 
+inline int dbias_group_rows(const KP& p) {
+  if (!row_ok(p, false)) return tiled_group_rows(p);
+  // one work-group per group and head, all of them at one time: two on a compute unit of up to 112 tokens, one of more (win_bwd.hip)
+  const int most = p.S > 112 ? 256 : 512;
+  int rows = (p.share_units + most - 1) / most;
+  if (p.bias_kind == 0 || win_ok(p)) return p.bias_kind == 0 ? 0 : rows;
+  // (a dense bias: two or three rows are not worth sums beyond what a workspace is made larger for)
+  while (rows > 1 && rows < 4 && (int64_t)(p.share_units / rows) * p.S * p.S * 4 > (12 << 20)) ++rows;
+  return rows < 64 ? rows : 64;
+}
+
 // the longest such groups (0: one group): 64 rows, but for shapes whose sums can go on in the output
 inline int dbias_longest_group(const KP& p) {
-  return win_ok(p) || (p.S & 3) || dbias_group_rows(p) == 0 ? 0 : 64;
+  return win_ok(p) || (p.S & 3) || tiled_group_rows(p) == 0 ? 0 : 64;
 }
 
 // calls f with the compile-time bias variant and causal flag of the launch

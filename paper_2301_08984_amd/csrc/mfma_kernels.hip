@@ -617,7 +617,7 @@ bool mfma_supported(const KP& p, bool bf16) {
 // the specialised kernels (one translation unit each) serve what fast_ok() accepts; the
 // all-feature kernels above serve the rest
 hipError_t launch_mfma_fwd(const KP& p, bool recompute, hipStream_t st) {
-  if (!recompute && win_ok(p)) return launch_win_fwd(p, st);
+  if (!recompute && row_ok(p, true)) return launch_win_fwd(p, st);
   if (fast_ok(p)) return launch_fast_fwd(p, recompute, st);
   SS_DISPATCH_D(fwd_d, p, recompute, st)
 }
@@ -634,7 +634,7 @@ hipError_t launch_mfma_dbias(const KP& p, hipStream_t st) {
   SS_DISPATCH_D(dbias_d, p, st)
 }
 
-bool mfma_wants_bias_transpose(const KP& p) { return fast_ok(p) && p.bias_kind == 1; }
+bool mfma_wants_bias_transpose(const KP& p) { return fast_ok(p) && p.bias_kind == 1 && !row_ok(p, false); }
 // small shares with long rows: dQ and dK/dV share one launch
 bool mfma_fuses_dq_dkdv(const KP& p) { return fast_ok(p) && wg_shape(p) == WG_2x4; }
 hipError_t launch_mfma_dq_dkdv(const KP& p, hipStream_t st) {
@@ -644,7 +644,7 @@ hipError_t launch_mfma_dq_dkdv(const KP& p, hipStream_t st) {
 }
 bool mfma_fuses_recompute_dq(const KP& p) { return rdq_ok(p); }
 hipError_t launch_mfma_recompute_dq(const KP& p, hipStream_t st) {
-  return win_ok(p) ? launch_win_bwd(p, st) : launch_fast_recompute_dq(p, st);
+  return row_ok(p, false) ? launch_win_bwd(p, st) : launch_fast_recompute_dq(p, st);
 }
 int mfma_dbias_group_rows(const KP& p) { return dbias_group_rows(p); }
 

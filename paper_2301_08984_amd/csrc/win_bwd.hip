@@ -355,7 +355,12 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVE
 }
 
 template <int NB>
-void launch_blocks(const KP& p, hipStream_t st) {
+void launch_blocks(const KP& args, hipStream_t st) {
+  KP p = args;
+  if (!p.sm_partial) {  // nothing summed over rows: as few in a work-group as let the launch fit the chip in one round, at most 8 (64 rows x 4 heads x 128: 36 us with 8, 9.9 so)
+    const int64_t slots = 256 * (4 * WB_WAVES<NB> / NB), once = ((int64_t)(p.b1 - p.b0) * (p.h1 - p.h0) + slots - 1) / slots;
+    p.sm_gw = once < 8 ? (int)once : 8;
+  }
   const dim3 grid(p.h1 - p.h0, (p.b1 - 1) / p.sm_gw - p.b0 / p.sm_gw + 1);
   auto go = [&](auto region, auto bias, auto gated) { win_bwd_kernel<NB, region(), bias(), gated()><<<grid, 64 * NB, 0, st>>>(p); };
   auto with_bias = [&](auto region, auto bias) {

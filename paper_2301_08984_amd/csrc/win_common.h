@@ -105,11 +105,16 @@ __device__ inline void win_bias(const KP& p, const uint2* copy, char* buffer, in
     }
     __syncthreads();  // the buffer is free again
   } else {
-    m += ((int64_t)h * p.S + mc) * p.S;
+    // four entries at a time, at any alignment; the last block's one by one: they may end with the matrix
+    typedef __attribute__((ext_vector_type(2))) uint32_t u32x2_any __attribute__((aligned(2)));
+    m += ((int64_t)h * p.S + mc) * p.S + 4 * g;
 #pragma unroll
-    for (int c = 0; c < NB; ++c)
+    for (int c = 0; c < NB - 1; ++c) {
+      const u32x2_any y = *(const u32x2_any*)(m + 16 * c);
+      x[c][0] = y[0] & 0xffffu; x[c][1] = y[0] >> 16; x[c][2] = y[1] & 0xffffu; x[c][3] = y[1] >> 16;
+    }
 #pragma unroll
-      for (int e = 0; e < 4; ++e) x[c][e] = m[min(16 * c + 4 * g + e, p.S - 1)];
+    for (int e = 0; e < 4; ++e) x[NB - 1][e] = m[min(16 * (NB - 1) + e, p.S - 1 - 4 * g)];
   }
 #pragma unroll
   for (int c = 0; c < NB; ++c) {
