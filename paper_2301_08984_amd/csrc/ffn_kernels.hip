@@ -167,6 +167,10 @@ constexpr int items_before(int slot, int n, int slots) {
 //        barriers per MFMA.  For products with a contraction-contiguous operand (see Stager).
 //   FI = FJ = 2, KS = 4, NS = 3: 128 x 128 tile, for products with few tiles; the contraction may be cut into
 //        g.split parts (gemm_plan_tiled).  Forward of 127 tokens x 12288 x 6144: 185 -> 92 us.
+//   FI = 1, FJ = 2, KS = 4, NS = 5: 64 x 128 tile, for few rows of A and a B too large for the few-rows kernel: bound by what a compute unit
+//        has under way, 64 KB of B (three buffers of 128 x 128: 32).  Forward of 16 tokens x 12288 x 6144 (302 MB of weights): 75.3 -> 68.2 us, 4.4 TB/s;
+//        64 81.5 -> 77.6, 50 x 12288 x 2000 45.1 -> 40.8.  Not better: three buffers, two work-groups and twice the parts (73.6); 128 x 128
+//        with four buffers for every product (71.2, and 700 x 1600 x 2400, a step, 159 -> 166: stages past the end of a part).
 //   FI = 2, FJ = 3, KS = 4, NS = 3 and FI = 4, FJ = 3, KS = 2, NS = 4: 128 x 192 and 256 x 192 tiles, for
 //        sizes of which the others leave the last round of work-groups nearly empty (gemm_shape).
 // Stages travel global -> LDS directly, NS - 1 stages ahead of the multiplication, the load
@@ -180,10 +184,9 @@ constexpr int items_before(int slot, int n, int slots) {
 // EPI_ACC the accumulator starts from the fp32 partial result of the previous chunks, so a sum
 // cut into chunks at multiples of 16 is the same sum.
 // ---------------------------------------------------------------------------
-template <bool AT, bool BT, int EPI, int FI, int FJ, int KS>
+template <bool AT, bool BT, int EPI, int FI, int FJ, int KS, int NS>
 __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_kernel(GemmArgs g) {
-  constexpr bool SPLIT = FI == 2 && FJ == 2 && EPI != EPI_ACC;  // g.split parts
-  constexpr int NS = FI * FJ <= 8 ? 3 : 4;  // stage buffers
+  constexpr bool SPLIT = FI <= 2 && FJ == 2 && EPI != EPI_ACC;  // g.split parts
   constexpr int GBM = 64 * FI, GBN = 64 * FJ;
   using StageA = Stager<AT, FI, KS>;
   using StageB = Stager<!BT, FJ, KS>;
@@ -197,7 +200,8 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
   __shared__ __attribute__((aligned(1024))) char stage0[STAGE_BYTES];
   __shared__ __attribute__((aligned(1024))) char stage1[STAGE_BYTES];
   __shared__ __attribute__((aligned(1024))) char stage2[STAGE_BYTES];
-  __shared__ __attribute__((aligned(1024))) char stage3[NS == 4 ? STAGE_BYTES : 16];
+  __shared__ __attribute__((aligned(1024))) char stage3[NS >= 4 ? STAGE_BYTES : 16];
+  __shared__ __attribute__((aligned(1024))) char stage4[NS >= 5 ? STAGE_BYTES : 16];
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, hl = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = w >> 1, wn = w & 1;
@@ -333,8 +337,9 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
     }
     fetch_all(stage0);
     fetch_all(stage1);
-    if (NS == 4) fetch_all(stage2);
-    if constexpr (EPI == EPI_ACC16 && FJ != 3) {  // (three-fragment tiles do not continue sums)
+    if (NS >= 4) fetch_all(stage2);
+    if (NS >= 5) fetch_all(stage3);
+    if constexpr (EPI == EPI_ACC16 && FJ != 3 && FI != 1) {  // (these tiles do not continue sums)
      if (g.accumulate && part == 0) {
       // The partial sum of the earlier chunks is the output itself (bf16): read as whole rows (64 FJ
       // contiguous bytes per row), widened, and turned into the register layout through a piece of
@@ -397,7 +402,13 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
     }
     if (plain) {
       for (int kt = s0; kt < s1; kt += NS) {
-        if (NS == 4) {
+        if (NS == 5) {
+          stage(std::false_type{}, stage0, stage1, stage4);
+          stage(std::false_type{}, stage1, stage2, stage0);
+          stage(std::false_type{}, stage2, stage3, stage1);
+          stage(std::false_type{}, stage3, stage4, stage2);
+          stage(std::false_type{}, stage4, stage0, stage3);
+        } else if (NS == 4) {
           stage(std::false_type{}, stage0, stage1, stage3);
           stage(std::false_type{}, stage1, stage2, stage0);
           stage(std::false_type{}, stage2, stage3, stage1);
@@ -513,8 +524,8 @@ __global__ __launch_bounds__(256, (FI * FJ <= 8 && KS == 2) ? 2 : 1) void gemm_k
     asm volatile("" ::: "memory");
     constexpr int TLD = 128 * FJ + 16, LPR = 8 * FJ;
     constexpr int CY = FJ == 3 ? 3 : 1, RPC = 64 * CY / LPR;  // passes of 64 lanes until the columns repeat, rows they cover
-    static_assert(32 * TLD <= (NS == 4 ? STAGE_BYTES : STAGE_BYTES / 2), "epilogue staging does not fit");
-    char* tb = NS == 4 ? (w == 0 ? stage0 : w == 1 ? stage1 : w == 2 ? stage2 : stage3)
+    static_assert(32 * TLD <= (NS >= 4 ? STAGE_BYTES : STAGE_BYTES / 2), "epilogue staging does not fit");
+    char* tb = NS >= 4 ? (w == 0 ? stage0 : w == 1 ? stage1 : w == 2 ? stage2 : stage3)
                        : (w == 0 ? stage0 : w == 1 ? stage1 : w == 2 ? stage2 : stage0 + STAGE_BYTES / 2);
     int col[CY], rsub[CY];
     float bias[CY][4];
@@ -598,7 +609,7 @@ __global__ __launch_bounds__(256) void colsum_kernel(const uint16_t* A, int64_t 
 
 // Explicit instantiations: the host compiler emits the launch stub of the first implicit
 // instantiation only.
-#define SS_GEMM_INST(a, b, e, fi, fj, ks) template __global__ void gemm_kernel<a, b, e, fi, fj, ks>(GemmArgs);
+#define SS_GEMM_INST(a, b, e, fi, fj, ks) template __global__ void gemm_kernel<a, b, e, fi, fj, ks, fi * fj == 2 ? 5 : fi * fj <= 8 ? 3 : 4>(GemmArgs);
 SS_GEMM_INST(false, false, 0, 4, 2, 4) SS_GEMM_INST(false, false, 2, 4, 2, 4) SS_GEMM_INST(false, false, 4, 4, 2, 4)
 SS_GEMM_INST(false, true, 1, 4, 2, 4) SS_GEMM_INST(false, true, 2, 4, 2, 4) SS_GEMM_INST(false, true, 4, 4, 2, 4)
 SS_GEMM_INST(true, false, 3, 4, 2, 2)
@@ -609,13 +620,15 @@ SS_GEMM_INST(false, false, 0, 4, 3, 2) SS_GEMM_INST(false, false, 4, 4, 3, 2) SS
 SS_GEMM_INST(false, false, 0, 2, 2, 4) SS_GEMM_INST(false, false, 2, 2, 2, 4) SS_GEMM_INST(false, false, 4, 2, 2, 4)
 SS_GEMM_INST(false, true, 1, 2, 2, 4) SS_GEMM_INST(false, true, 2, 2, 2, 4) SS_GEMM_INST(false, true, 4, 2, 2, 4)
 SS_GEMM_INST(true, false, 3, 2, 2, 4)
+// 64 x 128 for few rows of A and a large B
+SS_GEMM_INST(false, false, 0, 1, 2, 4) SS_GEMM_INST(false, false, 4, 1, 2, 4)
 #undef SS_GEMM_INST
 
 template <bool AT, bool BT, int EPI, int FI, int FJ, int KS>
 hipError_t launch_one(const GemmArgs& g, hipStream_t st) {
   const int tiles = ((g.M + 64 * FI - 1) / (64 * FI)) * ((g.N + 64 * FJ - 1) / (64 * FJ));
-  const bool split = FI == 2 && EPI != EPI_ACC && g.split > 1 && g.parts;
-  gemm_kernel<AT, BT, EPI, FI, FJ, KS><<<split ? tiles * g.split : tiles, 256, 0, st>>>(g);
+  const bool split = FI <= 2 && EPI != EPI_ACC && g.split > 1 && g.parts;
+  gemm_kernel<AT, BT, EPI, FI, FJ, KS, FI * FJ == 2 ? 5 : FI * FJ <= 8 ? 3 : 4><<<split ? tiles * g.split : tiles, 256, 0, st>>>(g);
   return hipGetLastError();
 }
 
@@ -623,6 +636,9 @@ template <bool AT, bool BT, int EPI>
 hipError_t launch_shape(const GemmArgs& g, hipStream_t st) {
   const bool narrow = g.narrow || EPI == EPI_ACC || (EPI == EPI_ACC16 && g.accumulate);
   const GemmTile t = gemm_shape(g.M, g.N, g.K, g.split, narrow).tile;
+  // few rows of A: the tile that has most of B under way (see gemm_kernel); the same bits
+  if constexpr (!AT && !BT && EPI != EPI_ACC)
+    if (t == TILE_128x128 && g.M <= 64 && !(EPI == EPI_ACC16 && g.accumulate)) return launch_one<AT, BT, EPI, 1, 2, 4>(g, st);
   if (t == TILE_128x128) return launch_one<AT, BT, EPI, 2, 2, 4>(g, st);
   if (t == TILE_256x128) return launch_one<AT, BT, EPI, 4, 2, AT ? 2 : 4>(g, st);
   if constexpr (EPI != EPI_ACC) return t == TILE_128x192 ? launch_one<AT, BT, EPI, 2, 3, 4>(g, st) : launch_one<AT, BT, EPI, 4, 3, 2>(g, st);
