@@ -564,8 +564,11 @@ inline bool win_ok(const KP& p) {
 // kernels | these: backward, 16 x 4 x 100 30.4 | 16.5, 100 x 4 x 128 40.9 | 34.2, 64 x 8 x 128 41.1 | 34.6, 1000 x 8 x 112 339 | 221; without a bias 64 x 4 x 128
 // 16.2 | 9.9, 1000 x 8 x 144 407 | 245; without a gate 300 x 8 x 160 177 | 112.  Forward, 60 x 8 x 155 14.4 | 12.3, 120 x 8 x 140 23.6 | 18.9, 1000 x 8 x 160
 // 163 | 121; 100 x 8 x 128 11.7 | 15.0, 500 x 4 x 128 20.2 | 23.9, 150 x 8 x 100 14.4 | 15.1, 200 x 4 x 96 10.4 | 11.9.
+// Gated rows of 17 to 64 tokens with any bf16 bias, without a causal mask, too (without a gate: small_kernels.hip); the all-feature kernels | these, step: 512 rows x 8 heads x 64,
+// dense bias, 1607 | 72, no bias 200 x 8 x 64 69 | 27, 300 windows of 7 x 7 x 8 heads with regions 1278 | 47; backward 20 x 4 x 50 90 | 14; forward 20 x 4 x 64 9.2 | 9.7.
 inline bool row_ok(const KP& p, bool forward) {
   if (win_ok(p)) return true;
+  if (p.D == 32 && p.gated && p.S > 16 && p.S <= 64 && p.scale > 0.f && p.mask_kind != 1 && (p.bias_kind == 0 || p.bias_bf16)) return true;
   return p.D == 32 && p.S > 64 && p.S <= 160 && p.scale > 0.f && p.mask_kind == 0 && (p.bias_kind == 0 || (p.bias_kind == 1 && p.bias_bf16)) &&
          (forward ? p.S > 128 : !p.gated || p.S <= 144);
 }
@@ -595,7 +598,7 @@ inline int dbias_group_rows(const KP& p) {
   // one work-group per group and head, all of them at one time: two on a compute unit of up to 112 tokens, one of more (win_bwd.hip)
   const int most = p.S > 112 ? 256 : 512;
   int rows = (p.share_units + most - 1) / most;
-  if (p.bias_kind == 0 || win_ok(p)) return p.bias_kind == 0 ? 0 : rows;
+  if (p.bias_kind == 0 || win_ok(p) || p.S <= 64) return p.bias_kind == 0 ? 0 : rows;
   // (a dense bias: two or three rows are not worth sums beyond what a workspace is made larger for)
   while (rows > 1 && rows < 4 && (int64_t)(p.share_units / rows) * p.S * p.S * 4 > (12 << 20)) ++rows;
   return rows < 64 ? rows : 64;

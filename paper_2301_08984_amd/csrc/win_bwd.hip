@@ -32,7 +32,7 @@ template <int NB> constexpr int WB_WAVES = NB <= 4 ? 4 : NB == 8 ? 2 : 3;
 template <int NB> constexpr bool LDS_BIAS = NB == 9;
 
 template <int NB, bool REGION, bool BIAS, bool GATED>
-__global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVES<NB>, WB_WAVES<NB>))) void win_bwd_kernel(KP p) {
+__global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVES<NB> - (GATED && (NB == 3 || NB == 4)), WB_WAVES<NB> - (GATED && (NB == 3 || NB == 4))))) void win_bwd_kernel(KP p) {
 #pragma clang fp contract(off)
   constexpr int T = 16 * NB, STEPS = (NB + 1) / 2, TENSOR = T * WB_TOKEN, BLOCK = T * 32;
   constexpr bool KV2 = TWO_KV<NB>, ONE = ONE_PLACE<NB>, LB = BIAS && LDS_BIAS<NB>, TIGHT = NB == 7 || NB > 8;
@@ -364,10 +364,8 @@ void launch_blocks(const KP& args, hipStream_t st) {
   const dim3 grid(p.h1 - p.h0, (p.b1 - 1) / p.sm_gw - p.b0 / p.sm_gw + 1);
   auto go = [&](auto region, auto bias, auto gated) { win_bwd_kernel<NB, region(), bias(), gated()><<<grid, 64 * NB, 0, st>>>(p); };
   auto with_bias = [&](auto region, auto bias) {
-    if constexpr (NB > 4) {
-      if (p.gated) return go(region, bias, std::true_type{});
-    }
-    go(region, bias, std::false_type{});
+    if (p.gated) go(region, bias, std::true_type{});
+    else go(region, bias, std::false_type{});
   };
   auto with_mask = [&](auto region) {
     if (p.bias_kind) with_bias(region, std::true_type{});

@@ -21,6 +21,20 @@ def test_lengths(S, form):
     check_against_oracle(_cfg(11, 4, S, **kw), k=2, use_lse=form == "plain")
 
 
+@pytest.mark.parametrize("S", [16, 17, 32, 33, 48, 49, 64])
+@pytest.mark.parametrize("form", ["dense", "no_bias", "sbhd_heads"])
+def test_short_gated_rows(S, form):
+    kw = {"dense": {}, "no_bias": dict(bias=None), "sbhd_heads": dict(layout="sbhd", axis="head")}[form]
+    print(f"short gated rows {S} {form}", flush=True)
+    check_against_oracle(_cfg(37, 4, S, **kw), k=3, use_lse=form == "dense")
+
+
+@pytest.mark.parametrize("win", [(5, 5), (6, 7), (7, 7), (8, 8)], ids=lambda w: f"{w[0]}x{w[1]}")
+def test_short_gated_windows(win):
+    print(f"short gated windows {win}", flush=True)
+    check_against_oracle(_cfg(67, 3, win[0] * win[1], bias="relpos", win=win, mask="region" if win[0] == win[1] else None), k=4, lo=1)
+
+
 @pytest.mark.parametrize("B,H,S,k", [(301, 8, 100, 5), (257, 4, 129, 3), (64, 8, 128, 1), (150, 5, 144, 4)])
 def test_groups_of_rows(B, H, S, k):
     print(f"pair rows in groups {B} x {H} x {S}", flush=True)
