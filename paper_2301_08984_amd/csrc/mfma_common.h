@@ -565,7 +565,7 @@ inline bool win_ok(const KP& p) {
 // 16.2 | 9.9, 1000 x 8 x 144 407 | 245; without a gate 300 x 8 x 160 177 | 112.  Forward, 60 x 8 x 155 14.4 | 12.3, 120 x 8 x 140 23.6 | 18.9, 1000 x 8 x 160
 // 163 | 121; 100 x 8 x 128 11.7 | 15.0, 500 x 4 x 128 20.2 | 23.9, 150 x 8 x 100 14.4 | 15.1, 200 x 4 x 96 10.4 | 11.9.
 // Gated rows of 17 to 64 tokens with any bf16 bias, without a causal mask, too (without a gate: small_kernels.hip); the all-feature kernels | these, step: 512 rows x 8 heads x 64,
-// dense bias, 1607 | 72, no bias 200 x 8 x 64 69 | 27, 300 windows of 7 x 7 x 8 heads with regions 1278 | 47; backward 20 x 4 x 50 90 | 14; forward 20 x 4 x 64 9.2 | 9.7.
+// dense bias, 1607 | 72, no bias 200 x 8 x 64 69 | 27, 300 windows of 7 x 7 x 8 heads with regions 1278 | 47; backward 20 x 4 x 50 90 | 14; forward 512 x 8 x 64 36.7 | 21.7 (of small shares the launch, 8 - 10).
 inline bool row_ok(const KP& p, bool forward) {
   if (win_ok(p)) return true;
   if (p.D == 32 && p.gated && p.S > 16 && p.S <= 64 && p.scale > 0.f && p.mask_kind != 1 && (p.bias_kind == 0 || p.bias_bf16)) return true;
