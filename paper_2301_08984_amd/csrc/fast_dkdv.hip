@@ -409,9 +409,9 @@ void dbias_tile_kernel(KP p) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
         const float e = fast_exp2(fmaf(sa[v], c1, nlse2));
-        float t = pa[v];
-        if (CAUSAL) t = k0 + key_of(v, hl) > q ? 0.f : t;
-        acc[v] = __builtin_fmaf(e, t, acc[v]);
+        const float sum = __builtin_fmaf(e, pa[v], acc[v]);
+        // (a masked pair's exponential has no bound: its logit is not part of the LSE)
+        acc[v] = CAUSAL && k0 + key_of(v, hl) > q ? acc[v] : sum;
       }
     }
   }

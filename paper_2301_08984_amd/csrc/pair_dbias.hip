@@ -220,9 +220,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int v = 4 * (x & 3); v < 4 * (x & 3) + 4; ++v) {
           const int c = x >> 2;
           const float e = fast_exp2(fmaf(s[c][v], c1, nlse2));
-          float y = t[c][v];
-          if (CAUSAL) y = k0 + 32 * c + key_of(v, hl) > q ? 0.f : y;
-          acc[c][v] = __builtin_fmaf(e, y, acc[c][v]);
+          const float sum = __builtin_fmaf(e, t[c][v], acc[c][v]);
+          // (a masked pair's exponential has no bound: its logit is not part of the LSE)
+          acc[c][v] = CAUSAL && k0 + 32 * c + key_of(v, hl) > q ? acc[c][v] : sum;
         }
         __builtin_amdgcn_sched_barrier(0);
       }

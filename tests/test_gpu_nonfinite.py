@@ -117,3 +117,30 @@ def test_bf16_nonfinite_inputs(name, S, win, dense):
             ok = np.isfinite(r)
             if ok.any():
                 assert np.max(np.abs(x[ok] - r[ok])) <= 2e-2 * max(1.0, np.max(np.abs(r[ok]))), n
+
+
+@pytest.mark.parametrize("S", [131, 200, 1030])  # one head per work-group, and two (from 256 such work-groups on)
+def test_bf16_masked_logits_far_above_the_visible_ones(S):
+    """Causal mask with a pair bias: logits of masked pairs far above the LSE of their row, as a large entry or as visible keys that the
+    bias all but masks.  Their exponential overflows; the gradient of their bias is exactly 0."""
+    import torch
+    inp = make_inputs(seed=65, B=2, H=2, S=S, D=32, dtype="bf16", bias="dense", axis="row")
+    bias = inp["bias"]
+    bias[:, 3, 40] = 304.0
+    bias[1, S - 20, S - 2] = 304.0
+    bias[:, 5, :6] = -9984.0
+    bias[:, S // 2, : S // 2 + 1] = -9984.0
+    i, j = np.arange(S)[:, None], np.arange(S)[None]
+    ref = _reference(inp, bias, np.broadcast_to(j <= i, (2, S, S)), float(np.float32(1.0 / math.sqrt(32))))
+    dc = DeviceCase(inp, dtype="bf16", bias="dense", mask="causal")
+    for use_lse in (False, True):
+        print(f"bf16 masked logits S={S} use_lse={use_lse}", flush=True)
+        d = dc.desc("row", 0, 2, 1)
+        dc.fwd(d)
+        dc.bwd(d, use_lse=use_lse, poison=True)
+        torch.cuda.synchronize()
+        for n, r in ref.items():
+            x = dc.host(n)
+            assert np.isfinite(x).all(), (n, int((~np.isfinite(x)).sum()))
+            assert np.max(np.abs(x - r)) <= 2e-2 * max(1.0, np.max(np.abs(r))), n
+        assert np.all(dc.host("dBias")[:, j > i] == 0.0)
