@@ -487,8 +487,8 @@ hipError_t dbias_d(const KP& p, hipStream_t st) {
     default: return hipErrorInvalidValue;         \
   }
 hipError_t launch_fast_dkdv(const KP& p, hipStream_t st) {
-  // large shares at head size 128 without a bias: one gradient per work-group, tiles straight into LDS
-  if (p.D == 128 && p.bias_kind == 0 && wg_shape(p) == WG_4x1) return launch_fast_kv128(p, st);
+  // large shares at head size 128 without a bias: a wavefront per gradient, tiles straight into LDS
+  if (direct128_ok(p)) return launch_fast_kv128(p, st);
   SS_FAST_DISPATCH_D(dkdv_d, p, st)
 }
 hipError_t launch_fast_dbias(const KP& p, hipStream_t st) { SS_FAST_DISPATCH_D(dbias_d, p, st) }

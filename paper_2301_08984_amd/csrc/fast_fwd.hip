@@ -368,7 +368,7 @@ hipError_t launch_fast_fwd(const KP& p, bool recompute, hipStream_t st) {
   // small shares: 32-query work-groups whose wavefronts split the keys
   if (wg_shape(p) == WG_2x4) return launch_fast_fwd_wave(p, recompute, st);
   // large shares at head size 128 without a bias: tiles straight into LDS
-  if (p.D == 128 && p.bias_kind == 0 && wg_shape(p) == WG_4x1)
+  if (direct128_ok(p))
     return recompute && !p.gated ? launch_fast_stat128(p, st) : launch_fast_fwd128(p, recompute, st);
   // pair attention
   if (!recompute && pair_fwd_ok(p)) return launch_pair_fwd(p, st);

@@ -653,6 +653,14 @@ inline WgShape wg_shape(const KP& p) {
   return WG_2x4;
 }
 
+// Large shares at head size 128 without a bias: the kernels whose tiles go straight into LDS (fast_fwd128.hip, fast_stat128.hip, fast_dq128.hip, fast_kv128.hip).
+// They address a (row, head) slice with 32-bit offsets; longer ones (transposed storage) go to the kernels with 64-bit addresses.
+inline bool direct128_ok(const KP& p) {
+  if (p.D != 128 || p.bias_kind != 0 || wg_shape(p) != WG_4x1) return false;
+  const int64_t row_stride = p.ss > (int64_t)p.H * p.D ? p.ss : (int64_t)p.H * p.D;  // also of dO's scratch
+  return ((int64_t)(p.S - 1) * row_stride + p.D) * 2 < (1ll << 31);
+}
+
 // The forward of the smallest shape at head size 128, causal: two query blocks per work-group of eight wavefronts where
 // that leaves blocks enough for more than one per compute unit (12 heads x 2048, 384 of them: 27.5 -> 23.9 us; 8 x 3000, 376:
 // 33.6 -> 30.3; 3 x 8000, 375: 77.6 -> 72.2; 16 x 1024, 256: 12.2 -> 13.9; 4 x 4096, 256: 29.2 -> 37.6) and no more than two (16 x 2048, 512:
