@@ -7,7 +7,7 @@
 //
 // Before, a wavefront took 32 queries and walked the keys with a running maximum, K and V went through registers, and work-groups of more than 128 tokens took
 // one row each.  Us, 8 heads, regions: 512 windows of 12 x 12 tokens 67.7 -> 55.0, without a bias 58.2 -> 43.1, 11 x 11 39.6 -> 33.7, 10 x 10 38.1 -> 29.5,
-// 9 x 9 26.3 -> 25.3; 256 x 24 heads of 12 x 12 99 -> 77; 1024 x 16 of 9 x 9 (memory: 69) 90 -> 88.
+// 9 x 9 22.9 -> 21.7; 256 x 24 heads of 12 x 12 99 -> 77; 1024 x 16 of 9 x 9 (memory: 69) 87.5 -> 82.3.
 // What bounds it: 12 x 12: some 450 vector instructions a wavefront and row, half of them arithmetic on the scores, and reading and writing 64-byte pieces at 3 TB/s.
 #include "win_common.h"
 
@@ -18,17 +18,24 @@ namespace {
 template <int NB> constexpr int WF_GROUPS = NB == 2 ? 12 : NB == 3 ? 8 : NB == 4 ? 6 : NB == 5 ? 4 : NB == 6 ? 4 : NB == 10 ? 1 : 2;
 template <int NB> constexpr int WF_WAVES = (WF_GROUPS<NB> * NB + 3) / 4;
 template <int NB> constexpr bool WF_LDS_BIAS = NB == 9;
+// Region ids straight into LDS where a register for them is one too many (what is spilled is waited for when it is read back, and with it the row that was just
+// asked for): 81 to 96 tokens with a bias and regions, us: 1024 x 16 heads of 9 x 9 90.5 -> 82.3, 4096 x 8 173 -> 160, 512 x 8 23.6 -> 21.7.  Elsewhere a load and a
+// store more cost more than a register (1024 x 16 of 8 x 10 79.6 -> 83.3).
+template <int NB, bool BIAS> constexpr bool WF_ID_DMA = NB == 6 || (NB == 9 && BIAS);
+// The gate asked for ahead of the next row, where there are registers for it and the wait for that row was felt: 1024 x 16 heads, regions, 9 x 9 without a bias
+// 111.9 -> 106.9, 10 x 10 with one 144.8 -> 137.9.
+template <int NB, bool BIAS> constexpr bool WF_EARLY_GATE = NB == 7 || (NB == 6 && !BIAS);
 
 template <int NB, bool REGION, bool BIAS, bool LSE>
 __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WF_WAVES<NB>, WF_WAVES<NB>))) void win_fwd_kernel(KP p, int rows_per_wg) {
 #pragma clang fp contract(off)
   constexpr int T = 16 * NB, STEPS = (NB + 1) / 2, TENSOR = T * WB_TOKEN;
-  constexpr bool LB = BIAS && WF_LDS_BIAS<NB>;
+  constexpr bool LB = BIAS && WF_LDS_BIAS<NB>, ID_DMA = REGION && WF_ID_DMA<NB, BIAS>, EARLY_GATE = WF_EARLY_GATE<NB, BIAS>;
   // arrays of their own: the compiler then knows that a load into one does not feed a read of the other
   __shared__ __attribute__((aligned(1024))) char kv0[2 * TENSOR];
   __shared__ __attribute__((aligned(1024))) char kv1[2 * TENSOR];
   __shared__ uint2 bias_lds[LB ? NB * NB * 64 : 1];
-  __shared__ __attribute__((aligned(16))) int rids[2][REGION ? T : 4];
+  __shared__ __attribute__((aligned(16))) int rids[2][REGION ? (ID_DMA ? (T + 63) / 64 * 64 : T) : 4];
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const BlockId blk = xcd_block_id();  // heads of a row next to each other: they share cache lines
@@ -52,10 +59,17 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WF_WAVE
   bf16x8 qn;
   auto load_query = [&](int b) {
     qn = *(const bf16x8*)((const uint16_t*)p.Q + (int64_t)b * p.sb + mine + 8 * g);
-    if (REGION) id = p.region[(int64_t)(b % p.mask_period) * p.S + min(tid, p.S - 1)];
   };
+  auto load_ids = [&](int* to, int b) {
+    if (!REGION) return;
+    const int32_t* at = p.region + (int64_t)(b % p.mask_period) * p.S + min(tid, p.S - 1);
+    if (!ID_DMA) id = *at;
+    else if (64 * w < T) __builtin_amdgcn_global_load_lds((wb_glb_void*)at, (wb_lds_void*)(to + 64 * w), 4, 0, 0);
+  };
+  auto gate_at = [&](int b, int db) { return *(const uint2*)((const uint16_t*)p.G + (int64_t)b * p.sb + mine + 16 * db + 4 * g); };
   load_keys(kv0, bfirst);
   load_query(bfirst);
+  load_ids(rids[0], bfirst);
   uint32_t bz[BIAS ? NB : 1][2];
   if constexpr (BIAS) win_bias<NB>(p, (const uint2*)p.bias_q, kv1, h, w, lane, bz);
   // Waited for here: else the waits, for every load, come in every row.
@@ -69,18 +83,21 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WF_WAVE
   const float scale = in_vgpr(p.scale), c1 = in_vgpr(BIAS ? LOG2E : p.scale * LOG2E);  // score to logit, then to exponent of two
   uint32_t nat = wb_along(r, g), tr = wb_across(r, g);
 
-  auto row = [&](int b, char* kv, char* kv_next, int* rid) __attribute__((always_inline)) {
+  auto row = [&](int b, char* kv, char* kv_next, int* rid, int* rid_next) __attribute__((always_inline)) {
     asm volatile("" : "+v"(nat), "+v"(tr));  // sums with the buffers' places are not kept from row to row
     // This row is in LDS: the stores of O and of the statistics are younger than its last piece.  (As a builtin: a wait that the compiler does not know of
     // it repeats before the first read, on every load in flight by then.)
     __builtin_amdgcn_s_waitcnt(LSE ? 0xf72 : 0xf71);  // vmcnt(2), vmcnt(1)
     asm volatile("" ::: "memory");
-    if (REGION && tid < T) rid[tid] = id;
+    if (REGION && !ID_DMA && tid < T) rid[tid] = id;
     const bf16x8 qf = qn;
     wb_barrier();
+    uint2 gate[2];
+    if (EARLY_GATE && p.gated) gate[0] = gate_at(b, 0), gate[1] = gate_at(b, 1);
     if (b + 1 < blast) {
       load_keys(kv_next, b + 1);
       load_query(b + 1);
+      load_ids(rid_next, b + 1);
     }
     constexpr int AHEAD = 2;  // blocks of keys whose operands are under way
     bf16x8 kf[AHEAD];
@@ -152,7 +169,7 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WF_WAVE
 #pragma unroll
       for (int v = 0; v < 4; ++v) o[db][v] *= inv;
       if (p.gated) {
-        const uint2 u = *(const uint2*)((const uint16_t*)p.G + at + 16 * db + 4 * g);
+        const uint2 u = EARLY_GATE ? gate[db] : gate_at(b, db);
         const float z[4] = {__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u)};
 #pragma unroll
         for (int v = 0; v < 4; ++v) o[db][v] *= fast_rcp(1.f + fast_exp2(-z[v] * LOG2E));
@@ -162,13 +179,17 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WF_WAVE
     const u32x4 z = gather16(y);
     asm volatile("" ::: "memory");
     *(u32x4*)((uint16_t*)p.Y + at + 8 * store_chunk(g)) = z;
-    if (LSE) p.lse_out[(int64_t)(b - p.lse_b0) * p.lse_sb + (int64_t)(h - p.lse_h0) * p.lse_sh + me] = (log2f(l) - nm) * LN2;
+    if (LSE) {
+      int x = lane;
+      asm volatile("" : "+v"(x));  // (an address formed here, not kept from row to row)
+      p.lse_out[(int64_t)(b - p.lse_b0) * p.lse_sb + (int64_t)(h - p.lse_h0) * p.lse_sh + min(16 * w + (x & 15), p.S - 1)] = (log2f(l) - nm) * LN2;
+    }
     asm volatile("" ::: "memory");
   };
   for (int b = bfirst;; b += 2) {
-    row(b, kv0, kv1, rids[0]);
+    row(b, kv0, kv1, rids[0], rids[1]);
     if (b + 1 >= blast) break;
-    row(b + 1, kv1, kv0, rids[1]);
+    row(b + 1, kv1, kv0, rids[1], rids[0]);
     if (b + 2 >= blast) break;
   }
 }
