@@ -196,10 +196,14 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WF_WAVE
 
 template <int NB>
 void launch_blocks(const KP& p, hipStream_t st) {
-  // A run of rows for as many work-groups as the chip holds at a time; of up to 96 tokens, whose fetches would fill the L2s, rounds of at most 6 rows where
-  // that would be more than 8 (4096 x 16 heads of 7 x 7: 177 us, rounds of 4 the same, of 12 187; 1024 x 16 heads of 9 x 9: 98 us in one round, 95 so, before the lane addresses were kept; 256 x 24 of 12 x 12: 85 so, 77 in one).
+  // A run of rows for as many work-groups as the chip holds at a time, in several rounds where that would be a long one: the heads of a row, which share its
+  // cache lines, drift apart.  Of up to 96 tokens rounds of at most 6 rows from 9 on (4096 x 16 heads of 7 x 7: 177 us, rounds of 4 the same, of 12 187).  Of up to
+  // 112, of 16 rows and more (one round | so, regions: 1024 x 16 heads of 10 x 10 124 | 113, 1024 x 32 252 | 213; 1536 x 12, where rounds would be of 18, 122 | 121); of up to
+  // 128, of 8 and more from 24 on (11 x 11: 768 x 16 114 | 96, 1024 x 16 157 | 127, 1024 x 32 322 | 239, 4096 x 8 285 | 243; 768 x 12, 18 rows, 68 | 70).  Of more tokens
+  // one (256 x 24 of 12 x 12: 85 in rounds, 77 in one; 4096 x 8 349 | 328).
   const int64_t rows = p.b1 - p.b0, heads = p.h1 - p.h0, slots = 256 * WF_GROUPS<NB>;
-  const int64_t once = (rows * heads + slots - 1) / slots, rounds = NB > 6 || once <= 8 ? 1 : (once + 5) / 6;
+  const int64_t once = (rows * heads + slots - 1) / slots;
+  const int64_t rounds = NB > 8 ? 1 : NB == 8 ? (once < 24 ? 1 : once / 8) : NB == 7 ? (once < 16 ? 1 : once / 16) : once <= 8 ? 1 : (once + 5) / 6;
   const int64_t of_head = slots * rounds / heads > 1 ? slots * rounds / heads : 1;
   const int run = (int)((rows + of_head - 1) / of_head);
   const dim3 grid((unsigned)heads, 1, (unsigned)((rows + run - 1) / run));

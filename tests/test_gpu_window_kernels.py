@@ -51,3 +51,33 @@ def test_sub_range_of_many_rows():
     cfg = _cfg((9, 9), B=70, H=64, mask=None)
     print("window sub-range", flush=True)
     check_against_oracle(cfg, lo=3, hi=67, k=5)
+
+
+@pytest.mark.parametrize("B,H,S", [(1030, 8, 81), (1100, 15, 97), (1030, 16, 112), (777, 16, 113), (519, 32, 128), (300, 8, 144)])
+def test_runs_of_rows_of_every_length(B, H, S):
+    """Forward: a row's results do not depend on how many rows its work-group walks, nor in how many rounds the launch runs them."""
+    import torch
+    from paper_2301_08984_amd import binding as ss
+    gen = torch.Generator(device="cuda").manual_seed(S)
+    q, k, v, g = (torch.randn((B, S, H, 32), generator=gen, device="cuda").bfloat16() for _ in range(4))
+    bias = torch.randn((H, S, S), generator=gen, device="cuda").bfloat16()
+    ids = torch.stack([torch.arange(S, dtype=torch.int32, device="cuda") * n // S for n in (1, 2, 3)]).contiguous()
+    print(f"runs of rows {B} x {H} x {S}", flush=True)
+    for gated in (False, True):
+        out = []
+        for lo, hi in ((0, B), (B // 2, B // 2 + 7), (B - 3, B)):
+            y, lse = torch.full_like(q, float("nan")), torch.full((B, H, S), float("nan"), device="cuda")
+            d = ss.make_desc(B, H, S, 32, ss.SS_BF16, 32 ** -0.5, ss.SS_AXIS_ROW, lo, hi, 1, stride_b=S * H * 32, stride_s=H * 32, stride_h=32,
+                             bias_kind=ss.SS_BIAS_DENSE, mask_kind=ss.SS_MASK_REGION, mask_period=3, gated=gated)
+            ss.ss_attn_fwd(d, q, k, v, bias, ids, g if gated else None, y, lse, None, 0, torch.cuda.current_stream().cuda_stream)
+            out.append((lo, hi, y, lse))
+        torch.cuda.synchronize()
+        for lo, hi, y, lse in out[1:]:
+            assert not torch.isnan(y[lo:hi]).any() and not torch.isnan(lse[lo:hi]).any()
+            assert torch.equal(y[lo:hi], out[0][2][lo:hi]) and torch.equal(lse[lo:hi], out[0][3][lo:hi])
+        b = B - 2  # one row in fp32
+        s = torch.einsum("ihd,jhd->hij", q[b].float(), k[b].float()) * 32 ** -0.5 + bias.float()
+        s.masked_fill_(ids[b % 3][:, None] != ids[b % 3][None], float("-inf"))
+        ref = torch.einsum("hij,jhd->ihd", torch.softmax(s, -1), v[b].float())
+        ref = ref * torch.sigmoid(g[b].float()) if gated else ref
+        assert ((out[0][2][b].float() - ref).norm() / ref.norm()).item() <= 1e-2  # bf16 probabilities and results
