@@ -30,12 +30,21 @@ template <int NB> constexpr bool ONE_PLACE = NB <= 4 || NB == 7 || NB == 9 || NB
 template <int NB> constexpr int WB_WAVES = NB <= 4 ? 4 : NB == 8 ? 2 : 3;
 // the bias in LDS where the registers do not hold it (of ten wavefronts LDS does not, either)
 template <int NB> constexpr bool LDS_BIAS = NB == 9;
+// What is spilled is waited for when it is read back, and with it the row that was just asked for.  Left to itself the compiler adds dS to the sums over
+// rows, and packs P and dS, at the row's end: it keeps all of them in fp32 until then.  Where the registers do not hold that: each block of keys is finished
+// before the next, and O is formed as soon as the exponentials are there (elsewhere that costs 2 %).  Gated windows with regions and a bias, 512 x 8, us:
+// 9 x 9 101 -> 82.5, 10 x 10 120 -> 110, 12 x 12 232 -> 157 (without regions 201 -> 147); with the kernels before these 113, 154, 316 (280).
+template <int NB, bool REGION, bool BIAS, bool GATED> constexpr bool AT_ONCE = BIAS && (NB == 10 || (GATED && (NB == 9 || (REGION && (NB == 6 || NB == 7)))));
+// Ten wavefronts with a bias: dP of a block is formed again where it is used, from the same operands, instead of kept from the mean on (40 registers).  512 x 8 of
+// 10 x 16 with regions 227 -> 139, gated 589 -> 329 (424 with the kernels before these), 300 x 8 x 160 with a dense bias 135 -> 85.
+template <int NB, bool BIAS> constexpr bool DP_AGAIN = BIAS && NB == 10;
 
 template <int NB, bool REGION, bool BIAS, bool GATED>
 __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVES<NB> - (GATED && (NB == 3 || NB == 4)), WB_WAVES<NB> - (GATED && (NB == 3 || NB == 4))))) void win_bwd_kernel(KP p) {
 #pragma clang fp contract(off)
   constexpr int T = 16 * NB, STEPS = (NB + 1) / 2, TENSOR = T * WB_TOKEN, BLOCK = T * 32;
   constexpr bool KV2 = TWO_KV<NB>, ONE = ONE_PLACE<NB>, LB = BIAS && LDS_BIAS<NB>, TIGHT = NB == 7 || NB > 8;
+  constexpr bool NOW = AT_ONCE<NB, REGION, BIAS, GATED>, AGAIN = DP_AGAIN<NB, BIAS>, ID_DMA = REGION && GATED && AGAIN;  // (region ids: straight into LDS)
   // arrays of their own: the compiler then knows that a load into one does not feed a read of another
   __shared__ __attribute__((aligned(1024))) char qg0[2 * TENSOR];
   __shared__ __attribute__((aligned(1024))) char qg1[2 * TENSOR];
@@ -43,7 +52,7 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVE
   __shared__ __attribute__((aligned(1024))) char kv1[KV2 ? 2 * TENSOR : 16];
   __shared__ __attribute__((aligned(1024))) char hand[(ONE ? 1 : 2) * NB * BLOCK];  // P, dS: per block of 16 keys a row of 32 bytes per query
   __shared__ uint2 bias_lds[LB ? NB * NB * 64 : 1];
-  __shared__ __attribute__((aligned(16))) int rids[2][REGION ? T : 4];
+  __shared__ __attribute__((aligned(16))) int rids[2][REGION ? (ID_DMA ? (T + 63) / 64 * 64 : T) : 4];
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const BlockId blk = xcd_block_id();  // heads of a row next to each other: they share cache lines
@@ -73,8 +82,11 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVE
     __builtin_amdgcn_sched_barrier(0);
   };
   int id = 0;
-  auto load_id = [&](int b) {
-    if (REGION) id = p.region[(int64_t)(b % p.mask_period) * p.S + min(64 * w + anew(), p.S - 1)];
+  auto load_id = [&](int* to, int b) {
+    if (!REGION) return;
+    const int32_t* at = p.region + (int64_t)(b % p.mask_period) * p.S + min(64 * w + anew(), p.S - 1);
+    if (!ID_DMA) id = *at;
+    else if (64 * w < T) __builtin_amdgcn_global_load_lds((wb_glb_void*)at, (wb_lds_void*)(to + 64 * w), 4, 0, 0);
   };
   u32x4 gate = {0, 0, 0, 0};  // of the lane's piece of dY
   auto load_gate = [&](int b) {
@@ -82,7 +94,7 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVE
   };
   load_pair(kv0, p.K, p.V, bfirst);
   load_pair(qg0, p.Q, p.dY, bfirst);
-  load_id(bfirst);
+  load_id(rids[0], bfirst);
   load_gate(bfirst);
 
   uint32_t bz[BIAS ? NB : 1][2];
@@ -117,13 +129,13 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVE
   // keys 16 w .. of the same queries of P or dS
   auto read_hand = [&](const char* from, int t) { return wb_tr_pair(from + take + 1024 * t, 512, 2 * t + 1 < NB); };
 
-  auto row = [&](int b, char* qg, char* kv, char* qg_next, char* kv_next, int* rid) __attribute__((always_inline)) {
+  auto row = [&](int b, char* qg, char* kv, char* qg_next, char* kv_next, int* rid, int* rid_next) __attribute__((always_inline)) {
     if (TIGHT) asm volatile("" : "+v"(nat), "+v"(tr), "+v"(give), "+v"(take));  // sums with the buffers' places are not kept from row to row
     // This row is in LDS: three stores (dQ, dK, dV) are younger than its last piece, or two where K and V come after dQ.
     // (As a builtin: a wait that the compiler does not know of it repeats before the first read, on every load in flight by then.)
     __builtin_amdgcn_s_waitcnt(KV2 ? 0xf73 : 0xf72);  // vmcnt(3), vmcnt(2)
     asm volatile("" ::: "memory");
-    if (REGION && tid < T) rid[tid] = id;
+    if (REGION && !ID_DMA && tid < T) rid[tid] = id;
     if (GATED) {  // dO = dY * gate, of the lane's own piece
       u32x4* at = (u32x4*)(qg + TENSOR + 1024 * w + 16 * lane);
       u32x4 o = *at;
@@ -140,10 +152,29 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVE
     if (more) {
       if (KV2) load_pair(kv_next, p.K, p.V, b + 1);
       load_pair(qg_next, p.Q, p.dY, b + 1);
-      load_id(b + 1);
+      load_id(rid_next, b + 1);
       load_gate(b + 1);
     }
-    uint2 pw[NB], dw[NB], ew[GATED ? NB : 1];  // P, dS and, for O, P before it is divided by the sum, of this lane's query, packed
+    uint2 pw[NB], dw[NB], ew[GATED && !NOW ? NB : 1];  // P, dS and, for O, P before it is divided by the sum, of this lane's query, packed
+    auto pack = [](const f32x4& x) { return uint2{pack2_bf16(x[0], x[1]), pack2_bf16(x[2], x[3])}; };
+    auto operand = [](uint2 lo, uint2 hi) {
+      union { u32x4 u; bf16x8 v; } o;
+      o.u = u32x4{lo.x, lo.y, hi.x, hi.y};
+      return o.v;
+    };
+    auto ones = [] {
+      union { u32x4 u; bf16x8 v; } o;
+      o.u = u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+      return o.v;
+    };
+    // O from the probabilities before they are divided by their sum (error of dG 2.21e-3 if after: the largest are exact), and the sum of those, rounded as they are
+    f32x4 o[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}}, esum = o[0];
+    auto add_to_o = [&](int t, uint2 lo, uint2 hi) __attribute__((always_inline)) {
+      const bf16x8 ef = operand(lo, hi);
+      esum = mfma16(ones(), ef, esum);
+#pragma unroll
+      for (int db = 0; db < 2; ++db) o[db] = mfma16(read_tr(kv + TENSOR, t, db), ef, o[db]);
+    };
     {
       const bf16x8 qf = *(const bf16x8*)(qg + nat + 1024 * w), gf = *(const bf16x8*)(qg + TENSOR + nat + 1024 * w);
       f32x4 s[NB], dp[NB];
@@ -152,7 +183,7 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVE
       uint2 bn[AHEAD];
       auto read_keys = [&](int c) __attribute__((always_inline)) {
         kf[c % AHEAD] = *(const bf16x8*)(kv + nat + 1024 * c);
-        vf[c % AHEAD] = *(const bf16x8*)(kv + TENSOR + nat + 1024 * c);
+        if (!AGAIN) vf[c % AHEAD] = *(const bf16x8*)(kv + TENSOR + nat + 1024 * c);
         if (LB) bn[c % AHEAD] = bias_lds[(w * NB + c) * 64 + lane];
       };
 #pragma unroll
@@ -162,7 +193,7 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVE
 #pragma unroll
         for (int v = 0; v < 4; ++v) s[c][v] = BIAS || c < NB - 1 || 16 * c + 4 * g + v < p.S ? 0.f : -INFINITY;
         s[c] = mfma16(kf[c % AHEAD], qf, s[c]);
-        dp[c] = mfma16(vf[c % AHEAD], gf, f32x4{0.f, 0.f, 0.f, 0.f});
+        if (!AGAIN) dp[c] = mfma16(vf[c % AHEAD], gf, f32x4{0.f, 0.f, 0.f, 0.f});
         if (BIAS) {  // logits
           uint32_t lo = bz[BIAS ? c : 0][0], hi = bz[BIAS ? c : 0][1];
           if (LB) {
@@ -178,7 +209,7 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVE
         }
         if (c + AHEAD < NB) read_keys(c + AHEAD);
       }
-      const bool masked = REGION && ids_differ<NB>(rid, lane);
+      const bool masked = REGION && ids_differ<NB>(rid, AGAIN ? anew() : lane);
       const int my_rid = masked ? rid[me] : 0;
       if (masked) {
 #pragma unroll
@@ -197,14 +228,35 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVE
         for (int v = 0; v < 4; ++v) top[v] = fmaxf(top[v], s[c][v]);
       const float nm = -groups_max(fmaxf(fmaxf(top[0], top[1]), fmaxf(top[2], top[3]))) * c1;
       float sum[4] = {0.f, 0.f, 0.f, 0.f}, mean[4] = {0.f, 0.f, 0.f, 0.f};
+      uint32_t vat = nat;
+      auto read_values = [&](int c) __attribute__((always_inline)) { vf[c % AHEAD] = *(const bf16x8*)(kv + TENSOR + vat + 1024 * c); };
+      auto values_anew = [&] {
+        asm volatile("" : "+v"(vat));
 #pragma unroll
-      for (int c = 0; c < NB; ++c)
+        for (int c = 0; c < AHEAD; ++c) read_values(c);
+      };
+      if (AGAIN) values_anew();  // (opaque: not the same reads as before)
+#pragma unroll
+      for (int c = 0; c < NB; ++c) {
+        const f32x4 d = AGAIN ? mfma16(vf[c % AHEAD], gf, f32x4{0.f, 0.f, 0.f, 0.f}) : dp[c];
+        if (AGAIN && c + AHEAD < NB) read_values(c + AHEAD);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           s[c][v] = fast_exp2(fmaf(s[c][v], c1, nm));
           sum[v] += s[c][v];
-          mean[v] = fmaf(s[c][v], dp[c][v], mean[v]);
+          mean[v] = fmaf(s[c][v], d[v], mean[v]);
         }
+        if (AGAIN) asm volatile("" : "+v"(mean[0]), "+v"(mean[1]), "+v"(mean[2]), "+v"(mean[3]), "+v"(sum[0]), "+v"(sum[1]), "+v"(sum[2]), "+v"(sum[3]));
+      }
+      if (GATED && NOW) {
+#pragma unroll
+        for (int t = 0; t < STEPS; ++t) {
+          const uint2 e[2] = {pack(s[2 * t]), 2 * t + 1 < NB ? pack(s[min(2 * t + 1, NB - 1)]) : uint2{0, 0}};
+          add_to_o(t, e[0], e[1]);
+          if (AGAIN) __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      if (AGAIN) values_anew();
       // queries past the end (the last one again) contribute nothing
       const float inv = me < p.S ? 1.f / groups_sum((sum[0] + sum[1]) + (sum[2] + sum[3])) : 0.f;
       const float delta = groups_sum((mean[0] + mean[1]) + (mean[2] + mean[3])) * inv;
@@ -213,11 +265,13 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVE
 #pragma unroll
       for (int c = 0; c < NB; ++c) {
         float pr[4], ds[4];
-        if (GATED) ew[GATED ? c : 0] = uint2{pack2_bf16(s[c][0], s[c][1]), pack2_bf16(s[c][2], s[c][3])};
+        if (GATED && !NOW) ew[GATED && !NOW ? c : 0] = pack(s[c]);
+        const f32x4 d = AGAIN ? mfma16(vf[c % AHEAD], gf, f32x4{0.f, 0.f, 0.f, 0.f}) : dp[c];
+        if (AGAIN && c + AHEAD < NB) read_values(c + AHEAD);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           pr[v] = s[c][v] * inv;
-          ds[v] = pr[v] * (dp[c][v] - delta);
+          ds[v] = pr[v] * (d[v] - delta);
         }
         if (REGION) {
           int cut = unsound;  // opaque: one version of the loop
@@ -232,11 +286,14 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVE
             }
           }
         }
-        if (BIAS)
+        if (BIAS) {
 #pragma unroll
           for (int v = 0; v < 4; ++v) acc[BIAS ? c : 0][v] += ds[v];
+          if (NOW) asm volatile("" : "+v"(acc[BIAS ? c : 0]));
+        }
         pw[c] = uint2{pack2_bf16(pr[0], pr[1]), pack2_bf16(pr[2], pr[3])};
         dw[c] = uint2{pack2_bf16(ds[0], ds[1]), pack2_bf16(ds[2], ds[3])};
+        if (NOW) asm volatile("" : "+v"(pw[c].x), "+v"(pw[c].y), "+v"(dw[c].x), "+v"(dw[c].y));
       }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -244,7 +301,7 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVE
 #pragma unroll
       for (int c = 0; c < NB; ++c) *(uint2*)(to + c * BLOCK + 512 * w + give) = x[c];
     };
-    auto operand = [](const auto& x, int t) {
+    auto both = [](const auto& x, int t) {
       union { u32x4 u; bf16x8 v; } o;
       const uint2 hi = 2 * t + 1 < NB ? x[min(2 * t + 1, NB - 1)] : uint2{0, 0};
       o.u = u32x4{x[2 * t].x, x[2 * t].y, hi.x, hi.y};
@@ -256,13 +313,11 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVE
     // taken off along the mean key of the rounded probabilities.
     f32x4 a[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}}, k1[2] = {a[0], a[1]};
     f32x4 psum = a[0], dsum = a[0];
-    union { u32x4 u; bf16x8 v; } ones;
-    ones.u = u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
 #pragma unroll
     for (int t = 0; t < STEPS; ++t) {
-      const bf16x8 pf = operand(pw, t), df = operand(dw, t);
-      psum = mfma16(ones.v, pf, psum);
-      dsum = mfma16(ones.v, df, dsum);
+      const bf16x8 pf = both(pw, t), df = both(dw, t);
+      psum = mfma16(ones(), pf, psum);
+      dsum = mfma16(ones(), df, dsum);
 #pragma unroll
       for (int db = 0; db < 2; ++db) {
         const bf16x8 kt = read_tr(kv, t, db);
@@ -285,20 +340,14 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVE
       *(u32x4*)(token < p.S ? at : (uint16_t*)p.delta) = z;
     };
     if (GATED) {
-      // dG = dY O g (1 - g), O divided by the sum of the probabilities as they were rounded (before they are divided, the largest are exact:
-      // error of dG 2.21e-3 if after)
-      f32x4 o[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}}, esum = o[0];
+      if (!NOW) {
 #pragma unroll
-      for (int t = 0; t < STEPS; ++t) {
-        const bf16x8 ef = operand(ew, t);
-        esum = mfma16(ones.v, ef, esum);
-#pragma unroll
-        for (int db = 0; db < 2; ++db) o[db] = mfma16(read_tr(kv + TENSOR, t, db), ef, o[db]);
+        for (int t = 0; t < STEPS; ++t) add_to_o(t, ew[2 * t], 2 * t + 1 < NB ? ew[min(2 * t + 1, NB - 1)] : uint2{0, 0});
       }
-      const float inv = 1.f / esum[0];
+      const float inv = 1.f / esum[0];  // dG = dY O g (1 - g)
 #pragma unroll
       for (int db = 0; db < 2; ++db) {
-        const int64_t at = row_at(b) + (int64_t)min(16 * w + (anew() & 15), p.S - 1) * p.ss + 16 * db + 4 * g;
+        const int64_t at = row_at(b) + (int64_t)min(16 * w + (anew() & 15), p.S - 1) * p.ss + 16 * db + 4 * (NOW && REGION ? anew() >> 4 : g);
         const uint2 ux = *(const uint2*)((const uint16_t*)p.dY + at), ug = *(const uint2*)((const uint16_t*)p.G + at);
         const float y[4] = {__uint_as_float(ux.x << 16), __uint_as_float(ux.x & 0xffff0000u), __uint_as_float(ux.y << 16), __uint_as_float(ux.y & 0xffff0000u)};
         const float z[4] = {__uint_as_float(ug.x << 16), __uint_as_float(ug.x & 0xffff0000u), __uint_as_float(ug.y << 16), __uint_as_float(ug.y & 0xffff0000u)};
@@ -338,19 +387,20 @@ __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WB_WAVE
     store(p.dK, a, p.scale);
   };
   for (int b = bfirst;; b += 2) {
-    row(b, qg0, kv0, qg1, KV2 ? kv1 : kv0, rids[0]);
+    row(b, qg0, kv0, qg1, KV2 ? kv1 : kv0, rids[0], rids[1]);
     if (b + 1 >= blast) break;
-    row(b + 1, qg1, KV2 ? kv1 : kv0, qg0, kv0, rids[1]);
+    row(b + 1, qg1, KV2 ? kv1 : kv0, qg0, kv0, rids[1], rids[0]);
     if (b + 2 >= blast) break;
   }
-  if (BIAS && part && me < p.S) {
-    int at = me * p.S + 4 * g;  // opaque: the addresses are not to be kept in registers from the load of the partial sum on
-    asm volatile("" : "+v"(at));
+  int l = lane;  // opaque: the addresses are not to be kept in registers from the load of the partial sum on
+  asm volatile("" : "+v"(l));
+  if (BIAS && part && 16 * w + (l & 15) < p.S) {
+    const int at = (16 * w + (l & 15)) * p.S + 4 * (l >> 4);
 #pragma unroll
     for (int c = 0; c < NB; ++c)
 #pragma unroll
       for (int v = 0; v < 4; ++v)
-        if (c < NB - 1 || 16 * c + 4 * g + v < p.S) part[at + 16 * c + v] = acc[BIAS ? c : 0][v];
+        if (c < NB - 1 || 16 * c + 4 * (l >> 4) + v < p.S) part[at + 16 * c + v] = acc[BIAS ? c : 0][v];
   }
 }
 

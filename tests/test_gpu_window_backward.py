@@ -39,3 +39,16 @@ def test_short_rows_with_a_dense_bias_and_cut_groups():
         cfg = dict(seed=1500 + S, B=611, H=5, S=S, D=32, dtype="bf16", bias="dense", mask=None, axis="row")
         print(f"short rows {S}", flush=True)
         check_against_oracle(cfg, lo=3, hi=600, k=k)
+
+
+@pytest.mark.parametrize("win", [(8, 11), (8, 12), (7, 15), (9, 15), (12, 12), (7, 21), (10, 16)], ids=lambda w: f"{w[0]}x{w[1]}")
+@pytest.mark.parametrize("gated", [True, False], ids=["gated", "plain"])
+def test_several_rows_with_bias_and_regions(win, gated):
+    """Blocks that are finished one at a time (AT_ONCE, DP_AGAIN): several rows a work-group, through both buffers, with masked and unmasked rows in turn."""
+    S = win[0] * win[1]
+    cfg = dict(seed=1700 + S, B=335, H=4, S=S, D=32, dtype="bf16", bias="relpos", win=win, mask=None, gated=gated, axis="row")
+    inp = make_inputs(**cfg)
+    inp["region_ids"] = (np.arange(S)[None] * np.arange(1, 4)[:, None] // S).astype(np.int32)
+    cfg["mask"] = "region"
+    print(f"window backward, several rows {win} {gated}", flush=True)
+    check_against_oracle(cfg, k=3, inputs=inp)

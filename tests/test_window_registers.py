@@ -22,3 +22,10 @@ def test_forward(tmp_path):
     scratch = scratch_bytes("win_fwd.hip", tmp_path)
     assert len(scratch) == 9 * 8  # blocks of 16 tokens, regions, bias, statistics
     assert {k: v for k, v in scratch.items() if v} == {}
+
+
+def test_backward(tmp_path):
+    """12 bytes at most: an address that only the start and the end of a work-group use, or one reload in two rows."""
+    scratch = scratch_bytes("win_bwd.hip", tmp_path)
+    assert len(scratch) == 9 * 8  # blocks of 16 tokens, regions, bias, gate
+    assert {k: v for k, v in scratch.items() if v > 12} == {}
