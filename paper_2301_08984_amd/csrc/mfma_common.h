@@ -560,17 +560,18 @@ inline bool win_ok(const KP& p) {
   return p.bias_kind == 2 || p.mask_kind == 2;
 }
 // Rows of pair attention take the same kernels, head size 32, no mask, a dense bf16 bias or none: the backward of 65 to 160 tokens, with a gate up to 144, beyond
-// which it spills (1000 rows x 8 heads x 160, step: 800 us with the tiled kernels, 1109 with this one); the forward of 129 to 160.  Us, gated, dense bias, tiled
+// which it spills (1000 rows x 8 heads x 160, step: 800 us with the tiled kernels, 1109 with this one); the forward of 129 to 160, of up to 128 (row, head)
+// pairs only without a bias, which a work-group gathers before its first row.  Us, gated, dense bias, tiled
 // kernels | these: backward, 16 x 4 x 100 30.4 | 16.5, 100 x 4 x 128 40.9 | 34.2, 64 x 8 x 128 41.1 | 34.6, 1000 x 8 x 112 339 | 221; without a bias 64 x 4 x 128
 // 16.2 | 9.9, 1000 x 8 x 144 407 | 245; without a gate 300 x 8 x 160 177 | 112.  Forward, 60 x 8 x 155 14.4 | 12.3, 120 x 8 x 140 23.6 | 18.9, 1000 x 8 x 160
-// 163 | 121; 100 x 8 x 128 11.7 | 15.0, 500 x 4 x 128 20.2 | 23.9, 150 x 8 x 100 14.4 | 15.1, 200 x 4 x 96 10.4 | 11.9.
+// 163 | 121; 4 x 129 6.5 | 7.7, 128 x 160 6.5 | 7.1 (without a bias 5.1 | 4.4), 136 x 129 8.2 | 7.9, 144 x 160 7.8 | 7.1; 100 x 8 x 128 11.7 | 15.0, 500 x 4 x 128 20.2 | 23.9, 150 x 8 x 100 14.4 | 15.1, 200 x 4 x 96 10.4 | 11.9.
 // Gated rows of 17 to 64 tokens with any bf16 bias, without a causal mask, too (without a gate: small_kernels.hip); the all-feature kernels | these, step: 512 rows x 8 heads x 64,
 // dense bias, 1607 | 72, no bias 200 x 8 x 64 69 | 27, 300 windows of 7 x 7 x 8 heads with regions 1278 | 47; backward 20 x 4 x 50 90 | 14; forward 512 x 8 x 64 36.7 | 21.7 (of small shares the launch, 8 - 10).
 inline bool row_ok(const KP& p, bool forward) {
   if (win_ok(p)) return true;
   if (p.D == 32 && p.gated && p.S > 16 && p.S <= 64 && p.scale > 0.f && p.mask_kind != 1 && (p.bias_kind == 0 || p.bias_bf16)) return true;
   return p.D == 32 && p.S > 64 && p.S <= 160 && p.scale > 0.f && p.mask_kind == 0 && (p.bias_kind == 0 || (p.bias_kind == 1 && p.bias_bf16)) &&
-         (forward ? p.S > 128 : !p.gated || p.S <= 144);
+         (forward ? p.S > 128 && (p.bias_kind == 0 || p.share_units > 128) : !p.gated || p.S <= 144);
 }
 
 // Work-group shape of the forward / dQ kernels: query wavefronts x key-tile groups.  Large shares

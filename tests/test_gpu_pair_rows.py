@@ -41,6 +41,14 @@ def test_groups_of_rows(B, H, S, k):
     check_against_oracle(_cfg(B, H, S), lo=3, hi=B - 2, k=k)
 
 
+@pytest.mark.parametrize("S", [129, 144, 145, 160])
+@pytest.mark.parametrize("B", [32, 33])
+def test_forward_on_both_sides_of_its_line(B, S):
+    """Up to 128 (row, head) pairs a forward with a bias takes the tiled kernels, beyond them the kernel that holds a row's scores."""
+    print(f"pair rows, forward {B} x 4 x {S}", flush=True)
+    check_against_oracle(_cfg(B, 4, S, gated=S % 2 == 0))
+
+
 def test_captured_and_eager_calls_agree():
     import torch
     cfg = _cfg(130, 4, 132)
