@@ -464,11 +464,13 @@ template <int D>
 hipError_t dbias_d(const KP& p, hipStream_t st) {
   // callers guarantee S > 64 (fast_ok)
   const int ng = p.sm_partial ? (p.b1 - 1) / p.sm_gw - p.b0 / p.sm_gw + 1 : 1, heads = p.h1 - p.h0, tiles = (p.S + 63) / 64;
-  const int64_t lim = 1ll << 30;
+  const int64_t lim = 1ll << 30, live = p.mask_kind == 1 ? (int64_t)tiles * (tiles + 1) / 2 : (int64_t)tiles * tiles;
   // Neighbouring heads 64 bytes apart: two per work-group (pair_dbias.hip), whose start takes longer, where that leaves a work-group for every compute
   // unit (one head | two, us: 16 of them, 16 rows x 4 heads x 100: 11.3 | 13.1; 128, 16 x 8 x 200: 12.3 | 13.3; 256, 18 x 8 x 472: 22.6 | 22.3; 300, 46 x 4 x
-  // 295: 20.6 | 18.5; 400, 100 x 4 x 512: 53.6 | 40.6; 576, 128 rows of 8 x 384: 79 | 65)
-  if (D == 32 && heads % 2 == 0 && p.sh == D && p.do_sh == D && (int64_t)tiles * tiles * (heads / 2) * ng >= 256 &&
+  // 295: 20.6 | 18.5; 400, 100 x 4 x 512: 53.6 | 40.6; 576, 128 rows of 8 x 384: 79 | 65).  With a causal mask the tiles below the diagonal count, the others
+  // end at once (whole backward: 156 of them, 256 x 4 x 768 739 | 765; 180, 46 x 4 x 295 61.1 | 62.5; 192, 64 x 16 x 65 50.1 | 51.7; 240, 300 x 8 x 130 202 | 205;
+  // 272, 64 x 4 x 1024 335 | 314; 288, 100 x 4 x 512 194 | 183; 315, 200 x 6 x 300 210 | 199)
+  if (D == 32 && heads % 2 == 0 && p.sh == D && p.do_sh == D && live * (heads / 2) * ng >= 256 &&
       ((int64_t)(p.S - 1) * p.ss + 2 * D) * 2 < lim && ((int64_t)(p.S - 1) * p.do_ss + 2 * D) * 2 < lim)
     return launch_pair_dbias(p, st);
   const dim3 g(tiles, tiles, heads * ng);

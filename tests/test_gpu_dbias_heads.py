@@ -1,4 +1,4 @@
-"""Bias gradient of two heads per work-group: from 384 such work-groups on (here 450, 400, and 400 in four groups of rows)."""
+"""Bias gradient of two heads per work-group: from 256 such work-groups on (here 450, 400, and 400 in four groups of rows)."""
 import pytest
 
 from parity import check_against_oracle

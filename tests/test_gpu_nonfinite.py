@@ -86,7 +86,7 @@ def test_fp32_nonfinite_inputs(name, mask, S, D, flags):
                 assert np.max(np.abs(x[ok] - r[ok])) <= 2e-5 * max(1.0, np.max(np.abs(r[ok]))), n
 
 
-@pytest.mark.parametrize("S,win,dense", [(81, (9, 9), False), (144, (12, 12), False), (131, None, True), (200, None, True)])
+@pytest.mark.parametrize("S,win,dense", [(81, (9, 9), False), (144, (12, 12), False), (160, (10, 16), False), (131, None, True), (200, None, True)])
 @pytest.mark.parametrize("name", ["nan_key", "nan_bias", "masking_bias"])
 def test_bf16_nonfinite_inputs(name, S, win, dense):
     """The window kernels and the one-walk kernel with a pair bias of an odd and of an even length: NaN reaches
@@ -119,12 +119,12 @@ def test_bf16_nonfinite_inputs(name, S, win, dense):
                 assert np.max(np.abs(x[ok] - r[ok])) <= 2e-2 * max(1.0, np.max(np.abs(r[ok]))), n
 
 
-@pytest.mark.parametrize("S", [131, 200, 1030])  # one head per work-group, and two (from 256 such work-groups on)
-def test_bf16_masked_logits_far_above_the_visible_ones(S):
+@pytest.mark.parametrize("H,S", [(2, 131), (2, 200), (4, 1030)])  # one head per work-group, and two (from 256 tiles below the diagonal on)
+def test_bf16_masked_logits_far_above_the_visible_ones(H, S):
     """Causal mask with a pair bias: logits of masked pairs far above the LSE of their row, as a large entry or as visible keys that the
     bias all but masks.  Their exponential overflows; the gradient of their bias is exactly 0."""
     import torch
-    inp = make_inputs(seed=65, B=2, H=2, S=S, D=32, dtype="bf16", bias="dense", axis="row")
+    inp = make_inputs(seed=65, B=2, H=H, S=S, D=32, dtype="bf16", bias="dense", axis="row")
     bias = inp["bias"]
     bias[:, 3, 40] = 304.0
     bias[1, S - 20, S - 2] = 304.0

@@ -1,4 +1,5 @@
-"""Bias gradient with 64 queries x 64 keys of two heads per work-group (from 256 such work-groups in a launch on): edges of its tiles, odd lengths,
+"""Bias gradient with 64 queries x 64 keys of two heads per work-group (from 256 such work-groups in a launch on, with a causal mask those below the
+diagonal): edges of its tiles, odd lengths,
 transposed storage, the causal mask, groups of rows, sums that go on from chunk to chunk, and, on fewer work-groups, one head at a time with
 the same bits."""
 import os
@@ -12,8 +13,10 @@ from parity import check_against_oracle
 from test_wave_isa import pending_read_violations
 
 CASES = {  # rows, heads, tokens
-    "groups_65": dict(B=70, H=16, S=65),
+    "groups_65_causal": dict(B=300, H=12, S=65, mask="causal"),
+    "groups_193": dict(B=70, H=16, S=193),
     "groups_129_causal": dict(B=40, H=16, S=129, mask="causal"),
+    "groups_193_causal": dict(B=70, H=24, S=193, mask="causal"),
     "sbhd_191": dict(B=40, H=12, S=191, layout="sbhd"),
     "one_row_1000": dict(B=1, H=4, S=1000),
     "odd_833": dict(B=3, H=4, S=833),
