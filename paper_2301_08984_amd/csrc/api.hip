@@ -122,7 +122,13 @@ WsLayout layout_with(const ss_attn_desc* d, int gw) {
     off += align_up((size_t)w.ring * w.hs * d->S * d->S * 4);
   }
   w.biasT = off;
-  if (d->bias_kind == SS_BIAS_DENSE && d->bias_dtype == SS_BF16) off += align_up((size_t)d->H * d->S * d->S * 2);
+  // Rows of pair attention whose one kernel reads no transposed bias and whose longest group is the whole share: its place is left to the groups' sums.  With many
+  // heads they decide how many work-groups there are (one per head and group): backward of 100 rows x 62 heads x 160 586 us in one group, 490 with the tiled
+  // kernels, 319 in two; 100 x 76 x 144, gated, 714, 658, 441.  Not of up to 112 tokens, two work-groups a compute unit (100 x 172 x 96 in one 286, in two 320), and
+  // not for two or three rows (4 x 128 x 128 24 | 30).
+  const KP p = base_params(d);
+  const bool left = w.gw >= 4 && !ssa::win_ok(p) && d->S > 112 && ssa::row_ok(p, false) && ssa::dbias_longest_group(p) == 0;
+  if (d->bias_kind == SS_BIAS_DENSE && d->bias_dtype == SS_BF16 && !left) off += align_up((size_t)d->H * d->S * d->S * 2);
   w.total = off;
   return w;
 }

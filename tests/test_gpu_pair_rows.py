@@ -49,6 +49,22 @@ def test_forward_on_both_sides_of_its_line(B, S):
     check_against_oracle(_cfg(B, 4, S, gated=S % 2 == 0))
 
 
+@pytest.mark.parametrize("B,H,S,axis,gated", [(9, 62, 160, "row", False), (14, 76, 144, "head", True)])
+def test_many_heads_in_two_groups(B, H, S, axis, gated):
+    """Groups of rows whose sums take the place of the transposed bias; the same bits for every k."""
+    import torch
+    cfg = _cfg(B, H, S, axis=axis, gated=gated)
+    print(f"pair rows, many heads {B} x {H} x {S}", flush=True)
+    dc, _ = check_against_oracle(cfg, k=1)
+    want = {n: getattr(dc, n).clone() for n in ("dQ", "dK", "dV", "dBias")}
+    for k in (2, 5):
+        dc.ws = None
+        dc.bwd(dc.desc(axis, 0, H if axis == "head" else B, k), poison=True)
+        torch.cuda.synchronize()
+        for n, x in want.items():
+            assert torch.equal(getattr(dc, n), x), (k, n)
+
+
 def test_captured_and_eager_calls_agree():
     import torch
     cfg = _cfg(130, 4, 132)

@@ -101,3 +101,14 @@ def test_library_device_memory_is_what_the_header_says():
     value = lambda name: eval(re.sub(r"SS_\w+", lambda m: str(value(m.group(0))), macros[name]).replace("u", ""))
     assert value("SS_ATTN_STATIC_SCRATCH_BYTES") == ss.SS_ATTN_STATIC_SCRATCH_BYTES
     assert value("SS_LIBRARY_DEVICE_BYTES") == ss.SS_LIBRARY_DEVICE_BYTES
+
+
+@pytest.mark.parametrize("B,H,S,gated", [(100, 62, 160, False), (300, 64, 157, False), (100, 76, 144, True), (33, 90, 144, True), (50, 100, 144, False)])
+def test_many_heads_keep_groups_of_rows(B, H, S, gated):
+    """One work-group per head and group of rows: one group would leave most of the chip idle.  Two groups' sums take the place of the transposed bias
+    and no more than the spare beside it."""
+    d = _desc(B, H, S, 1, bias=ss.SS_BIAS_DENSE, gated=gated)
+    transposed = _up(H * S * S * 2)
+    assert _bytes(d) == _least(d) - transposed + _up(2 * H * S * S * 4)
+    finest = _desc(B, H, S, B, bias=ss.SS_BIAS_DENSE, gated=gated)
+    assert _least(finest) < _bytes(finest) <= _least(finest) + 12 * MIB
