@@ -13,14 +13,14 @@ namespace {
 // 256 rows 373 | 329; odd lengths, whose parked tiles are loaded unaligned: 64 x 8 x 501: 58.0 | 58.3, 512 x 4 x 301: 107 | 92.
 // Backward: dK / dV 9 % shorter (1024 x 4 x 1024: 2037 -> 1850 us), and the copy replaces the transposed bf16 one; the
 // recompute + dQ kernel gains nothing from a copy of its own (2469 | 2510).
-// Windows (win_fwd.hip, win_bwd.hip: packed bf16): without one a work-group gathers the bias from the table in LDS or from the dense matrix.  Without | with,
-// us, 12 x 12 tokens with regions, 64 x 8 and 512 x 8 rows x heads: dense forward 27.3 | 18.4, 65.9 | 54.8, backward 44.3 | 40.5, 128 | 126 (11 x 11, 512 x 8:
-// 90 | 92).  From the table: backward 3 us shorter without, so never; forward 11.0 | 16.2, 51.7 | 55.2: the copy's launch remains, one rule for both kinds of
-// bias, until the launches that callers see in a profile may change.
+// Windows (win_fwd.hip, win_bwd.hip: packed bf16): a dense bias only.  Without a copy a work-group gathers it from the matrix; without | with, us, 12 x 12 tokens with
+// regions, 64 x 8 and 512 x 8 rows x heads: forward 27.3 | 18.4, 65.9 | 54.8, backward 44.3 | 40.5, 128 | 126 (11 x 11, 512 x 8: 90 | 92).  From a table, which a
+// work-group gathers in LDS, the copy's launch costs more than it saves: forward, 64 x 8 11.0 | 16.7, 512 x 8 49.7 | 53.7,
+// 256 x 24 59.3 | 65.0, 1024 x 16 162.8 | 167.3, 512 x 8 of 10 x 16 40.6 | 45.7; backward 3 us.
 inline int64_t win_packed_bytes(int S, int heads) { return (int64_t)heads * ((S + 15) / 16) * ((S + 15) / 16) * 512; }
 inline size_t bias_copy_bytes_for(const KP& p, bool backward, int64_t rows, int heads) {
   if (win_ok(p)) {
-    if (p.bias_kind == 0 || (backward ? p.bias_kind == 2 || rows * heads < (p.S <= 128 ? 1024 : 64) : p.S <= 128 || rows * heads < 512)) return 0;
+    if (p.bias_kind != 1 || (!backward && p.S <= 128) || rows * heads < (backward ? (p.S <= 128 ? 1024 : 64) : 512)) return 0;
     return (size_t)win_packed_bytes(p.S, heads);
   }
   if (row_ok(p, !backward) || !pair_fwd_ok(p) || p.S > 16384) return 0;
@@ -50,20 +50,14 @@ __global__ __launch_bounds__(256) void bias_copy_kernel(const uint16_t* src, flo
     out[64 * g] = x;
   }
 }
-// an entry of a window's bias, from the relative-position table or the dense matrix: query i, key j
-__device__ inline uint16_t win_bias_entry(const KP& p, int h, int i, int j) {
-  const uint16_t* b = (const uint16_t*)p.bias;
-  if (p.bias_kind != 2) return b[((int64_t)h * p.S + i) * p.S + j];
-  const int rowlen = 2 * p.win_w - 1, dy = i / p.win_w - j / p.win_w + p.win_h - 1, dx = i % p.win_w - j % p.win_w + p.win_w - 1;
-  return b[(int64_t)h * ((2 * p.win_h - 1) * rowlen) + dy * rowlen + dx];
-}
 // What the kernels of windows read (win_common.h): bf16, blocks of 16 queries x 16 keys, lane l the query l % 16 and four keys from 4 (l / 16) on; -inf
 // past the last key.  x = block of keys, y = block of queries, z = head.
 __global__ __launch_bounds__(64) void win_bias_pack_kernel(KP p, uint2* dst) {
   const int lane = threadIdx.x, i = min(16 * (int)blockIdx.y + (lane & 15), p.S - 1), j0 = 16 * blockIdx.x + 4 * (lane >> 4);
+  const uint16_t* row = (const uint16_t*)p.bias + ((int64_t)(p.bc_h0 + blockIdx.z) * p.S + i) * p.S;
   uint32_t x[4];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) x[e] = j0 + e < p.S ? win_bias_entry(p, p.bc_h0 + blockIdx.z, i, min(j0 + e, p.S - 1)) : 0xff80u;
+  for (int e = 0; e < 4; ++e) x[e] = j0 + e < p.S ? row[min(j0 + e, p.S - 1)] : 0xff80u;
   dst[((blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x) * 64 + lane] = uint2{x[0] | x[1] << 16, x[2] | x[3] << 16};
 }
 // Makes the copy that bias_copy_bytes_for asks for, of the heads [h0, h1), and points `p` at it.
