@@ -192,10 +192,14 @@ const char* ss_attn_kernel_family(const ss_attn_desc* desc);
  * summed duration in milliseconds and the number of launches of one kernel since
  * the last read, and resets both.  Not thread-safe. */
 typedef enum {
-  SS_K_FWD = 0, SS_K_RECOMPUTE = 1, SS_K_DQ = 2, SS_K_DKDV = 3, SS_K_DBIAS = 4, SS_K_TABLE_REDUCE = 5,
-  SS_K_DQ_DKDV = 6,   /* dQ and dK/dV in one launch (small shares with long rows; windows of 65 to 160 tokens, with
-                       the recompute pass and the bias gradient) */
-  SS_K_DBIAS_FOLD = 7, /* fold of completed bias-gradient group partials into the result */
+  SS_K_FWD = 0, SS_K_RECOMPUTE = 1, SS_K_DQ = 2,
+  SS_K_DKDV = 3,      /* dK/dV; the whole backward of rows of up to 64 tokens without a gate, head size 32 */
+  SS_K_DBIAS = 4,
+  SS_K_TABLE_REDUCE = 5, /* relative-position tables: the two launches that reduce completed group partials, or the reduction of a
+                          dense gradient; and the launch that lays out a bias, of windows, pair attention or transposed */
+  SS_K_DQ_DKDV = 6,   /* dQ and dK/dV in one launch (small shares with long rows; windows and rows of pair attention of 65 to
+                       160 tokens and gated rows of 17 to 64, with the recompute pass and the bias gradient) */
+  SS_K_DBIAS_FOLD = 7, /* fold of completed group partials of a dense bias's gradient into the result */
   SS_K_RECOMPUTE_DQ = 8, /* recompute pass and dQ in one launch (head size 32, large shares; fp32, whose
                             SS_K_DKDV launch takes the bias gradient too) */
   SS_K_COUNT = 9

@@ -72,9 +72,12 @@ struct WsLayout {
   int gw, g0, ngroups, slice, ring, hs;
 };
 
-// Rows per bias-gradient group of the short-sequence kernels, one wavefront each: 8 (the groups' sums cost a
-// pass over H x S x S per group), fewer while twice as many groups still fit the 2048 wavefronts that the
-// chip holds.  Backward of 17 rows x 8 heads x 49: 60 -> 27 us.
+// Rows per bias-gradient group of short sequences: 8 (the groups' sums cost a pass over H x S x S per group),
+// fewer while twice as many groups are no more than 2048: the wavefronts of small_kernels.hip, one a group, that
+// the chip holds.  Of the work-groups of win_bwd.hip, one a group too, it holds 2048, 1280 and 1024 of up to 32, 48 and 64 tokens.
+// Backward, us, at most 2048 | 1024 groups: causal mask (small_kernels.hip), 300 rows x 12 heads x 49 44.4 | 45.5, 1000 x 3 x 64 48.7 | 47.6;
+// regions (win_bwd.hip), 300 windows of 7 x 7 x 12 heads 37.2 | 33.2, 200 of 8 x 8 x 8 34.9 | 28.9, 64 x 4 16.3 | 15.9, 500 of 6 x 6 x 6 26.7 | 25.5, 128 rows x 8
+// heads x 49 the same.  One line for both, as the order of the additions, and with it the last bits of the gradient, goes by it.
 constexpr int SMALL_GROUP_ROWS = 8;
 inline int small_group_rows(int share_units) {
   int gw = SMALL_GROUP_ROWS;

@@ -556,11 +556,13 @@ inline bool fast_ok(const KP& p) {
 // region mask (a bf16 bias of either kind, or none; no causal mask), a positive scale
 inline bool win_ok(const KP& p) {
   if (p.D != 32 || p.S <= 64 || p.S > 160 || !(p.scale > 0.f) || p.mask_kind == 1) return false;
-  if (p.bias_kind != 0 && (!p.bias_bf16 || !(p.scale > 1e-9f && p.scale < 1e9f))) return false;  // bias / scale, as in fast_ok
+  // (scales outside these go to the all-feature kernels as those of fast_ok do, which form bias / scale; nothing here does)
+  if (p.bias_kind != 0 && (!p.bias_bf16 || !(p.scale > 1e-9f && p.scale < 1e9f))) return false;
   return p.bias_kind == 2 || p.mask_kind == 2;
 }
-// Rows of pair attention take the same kernels, head size 32, no mask, a dense bf16 bias or none: the backward of 65 to 160 tokens, with a gate up to 144, beyond
-// which it spills (1000 rows x 8 heads x 160, step: 800 us with the tiled kernels, 1109 with this one); the forward of 129 to 160, of up to 128 (row, head)
+// Rows of pair attention take the same kernels, head size 32, no mask, a dense bf16 bias or none: the backward of 65 to 160 tokens, with a gate up to 144 (that line
+// is from when ten wavefronts with a gate spilled; they no longer do and would be the faster ones: backward, tiled kernels | these, dense bias, 1000 rows x 8 heads x 160
+// 638 | 552 us, 300 x 8 x 160 192 | 112, 100 x 60 x 160 513 | 492, 16 x 4 x 150 33.8 | 22.8, no bias 1000 x 8 x 160 408 | 264); the forward of 129 to 160, of up to 128 (row, head)
 // pairs only without a bias, which a work-group gathers before its first row.  Us, gated, dense bias, tiled
 // kernels | these: backward, 16 x 4 x 100 30.4 | 16.5, 100 x 4 x 128 40.9 | 34.2, 64 x 8 x 128 41.1 | 34.6, 1000 x 8 x 112 339 | 221; without a bias 64 x 4 x 128
 // 16.2 | 9.9, 1000 x 8 x 144 407 | 245; without a gate 300 x 8 x 160 177 | 112.  Forward, 60 x 8 x 155 14.4 | 12.3, 120 x 8 x 140 23.6 | 18.9, 1000 x 8 x 160

@@ -94,9 +94,9 @@ __device__ inline void wave_lds_sync() {
 // What a score costs in vector instructions: the logit t = s * scale + bias (one unpacking and one fused instruction; the bias is added in its own
 // units, so that it needs no factor of its own), the exponential of t * log2(e) less the row's constant (a fused instruction and a
 // quarter-rate one).  Registers that hold nothing but padding are left out: KG is the number of groups of 8 tokens of the second block of 32
-// that hold any, 3 for up to 56 tokens.  Step of 300 windows of 7 x 7 x 12 heads 71.1 -> 69.2 us, 64 x 4, region mask, 37.7 -> 36.8, 1024 of 8 x 8 x 8
-// 135.6 -> 134.0; of 4096 x 16, bound by memory, 683 -> 677.  (A transposed copy of the bias tile for the backward, 16 reads of 8 bytes instead of 64 of 2:
-// no change at 7 x 7, 76 -> 83 at 8 x 8.)
+// that hold any, 3 for up to 56 tokens.  What both gained on calls that these kernels serve, forward, backward, us: causal mask, dense bias, 300 rows x 12 heads x 49
+// 19.5 -> 19.0, 47.3 -> 45.7, 1024 x 8 x 64 27.6 -> 27.4, 81.7 -> 81.9; regions, 4096 windows of 4 x 4 x 8 heads 64.2 -> 59.5, 160 -> 142; a table in fp32, 300 of 7 x 7 x 12
+// 22.9 -> 22.2, 53.8 -> 48.7, 1024 of 8 x 8 x 8 31.1 -> 30.8, 87.7 -> 83.3 (the tables' backward also by table_fold.h).
 template <int KG>
 constexpr int live(int blk) { return blk == 0 ? 16 : 4 * KG; }  // registers of a block
 __device__ inline void unpack4(uint2 u, float (&x)[4]) {

@@ -15,7 +15,7 @@ namespace {
 typedef f32x4 f32x4_at4 __attribute__((aligned(4)));
 
 constexpr int FOLD_ELEMS = 40 * 160;  // S <= 64: 32 x 64; S <= 160: 40 x 160
-inline int fold_parts(int S) { return S > 64 ? 4 : S >= 16 ? 2 : 1; }  // a part's table fits its place: (2 a - 1) (2 b - 1) < 4 S <= S / Z * S
+inline int fold_parts(int S) { return S > 64 ? 4 : S >= 16 ? 2 : 1; }  // a part's table fits its place: (2 a - 1) (2 b - 1) < 4 S <= S / Z * S from 4 tokens on; 1, 2 and 3 have 1, 3 and 5 entries of S * S
 
 // Q runs of four entries a thread
 template <int Q>
