@@ -22,15 +22,16 @@ template <int NB> constexpr bool WF_LDS_BIAS = NB == 9;
 // asked for): 81 to 96 tokens with a bias and regions, us: 1024 x 16 heads of 9 x 9 90.5 -> 82.3, 4096 x 8 173 -> 160, 512 x 8 23.6 -> 21.7.  Elsewhere a load and a
 // store more cost more than a register (1024 x 16 of 8 x 10 79.6 -> 83.3).
 template <int NB, bool BIAS> constexpr bool WF_ID_DMA = NB == 6 || (NB == 9 && BIAS);
-// The gate asked for ahead of the next row, where there are registers for it and the wait for that row was felt: 1024 x 16 heads, regions, 9 x 9 without a bias
-// 111.9 -> 106.9, 10 x 10 with one 144.8 -> 137.9.
-template <int NB, bool BIAS> constexpr bool WF_EARLY_GATE = NB == 7 || (NB == 6 && !BIAS);
+// The gate asked for ahead of the next row, where there are registers for it and the wait for that row was felt, us: 1024 x 16 heads, regions, 9 x 9 without a bias
+// 111.9 -> 106.9, 10 x 10 with one 144.8 -> 137.9; 800 x 8 of 5 x 14 with regions and no bias 33.9 -> 31.6 (32.6 with the kernels before these), of 5 x 16 36.2 -> 34.0
+// (34.2), of 9 x 9 with a bias and no regions 39.8 -> 38.1 (38.2), of 6 x 16 42.8 -> 40.2 (40.0).
+template <int NB, bool REGION, bool BIAS> constexpr bool WF_EARLY_GATE = NB == 5 || NB == 7 || (NB == 6 && !(REGION && BIAS));
 
 template <int NB, bool REGION, bool BIAS, bool LSE>
 __global__ __launch_bounds__(64 * NB) __attribute__((amdgpu_waves_per_eu(WF_WAVES<NB>, WF_WAVES<NB>))) void win_fwd_kernel(KP p, int rows_per_wg) {
 #pragma clang fp contract(off)
   constexpr int T = 16 * NB, STEPS = (NB + 1) / 2, TENSOR = T * WB_TOKEN;
-  constexpr bool LB = BIAS && WF_LDS_BIAS<NB>, ID_DMA = REGION && WF_ID_DMA<NB, BIAS>, EARLY_GATE = WF_EARLY_GATE<NB, BIAS>;
+  constexpr bool LB = BIAS && WF_LDS_BIAS<NB>, ID_DMA = REGION && WF_ID_DMA<NB, BIAS>, EARLY_GATE = WF_EARLY_GATE<NB, REGION, BIAS>;
   // arrays of their own: the compiler then knows that a load into one does not feed a read of the other
   __shared__ __attribute__((aligned(1024))) char kv0[2 * TENSOR];
   __shared__ __attribute__((aligned(1024))) char kv1[2 * TENSOR];
