@@ -202,9 +202,13 @@ void launch_blocks(const KP& p, hipStream_t st) {
   // 112, of 16 rows and more (one round | so, regions: 1024 x 16 heads of 10 x 10 124 | 113, 1024 x 32 252 | 213; 1536 x 12, where rounds would be of 18, 122 | 121); of up to
   // 128, of 8 and more from 24 on (11 x 11: 768 x 16 114 | 96, 1024 x 16 157 | 127, 1024 x 32 322 | 239, 4096 x 8 285 | 243; 768 x 12, 18 rows, 68 | 70).  Of more tokens
   // one (256 x 24 of 12 x 12: 85 in rounds, 77 in one; 4096 x 8 349 | 328).
+  // Of 65 to 96 without a bias, which a work-group would have to gather first, and six heads or more (of up to 80 eight): rounds of at most 4 rows (as above | so, with the kernels before
+  // these; regions: 900 x 8 heads of 6 x 16 35.2 | 30.5, 31.5; 512 x 16 39.7 | 35.0, 35.7; gated 48.5 | 43.3, 41.8; 900 x 8 of 5 x 16 29.2 | 25.6, 30.4; 700 x 8 of 9 x 9
+  // 25.0 | 24.7, 26.5; 1024 x 6 of 6 x 16 30.2 | 28.5, 27.7; of fewer heads 2048 x 6 of 5 x 13 37.4 | 38.4, 45.3, 2000 x 3 of 9 x 9 25.8 | 26.7, 28.2, 1600 x 4 of 6 x 16 30.0 | 28.5, 28.9).
   const int64_t rows = p.b1 - p.b0, heads = p.h1 - p.h0, slots = 256 * WF_GROUPS<NB>;
   const int64_t once = (rows * heads + slots - 1) / slots;
-  const int64_t rounds = NB > 8 ? 1 : NB == 8 ? (once < 24 ? 1 : once / 8) : NB == 7 ? (once < 16 ? 1 : once / 16) : once <= 8 ? 1 : (once + 5) / 6;
+  const int64_t rounds = NB > 8 ? 1 : NB == 8 ? (once < 24 ? 1 : once / 8) : NB == 7 ? (once < 16 ? 1 : once / 16) :
+                         NB > 4 && p.bias_kind == 0 && heads >= (NB == 5 ? 8 : 6) ? (once + 3) / 4 : once <= 8 ? 1 : (once + 5) / 6;
   const int64_t of_head = slots * rounds / heads > 1 ? slots * rounds / heads : 1;
   const int run = (int)((rows + of_head - 1) / of_head);
   const dim3 grid((unsigned)heads, 1, (unsigned)((rows + run - 1) / run));

@@ -86,9 +86,9 @@ def test_runs_of_rows_of_every_length(B, H, S):
 @pytest.mark.parametrize("win", [(5, 13), (5, 16), (9, 9), (8, 12)], ids=lambda w: f"{w[0]}x{w[1]}")
 @pytest.mark.parametrize("form", ["regions", "bias", "both"])
 def test_gates_of_several_rows(win, form):
-    """A work-group walks several rows, whose gates some kernels ask for before the next row and some after it."""
+    """A work-group walks several rows, whose gates some kernels ask for before the next row and some after it; without a bias in two rounds."""
     from paper_2301_08984_amd.workloads import make_inputs
-    cfg = _cfg(win, B=401, H=6, mask=None, bias=None if form == "regions" else "relpos", gated=True)
+    cfg = _cfg(win, **(dict(B=601, H=8, bias=None) if form == "regions" else dict(B=401, H=6)), mask=None, gated=True)
     inp = make_inputs(**cfg)
     if form != "bias":
         inp["region_ids"] = (np.arange(cfg["S"])[None] * np.arange(1, 4)[:, None] // cfg["S"]).astype(np.int32)
